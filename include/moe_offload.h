@@ -306,9 +306,14 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                kernel (one block sees both experts' rows; no atomics, no separate residual kernel);
  *                0: the general kernels also for one token;
  *   "mfma_min_batch" batches at least this large (default 3, from where on they are the faster ones on MI355X; 16
- *                is the benchmark definition's threshold) run 4-bit group-64 experts on the matrix cores (grouped
- *                dequantize+GEMM); smaller batches, and other formats, use the GEMV kernels;
- *   "mfma_form"  which matrix-core kernels.  0 (default): form 5.  4: persistent streaming kernels with
+ *                is the benchmark definition's threshold) run on the matrix cores (grouped dequantize+GEMM): 4-bit
+ *                group-64 experts in every form below, 4-bit group-128, 3-bit and 2-bit experts in forms 0 and 6 (2-bit
+ *                layers with a scale above 32000, or two-level ones above 500, excepted); smaller batches, 4-bit
+ *                group-32 experts and other formats in forms 1 to 5 use the GEMV kernels;
+ *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 for prompts and large batches (4-bit group-64 experts: where
+ *                an expert has more than 32 tokens of the step; other formats: always), else form 5.  6: tile kernels,
+ *                every format, up to 192 tokens of one expert multiplied per pass over its weights, codes
+ *                exact and groups scaled in fp32 (2-bit: exact fp16 products of code and scale).  4: persistent streaming kernels with
  *                tiles of 16 tokens -- one tile per expert while no expert has more than 16 tokens of a window of up to
  *                256 / top_k tokens of the step, else two, decided per window from its routing alone, so that a token's
  *                result does not depend on which experts share a launch -- each dequantised weight rounded once to fp16

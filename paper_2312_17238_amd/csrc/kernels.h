@@ -7,3 +7,4 @@
 #include "kernels_mfma.h"
 #include "kernels_mfma_stream.h"
 #include "kernels_mfma16.h"
+#include "kernels_tile.h"

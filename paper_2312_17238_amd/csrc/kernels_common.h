@@ -203,6 +203,15 @@ __device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t k
     return d;
 }
 
+// An fp32 number as two bf16 that together carry 16 bits of it: high part in the low half-word, low part in the other.
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t split2(float v)
+{
+    const __bf16 h = (__bf16)v;
+    const bf2_t p = {h, (__bf16)(v - (float)h)};
+    return __builtin_bit_cast(uint32_t, p);
+}
+
 // wave-uniform value as a scalar, so that addresses derived from it are computed on the scalar unit
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 

@@ -39,6 +39,12 @@ struct GateArgs {
     int32_t *route_idx;             // [K] device, or null
     float *route_w;                 // [K] device
     int32_t *route_log;             // [K] device: this step's slot of the log ring
+    // For the tile kernels (TILE): every pair's expert and combine weight in device memory, and the sums of h over
+    // groups of xs_group (16 or 64) elements, rows padded with zeros to xs_stride.
+    uint8_t *pair_expert;           // [b*K + j]
+    float *pair_w;                  // [b*K + j]
+    uint32_t *xs;                   // [b][xs_stride], split in two
+    int32_t xs_stride, xs_group;
 };
 
 constexpr int GATE_THREADS = 1024;
@@ -51,10 +57,11 @@ constexpr int GATE_WAVES = GATE_THREADS / WAVE;
 // are not needed and the registers go to this thread's first slice of W_g instead, requested before the norm's
 // reduction so that its memory latency overlaps the norm rather than following it (after the thread's slice of x:
 // loads return in order, and the norm waits for x).
+// TILE: also leaves what the tile kernels need in device memory -- every pair's expert and weight, the sums of h.
 // After the one barrier that collects the waves' partial logits, wave 0 finishes alone: lane e holds logit e (lane
 // 16 + e the next layer's), the selection runs on values read from those lanes, and the exponentials, divisions and
 // stores of the K chosen experts (and of the next layer's probabilities) are one per lane.
-template <bool SPEC>
+template <bool SPEC, bool TILE = false>
 __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a)
 {
     constexpr int NACC = SPEC ? 32 : 16;
@@ -117,6 +124,16 @@ __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a)
         if (a.yacc) *reinterpret_cast<float4 *>(a.yacc + (size_t)b * a.H + i) = make_float4(0.f, 0.f, 0.f, 0.f);
         const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
                      h3 = half_bits_to_f64(hv[3]);
+        if constexpr (TILE) {     // 4 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
+            float sum = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
+            sum += dpp_f<0xB1>(sum);
+            sum += dpp_f<0x4E>(sum);
+            if (a.xs_group == 64) {
+                sum += dpp_f<0x141>(sum);
+                sum += dpp_f<0x140>(sum);
+            }
+            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = split2(sum);
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             if (e < n1) {
@@ -134,6 +151,7 @@ __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a)
                 }
         }
     }
+    if (TILE && a.H / a.xs_group + tid < a.xs_stride) a.xs[(size_t)b * a.xs_stride + a.H / a.xs_group + tid] = 0u;
     // all logits' wave sums at once; accumulators of experts that do not exist hold zeros
     if constexpr (SPEC) {
         wave_sum_many_f64<32>(acc, lane);
@@ -201,6 +219,10 @@ __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a)
         if (lane < a.K) {
             o->idx[b * a.K + lane] = mine;
             o->w[b * a.K + lane] = wgt;
+            if constexpr (TILE) {
+                a.pair_expert[b * a.K + lane] = (uint8_t)mine;
+                a.pair_w[b * a.K + lane] = wgt;
+            }
         }
         if (lane < n1) o->logits[b * n1 + lane] = t;
     }

@@ -1,0 +1,785 @@
+// Grouped dequantize+GEMM on the matrix cores for batches and prompts, every weight format.
+//
+// A block multiplies one expert's tokens (or up to TOK of them) with ROWS memory rows.  k_tile<.., BIG>: 8 waves, 256
+// rows x up to 192 tokens, a wave 64 rows x up to 96 tokens (two waves share each 64 rows).  k_tile<.., small>: 4
+// waves, 128 rows x up to 32 tokens, a wave 64 rows and every second unit of the contraction.
+//
+// A unit is 64 codes of a row, a set four units: 128 bytes of 4-bit codes, which 8 lanes read in one piece.  Weights
+// cross LDS once (v_mfma_f32_32x32x16 wants a row per lane; loaded that way from memory every 16-byte piece would be a
+// line of its own to the compute unit's address path: measured 806 us for w1/w3 of a 1024-token prompt, all of it
+// that path), the metadata decoded by the thread that stages it.  The order of the contraction is free: lane half hh
+// takes the 32 codes at 32 hh of a unit, 16 consecutive bytes, and k-step j of it the activations 32 hh + 8 j .. + 7.
+//
+// Arithmetic.  A weight is s (q - z) with real z, and with any constant ZC
+//     sum_k s (q - z) x  =  sum_groups s (sum_k (q - ZC) x)  +  sum_groups s (ZC - z) X,     X = sum of the group's x.
+// q - ZC is exact in fp16.  First term, groups of 64 codes or more: the group's product comes out of the matrix cores in
+// fp32 and is scaled by the fp32 s with one fused multiply-add per accumulator register; no weight is rounded.
+// (Codes as the subnormal fp16 numbers their bits spell need no exponent and no subtraction, but the matrix cores
+// accumulate products of subnormals with fewer bits: 6 % more error in y.)
+// 2-bit codes (groups of 16; ZC = 1): q - 1 is one of -1, 0, 1, 2 and (q - 1) s is exact in fp16 for an fp16 s, so the
+// scaled weight goes in directly; an fp32 s (two-level metadata) goes in as two fp16 numbers, in two products.
+// Second term: a contraction over groups instead of codes.  X and D = s (ZC - z) are fp32 numbers split into two bf16
+// each (what is lost is 2^-17 of the term, itself a fraction of the result); per group the four k-slots
+// (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl) give the whole product, so one bf16 matrix instruction takes four groups; correcting
+// every group's product in the accumulators instead would double the vector work per group.  The X come from whoever
+// produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros to a multiple of
+// four groups.
+//
+// Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 666 + 344 (0.72 PFLOP/s; the
+// 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 427 + 220, 16 tokens 2-bit 126 + 63 (GEMV kernels
+// 17 x (45 + 28) and more, 213 + 103).  What bounds them: matrix and vector instructions of the two waves on a SIMD overlap
+// only in part (without any load from memory or LDS: 478 + 231), the rest is latency between the barriers.
+//
+// BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
+// other at the end of the unit before, so that one's vector work runs under the other's matrix work.
+//
+// MFMA layouts (v_mfma_f32_32x32x16): A lane l = token l%32, k-slots 8*(l/32)..+7; B lane l = memory row l%32, the same
+// k-slots; D lane l, register i = token 8*(i/4) + 4*(l/32) + i%4, memory row l%32.
+#pragma once
+#include "kernels_mfma16.h"
+#include <type_traits>
+
+namespace moe {
+
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+
+constexpr int TE_XCD = 8;                // blocks of one row block go to one XCD, whose L2 then serves its token blocks
+
+struct TileExpert {
+    const uint8_t *blob;
+    int32_t first, count;                // its pairs: positions first .. first + count - 1 of plist
+    int32_t tb;                          // token blocks
+    int32_t item0;                       // its first item in every XCD's sequence
+};
+
+struct TeArgs {
+    TileExpert e[16];
+    int32_t n_exp;
+    const uint16_t *plist;               // pair ids (token * top_k + choice), expert by expert, ascending within one
+    const float *pair_w;                 // combine weight of every pair
+    const uint16_t *act;                 // w1/w3: h [B][K];  w2: a [B*top_k][K]
+    const uint32_t *xs;                  // sums of act per group, split in two: [row of act][xs_stride]
+    uint16_t *a;                         // w1/w3: SwiGLU activations [pair][N]
+    uint32_t *xs_out;                    // ... and their sums
+    float *ypart;                        // w2: rows of N, one per pair (k_parts == 1) or per (position, part)
+    uint32_t *ytab;
+    int32_t K, N, top_k;
+    int32_t xs_stride, xs_out_stride;
+    uint32_t stride, meta_off, meta2_off, b_off;
+    int32_t unit_shift, run_shift;       // group of unit u: u >> unit_shift; run of group g: g >> run_shift
+    uint64_t mat_off;
+    int32_t units_per_part, k_parts, part_base;
+    int32_t jobs;                        // row blocks * k_parts
+    uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
+};
+
+// ---------------------------------------------------------------------------------------------
+// loads
+// ---------------------------------------------------------------------------------------------
+
+__device__ __forceinline__ uint32_t bl32(__amdgpu_buffer_rsrc_t r, uint32_t v, int s = 0) { return __builtin_amdgcn_raw_buffer_load_b32(r, (int)v, s, 0); }
+__device__ __forceinline__ uint2 bl64(__amdgpu_buffer_rsrc_t r, uint32_t v, int s = 0)
+{
+    const u32x2_t x = __builtin_amdgcn_raw_buffer_load_b64(r, (int)v, s, 0);
+    return make_uint2(x.x, x.y);
+}
+__device__ __forceinline__ uint4 bl128(__amdgpu_buffer_rsrc_t r, uint32_t v, int s = 0)
+{
+    const u32x4_t x = __builtin_amdgcn_raw_buffer_load_b128(r, (int)v, s, 0);
+    return make_uint4(x.x, x.y, x.z, x.w);
+}
+constexpr uint32_t TE_NONE = 0x80000000u;    // an offset past every buffer's end: zeros, no request
+
+// k-slots of two groups of the contraction over groups: X as (h l h l), D as (h h l l)
+__device__ __forceinline__ bf8_t slots_x(uint2 v)
+{
+    const u32x4_t r = {v.x, v.x, v.y, v.y};
+    return __builtin_bit_cast(bf8_t, r);
+}
+__device__ __forceinline__ bf8_t slots_d(uint2 v)
+{
+    const u32x4_t r = {__builtin_amdgcn_perm(v.x, v.x, 0x01000100u), __builtin_amdgcn_perm(v.x, v.x, 0x03020302u),
+                       __builtin_amdgcn_perm(v.y, v.y, 0x01000100u), __builtin_amdgcn_perm(v.y, v.y, 0x03020302u)};
+    return __builtin_bit_cast(bf8_t, r);
+}
+
+// eight centred codes of a word in the 4-bit layout
+__device__ __forceinline__ h8_t centred4(uint32_t w, const BiasPatterns &p, uint32_t k1024, uint32_t k64)
+{
+    const u32x4_t b = __builtin_bit_cast(u32x4_t, codes_biased(w, p));
+    const h2_t r0 = as_h2(b[0]) + as_h2(k1024), r1 = as_h2(b[1]) + as_h2(k64), r2 = as_h2(b[2]) + as_h2(k1024), r3 = as_h2(b[3]) + as_h2(k64);
+    h8_t r;
+    r[0] = r0.x; r[1] = r0.y; r[2] = r1.x; r[3] = r1.y; r[4] = r2.x; r[5] = r2.y; r[6] = r3.x; r[7] = r3.y;
+    return r;
+}
+
+// What the format policies know of a matrix: offsets inside a row, units of a row.  Loads of codes address with one
+// vector register per thread and a scalar: the slab of rows that a load of the block covers lies wholly inside or outside
+// the matrix (rows come in multiples of 64), one outside repeats the last.  A set that reaches past a row's end reads up
+// to 96 bytes of what follows the row (at most of the memory behind the expert buffers, which the same allocation holds).
+struct TeGeom { uint32_t stride, meta_off, meta2_off, b_off; int32_t unit_shift, run_shift, units; };
+
+// One (scale, zero) per unit, fp16 pair or byte pair and quad: item p = (row p / 4, unit p % 4 of the set).
+template <bool META8, int N> struct TeMeta;
+template <int N> struct TeMeta<false, N> {
+    uint32_t m[N];
+    __device__ __forceinline__ void fetch(int i, __amdgpu_buffer_rsrc_t r, uint32_t row, int u, const TeGeom &g) { m[i] = bl32(r, row + g.meta_off + 4u * (uint32_t)(u >> g.unit_shift)); }
+    __device__ __forceinline__ void get(int i, float &s, float &z) const { s = lo_half(m[i]); z = hi_half(m[i]); }
+};
+template <int N> struct TeMeta<true, N> {
+    uint32_t m[N];
+    uint2 quad[N];
+    __device__ __forceinline__ void fetch(int i, __amdgpu_buffer_rsrc_t r, uint32_t row, int u, const TeGeom &g)
+    {
+        const uint32_t grp = (uint32_t)(u >> g.unit_shift);
+        m[i] = __builtin_amdgcn_raw_buffer_load_b16(r, (int)(row + g.meta_off + 2u * grp), 0, 0);
+        quad[i] = bl64(r, row + g.meta2_off + 8u * (grp >> g.run_shift));
+    }
+    __device__ __forceinline__ void get(int i, float &s, float &z) const { decode_meta8(m[i], quad[i], s, z); }
+};
+
+// ---------------------------------------------------------------------------------------------
+// format policies.  Stage: what a thread holds of one set on its way to LDS; a row's record in LDS: CODES bytes of
+// codes, then (GS) four fp32 scales; D: split zero-point factors, DB bytes per row.  GS: scaled in the accumulators.
+// ---------------------------------------------------------------------------------------------
+
+template <int FMT, int ROWS, int THREADS> struct Te;
+
+template <bool META8, int ROWS, int THREADS>
+struct TeScaled {                        // the part that 4-bit and 3-bit formats share
+    static constexpr bool GS = true;
+    static constexpr int GPU = 1, PLANES = 1, DB = 16;                   // groups per unit; bytes of D per row and set
+    static constexpr float POST = 1.f;                                   // what the totals are multiplied with at the end
+    static constexpr int NM = ROWS * 4 / THREADS;
+    TeMeta<META8, NM> meta;
+    __device__ __forceinline__ void fetch_meta(__amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const int r = min(row0 + tid / 4 + i * (THREADS / 4), n_rows - 1);
+            meta.fetch(i, rs, live ? (uint32_t)r * g.stride : TE_NONE, min(u + tid % 4, g.units - 1), g);   // a finite scale also for units past the end
+        }
+    }
+    template <int REC, int SOFF>
+    __device__ __forceinline__ void commit_meta(uint8_t *rec, uint8_t *d, float zc, int tid) const
+    {
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            float s, z;
+            meta.get(i, s, z);
+            *reinterpret_cast<float *>(rec + (tid / 4) * REC + (tid % 4) * 4 + SOFF + i * (THREADS / 4) * REC) = s;
+            *reinterpret_cast<uint32_t *>(d + tid * 4 + i * THREADS * 4) = split2(s * (zc - z));
+        }
+    }
+};
+
+template <bool META8, int ROWS, int THREADS>
+struct Te4 : TeScaled<META8, ROWS, THREADS> {
+    static constexpr float ZC = 8.f;
+    static constexpr int SOFF = 128, REC = 144, NC = ROWS * 8 / THREADS;
+    uint4 c[NC];
+    struct Raw { uint4 q; };
+    __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
+    {
+        constexpr int SLAB = THREADS / 8;
+        const uint32_t v = live ? (uint32_t)(tid / 8) * g.stride + (uint32_t)(tid % 8) * 16u : TE_NONE;
+#pragma unroll
+        for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) c[i] = bl128(rs, v, min(row0 + i * SLAB, n_rows - SLAB) * (int)g.stride + u * 32);
+        if (h == 1) this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
+    }
+    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, int tid) const
+    {
+        uint8_t *const to = rec + (tid / 8) * REC + (tid % 8) * 16;
+#pragma unroll
+        for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) *reinterpret_cast<uint4 *>(to + i * (THREADS / 8) * REC) = c[i];
+        if (h == 1) this->template commit_meta<REC, SOFF>(rec, d, ZC, tid);
+    }
+    static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u) { r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16); }
+    static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[1][4])
+    {
+        constexpr uint32_t K1024 = 0xE408E408u, K64 = 0xD480D480u;       // -1032, -72
+        const BiasPatterns p = bias_patterns();
+        b[0][0] = centred4(r.q.x, p, K1024, K64);
+        b[0][1] = centred4(r.q.y, p, K1024, K64);
+        b[0][2] = centred4(r.q.z, p, K1024, K64);
+        b[0][3] = centred4(r.q.w, p, K1024, K64);
+    }
+};
+template <int R, int T> struct Te<4, R, T> : Te4<false, R, T> {};
+template <int R, int T> struct Te<48, R, T> : Te4<true, R, T> {};
+
+template <bool META8, int ROWS, int THREADS>
+struct Te3 : TeScaled<META8, ROWS, THREADS> {
+    static constexpr float ZC = 4.f;
+    static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS, NB = ROWS * 2 / THREADS;
+    uint4 a[NA], b[NB];
+    struct Raw { uint2 a; uint32_t b; };
+    __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
+    {
+        if (h == 0) {
+            // 64 rows per half block of threads: with 8 waves a load covers two slabs of 64
+            const uint32_t v = live ? (uint32_t)(tid / 4 % 64) * g.stride + (uint32_t)(tid % 4) * 16u : TE_NONE;
+#pragma unroll
+            for (int i = 0; i < NA; ++i) a[i] = bl128(rs, v, min(row0 + (i * THREADS / 4) + uniform(tid / 256) * 64, n_rows - 64) * (int)g.stride + u * 16);
+        } else {
+            const uint32_t v = live ? (uint32_t)(tid / 2 % 64) * g.stride + (uint32_t)(tid % 2) * 16u : TE_NONE;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) b[i] = bl128(rs, v, min(row0 + (i * THREADS / 2) + uniform(tid / 128) * 64, n_rows - 64) * (int)g.stride + (int)g.b_off + u * 8);
+            this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
+        }
+    }
+    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, int tid) const
+    {
+        if (h == 0) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) *reinterpret_cast<uint4 *>(rec + (tid / 4) * REC + (tid % 4) * 16 + i * (THREADS / 4) * REC) = a[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) *reinterpret_cast<uint4 *>(rec + (tid / 2) * REC + (tid % 2) * 16 + 64 + i * (THREADS / 2) * REC) = b[i];
+            this->template commit_meta<REC, SOFF>(rec, d, ZC, tid);
+        }
+    }
+    static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u)
+    {
+        r.a = *reinterpret_cast<const uint2 *>(row + u * 16 + hh * 8);
+        r.b = *reinterpret_cast<const uint32_t *>(row + 64 + u * 8 + hh * 4);
+    }
+    static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[1][4])
+    {
+        constexpr uint32_t K1024 = 0xE404E404u, K64 = 0xD440D440u;       // -1028, -68
+        const BiasPatterns p = bias_patterns();
+        const uint32_t t0 = (r.a.x & 0x33333333u) | ((r.b << 2) & 0x44444444u), t1 = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & 0x44444444u);
+        const uint32_t t2 = (r.a.y & 0x33333333u) | (r.b & 0x44444444u), t3 = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & 0x44444444u);
+        b[0][0] = centred4(t0, p, K1024, K64);
+        b[0][1] = centred4(t1, p, K1024, K64);
+        b[0][2] = centred4(t2, p, K1024, K64);
+        b[0][3] = centred4(t3, p, K1024, K64);
+    }
+};
+template <int R, int T> struct Te<3, R, T> : Te3<false, R, T> {};
+template <int R, int T> struct Te<38, R, T> : Te3<true, R, T> {};
+
+// eight codes (half of a 2-bit word) as (q - 1) s: fields of two bits under the exponents of 1024, 256, 64 and 16
+struct Patterns2 { uint32_t m[4], k[4]; };
+__device__ __forceinline__ Patterns2 patterns2()
+{
+    Patterns2 p = {{0x00030003u, 0x000C000Cu, 0x00300030u, 0x00C000C0u}, {0x64006400u, 0x5C005C00u, 0x54005400u, 0x4C004C00u}};
+    asm("" : "+s"(p.m[0]), "+s"(p.m[1]), "+s"(p.m[2]), "+s"(p.m[3]), "+v"(p.k[0]), "+v"(p.k[1]), "+v"(p.k[2]), "+v"(p.k[3]));
+    return p;
+}
+__device__ __forceinline__ void centred2(uint32_t w, const Patterns2 &p, h2_t (&c)[4])
+{
+    constexpr uint32_t off[4] = {0xE401E401u, 0xDC04DC04u, 0xD410D410u, 0xCC40CC40u};       // -1025, -257, -65, -17
+#pragma unroll
+    for (int n = 0; n < 4; ++n) c[n] = as_h2((w & p.m[n]) | p.k[n]) + as_h2(off[n]);
+}
+
+// 2-bit codes, groups of 16; record of a unit: (codes, scale) words of its four groups, 32 bytes
+template <bool META8, int ROWS, int THREADS>
+struct Te2 {
+    static constexpr bool GS = false;
+    static constexpr int GPU = 4, PLANES = META8 ? 2 : 1, DB = META8 ? 80 : 0, REC = 144, SOFF = 0;   // one-level: D from the record's (scale, zero)
+    static constexpr int NC = ROWS * 8 / THREADS, NA = ROWS * 4 / THREADS;
+    // two-level scales are split into two fp16: lifted by 64 the low part of any usual scale is a normal number
+    static constexpr float PRE = META8 ? 64.f : 1.f, POST = 1.f / PRE;
+    uint4 c[META8 ? NA : NC];
+    uint2 mp[META8 ? NA : 1], quad[META8 ? NA : 1];
+    struct Raw { uint4 q; };
+    __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
+    {
+        if constexpr (!META8) {
+            constexpr int SLAB = THREADS / 8;
+            const uint32_t v = live ? (uint32_t)(tid / 8) * g.stride + (uint32_t)(tid % 8) * 16u : TE_NONE;
+#pragma unroll
+            for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) c[i] = bl128(rs, v, min(row0 + i * SLAB, n_rows - SLAB) * (int)g.stride + u * 32);
+        } else {
+            const uint32_t row = (uint32_t)(tid / 4 % 64) * g.stride, un = (uint32_t)(tid % 4);
+#pragma unroll
+            for (int i = h * NA / 2; i < (h + 1) * NA / 2; ++i) {
+                const int at = min(row0 + (i * THREADS / 4) + uniform(tid / 256) * 64, n_rows - 64) * (int)g.stride;
+                c[i] = bl128(rs, live ? row + un * 16u : TE_NONE, at + u * 16);
+                mp[i] = bl64(rs, live ? row + un * 8u : TE_NONE, at + (int)g.meta_off + u * 8);
+                quad[i] = bl64(rs, live ? row + 8u * (uint32_t)((min(u + (int)un, g.units - 1) * 4) >> g.run_shift) : TE_NONE, at + (int)g.meta2_off);
+            }
+        }
+    }
+    // valid: units of the set that exist; what lies behind a row's end is no scale, so those units' records are zeros
+    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int valid, int tid) const
+    {
+        if constexpr (!META8) {
+            const bool in = (tid % 8) / 2 < valid;
+            uint8_t *const to = rec + (tid / 8) * REC + (tid % 8) * 16;
+#pragma unroll
+            for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) *reinterpret_cast<uint4 *>(to + i * (THREADS / 8) * REC) = in ? c[i] : make_uint4(0, 0, 0, 0);
+        } else {
+            const bool in = tid % 4 < valid;
+            uint8_t *const to = rec + (tid / 4) * REC + (tid % 4) * 32, *const dd = d + (tid / 4) * DB + (tid % 4) * 16;
+#pragma unroll
+            for (int i = h * NA / 2; i < (h + 1) * NA / 2; ++i) {
+                const uint32_t pr[4] = {mp[i].x, mp[i].x >> 16, mp[i].y, mp[i].y >> 16};
+                uint32_t ss[4], dv[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    float s, z;
+                    decode_meta8(pr[k], quad[i], s, z);
+                    s = in ? s * PRE : 0.f;
+                    z = in ? z : 0.f;
+                    const _Float16 hi = (_Float16)s;
+                    const h2_t p = {hi, (_Float16)(s - (float)hi)};
+                    ss[k] = __builtin_bit_cast(uint32_t, p);
+                    dv[k] = split2(s - s * z);
+                }
+                *reinterpret_cast<uint4 *>(to + i * (THREADS / 4) * REC) = make_uint4(c[i].x, ss[0], c[i].y, ss[1]);
+                *reinterpret_cast<uint4 *>(to + i * (THREADS / 4) * REC + 16) = make_uint4(c[i].z, ss[2], c[i].w, ss[3]);
+                *reinterpret_cast<uint4 *>(dd + i * (THREADS / 4) * DB) = make_uint4(dv[0], dv[1], dv[2], dv[3]);
+            }
+        }
+    }
+    static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u) { r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16); }
+    // the two groups' zero-point factors, split in two
+    static __device__ __forceinline__ uint2 factors(const uint8_t *row, const uint8_t *drow, int hh, int u)
+    {
+        if constexpr (META8) return *reinterpret_cast<const uint2 *>(drow + u * 16 + hh * 8);
+        Raw r;
+        read(r, row, hh, u);
+        const float s0 = lo_half(r.q.y), s1 = lo_half(r.q.w);
+        return make_uint2(split2(s0 - s0 * hi_half(r.q.y)), split2(s1 - s1 * hi_half(r.q.w)));
+    }
+    static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[PLANES][4])
+    {
+        const Patterns2 p = patterns2();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t w = k < 2 ? r.q.x : r.q.z, m = k < 2 ? r.q.y : r.q.w;
+            h2_t c[4];
+            centred2((k & 1) ? w >> 8 : w, p, c);
+#pragma unroll
+            for (int pl = 0; pl < PLANES; ++pl) {
+                const _Float16 s = as_h2(m)[pl];                         // one-level: the pair's scale; two-level: high, low part
+                const h2_t s2 = {s, s};
+                const h2_t v0 = c[0] * s2, v1 = c[1] * s2, v2 = c[2] * s2, v3 = c[3] * s2;
+                h8_t x;
+                x[0] = v0.x; x[1] = v0.y; x[2] = v1.x; x[3] = v1.y; x[4] = v2.x; x[5] = v2.y; x[6] = v3.x; x[7] = v3.y;
+                b[pl][k] = x;
+            }
+        }
+    }
+};
+template <int R, int T> struct Te<2, R, T> : Te2<false, R, T> {};
+template <int R, int T> struct Te<28, R, T> : Te2<true, R, T> {};
+
+// ---------------------------------------------------------------------------------------------
+
+template <int FMT, bool BIG> struct TeCfg {
+    static constexpr int THREADS = BIG ? 512 : 256, RG = BIG ? 4 : 2, ROWS = RG * 64;
+    using F = Te<FMT, ROWS, THREADS>;
+    static constexpr int MT = BIG ? (F::PLANES == 1 ? 3 : 2) : 1;                // token tiles of 32 per wave
+    static constexpr int TOK = BIG ? 2 * MT * 32 : 32;
+    static constexpr int SU = BIG ? 1 : 4;                               // units of activations per staging step
+    static constexpr int PITCH = SU * 128 + 16;                          // staged bytes per token (+16: bank spread)
+    static constexpr int NP = TOK * SU * 8 / THREADS;                    // 16-byte pieces per thread and step
+    static constexpr int REC = F::REC;
+    static constexpr int ABUF = TOK * PITCH, BBUF = ROWS * REC, DBUF = ROWS * F::DB;
+    // sums: 16 bytes are four groups, of a set (GS) or of one unit: XQ pieces per token and staging step
+    static constexpr int XQ = F::GS ? 1 : SU, XPITCH = XQ == 1 ? 16 : XQ * 16 + 16, XBUF = TOK * XPITCH;
+    static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_T = OFF_X + 2 * XBUF;
+    static constexpr int LDS = OFF_T + TOK * 8;
+    using Tot = std::conditional_t<F::GS, float[16], f32x16_t>;
+    static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
+    static_assert(OFF_X >= TOK * APITCH && LDS <= (BIG || F::PLANES == 2 ? 160 : 80) * 1024, "the epilogue reuses the staging buffers");
+};
+
+template <int FMT, bool W13, bool BIG>
+__global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A)
+{
+    using C = TeCfg<FMT, BIG>;
+    using F = typename C::F;
+    constexpr int THREADS = C::THREADS, ROWS = C::ROWS, NP = C::NP, SU = C::SU, PPT = SU * 8;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    int32_t *const l_pair = reinterpret_cast<int32_t *>(lds + C::OFF_T);
+    float *const l_w = reinterpret_cast<float *>(l_pair + C::TOK);
+    const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6), hh = lane >> 5, col = lane & 31;
+    const int rg = wv % C::RG, half = wv / C::RG;                        // rows of the wave; token half (BIG) or unit parity
+
+    // ---------------- the item ----------------
+    int j = (int)blockIdx.x / TE_XCD, e = 0;
+    while (e + 1 < A.n_exp && j >= A.e[e + 1].item0) ++e;
+    const TileExpert ex = A.e[e];
+    j -= ex.item0;
+    const int job = (j / ex.tb) * TE_XCD + (int)blockIdx.x % TE_XCD, t = j % ex.tb;
+    if (job >= A.jobs) return;                                           // whole block, before any barrier
+    const int rb = job / A.k_parts, part = job % A.k_parts;
+    const int tiles = (ex.count + 31) / 32;
+    const int tile0 = t * tiles / ex.tb, n_tiles = (t + 1) * tiles / ex.tb - tile0;
+    const int tok0 = tile0 * 32, n_tok = min(ex.count - tok0, n_tiles * 32);
+    const int n_rows = W13 ? 2 * A.N : A.N, row0 = rb * ROWS;
+    const int u0 = part * A.units_per_part, u1 = min(A.K / 64, u0 + A.units_per_part);
+    if (tid < C::TOK) {
+        const int p = tid < n_tok ? (int)A.plist[ex.first + tok0 + tid] : -1;
+        l_pair[tid] = p;
+        l_w[tid] = p >= 0 && !W13 ? A.pair_w[p] : 0.f;
+    }
+    __syncthreads();
+
+    // ---------------- staging ----------------
+    const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(ex.blob + A.mat_off), 0, n_rows * (int)A.stride, 0x00020000);
+    const __amdgpu_buffer_rsrc_t a_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(A.act), 0, (int)A.act_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(A.xs), 0, (int)A.xs_bytes, 0x00020000);
+    const TeGeom geo = {A.stride, A.meta_off, A.meta2_off, A.b_off, A.unit_shift, A.run_shift, A.K / 64};
+    auto act_row = [&](int tk) __attribute__((always_inline)) { const int p = l_pair[tk]; return W13 ? p / A.top_k : p; };
+    uint32_t a_off[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int tk = tid / PPT + i * (THREADS / PPT);
+        a_off[i] = tk < n_tok ? (uint32_t)act_row(tk) * (uint32_t)A.K * 2u + (uint32_t)(tid % PPT) * 16u : TE_NONE;
+    }
+    // sums: piece p of a step is token p / XQ; threads too many repeat a piece (a branch less)
+    constexpr int XQ = C::XQ, XU = F::GS ? 1 : 4;                        // XU: groups per unit
+    static_assert(C::TOK * XQ <= THREADS && THREADS % XQ == 0, "one piece per thread");
+    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * 16;
+    const uint32_t x_off = xp / XQ < n_tok ? (uint32_t)act_row(xp / XQ) * (uint32_t)A.xs_stride * 4u + (uint32_t)(xp % XQ) * 16u : TE_NONE;
+    uint4 st[NP], stx;
+    auto fetch_a = [&](int u) __attribute__((always_inline)) {                                          // units u .. u + SU - 1; zeros from u1 on
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int un = SU == 1 ? u : u + (tid % PPT) / 8;
+            st[i] = bl128(a_rs, un < u1 ? a_off[i] : TE_NONE, u * 128);
+        }
+    };
+    auto commit_a = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            *reinterpret_cast<uint4 *>(lds + (tid / PPT) * C::PITCH + (tid % PPT) * 16 + b * C::ABUF + i * (THREADS / PPT) * C::PITCH) = st[i];
+        }
+    };
+    auto fetch_x = [&](int u) __attribute__((always_inline)) { stx = bl128(x_rs, (F::GS ? u : u + xp % XQ) < u1 ? x_off : TE_NONE, u * (XU * 4)); };
+    auto commit_x = [&](int b) __attribute__((always_inline)) { *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = stx; };
+    // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
+    auto fetch_b = [&](F &f, int h, int u) __attribute__((always_inline)) { f.fetch(h, w_rs, geo, row0, n_rows, u < u1 ? u : u0, u < u1, tid); };
+    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, tid); };
+
+    // Left alone the scheduler moves a step's loads down to just before the LDS stores that wait for them: requests stay
+    // above the first mark, stores below the second; everything else may cross.
+    auto loads_above = [&]() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+    auto stores_below = [&]() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0x1 | 0x2 | 0x4 | 0x8 | 0x10 | 0x20 | 0x40 | 0x100); };
+
+    // ---------------- multiply ----------------
+    const uint8_t *const my_rec = lds + C::OFF_B + (rg * 64 + col) * C::REC;      // + 32 rows: the wave's second tile
+    auto unpack = [&](h8_t (&b)[2][F::PLANES][4], int bb, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            typename F::Raw raw;
+            F::read(raw, my_rec + bb * C::BBUF + rt * 32 * C::REC, hh, u);
+            F::decode(raw, b[rt]);
+        }
+    };
+    // totals of NT token tiles: plain registers where the vector unit adds to them, whole tuples where only the matrix cores do
+    // one unit of the wave's NT token tiles (from LDS address src) into the totals; xsrc: the unit's sums (2-bit codes)
+    auto multiply = [&](auto nt_tag, auto &tot, const h8_t (&b)[2][F::PLANES][4], const uint8_t *src, int bb, int u, const uint8_t *xsrc) __attribute__((always_inline)) {
+        constexpr int NT = decltype(nt_tag)::value;
+        float sc[2];
+        bf8_t d[2];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            if constexpr (F::GS) sc[rt] = *reinterpret_cast<const float *>(my_rec + bb * C::BBUF + rt * 32 * C::REC + F::SOFF + u * 4);
+            else d[rt] = slots_d(F::factors(my_rec + bb * C::BBUF + rt * 32 * C::REC, lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * 32 + col) * F::DB, hh, u));
+        }
+#pragma unroll
+        for (int mt = 0; mt < NT; ++mt) {
+            h8_t a[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + mt * 32 * C::PITCH + k * 16);
+            if constexpr (F::GS) {
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) {
+                    f32x16_t g;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) g[i] = 0.f;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) g = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k], b[rt][0][k], g, 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) tot[rt][mt][i] = __builtin_fmaf(sc[rt], g[i], tot[rt][mt][i]);
+                }
+            } else {
+                const uint2 xv = *reinterpret_cast<const uint2 *>(xsrc + mt * 32 * C::XPITCH);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int pl = 0; pl < F::PLANES; ++pl)
+#pragma unroll
+                        for (int rt = 0; rt < 2; ++rt) tot[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k], b[rt][pl][k], tot[rt][mt], 0, 0, 0);
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) tot[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(slots_x(xv), d[rt], tot[rt][mt], 0, 0, 0);
+            }
+        }
+    };
+    // GS: the zero-point term of a set
+    auto zero_term = [&](auto nt_tag, auto &tot, int tile, int bb) __attribute__((always_inline)) {
+        if constexpr (F::GS) {
+            constexpr int NT = decltype(nt_tag)::value;
+            bf8_t d[2];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) d[rt] = slots_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * 32 + col) * F::DB + hh * 8));
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt) {
+                const bf8_t xv = slots_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + ((tile + mt) * 32 + col) * C::XPITCH + hh * 8));
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) {
+                    f32x16_t z;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) z[i] = 0.f;
+                    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, d[rt], z, 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) tot[rt][mt][i] += z[i];
+                }
+            }
+        }
+    };
+    auto clear = [&](auto nt_tag, auto &tot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int mt = 0; mt < decltype(nt_tag)::value; ++mt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) tot[rt][mt][i] = 0.f;
+    };
+
+    // ---------------- epilogue: NT tiles from tile number `tile` of the block on; all waves pass its barriers ----------------
+    // w1/w3: even columns hold w1's rows, odd ones w3's: SiLU(u) v, rounded to fp16, collected in LDS so that rows of a
+    // leave in 16-byte pieces and their sums per group are taken on the way
+    auto finish = [&](auto nt_tag, const auto &tot, int tile, bool owner) __attribute__((always_inline)) {
+        constexpr int NT = decltype(nt_tag)::value;
+        if constexpr (W13) {
+            if (owner) {
+#pragma unroll
+                for (int mt = 0; mt < NT; ++mt)
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const float v = tot[rt][mt][i] * F::POST, other = dpp_f<0xB1>(v);
+                            const int tk = (tile + mt) * 32 + 8 * (i / 4) + 4 * hh + (i % 4);
+                            if ((lane & 1) == 0)
+                                *reinterpret_cast<uint16_t *>(lds + tk * C::APITCH + rg * 64 + rt * 32 + col) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
+                        }
+            }
+            __syncthreads();
+            constexpr int CPT = C::ACOLS / 8, XG = F::GPU == 1 ? 64 : 16;         // 16-byte pieces per token, columns per sum
+            for (int p = tid; p < n_tiles * 32 * CPT; p += THREADS) {
+                const int tk = p / CPT, c = p % CPT, colg = rb * C::ACOLS + c * 8;
+                const bool in = colg < A.N;                              // N is a multiple of 64: a piece is in or out as a whole
+                const u32x4_t q = *reinterpret_cast<const u32x4_t *>(lds + tk * C::APITCH + c * 16);
+                const h2_t ones = {(_Float16)1.f, (_Float16)1.f};
+                float x = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x = __builtin_amdgcn_fdot2(as_h2(q[i]), ones, x, false);
+                x = in ? x : 0.f;
+                x += dpp_f<0xB1>(x);                                     // two lanes: 16 columns
+                if constexpr (XG == 64) {
+                    x += dpp_f<0x4E>(x);
+                    x += dpp_f<0x141>(x);
+                }
+                if (tk < n_tok) {
+                    const int pr = l_pair[tk];
+                    if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
+                    uint32_t *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
+                    const int g = colg / XG;
+                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = split2(x);
+                    if (c == 0 && (rb + 1) * C::ACOLS >= A.N)            // the padding behind the last group that no row block covers
+                        for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = 0u;
+                }
+            }
+        } else {
+            if (rb == 0 && part == 0 && tid < n_tok) {                   // one block per token block tells k_combine where the rows are
+                const int pr = l_pair[tid];
+                const int row = A.k_parts == 1 ? pr : A.part_base + (ex.first + tok0 + tid) * A.k_parts;
+                A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)A.k_parts);
+            }
+            if (!owner) return;
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int tk = (tile + mt) * 32 + 8 * (i / 4) + 4 * hh + (i % 4);
+                    if (tk >= n_tok) continue;
+                    const int row = A.k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * A.k_parts + part;
+                    const float w = l_w[tk];
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt) {
+                        const int mrow = row0 + rg * 64 + rt * 32 + col;
+                        if (mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = w * (tot[rt][mt][i] * F::POST);
+                    }
+                }
+        }
+    };
+
+    if constexpr (BIG) {
+        // units one by one: activations double buffered per unit, weights per set
+        const int nt0 = (n_tiles + 1) / 2;
+        {
+            F f;
+            fetch_a(u0);
+            fetch_x(u0);
+            fetch_b(f, 0, u0);
+            fetch_b(f, 1, u0);
+            commit_a(0);
+            commit_x(0);
+            commit_b(f, 0, 0, u0);
+            commit_b(f, 1, 0, u0);
+        }
+        __syncthreads();
+        auto body = [&](auto nt_tag, auto late_tag) __attribute__((always_inline)) {
+            constexpr int NT = decltype(nt_tag)::value;
+            constexpr bool LATE = decltype(late_tag)::value;             // unpacks a unit ahead, after its matrix work
+            const int tile = LATE ? nt0 : 0;
+            typename C::Tot tot[2][NT > 0 ? NT : 1];
+            clear(nt_tag, tot);
+            h8_t b[2][F::PLANES][4];
+            if (LATE && NT > 0) unpack(b, 0, 0);
+            int bb = 0;
+            F f;
+            for (int u = u0; u < u1; u += 4) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    fetch_a(u + s + 1);
+                    if (s == 0) fetch_b(f, 0, u + 4);
+                    if (s == 1) fetch_b(f, 1, u + 4);
+                    if (!F::GS) fetch_x(u + s + 1);
+                    else if (s == 1) fetch_x(u + 4);
+                    loads_above();
+                    if constexpr (NT > 0) {
+                        if (!LATE) unpack(b, bb, s);
+                        multiply(nt_tag, tot, b, lds + (s & 1) * C::ABUF + (tile * 32 + col) * C::PITCH + hh * 64, bb, s,
+                                 lds + C::OFF_X + (s & 1) * C::XBUF + (tile * 32 + col) * C::XPITCH + hh * 8);
+                        if (s == 3) zero_term(nt_tag, tot, tile, bb);
+                        if (LATE) unpack(b, s == 3 ? bb ^ 1 : bb, (s + 1) & 3);
+                    }
+                    stores_below();
+                    commit_a((s & 1) ^ 1);
+                    if (s == 0) commit_b(f, 0, bb ^ 1, u + 4);
+                    if (!F::GS) commit_x((s & 1) ^ 1);
+                    else if (s == 1) commit_x(bb ^ 1);
+                    if (s == 1) commit_b(f, 1, bb ^ 1, u + 4);
+                    if (s == 3) bb ^= 1;
+                    __syncthreads();
+                }
+            }
+            finish(nt_tag, tot, tile, true);
+        };
+        using std::integral_constant;
+        using std::false_type;
+        using std::true_type;
+        const int nt = half ? n_tiles - nt0 : nt0;
+        if (half == 0) {
+            if (nt == 3) body(integral_constant<int, 3>{}, false_type{});
+            else if (nt == 2) body(integral_constant<int, 2>{}, false_type{});
+            else body(integral_constant<int, 1>{}, false_type{});
+        } else {
+            if (nt == 3) body(integral_constant<int, 3>{}, true_type{});
+            else if (nt == 2) body(integral_constant<int, 2>{}, true_type{});
+            else if (nt == 1) body(integral_constant<int, 1>{}, true_type{});
+            else body(integral_constant<int, 0>{}, true_type{});
+        }
+    } else {
+        // set by set, each wave every second unit; two sets of weights on their way
+        using one = std::integral_constant<int, 1>;
+        typename C::Tot tot[2][1];
+        clear(one{}, tot);
+        F f0, f1;
+        fetch_a(u0);
+        fetch_x(u0);
+        for (int h = 0; h < 2; ++h) fetch_b(f0, h, u0);
+        for (int h = 0; h < 2; ++h) fetch_b(f1, h, u0 + 4);
+        commit_a(0);
+        commit_x(0);
+        for (int h = 0; h < 2; ++h) commit_b(f0, h, 0, u0);
+        __syncthreads();
+        auto set = [&](F &in, const F &out, int u, int bb) __attribute__((always_inline)) {
+            fetch_a(u + 4);
+            fetch_x(u + 4);
+            for (int h = 0; h < 2; ++h) fetch_b(in, h, u + 8);
+            loads_above();
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                h8_t b[2][F::PLANES][4];
+                const int un = 2 * s + half;
+                unpack(b, bb, un);
+                multiply(one{}, tot, b, lds + bb * C::ABUF + col * C::PITCH + un * 128 + hh * 64, bb, un, lds + C::OFF_X + bb * C::XBUF + col * C::XPITCH + un * 16 + hh * 8);
+            }
+            if (half == bb) zero_term(one{}, tot, 0, bb);
+            stores_below();
+            for (int h = 0; h < 2; ++h) commit_b(out, h, bb ^ 1, u + 4);
+            commit_a(bb ^ 1);
+            commit_x(bb ^ 1);
+            __syncthreads();
+        };
+        for (int u = u0; u < u1; u += 8) {
+            set(f0, f1, u, 0);
+            set(f1, f0, u + 4, 1);                                       // past the end: zeros from commit_a on, one set of work for nothing
+        }
+        // the two unit parities of a row group, added in that order
+        float *const red = reinterpret_cast<float *>(lds);
+        if (half == 1) {
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) red[((rg * 2 + rt) * 16 + i) * 64 + lane] = tot[rt][0][i];
+        }
+        __syncthreads();
+        if (half == 0) {
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) tot[rt][0][i] += red[((rg * 2 + rt) * 16 + i) * 64 + lane];
+        }
+        __syncthreads();
+        finish(one{}, tot, 0, half == 0);
+    }
+}
+
+// The pairs of a step sorted by expert, ascending within one expert: a counting sort in one block of 16 waves.
+constexpr int SORT_THREADS = 1024;
+__global__ __launch_bounds__(SORT_THREADS) void k_sort_pairs(const uint8_t *expert, int n, uint16_t *plist)
+{
+    constexpr int CHUNKS = GATE_MAX_TOKENS * 4 / 64;                     // chunks of 64 pairs (64)
+    __shared__ int32_t cnt[16][CHUNKS];
+    __shared__ int32_t wave_tot[SORT_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint64_t below = (1ull << lane) - 1;
+    for (int c = wv; c < CHUNKS; c += SORT_THREADS / 64) {
+        const int q = c * 64 + lane, e = q < n ? (int)expert[q] : -1;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint64_t m = __ballot(e == k);
+            if (lane == 0) cnt[k][c] = __popcll(m);
+        }
+    }
+    __syncthreads();
+    // exclusive prefix sum over (expert, chunk): one entry per thread
+    static_assert(16 * CHUNKS == SORT_THREADS, "one entry per thread");
+    const int own = cnt[tid / CHUNKS][tid % CHUNKS];
+    int inc = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int v = __shfl_up(inc, d);
+        if (lane >= d) inc += v;
+    }
+    if (lane == 63) wave_tot[wv] = inc;
+    __syncthreads();
+    int base = inc - own;
+    for (int w = 0; w < wv; ++w) base += wave_tot[w];
+    cnt[tid / CHUNKS][tid % CHUNKS] = base;
+    __syncthreads();
+    for (int c = wv; c < CHUNKS; c += SORT_THREADS / 64) {
+        const int q = c * 64 + lane, e = q < n ? (int)expert[q] : -1;
+        int pos = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint64_t m = __ballot(e == k);
+            if (e == k) pos = cnt[k][c] + __popcll(m & below);
+        }
+        if (e >= 0) plist[pos] = (uint16_t)q;
+    }
+}
+
+}  // namespace moe

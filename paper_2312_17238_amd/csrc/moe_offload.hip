@@ -152,6 +152,15 @@ struct moe_ctx {
     uint64_t ypart_extra_used = 0;      // floats of it taken by the launches of the current step
     std::vector<int32_t> w2_parts;      // per window of the current step: parts the matrix-core w2 launches split their contraction into
     std::vector<uint8_t> win_small;     // ... and whether no expert has more than 16 tokens of the window (the 16-token tile form fits)
+    // Tile kernels: what the gate kernel leaves in device memory (expert and combine weight of every pair, sums of h per
+    // group), the pairs sorted by expert, and the sums of a per group; per step, from its routing: each expert's first
+    // position in that list and its pairs, and the parts the w2 launches split their contraction into.
+    uint8_t *pair_expert = nullptr;
+    float *pair_w = nullptr;
+    uint16_t *plist = nullptr;
+    uint32_t *xs_h = nullptr, *xs_a = nullptr;
+    int32_t tile_first[MOE_MAX_EXPERTS] = {}, tile_count[MOE_MAX_EXPERTS] = {}, tile_parts = 1;
+    bool tile_big = false;
     uint8_t *noalloc_scratch = nullptr; // this device's copy of the file-scope scratch array (moe_layer_step_noalloc)
     GateHostOut *gate_out = nullptr;    // host pointer
     GateHostOut *gate_out_dev = nullptr;// the same memory as the device sees it
@@ -202,6 +211,7 @@ struct moe_layer {
     uint16_t *gamma_dev = nullptr;
     uint8_t *host_blobs = nullptr;
     std::vector<uint32_t> loaded;       // bit m set: matrix m of the expert was loaded
+    std::atomic<bool> wide_scale{false};// a loaded 2-bit scale is too large for the tile kernels' fp16 products (below)
     std::atomic<bool> wide_meta{false}; // a loaded (scale, zero) pair is too large for the rank-1 matrix-core form (below)
     std::vector<int32_t> own_bufs;      // the k pool buffers created for this layer
     // Where each expert's blob lives on the host: buffer index into host_blobs, or -1 while it is on the device
@@ -243,7 +253,7 @@ static bool layer_cfg_ok(const moe_layer_config_t *c)
            c->scale_group >= 0 && blob_layout(c->hidden, c->ffn, c->bits, c->group, c->scale_group).ok;
 }
 
-struct ScratchPlan { uint64_t staging, h, a, yacc, ypart, ytab, ypart_extra_floats, x0, x1, barrier, route, route_log, total; };
+struct ScratchPlan { uint64_t staging, h, a, yacc, ypart, ytab, ypart_extra_floats, x0, x1, barrier, route, route_log, pair_expert, pair_w, plist, xs_h, xs_a, total; };
 
 static ScratchPlan plan_scratch(const moe_ctx_config_t *c)
 {
@@ -264,6 +274,12 @@ static ScratchPlan plan_scratch(const moe_ctx_config_t *c)
     p.barrier = off; off += 4096 + 2 * SEQ_FLAG_STRIDE * 4;     // one flag per block of the persistent kernels (at most 1024 compute units); then [2 experts][blocks]
     p.route = off; off += 256;        // device-side routing: MOE_MAX_TOPK selections and as many combine weights
     p.route_log = off; off += align_u64((uint64_t)ROUTE_LOG_ENTRIES * MOE_MAX_TOPK * sizeof(int32_t), 256);
+    p.pair_expert = off; off += align_u64(pairs, 256);
+    p.pair_w = off; off += align_u64(pairs * 4, 256);
+    p.plist = off; off += align_u64(pairs * 2, 256);
+    // sums of activations per group, 4 bytes each: room for the smallest groups (16) and rows padded to multiples of 4
+    p.xs_h = off; off += align_u64((uint64_t)c->max_batch * (c->max_hidden / 16) * 4, 256);
+    p.xs_a = off; off += align_u64(pairs * (c->max_ffn / 16) * 4, 256);
     p.total = off;
     return p;
 }
@@ -348,6 +364,11 @@ try {
     c->route_idx = reinterpret_cast<int32_t *>(base + p.route);
     c->route_w = reinterpret_cast<float *>(base + p.route + 128);
     c->route_log_dev = reinterpret_cast<int32_t *>(base + p.route_log);
+    c->pair_expert = base + p.pair_expert;
+    c->pair_w = reinterpret_cast<float *>(base + p.pair_w);
+    c->plist = reinterpret_cast<uint16_t *>(base + p.plist);
+    c->xs_h = reinterpret_cast<uint32_t *>(base + p.xs_h);
+    c->xs_a = reinterpret_cast<uint32_t *>(base + p.xs_a);
     hipError_t e = hipMemset(c->barrier, 0, 4096 + 2 * SEQ_FLAG_STRIDE * 4);
     if (e == hipSuccess) {
         int dev = 0;
@@ -627,6 +648,15 @@ static bool pair_fits_rank1(uint16_t scale, uint16_t zero)
     return std::isfinite(s) && std::isfinite(z) && (1024.f + std::fabs(z)) * std::fabs(s) <= 16384.f;
 }
 
+// The tile kernels multiply 2-bit codes (at most 2 in size, centred) with their scale in fp16, two-level scales lifted by
+// 64 first: layers with larger scales than that allows stay on the GEMV kernels.
+static bool scale_fits_tile(uint16_t scale) { return std::fabs(half_bits_to_float(scale)) <= 32000.f; }
+static bool run_fits_tile(const uint16_t m[4])
+{
+    const float step = std::fabs(half_bits_to_float(m[0])), zero = half_bits_to_float(m[1]);
+    return std::max(std::fabs(255.f - zero), std::fabs(zero)) * step <= 500.f;
+}
+
 extern "C" int32_t moe_layer_load_expert(moe_layer_t *l, int32_t expert, int32_t matrix, const uint8_t *codes,
                                          const uint16_t *scale, const uint16_t *zero)
 try {
@@ -642,6 +672,9 @@ try {
         if (watch && !l->wide_meta.load(std::memory_order_relaxed))
             for (uint32_t g = 0; g < groups; ++g)
                 if (!pair_fits_rank1(sr[g], zr[g])) { l->wide_meta.store(true, std::memory_order_relaxed); break; }
+        if (b.bits == 2)
+            for (uint32_t g = 0; g < groups; ++g)
+                if (!scale_fits_tile(sr[g])) { l->wide_scale.store(true, std::memory_order_relaxed); break; }
         pack_row(b, m, codes + (uint64_t)r * m.cols, sr, zr, dst);
     });
 } catch (...) {
@@ -658,6 +691,9 @@ try {
     const MatLayout &m = mat_of(b, matrix);
     const uint32_t groups = m.cols / b.group, runs = (groups + m.run_len - 1) / m.run_len;
     return load_matrix(l, expert, matrix, codes, [&](uint32_t r, uint8_t *dst) {
+        if (b.bits == 2)
+            for (uint32_t j = 0; j < runs; ++j)
+                if (!run_fits_tile(run_meta + ((uint64_t)r * runs + j) * 4)) { l->wide_scale.store(true, std::memory_order_relaxed); break; }
         pack_row_meta8(b, m, codes + (uint64_t)r * m.cols, scale_code + (uint64_t)r * groups, zero_code + (uint64_t)r * groups,
                        run_meta + (uint64_t)r * runs * 4, dst);
     });
@@ -1083,8 +1119,9 @@ static int32_t launch_gate(moe_ctx *c, GateArgs ga, int32_t batch)
 {
     if (++c->gate_seq == 0) ++c->gate_seq;             // 0 is what a fresh context holds
     ga.seq = c->gate_seq;
-    int32_t rc = ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true>, dim3(batch), dim3(GATE_THREADS), 0, ga)
-                        : launch_timed(c, PROF_GATE, 0, k_gate<false>, dim3(batch), dim3(GATE_THREADS), 0, ga);
+    const dim3 grid(batch), block(GATE_THREADS);
+    int32_t rc = ga.xs ? (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true, true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false, true>, grid, block, 0, ga))
+                       : (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false>, grid, block, 0, ga));
     if (rc) return rc;
     if (!c->sync_wait) HIPCHK(hipEventRecord(c->ev_gate, c->compute));
     return wait_gate(c, batch, ga.seq);
@@ -1307,7 +1344,7 @@ static int32_t launch_token(moe_layer *l, const FusedArgs &A, bool one_launch, b
 
 // Matrix-core path for one pass: every expert of the pass with all its tokens, two launches (w1/w3, w2)
 // plus the group-sum tables of their activation operands.
-struct PassExpert { const uint8_t *blob; std::vector<int> pairs; };
+struct PassExpert { const uint8_t *blob; std::vector<int> pairs; int32_t expert; };
 
 // Streaming matrix-core form: persistent blocks over (entry, 128-row block, K part) items.
 // An expert with more than 32 tokens becomes two entries (token tiles) that read the same weights.
@@ -1445,12 +1482,136 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
     return MOE_OK;
 }
 
-static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts, const float *w, int batch)
+// ---- tile kernels ----
+
+// Codes per sum of activations: the groups of the zero-point term.
+static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
+static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
+
+static bool tile_format(const moe_layer *l)
+{
+    const BlobLayout &b = l->lay;
+    if (b.bits == 2 && l->wide_scale.load(std::memory_order_relaxed)) return false;
+    const bool fits32 = 2ull * b.ffn * b.m13.row_stride < (1ull << 31) && (uint64_t)b.hidden * b.m2.row_stride < (1ull << 31);
+    return fits32 && (b.bits != 4 || b.group >= 64);
+}
+
+constexpr int TE_SMALL_TOKENS = 32;
+// token blocks of an expert: tiles of 32, up to as many per block as the kernel holds
+static int tile_blocks(const BlobLayout &b, int count, bool big)
+{
+    const int per = big ? (b.bits == 2 && b.scale_group ? TeCfg<28, true>::TOK : TeCfg<4, true>::TOK) / 32 : 1;
+    return ((count + 31) / 32 + per - 1) / per;
+}
+
+// The step's pairs per expert, where they lie in the sorted list, which kernel runs and into how many parts w2 splits
+// its contraction -- all from the routing alone, so that a result does not depend on which experts share a launch.
+static void tile_plan(moe_layer *l, const int32_t *idx, int batch)
+{
+    moe_ctx *c = l->ctx;
+    const BlobLayout &b = l->lay;
+    const int E = l->cfg.n_experts, pairs = batch * l->cfg.top_k;
+    int32_t *cnt = c->tile_count;
+    for (int e = 0; e < E; ++e) cnt[e] = 0;
+    for (int q = 0; q < pairs; ++q) cnt[idx[q]]++;
+    int first = 0, blocks = 0, most = 0;
+    for (int e = 0; e < E; ++e) { c->tile_first[e] = first; first += cnt[e]; most = std::max(most, cnt[e]); }
+    c->tile_big = most > TE_SMALL_TOKENS;
+    for (int e = 0; e < E; ++e) blocks += tile_blocks(b, cnt[e], c->tile_big);
+    const int n_cu = c->n_cu > 0 ? c->n_cu : 256, rows = c->tile_big ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
+    const int sets = (b.ffn / 64 + 3) / 4;
+    const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
+    int want = (2 * n_cu + rb * blocks - 1) / std::max(1, rb * blocks);
+    c->tile_parts = std::max(1, std::min(std::min(want, sets), cap));
+}
+
+template <int FMT, bool W13>
+static int32_t launch_tile_fmt(moe_ctx *c, bool big, int grid, uint64_t bytes, const TeArgs &A)
+{
+    static bool lds_attr_set = false;      // above the default dynamic LDS limit
+    if (!lds_attr_set) {
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tile<FMT, W13, true>), hipFuncAttributeMaxDynamicSharedMemorySize, TeCfg<FMT, true>::LDS));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tile<FMT, W13, false>), hipFuncAttributeMaxDynamicSharedMemorySize, TeCfg<FMT, false>::LDS));
+        lds_attr_set = true;
+    }
+    const int kind = W13 ? PROF_W13 : PROF_W2;
+    return big ? launch_timed(c, kind, bytes, k_tile<FMT, W13, true>, dim3(grid), dim3(TeCfg<FMT, true>::THREADS), TeCfg<FMT, true>::LDS, A)
+               : launch_timed(c, kind, bytes, k_tile<FMT, W13, false>, dim3(grid), dim3(TeCfg<FMT, false>::THREADS), TeCfg<FMT, false>::LDS, A);
+}
+
+template <bool W13>
+static int32_t launch_tile_half(moe_layer *l, bool big, int grid, uint64_t bytes, const TeArgs &A)
+{
+    switch (fmt_of(l->lay)) {
+    case 4: return launch_tile_fmt<4, W13>(l->ctx, big, grid, bytes, A);
+    case 48: return launch_tile_fmt<48, W13>(l->ctx, big, grid, bytes, A);
+    case 3: return launch_tile_fmt<3, W13>(l->ctx, big, grid, bytes, A);
+    case 38: return launch_tile_fmt<38, W13>(l->ctx, big, grid, bytes, A);
+    case 2: return launch_tile_fmt<2, W13>(l->ctx, big, grid, bytes, A);
+    case 28: return launch_tile_fmt<28, W13>(l->ctx, big, grid, bytes, A);
+    default: return fail(MOE_EINVAL, "no tile kernel for this format");
+    }
+}
+
+static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts, int batch)
+{
+    moe_ctx *c = l->ctx;
+    const BlobLayout &b = l->lay;
+    const int K = l->cfg.top_k, xg = tile_sum_group(b);
+    TeArgs A{};
+    for (const PassExpert &pe : experts) {
+        TileExpert &te = A.e[A.n_exp++];
+        te.blob = pe.blob;
+        te.first = c->tile_first[pe.expert];
+        te.count = c->tile_count[pe.expert];
+    }
+    const bool big = c->tile_big;
+    const int rows = big ? 256 : 128;
+    A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
+    A.top_k = K; A.part_base = batch * K;
+    A.unit_shift = b.group == 128 ? 1 : 0;
+    auto matrix = [&](const MatLayout &m, int Kdim, int N) {
+        A.K = Kdim; A.N = N;
+        A.stride = m.row_stride; A.meta_off = m.meta_off; A.meta2_off = m.meta2_off; A.b_off = (uint32_t)(Kdim / 64) * 16u;
+        A.run_shift = (m.run_len == 0 || m.run_len >= m.cols / (uint32_t)b.group) ? 31 : __builtin_ctz(m.run_len);
+        A.xs_stride = tile_sum_stride(Kdim, xg);
+    };
+    // items: (row block, part) jobs dealt to the XCDs round robin, an expert's token blocks of one job next to each other
+    auto shape = [&](int row_blocks, int parts) {
+        const int sets = (A.K / 64 + 3) / 4, sp = (sets + parts - 1) / parts;
+        A.units_per_part = sp * 4;
+        A.k_parts = (sets + sp - 1) / sp;
+        A.jobs = row_blocks * A.k_parts;
+        const int per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
+        int items = 0;
+        for (int i = 0; i < A.n_exp; ++i) {
+            A.e[i].tb = tile_blocks(b, A.e[i].count, big);
+            A.e[i].item0 = items;
+            items += per_xcd * A.e[i].tb;
+        }
+        return items * TE_XCD;
+    };
+    matrix(b.m13, b.hidden, b.ffn);
+    A.mat_off = b.off_w13;
+    A.act = c->h_buf; A.act_bytes = (uint32_t)batch * b.hidden * 2;
+    A.xs = c->xs_h; A.xs_bytes = (uint32_t)batch * A.xs_stride * 4;
+    A.xs_out = c->xs_a; A.xs_out_stride = tile_sum_stride(b.ffn, xg);
+    int32_t rc = launch_tile_half<true>(l, big, shape((2 * b.ffn + rows - 1) / rows, 1), (uint64_t)A.n_exp * 2 * b.ffn * b.m13.row_stride, A);
+    if (rc) return rc;
+    matrix(b.m2, b.ffn, b.hidden);
+    A.mat_off = b.off_w2;
+    A.act = c->a_buf; A.act_bytes = (uint32_t)batch * K * b.ffn * 2;
+    A.xs = c->xs_a; A.xs_bytes = (uint32_t)batch * K * A.xs_stride * 4;
+    return launch_tile_half<false>(l, big, shape((b.hidden + rows - 1) / rows, c->tile_parts), (uint64_t)A.n_exp * b.hidden * b.m2.row_stride, A);
+}
+
+static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts, const float *w, int batch, bool use_tile)
 {
     moe_ctx *c = l->ctx;
     const BlobLayout &b = l->lay;
     const int K = l->cfg.top_k;
     // the row-staging form takes up to 64 tokens per expert, indexes pairs with one byte and reads fp16 pairs only
+    if (use_tile) return launch_tile(l, experts, batch);
     if (c->mfma_form != 1 || batch > 64 || batch * K > MF_MAX_PAIRS || b.scale_group > 0) return launch_mfma_stream(l, experts, w, batch);
     MfmaArgs A{};
     int n = 0, first = 0, max_tok = 0;
@@ -1637,8 +1798,22 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     ga.x = x_in; ga.wg = l->gate_w_dev; ga.wg2 = spec ? next->gate_w_dev : nullptr;
     ga.gamma = l->gamma_dev; ga.h_out = c->h_buf; ga.h_out2 = h_out; ga.out = c->gate_out_dev;
     ga.eps = (double)cf.rms_eps; ga.H = cf.hidden; ga.E = cf.n_experts; ga.E2 = spec ? next->cfg.n_experts : 0; ga.K = cf.top_k;
+    // 4-bit group-64 layers: the tile kernels take over where an expert has more than 32 tokens, below that the 16-token
+    // kernels are the faster ones (w1/w3 + w2 of a Mixtral-shaped layer, batch 16: 88 + 50 against 130 + 65 us; batch 64:
+    // 128 + 69 against 137 + 66);
+    // which of the two it is turns on the routing, so from 33 tokens on the gate kernel prepares for both
+    const bool tiles16 = cf.bits == 4 && cf.group == 64;
+    const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && (!tiles16 || batch > TE_SMALL_TOKENS))) && tile_format(l);
+    if (tile_ready) {
+        ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
+        ga.xs = c->xs_h; ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
+    }
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;
+    if (tile_ready) {
+        hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
+        HIPCHK(hipGetLastError());
+    }
 
     const GateHostOut *go = c->gate_out;
     int32_t idx[MOE_MAX_BATCH * MOE_MAX_TOPK];
@@ -1686,8 +1861,13 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     bool spec_issued = false;          // the speculative copies went out early (prompt-sized batches, below)
     // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
     auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
-    const bool use_mfma = batch >= c->mfma_min_batch && cf.bits == 4 && cf.group == 64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2);
-    if (use_mfma) {
+    bool use_tile = false;
+    if (tile_ready) {
+        tile_plan(l, idx, batch);
+        use_tile = c->mfma_form == 6 || !tiles16 || c->tile_big;
+    }
+    const bool use_mfma = use_tile || (batch >= c->mfma_min_batch && cf.bits == 4 && cf.group == 64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2));
+    if (use_mfma && !use_tile) {
         // How many parts the w2 launches of a window split their contraction into decides the order in which a
         // pair's partial sums are added, so it must not depend on how the step's experts happen to be grouped into
         // launches (which follows from what is cached, in which buffers): it is fixed here from the routing alone,
@@ -1715,6 +1895,8 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     auto pass_expert = [&](int i) {
         PassExpert pe;
         pe.blob = c->bufs[plan.access[i].buf].ptr;
+        pe.expert = plan.access[i].expert;
+        if (use_tile) return pe;
         for (int q = 0; q < batch * cf.top_k; ++q)
             if (idx[q] == plan.access[i].expert) pe.pairs.push_back(q);
         return pe;
@@ -1725,7 +1907,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
         if (use_mfma) {
             std::vector<PassExpert> g;
             for (int i : set) g.push_back(pass_expert(i));
-            return launch_mfma(l, g, w, batch);
+            return launch_mfma(l, g, w, batch, use_tile);
         }
         std::vector<FfnEntry> entries;
         for (int i : set) {
@@ -1813,14 +1995,14 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
                 group.push_back(pass_expert(i));
             }
             if (!group.empty()) {
-                rc = launch_mfma(l, group, w, batch);
+                rc = launch_mfma(l, group, w, batch, use_tile);
                 if (rc) return rc;
             }
             for (int i : in_flight) {
                 PoolBuf &pb = c->bufs[plan.access[i].buf];
                 HIPCHK(hipStreamWaitEvent(c->compute, pb.ready, 0));
                 pb.pending = false;
-                rc = launch_mfma(l, std::vector<PassExpert>{pass_expert(i)}, w, batch);
+                rc = launch_mfma(l, std::vector<PassExpert>{pass_expert(i)}, w, batch, use_tile);
                 if (rc) return rc;
             }
             continue;
@@ -2072,7 +2254,7 @@ try {
     else if (n == "token_path") c->token_path = value != 0;
     else if (n == "spec_head_mb" && value >= 0) c->spec_head_bytes = (uint64_t)value << 20;
     else if (n == "mfma_min_batch" && value >= 1) c->mfma_min_batch = value;
-    else if (n == "mfma_form" && value >= 0 && value <= 5) c->mfma_form = value;
+    else if (n == "mfma_form" && value >= 0 && value <= 6) c->mfma_form = value;
     else if (n == "mfma16_waves" && (value == 4 || value == 8)) c->mfma16_waves = value;
     else if (n == "device_routing") c->device_routing = value != 0;
     else if (n == "staged_min_batch" && value >= 0) c->staged_min_batch = value;

@@ -1,0 +1,102 @@
+"""The tile kernels (grouped dequantize+GEMM for batches and prompts, every weight format) through the C ABI against
+the CPU oracle: edges of token tiles, of row blocks and of sets of units, every format, and that a result does not
+depend on which experts share a launch.  Bounds are those of the benchmark definition on y (harness.check_y)."""
+import numpy as np
+import pytest
+import torch
+
+import workload as W
+from oracle import moe_oracle as O
+from paper_2312_17238_amd import binding as B
+
+from harness import Model, run_teacher_forced, say
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = [((4, 64), 0), ((4, 64), 256), ((4, 128), 0), ((4, 128), 2), ((3, 64), 0), ((3, 64), 1), ((2, 16), 0), ((2, 16), 8)]
+
+
+def run(fmt, sg, H, F, E, K, k, Bn, T=1, seed=61, m=0):
+    model = Model(2 if m else 1, H, F, E, K, [fmt] * (2 if m else 1), k, m, 1e-5, max_batch=Bn, seed=seed, scale_group=sg)
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_form", 6)
+    xs = W.hidden_ar1(seed, T, Bn, H)
+    rows = (lambda t, l: sorted({0, 1, Bn // 2, Bn - 2, Bn - 1} & set(range(Bn)))) if Bn > 40 else None
+    _, _, errs = run_teacher_forced(model, xs, O.expert_ffn, rows=rows)
+    say(f"tile {fmt} {sg} H={H} F={F} E={E} K={K} k={k} B={Bn}: max abs {max(e[0] for e in errs):.2e} rel {max(e[1] for e in errs):.2e}")
+    model.close()
+
+
+@pytest.mark.parametrize("fmt,sg", FORMATS)
+@pytest.mark.parametrize("H,F,Bn", [(128, 128, 3), (384, 640, 33), (256, 896, 70)])
+def test_every_format(fmt, sg, H, F, Bn):
+    """One unit-quartet and less, rows and units that fill no block, no set; both kernels (up to and over 32 tokens)."""
+    run(fmt, sg, H, F, 4, 2, 4, Bn)
+
+
+@pytest.mark.parametrize("fmt", [(4, 64), (3, 64), (2, 16)])
+@pytest.mark.parametrize("Bn", [1, 31, 32, 33, 64, 65, 96, 97, 160, 192, 193, 385])
+def test_token_tiles(fmt, Bn):
+    """Every token needs the one expert there is: 1 to 13 token tiles, one to three token blocks, uneven halves."""
+    run(fmt, 0, 64, 192, 1, 1, 1, Bn)
+
+
+@pytest.mark.parametrize("fmt,sg", [((4, 64), 0), ((3, 64), 128), ((2, 16), 0)])
+@pytest.mark.parametrize("Bn,k,m", [(9, 2, 2), (48, 3, 2), (140, 2, 1)])
+def test_offloaded(fmt, sg, Bn, k, m):
+    """Fewer slots than needed experts: several passes, experts that arrive one by one, speculative loads."""
+    run(fmt, sg, 256, 512, 8, 2, k, Bn, T=3, m=m)
+
+
+@pytest.mark.parametrize("fmt", [(4, 64), (3, 64), (2, 16)])
+@pytest.mark.parametrize("Bn", [12, 120])
+def test_result_does_not_depend_on_the_cache(fmt, Bn):
+    """From a cold cache of few slots and with every expert resident: the same bits."""
+    ys = []
+    for k in (2, 8):
+        model = Model(1, 320, 576, 8, 2, [fmt], k, 0, 1e-5, max_batch=Bn, seed=62)
+        B.moe_ctx_set_option(model.stack.ctx, "mfma_form", 6)
+        x = W.hidden_ar1(62, 1, Bn, 320)[0].to(model.stack.device)
+        out = torch.empty_like(x)
+        for _ in range(2):
+            torch.cuda.synchronize()
+            model.stack.step_layer(0, x, out)
+            model.stack.synchronize()
+            ys.append(model.stack.read_y(Bn, 320).copy())
+        model.close()
+    for y in ys[1:]:
+        assert (y.view(np.uint32) == ys[0].view(np.uint32)).all()
+
+
+@pytest.mark.parametrize("sg", [0, 8])
+@pytest.mark.parametrize("factor", [1.0, 4e4])
+def test_large_2bit_scales(sg, factor):
+    """2-bit scales beyond what the fp16 products of the tile kernels hold: the layer stays on the GEMV kernels and
+    agrees with them bit for bit; ordinary scales agree within the order of the sums (fp16 activations between the
+    halves: half an ulp, 2^-11, may fall the other way)."""
+    H, F, Bn, E = 128, 256, 8, 2
+    ys = {}
+    for name, thr in (("tile", 3), ("gemv", 1000)):
+        model = Model(1, H, F, E, 1, [(2, 16)], E, 0, 1e-5, max_batch=Bn, seed=63, scale_group=sg)
+        model.stack.reset()
+        for e in range(E):
+            for i, mat in enumerate(W.quantized_expert(63, 0, e, H, F, 2, 16, model.device, sg)):
+                mat = list(mat)
+                if i == 0:          # w1 alone: u stays finite through SiLU, its product with v within fp16
+                    if sg:
+                        mat[3] = (mat[3].float() * torch.tensor([factor if factor > 1 else 1.0, 1.0, 1.0, 1.0], device=mat[3].device)).clamp(max=6e4).to(torch.float16)
+                    else:
+                        mat[1] = (mat[1].float() * (factor * 40 if factor > 1 else 1.0)).clamp(max=6e4).to(torch.float16)
+                model.stack.load_expert(0, e, i, *mat)
+        B.moe_ctx_set_option(model.stack.ctx, "mfma_min_batch", thr)
+        x = W.hidden_ar1(63, 1, Bn, H)[0].to(model.stack.device)
+        out = torch.empty_like(x)
+        torch.cuda.synchronize()
+        model.stack.step_layer(0, x, out)
+        model.stack.synchronize()
+        ys[name] = model.stack.read_y(Bn, H).copy()
+        model.close()
+    a, b = ys["tile"], ys["gemv"]
+    if factor > 1:
+        assert (a.view(np.uint32) == b.view(np.uint32)).all()
+    else:
+        assert np.linalg.norm(a - b) <= 2 ** -11 * np.linalg.norm(b)
