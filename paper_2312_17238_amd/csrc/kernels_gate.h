@@ -43,7 +43,8 @@ struct GateArgs {
     // groups of xs_group (16 or 64) elements, rows padded with zeros to xs_stride.
     uint8_t *pair_expert;           // [b*K + j]
     float *pair_w;                  // [b*K + j]
-    uint32_t *xs;                   // [b][xs_stride], split in two
+    uint2 *xs;                      // [b][xs_stride] (group_sums)
+    float xs_zc;
     int32_t xs_stride, xs_group;
 };
 
@@ -125,14 +126,18 @@ __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a)
         const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
                      h3 = half_bits_to_f64(hv[3]);
         if constexpr (TILE) {     // 4 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
-            float sum = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
-            sum += dpp_f<0xB1>(sum);
-            sum += dpp_f<0x4E>(sum);
+            float sa = (float)h0 + (float)h1, sb = (float)h2 + (float)h3;
+            sa += dpp_f<0xB1>(sa);
+            sb += dpp_f<0xB1>(sb);
+            sa += dpp_f<0x4E>(sa);
+            sb += dpp_f<0x4E>(sb);
             if (a.xs_group == 64) {
-                sum += dpp_f<0x141>(sum);
-                sum += dpp_f<0x140>(sum);
+                sa += dpp_f<0x141>(sa);
+                sb += dpp_f<0x141>(sb);
+                sa += dpp_f<0x140>(sa);
+                sb += dpp_f<0x140>(sb);
             }
-            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = split2(sum);
+            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = group_sums(sa, sb, a.xs_zc);
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e)
@@ -151,7 +156,7 @@ __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a)
                 }
         }
     }
-    if (TILE && a.H / a.xs_group + tid < a.xs_stride) a.xs[(size_t)b * a.xs_stride + a.H / a.xs_group + tid] = 0u;
+    if (TILE && a.H / a.xs_group + tid < a.xs_stride) a.xs[(size_t)b * a.xs_stride + a.H / a.xs_group + tid] = make_uint2(0u, 0u);
     // all logits' wave sums at once; accumulators of experts that do not exist hold zeros
     if constexpr (SPEC) {
         wave_sum_many_f64<32>(acc, lane);

@@ -1,8 +1,8 @@
 // Grouped dequantize+GEMM on the matrix cores for batches and prompts, every weight format.
 //
-// A block multiplies one expert's tokens (or up to TOK of them) with ROWS memory rows.  k_tile<.., BIG>: 8 waves, 256
-// rows x up to 192 tokens, a wave 64 rows x up to 96 tokens (two waves share each 64 rows).  k_tile<.., small>: 4
-// waves, 128 rows x up to 32 tokens, a wave 64 rows and every second unit of the contraction.
+// A block multiplies one expert's tokens (or up to TOK of them) with ROWS memory rows.  k_tile<.., TE_BIG>: 8 waves, 256
+// rows x up to 192 tokens, a wave 64 rows x up to 96 tokens (two waves share each 64 rows).  k_tile<.., 16 or 32>: 128
+// rows x up to that many tokens, the units of a set shared by the waves of 64 rows; two blocks per compute unit.
 //
 // A unit is 64 codes of a row, a set four units: 128 bytes of 4-bit codes, which 8 lanes read in one piece.  Weights
 // cross LDS once (v_mfma_f32_32x32x16 wants a row per lane; loaded that way from memory every 16-byte piece would be a
@@ -25,10 +25,16 @@
 // produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros to a multiple of
 // four groups.
 //
-// Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 666 + 344 (0.72 PFLOP/s; the
-// 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 427 + 220, 16 tokens 2-bit 126 + 63 (GEMV kernels
-// 17 x (45 + 28) and more, 213 + 103).  What bounds them: matrix and vector instructions of the two waves on a SIMD overlap
-// only in part (without any load from memory or LDS: 478 + 231), the rest is latency between the barriers.
+// Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 684 + 351 (0.7 PFLOP/s; the
+// 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 440 + 225 (GEMV kernels 6.3 ms together); 16 tokens
+// 3-bit 116 + 62, 2-bit 119 + 62 (GEMV kernels 213 + 103); 64 tokens 4-bit 131 + 65 (two 16-token tiles 129 + 71).  What
+// bounds them: matrix and vector instructions of the waves on a SIMD overlap only in part (1024 tokens without any load
+// from memory or LDS: 478 + 231), the rest is latency between the barriers; a fetch further ahead, fewer vector
+// instructions (subnormal codes) and padded rows of activations each changed less than the runs differ.
+//
+// MODE 16 and 32 (a block's tokens at most): the codes enter with the biases of their bit patterns (1024 and 64) and the
+// products start from minus what biases and ZC add up to, an fp32 number per token and group that comes with the sums
+// X; BIG has no registers left for that and subtracts from the codes.
 //
 // BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
 // other at the end of the unit before, so that one's vector work runs under the other's matrix work.
@@ -58,9 +64,9 @@ struct TeArgs {
     const uint16_t *plist;               // pair ids (token * top_k + choice), expert by expert, ascending within one
     const float *pair_w;                 // combine weight of every pair
     const uint16_t *act;                 // w1/w3: h [B][K];  w2: a [B*top_k][K]
-    const uint32_t *xs;                  // sums of act per group, split in two: [row of act][xs_stride]
+    const uint2 *xs;                     // sums of act per group (group_sums): [row of act][xs_stride]
     uint16_t *a;                         // w1/w3: SwiGLU activations [pair][N]
-    uint32_t *xs_out;                    // ... and their sums
+    uint2 *xs_out;                       // ... and their sums
     float *ypart;                        // w2: rows of N, one per pair (k_parts == 1) or per (position, part)
     uint32_t *ytab;
     int32_t K, N, top_k;
@@ -70,6 +76,7 @@ struct TeArgs {
     uint64_t mat_off;
     int32_t units_per_part, k_parts, part_base;
     int32_t jobs;                        // row blocks * k_parts
+    float zc;                            // the constant the codes are centred on
     uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
 };
 
@@ -195,6 +202,13 @@ struct Te4 : TeScaled<META8, ROWS, THREADS> {
         if (h == 1) this->template commit_meta<REC, SOFF>(rec, d, ZC, tid);
     }
     static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u) { r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16); }
+    // words of 8 codes in the 4-bit layout: the lane half's four, or those of quarter kb of the unit
+    static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4]) { t[0] = r.q.x; t[1] = r.q.y; t[2] = r.q.z; t[3] = r.q.w; }
+    static __device__ __forceinline__ void quarter(const uint8_t *row, int kb, int u, uint32_t (&t)[2])
+    {
+        const uint2 q = *reinterpret_cast<const uint2 *>(row + u * 32 + kb * 8);
+        t[0] = q.x; t[1] = q.y;
+    }
     static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[1][4])
     {
         constexpr uint32_t K1024 = 0xE408E408u, K64 = 0xD480D480u;       // -1032, -72
@@ -211,8 +225,9 @@ template <int R, int T> struct Te<48, R, T> : Te4<true, R, T> {};
 template <bool META8, int ROWS, int THREADS>
 struct Te3 : TeScaled<META8, ROWS, THREADS> {
     static constexpr float ZC = 4.f;
-    static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS, NB = ROWS * 2 / THREADS;
-    uint4 a[NA], b[NB];
+    static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS;
+    static_assert(NA >= 1 && ROWS * 2 <= THREADS, "region B is one piece per thread, repeated by threads too many");
+    uint4 a[NA], b;
     struct Raw { uint2 a; uint32_t b; };
     __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
     {
@@ -223,8 +238,7 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
             for (int i = 0; i < NA; ++i) a[i] = bl128(rs, v, min(row0 + (i * THREADS / 4) + uniform(tid / 256) * 64, n_rows - 64) * (int)g.stride + u * 16);
         } else {
             const uint32_t v = live ? (uint32_t)(tid / 2 % 64) * g.stride + (uint32_t)(tid % 2) * 16u : TE_NONE;
-#pragma unroll
-            for (int i = 0; i < NB; ++i) b[i] = bl128(rs, v, min(row0 + (i * THREADS / 2) + uniform(tid / 128) * 64, n_rows - 64) * (int)g.stride + (int)g.b_off + u * 8);
+            b = bl128(rs, v, min(row0 + uniform(tid % (ROWS * 2) / 128) * 64, n_rows - 64) * (int)g.stride + (int)g.b_off + u * 8);
             this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
         }
     }
@@ -234,8 +248,8 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
 #pragma unroll
             for (int i = 0; i < NA; ++i) *reinterpret_cast<uint4 *>(rec + (tid / 4) * REC + (tid % 4) * 16 + i * (THREADS / 4) * REC) = a[i];
         } else {
-#pragma unroll
-            for (int i = 0; i < NB; ++i) *reinterpret_cast<uint4 *>(rec + (tid / 2) * REC + (tid % 2) * 16 + 64 + i * (THREADS / 2) * REC) = b[i];
+            const int tb = tid % (ROWS * 2);
+            *reinterpret_cast<uint4 *>(rec + (tb / 2) * REC + (tb % 2) * 16 + 64) = b;
             this->template commit_meta<REC, SOFF>(rec, d, ZC, tid);
         }
     }
@@ -244,16 +258,30 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
         r.a = *reinterpret_cast<const uint2 *>(row + u * 16 + hh * 8);
         r.b = *reinterpret_cast<const uint32_t *>(row + 64 + u * 8 + hh * 4);
     }
+    static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4])
+    {
+        t[0] = (r.a.x & 0x33333333u) | ((r.b << 2) & 0x44444444u);
+        t[1] = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & 0x44444444u);
+        t[2] = (r.a.y & 0x33333333u) | (r.b & 0x44444444u);
+        t[3] = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & 0x44444444u);
+    }
+    static __device__ __forceinline__ void quarter(const uint8_t *row, int kb, int u, uint32_t (&t)[2])
+    {
+        const uint32_t a = *reinterpret_cast<const uint32_t *>(row + u * 16 + kb * 4);
+        const uint32_t b = *reinterpret_cast<const uint32_t *>(row + 64 + u * 8 + (kb >> 1) * 4) >> (2 * (kb & 1));
+        t[0] = (a & 0x33333333u) | ((b << 2) & 0x44444444u);
+        t[1] = ((a >> 2) & 0x33333333u) | ((b << 1) & 0x44444444u);
+    }
     static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[1][4])
     {
         constexpr uint32_t K1024 = 0xE404E404u, K64 = 0xD440D440u;       // -1028, -68
         const BiasPatterns p = bias_patterns();
-        const uint32_t t0 = (r.a.x & 0x33333333u) | ((r.b << 2) & 0x44444444u), t1 = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & 0x44444444u);
-        const uint32_t t2 = (r.a.y & 0x33333333u) | (r.b & 0x44444444u), t3 = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & 0x44444444u);
-        b[0][0] = centred4(t0, p, K1024, K64);
-        b[0][1] = centred4(t1, p, K1024, K64);
-        b[0][2] = centred4(t2, p, K1024, K64);
-        b[0][3] = centred4(t3, p, K1024, K64);
+        uint32_t t[4];
+        words(r, t);
+        b[0][0] = centred4(t[0], p, K1024, K64);
+        b[0][1] = centred4(t[1], p, K1024, K64);
+        b[0][2] = centred4(t[2], p, K1024, K64);
+        b[0][3] = centred4(t[3], p, K1024, K64);
     }
 };
 template <int R, int T> struct Te<3, R, T> : Te3<false, R, T> {};
@@ -345,6 +373,27 @@ struct Te2 {
         const float s0 = lo_half(r.q.y), s1 = lo_half(r.q.w);
         return make_uint2(split2(s0 - s0 * hi_half(r.q.y)), split2(s1 - s1 * hi_half(r.q.w)));
     }
+    // a quarter of a unit is one group: its two words of weights per plane
+    static __device__ __forceinline__ uint2 quarter(const uint8_t *row, int kb, int u, h8_t (&b)[PLANES][2])
+    {
+        const Patterns2 p = patterns2();
+        const uint2 q = *reinterpret_cast<const uint2 *>(row + u * 32 + kb * 8);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            h2_t c[4];
+            centred2(k ? q.x >> 8 : q.x, p, c);
+#pragma unroll
+            for (int pl = 0; pl < PLANES; ++pl) {
+                const _Float16 s = as_h2(q.y)[pl];
+                const h2_t s2 = {s, s};
+                const h2_t v0 = c[0] * s2, v1 = c[1] * s2, v2 = c[2] * s2, v3 = c[3] * s2;
+                h8_t x;
+                x[0] = v0.x; x[1] = v0.y; x[2] = v1.x; x[3] = v1.y; x[4] = v2.x; x[5] = v2.y; x[6] = v3.x; x[7] = v3.y;
+                b[pl][k] = x;
+            }
+        }
+        return q;
+    }
     static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[PLANES][4])
     {
         const Patterns2 p = patterns2();
@@ -370,29 +419,43 @@ template <int R, int T> struct Te<28, R, T> : Te2<true, R, T> {};
 
 // ---------------------------------------------------------------------------------------------
 
-template <int FMT, bool BIG> struct TeCfg {
-    static constexpr int THREADS = BIG ? 512 : 256, RG = BIG ? 4 : 2, ROWS = RG * 64;
+// MODE: tokens per block at most -- TE_BIG: several tiles of 32; 32 or 16: one tile of that many
+constexpr int TE_BIG = 0;
+
+template <int FMT, int MODE> struct TeCfg {
+    static constexpr bool BIG = MODE == TE_BIG;
+    // MODE 16: 8 waves or 4, measured (w1/w3 + w2 us, Mixtral-shaped, 16 tokens): 4-bit 106 + 55 / 112 + 57, two-level
+    // 2-bit 171 + 85 / 182 + 93; 3-bit 134 + 69 / 116 + 62, 2-bit 123 + 61 / 119 + 62.  MODE 32: 8 waves would not fit 128 registers.
+    static constexpr int THREADS = MODE == 32 || (MODE == 16 && (FMT == 3 || FMT == 38 || FMT == 2)) ? 256 : 512, RG = BIG ? 4 : 2, ROWS = RG * 64;
+    static constexpr int KW = THREADS / 64 / RG;                         // waves of a row group (MODE 16, 32: each a share of a set's units)
+    static constexpr int WAVES_EU = MODE == 16 && THREADS == 512 ? 4 : 2; // waves per SIMD
     using F = Te<FMT, ROWS, THREADS>;
     static constexpr int MT = BIG ? (F::PLANES == 1 ? 3 : 2) : 1;                // token tiles of 32 per wave
-    static constexpr int TOK = BIG ? 2 * MT * 32 : 32;
+    static constexpr int TOK = BIG ? 2 * MT * 32 : MODE;
     static constexpr int SU = BIG ? 1 : 4;                               // units of activations per staging step
     static constexpr int PITCH = SU * 128 + 16;                          // staged bytes per token (+16: bank spread)
     static constexpr int NP = TOK * SU * 8 / THREADS;                    // 16-byte pieces per thread and step
     static constexpr int REC = F::REC;
     static constexpr int ABUF = TOK * PITCH, BBUF = ROWS * REC, DBUF = ROWS * F::DB;
     // sums: 16 bytes are four groups, of a set (GS) or of one unit: XQ pieces per token and staging step
-    static constexpr int XQ = F::GS ? 1 : SU, XPITCH = XQ == 1 ? 16 : XQ * 16 + 16, XBUF = TOK * XPITCH;
-    static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_T = OFF_X + 2 * XBUF;
+    // (8 bytes each: the split sum, and minus the sum weighted with the codes' biases, which only GS at MODE 16 and 32 takes)
+    static constexpr int XQ = F::GS ? 2 : SU * 2, XPITCH = XQ == 2 ? 16 : XQ * 8 + 16, XBUF = TOK * XPITCH;
+    static constexpr bool BIASED = F::GS && !BIG;
+    static constexpr int PBUF = BIASED ? 4 * TOK * 4 : 0;
+    static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_P = OFF_X + 2 * XBUF, OFF_END = OFF_P + 2 * PBUF;
+    static constexpr int OFF_RED = THREADS / 64 * (MODE == 16 ? 4096 : 8192);    // MODE 16, 32: behind the waves' partial sums
+    static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
+    static constexpr int OFF_A = BIG ? 0 : OFF_RED, OFF_T = BIG || OFF_END > OFF_RED + TOK * APITCH ? OFF_END : OFF_RED + TOK * APITCH;
     static constexpr int LDS = OFF_T + TOK * 8;
     using Tot = std::conditional_t<F::GS, float[16], f32x16_t>;
-    static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
     static_assert(OFF_X >= TOK * APITCH && LDS <= (BIG || F::PLANES == 2 ? 160 : 80) * 1024, "the epilogue reuses the staging buffers");
 };
 
-template <int FMT, bool W13, bool BIG>
-__global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A)
+template <int FMT, bool W13, int MODE>
+__global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAVES_EU)) void k_tile(TeArgs A)
 {
-    using C = TeCfg<FMT, BIG>;
+    using C = TeCfg<FMT, MODE>;
+    constexpr bool BIG = C::BIG;
     using F = typename C::F;
     constexpr int THREADS = C::THREADS, ROWS = C::ROWS, NP = C::NP, SU = C::SU, PPT = SU * 8;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -409,9 +472,10 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
     const int job = (j / ex.tb) * TE_XCD + (int)blockIdx.x % TE_XCD, t = j % ex.tb;
     if (job >= A.jobs) return;                                           // whole block, before any barrier
     const int rb = job / A.k_parts, part = job % A.k_parts;
-    const int tiles = (ex.count + 31) / 32;
+    constexpr int TILE = BIG ? 32 : MODE;                                // tokens per tile
+    const int tiles = (ex.count + TILE - 1) / TILE;
     const int tile0 = t * tiles / ex.tb, n_tiles = (t + 1) * tiles / ex.tb - tile0;
-    const int tok0 = tile0 * 32, n_tok = min(ex.count - tok0, n_tiles * 32);
+    const int tok0 = tile0 * TILE, n_tok = min(ex.count - tok0, n_tiles * TILE);
     const int n_rows = W13 ? 2 * A.N : A.N, row0 = rb * ROWS;
     const int u0 = part * A.units_per_part, u1 = min(A.K / 64, u0 + A.units_per_part);
     if (tid < C::TOK) {
@@ -424,7 +488,7 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
     // ---------------- staging ----------------
     const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(ex.blob + A.mat_off), 0, n_rows * (int)A.stride, 0x00020000);
     const __amdgpu_buffer_rsrc_t a_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(A.act), 0, (int)A.act_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(A.xs), 0, (int)A.xs_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint2 *>(A.xs), 0, (int)A.xs_bytes, 0x00020000);
     const TeGeom geo = {A.stride, A.meta_off, A.meta2_off, A.b_off, A.unit_shift, A.run_shift, A.K / 64};
     auto act_row = [&](int tk) __attribute__((always_inline)) { const int p = l_pair[tk]; return W13 ? p / A.top_k : p; };
     uint32_t a_off[NP];
@@ -436,24 +500,31 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
     // sums: piece p of a step is token p / XQ; threads too many repeat a piece (a branch less)
     constexpr int XQ = C::XQ, XU = F::GS ? 1 : 4;                        // XU: groups per unit
     static_assert(C::TOK * XQ <= THREADS && THREADS % XQ == 0, "one piece per thread");
-    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * 16;
-    const uint32_t x_off = xp / XQ < n_tok ? (uint32_t)act_row(xp / XQ) * (uint32_t)A.xs_stride * 4u + (uint32_t)(xp % XQ) * 16u : TE_NONE;
-    uint4 st[NP], stx;
-    auto fetch_a = [&](int u) __attribute__((always_inline)) {                                          // units u .. u + SU - 1; zeros from u1 on
+    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * 8;
+    const uint32_t x_off = xp / XQ < n_tok ? (uint32_t)act_row(xp / XQ) * (uint32_t)A.xs_stride * 8u + (uint32_t)(xp % XQ) * 16u : TE_NONE;
+    struct Acts { uint4 a[NP], x; };                                     // activations and sums of one step on their way to LDS
+    auto fetch_a = [&](Acts &t, int u) __attribute__((always_inline)) {                                          // units u .. u + SU - 1; zeros from u1 on
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int un = SU == 1 ? u : u + (tid % PPT) / 8;
-            st[i] = bl128(a_rs, un < u1 ? a_off[i] : TE_NONE, u * 128);
+            t.a[i] = bl128(a_rs, un < u1 ? a_off[i] : TE_NONE, u * 128);
         }
     };
-    auto commit_a = [&](int b) __attribute__((always_inline)) {
+    auto commit_a = [&](const Acts &t, int b) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            *reinterpret_cast<uint4 *>(lds + (tid / PPT) * C::PITCH + (tid % PPT) * 16 + b * C::ABUF + i * (THREADS / PPT) * C::PITCH) = st[i];
+            *reinterpret_cast<uint4 *>(lds + (tid / PPT) * C::PITCH + (tid % PPT) * 16 + b * C::ABUF + i * (THREADS / PPT) * C::PITCH) = t.a[i];
         }
     };
-    auto fetch_x = [&](int u) __attribute__((always_inline)) { stx = bl128(x_rs, (F::GS ? u : u + xp % XQ) < u1 ? x_off : TE_NONE, u * (XU * 4)); };
-    auto commit_x = [&](int b) __attribute__((always_inline)) { *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = stx; };
+    auto fetch_x = [&](Acts &t, int u) __attribute__((always_inline)) { t.x = bl128(x_rs, (F::GS ? u : u + xp % XQ / 2) < u1 ? x_off : TE_NONE, u * (XU * 8)); };
+    auto commit_x = [&](const Acts &t, int b) __attribute__((always_inline)) {
+        *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
+        if constexpr (C::BIASED) {                                       // [unit of the set][token]
+            uint32_t *const to = reinterpret_cast<uint32_t *>(lds + C::OFF_P + b * C::PBUF) + (xp % XQ) * 2 * C::TOK + xp / XQ;
+            to[0] = t.x.y;
+            to[C::TOK] = t.x.w;
+        }
+    };
     // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
     auto fetch_b = [&](F &f, int h, int u) __attribute__((always_inline)) { f.fetch(h, w_rs, geo, row0, n_rows, u < u1 ? u : u0, u < u1, tid); };
     auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, tid); };
@@ -499,6 +570,7 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
                     for (int k = 0; k < 4; ++k) g = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k], b[rt][0][k], g, 0, 0, 0);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) tot[rt][mt][i] = __builtin_fmaf(sc[rt], g[i], tot[rt][mt][i]);
+                    __builtin_amdgcn_sched_barrier(0);                   // one product in registers at a time
                 }
             } else {
                 const uint2 xv = *reinterpret_cast<const uint2 *>(xsrc + mt * 32 * C::XPITCH);
@@ -544,72 +616,55 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
                 for (int i = 0; i < 16; ++i) tot[rt][mt][i] = 0.f;
     };
 
-    // ---------------- epilogue: NT tiles from tile number `tile` of the block on; all waves pass its barriers ----------------
-    // w1/w3: even columns hold w1's rows, odd ones w3's: SiLU(u) v, rounded to fp16, collected in LDS so that rows of a
-    // leave in 16-byte pieces and their sums per group are taken on the way
-    auto finish = [&](auto nt_tag, const auto &tot, int tile, bool owner) __attribute__((always_inline)) {
-        constexpr int NT = decltype(nt_tag)::value;
+    // ---------------- epilogue ----------------
+    // w1/w3: even columns hold w1's rows, odd ones w3's: SiLU(u) v, rounded to fp16, collected in LDS (put) so that rows of
+    // a leave in 16-byte pieces and their sums per group are taken on the way (copy_out).  w2: put stores.
+    auto put = [&](float v, int tk, int wrow) __attribute__((always_inline)) {
+        v *= F::POST;
         if constexpr (W13) {
-            if (owner) {
-#pragma unroll
-                for (int mt = 0; mt < NT; ++mt)
-#pragma unroll
-                    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const float v = tot[rt][mt][i] * F::POST, other = dpp_f<0xB1>(v);
-                            const int tk = (tile + mt) * 32 + 8 * (i / 4) + 4 * hh + (i % 4);
-                            if ((lane & 1) == 0)
-                                *reinterpret_cast<uint16_t *>(lds + tk * C::APITCH + rg * 64 + rt * 32 + col) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
-                        }
-            }
+            const float other = dpp_f<0xB1>(v);
+            if ((lane & 1) == 0)
+                *reinterpret_cast<uint16_t *>(lds + C::OFF_A + tk * C::APITCH + rg * 64 + wrow) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
+        } else {
+            const int mrow = row0 + rg * 64 + wrow;
+            const int row = A.k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * A.k_parts + part;
+            if (tk < n_tok && mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = l_w[tk] * v;
+        }
+    };
+    auto copy_out = [&]() __attribute__((always_inline)) {
+        if constexpr (W13) {
             __syncthreads();
             constexpr int CPT = C::ACOLS / 8, XG = F::GPU == 1 ? 64 : 16;         // 16-byte pieces per token, columns per sum
-            for (int p = tid; p < n_tiles * 32 * CPT; p += THREADS) {
+            for (int p = tid; p < n_tiles * TILE * CPT; p += THREADS) {
                 const int tk = p / CPT, c = p % CPT, colg = rb * C::ACOLS + c * 8;
                 const bool in = colg < A.N;                              // N is a multiple of 64: a piece is in or out as a whole
-                const u32x4_t q = *reinterpret_cast<const u32x4_t *>(lds + tk * C::APITCH + c * 16);
+                const u32x4_t q = *reinterpret_cast<const u32x4_t *>(lds + C::OFF_A + tk * C::APITCH + c * 16);
                 const h2_t ones = {(_Float16)1.f, (_Float16)1.f};
-                float x = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x = __builtin_amdgcn_fdot2(as_h2(q[i]), ones, x, false);
-                x = in ? x : 0.f;
-                x += dpp_f<0xB1>(x);                                     // two lanes: 16 columns
+                float xa = __builtin_amdgcn_fdot2(as_h2(q[0]), ones, 0.f, false), xb = __builtin_amdgcn_fdot2(as_h2(q[1]), ones, 0.f, false);
+                xa = in ? __builtin_amdgcn_fdot2(as_h2(q[2]), ones, xa, false) : 0.f;
+                xb = in ? __builtin_amdgcn_fdot2(as_h2(q[3]), ones, xb, false) : 0.f;
+                xa += dpp_f<0xB1>(xa);                                   // two lanes: 16 columns
+                xb += dpp_f<0xB1>(xb);
                 if constexpr (XG == 64) {
-                    x += dpp_f<0x4E>(x);
-                    x += dpp_f<0x141>(x);
+                    xa += dpp_f<0x4E>(xa);
+                    xb += dpp_f<0x4E>(xb);
+                    xa += dpp_f<0x141>(xa);
+                    xb += dpp_f<0x141>(xb);
                 }
                 if (tk < n_tok) {
                     const int pr = l_pair[tk];
                     if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
-                    uint32_t *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
+                    uint2 *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
                     const int g = colg / XG;
-                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = split2(x);
+                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = group_sums(xa, xb, A.zc);
                     if (c == 0 && (rb + 1) * C::ACOLS >= A.N)            // the padding behind the last group that no row block covers
-                        for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = 0u;
+                        for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
                 }
             }
-        } else {
-            if (rb == 0 && part == 0 && tid < n_tok) {                   // one block per token block tells k_combine where the rows are
-                const int pr = l_pair[tid];
-                const int row = A.k_parts == 1 ? pr : A.part_base + (ex.first + tok0 + tid) * A.k_parts;
-                A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)A.k_parts);
-            }
-            if (!owner) return;
-#pragma unroll
-            for (int mt = 0; mt < NT; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int tk = (tile + mt) * 32 + 8 * (i / 4) + 4 * hh + (i % 4);
-                    if (tk >= n_tok) continue;
-                    const int row = A.k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * A.k_parts + part;
-                    const float w = l_w[tk];
-#pragma unroll
-                    for (int rt = 0; rt < 2; ++rt) {
-                        const int mrow = row0 + rg * 64 + rt * 32 + col;
-                        if (mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = w * (tot[rt][mt][i] * F::POST);
-                    }
-                }
+        } else if (rb == 0 && part == 0 && tid < n_tok) {                // one block per token block tells k_combine where the rows are
+            const int pr = l_pair[tid];
+            const int row = A.k_parts == 1 ? pr : A.part_base + (ex.first + tok0 + tid) * A.k_parts;
+            A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)A.k_parts);
         }
     };
 
@@ -618,12 +673,13 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
         const int nt0 = (n_tiles + 1) / 2;
         {
             F f;
-            fetch_a(u0);
-            fetch_x(u0);
+            Acts t;
+            fetch_a(t, u0);
+            fetch_x(t, u0);
             fetch_b(f, 0, u0);
             fetch_b(f, 1, u0);
-            commit_a(0);
-            commit_x(0);
+            commit_a(t, 0);
+            commit_x(t, 0);
             commit_b(f, 0, 0, u0);
             commit_b(f, 1, 0, u0);
         }
@@ -638,14 +694,15 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
             if (LATE && NT > 0) unpack(b, 0, 0);
             int bb = 0;
             F f;
+            Acts t;
             for (int u = u0; u < u1; u += 4) {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    fetch_a(u + s + 1);
-                    if (s == 0) fetch_b(f, 0, u + 4);
+                    fetch_a(t, u + s + 1);
+                    if (s == 0) fetch_b(f, 0, u + 4);            // weights of the next set in two halves: registers
                     if (s == 1) fetch_b(f, 1, u + 4);
-                    if (!F::GS) fetch_x(u + s + 1);
-                    else if (s == 1) fetch_x(u + 4);
+                    if (!F::GS) fetch_x(t, u + s + 1);
+                    else if (s == 1) fetch_x(t, u + 4);
                     loads_above();
                     if constexpr (NT > 0) {
                         if (!LATE) unpack(b, bb, s);
@@ -655,16 +712,22 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
                         if (LATE) unpack(b, s == 3 ? bb ^ 1 : bb, (s + 1) & 3);
                     }
                     stores_below();
-                    commit_a((s & 1) ^ 1);
+                    commit_a(t, (s & 1) ^ 1);
                     if (s == 0) commit_b(f, 0, bb ^ 1, u + 4);
-                    if (!F::GS) commit_x((s & 1) ^ 1);
-                    else if (s == 1) commit_x(bb ^ 1);
+                    if (!F::GS) commit_x(t, (s & 1) ^ 1);
+                    else if (s == 1) commit_x(t, bb ^ 1);
                     if (s == 1) commit_b(f, 1, bb ^ 1, u + 4);
                     if (s == 3) bb ^= 1;
                     __syncthreads();
                 }
             }
-            finish(nt_tag, tot, tile, true);
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt) put(tot[rt][mt][i], (tile + mt) * 32 + 8 * (i / 4) + 4 * hh + (i % 4), rt * 32 + col);
+            copy_out();
         };
         using std::integral_constant;
         using std::false_type;
@@ -681,59 +744,154 @@ __global__ __launch_bounds__((TeCfg<FMT, BIG>::THREADS), 2) void k_tile(TeArgs A
             else body(integral_constant<int, 0>{}, true_type{});
         }
     } else {
-        // set by set, each wave every second unit; two sets of weights on their way
-        using one = std::integral_constant<int, 1>;
-        typename C::Tot tot[2][1];
-        clear(one{}, tot);
+        // set by set, the units of a set shared by the waves of a row group; two sets of weights on their way
+        constexpr int RT = MODE == 32 ? 2 : 4, NR = MODE == 32 ? 16 : 4;         // row tiles of a wave, registers of a tile
+        constexpr int RROWS = 64 / RT;                                   // rows per tile: 32 or 16
+        const int rcol = lane % RROWS, kb = lane / RROWS;                // the lane's row of a tile, its half or quarter of a unit
+        using Acc = std::conditional_t<MODE == 32, f32x16_t, f32x4_t>;
+        auto mm = [&](h8_t a, h8_t b, Acc c) __attribute__((always_inline)) {
+            if constexpr (MODE == 32) return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+            else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+        };
+        auto mmb = [&](bf8_t a, bf8_t b, Acc c) __attribute__((always_inline)) {
+            if constexpr (MODE == 32) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+            else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+        };
+        Acc tot[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int i = 0; i < NR; ++i) tot[rt][i] = 0.f;
+        const BiasPatterns bp = bias_patterns();
+        const uint8_t *const rec0 = lds + C::OFF_B + (rg * 64 + rcol) * C::REC;
+        // one unit of the wave's rows
+        auto unit = [&](int bb, int un) __attribute__((always_inline)) {
+            constexpr int KS = MODE == 32 ? 4 : 2;                       // k-steps of a unit
+            const uint8_t *src = lds + bb * C::ABUF + rcol * C::PITCH + un * 128 + kb * (KS * 16);
+            h8_t a[KS];
+#pragma unroll
+            for (int k = 0; k < KS; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + k * 16);
+            if constexpr (F::GS) {
+                // the codes with their biases; the products start from minus what biases and centre add up to
+                Acc p0;
+                const float *const pp = reinterpret_cast<const float *>(lds + C::OFF_P + bb * C::PBUF) + un * C::TOK + 4 * kb;
+#pragma unroll
+                for (int i = 0; i < NR; i += 4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(pp + 2 * i);
+                    p0[i] = v.x; p0[i + 1] = v.y; p0[i + 2] = v.z; p0[i + 3] = v.w;
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const uint8_t *rec = rec0 + bb * C::BBUF + rt * RROWS * C::REC;
+                    const float sc = *reinterpret_cast<const float *>(rec + F::SOFF + un * 4);
+                    uint32_t t[KS];
+                    if constexpr (MODE == 32) {
+                        typename F::Raw raw;
+                        F::read(raw, rec, kb, un);
+                        F::words(raw, t);
+                    } else {
+                        F::quarter(rec, kb, un, t);
+                    }
+                    Acc g = p0;
+#pragma unroll
+                    for (int k = 0; k < KS; ++k) g = mm(a[k], codes_biased(t[k], bp), g);
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) tot[rt][i] = __builtin_fmaf(sc, g[i], tot[rt][i]);
+                }
+            } else {
+                const uint8_t *const xp0 = lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + un * 16;
+                bf8_t xv;
+                if constexpr (MODE == 32) {
+                    xv = slots_x(*reinterpret_cast<const uint2 *>(xp0 + kb * 8));
+                } else {                                                 // one group per lane: half of its slots
+                    const uint32_t x = *reinterpret_cast<const uint32_t *>(xp0 + kb * 4);
+                    xv = __builtin_bit_cast(bf8_t, u32x4_t{x, x, 0u, 0u});
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const uint8_t *rec = rec0 + bb * C::BBUF + rt * RROWS * C::REC;
+                    const uint8_t *drow = lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * RROWS + rcol) * F::DB;
+                    h8_t b[F::PLANES][KS];
+                    bf8_t d;
+                    if constexpr (MODE == 32) {
+                        typename F::Raw raw;
+                        F::read(raw, rec, kb, un);
+                        F::decode(raw, b);
+                        d = slots_d(F::factors(rec, drow, kb, un));
+                    } else {
+                        const uint2 q = F::quarter(rec, kb, un, b);
+                        uint32_t v;
+                        if constexpr (F::DB > 0) v = *reinterpret_cast<const uint32_t *>(drow + un * 16 + kb * 4);
+                        else v = split2(lo_half(q.y) - lo_half(q.y) * hi_half(q.y));
+                        d = slots_d(make_uint2(v, 0u));
+                    }
+#pragma unroll
+                    for (int k = 0; k < KS; ++k)
+#pragma unroll
+                        for (int pl = 0; pl < F::PLANES; ++pl) tot[rt] = mm(a[k], b[pl][k], tot[rt]);
+                    tot[rt] = mmb(xv, d, tot[rt]);
+                }
+            }
+        };
+        // GS: the zero-point term of a set (its four groups: with 16-token tiles half of the k-slots)
+        auto set_term = [&](int bb) __attribute__((always_inline)) {
+            uint2 xw = *reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + (kb & 1) * 8);
+            if (MODE == 16 && kb > 1) xw = make_uint2(0u, 0u);
+            const bf8_t xv = slots_x(xw);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+                tot[rt] = mmb(xv, slots_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * RROWS + rcol) * F::DB + (kb & 1) * 8)), tot[rt]);
+        };
+        // Two sets are on their way, activations as well as weights (one alone takes longer to arrive than a set to multiply)
         F f0, f1;
-        fetch_a(u0);
-        fetch_x(u0);
-        for (int h = 0; h < 2; ++h) fetch_b(f0, h, u0);
-        for (int h = 0; h < 2; ++h) fetch_b(f1, h, u0 + 4);
-        commit_a(0);
-        commit_x(0);
-        for (int h = 0; h < 2; ++h) commit_b(f0, h, 0, u0);
+        Acts t0, t1;
+        auto fetch = [&](F &f, Acts &t, int u) __attribute__((always_inline)) {
+            fetch_a(t, u);
+            fetch_x(t, u);
+            for (int h = 0; h < 2; ++h) fetch_b(f, h, u);
+        };
+        auto commit = [&](const F &f, const Acts &t, int b, int u) __attribute__((always_inline)) {
+            commit_a(t, b);
+            commit_x(t, b);
+            for (int h = 0; h < 2; ++h) commit_b(f, h, b, u);
+        };
+        fetch(f0, t0, u0);
+        fetch(f1, t1, u0 + 4);
+        commit(f0, t0, 0, u0);
         __syncthreads();
-        auto set = [&](F &in, const F &out, int u, int bb) __attribute__((always_inline)) {
-            fetch_a(u + 4);
-            fetch_x(u + 4);
-            for (int h = 0; h < 2; ++h) fetch_b(in, h, u + 8);
+        auto set = [&](F &fin, Acts &tin, const F &fout, const Acts &tout, int u, int bb) __attribute__((always_inline)) {
+            fetch(fin, tin, u + 8);
             loads_above();
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                h8_t b[2][F::PLANES][4];
-                const int un = 2 * s + half;
-                unpack(b, bb, un);
-                multiply(one{}, tot, b, lds + bb * C::ABUF + col * C::PITCH + un * 128 + hh * 64, bb, un, lds + C::OFF_X + bb * C::XBUF + col * C::XPITCH + un * 16 + hh * 8);
-            }
-            if (half == bb) zero_term(one{}, tot, 0, bb);
+            for (int un = 0; un < 4; un += C::KW) unit(bb, un + half);
+            if constexpr (F::GS) if (half == bb) set_term(bb);
             stores_below();
-            for (int h = 0; h < 2; ++h) commit_b(out, h, bb ^ 1, u + 4);
-            commit_a(bb ^ 1);
-            commit_x(bb ^ 1);
+            commit(fout, tout, bb ^ 1, u + 4);
             __syncthreads();
         };
         for (int u = u0; u < u1; u += 8) {
-            set(f0, f1, u, 0);
-            set(f1, f0, u + 4, 1);                                       // past the end: zeros from commit_a on, one set of work for nothing
+            set(f0, t0, f1, t1, u, 0);
+            set(f1, t1, f0, t0, u + 4, 1);                               // past the end: zeros, one set of work for nothing
         }
-        // the two unit parities of a row group, added in that order
+        // the waves of a row group hold partial sums of the same outputs: each adds up its share of the row tiles, in the
+        // order of the waves
         float *const red = reinterpret_cast<float *>(lds);
-        if (half == 1) {
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt)
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) red[((rg * 2 + rt) * 16 + i) * 64 + lane] = tot[rt][0][i];
-        }
+            for (int i = 0; i < NR; ++i) red[((wv * RT + rt) * NR + i) * 64 + lane] = tot[rt][i];
         __syncthreads();
-        if (half == 0) {
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt)
+        for (int r = 0; r < RT / C::KW; ++r)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) tot[rt][0][i] += red[((rg * 2 + rt) * 16 + i) * 64 + lane];
-        }
-        __syncthreads();
-        finish(one{}, tot, 0, half == 0);
+            for (int i = 0; i < NR; ++i) {
+                const int rt = half * (RT / C::KW) + r;
+                float v = 0.f;
+#pragma unroll
+                for (int w = 0; w < C::KW; ++w) v += red[(((w * C::RG + rg) * RT + rt) * NR + i) * 64 + lane];
+                put(v, MODE == 32 ? 8 * (i / 4) + 4 * kb + i % 4 : 4 * kb + i, rt * RROWS + rcol);
+            }
+        copy_out();
     }
 }
 

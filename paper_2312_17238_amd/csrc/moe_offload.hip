@@ -158,9 +158,8 @@ struct moe_ctx {
     uint8_t *pair_expert = nullptr;
     float *pair_w = nullptr;
     uint16_t *plist = nullptr;
-    uint32_t *xs_h = nullptr, *xs_a = nullptr;
-    int32_t tile_first[MOE_MAX_EXPERTS] = {}, tile_count[MOE_MAX_EXPERTS] = {}, tile_parts = 1;
-    bool tile_big = false;
+    uint2 *xs_h = nullptr, *xs_a = nullptr;
+    int32_t tile_first[MOE_MAX_EXPERTS] = {}, tile_count[MOE_MAX_EXPERTS] = {}, tile_parts = 1, tile_mode = TE_BIG, tile_most = 0;
     uint8_t *noalloc_scratch = nullptr; // this device's copy of the file-scope scratch array (moe_layer_step_noalloc)
     GateHostOut *gate_out = nullptr;    // host pointer
     GateHostOut *gate_out_dev = nullptr;// the same memory as the device sees it
@@ -277,9 +276,9 @@ static ScratchPlan plan_scratch(const moe_ctx_config_t *c)
     p.pair_expert = off; off += align_u64(pairs, 256);
     p.pair_w = off; off += align_u64(pairs * 4, 256);
     p.plist = off; off += align_u64(pairs * 2, 256);
-    // sums of activations per group, 4 bytes each: room for the smallest groups (16) and rows padded to multiples of 4
-    p.xs_h = off; off += align_u64((uint64_t)c->max_batch * (c->max_hidden / 16) * 4, 256);
-    p.xs_a = off; off += align_u64(pairs * (c->max_ffn / 16) * 4, 256);
+    // sums of activations per group, 8 bytes each: room for the smallest groups (16) and rows padded to multiples of 4
+    p.xs_h = off; off += align_u64((uint64_t)c->max_batch * (c->max_hidden / 16) * 8, 256);
+    p.xs_a = off; off += align_u64(pairs * (c->max_ffn / 16) * 8, 256);
     p.total = off;
     return p;
 }
@@ -367,8 +366,8 @@ try {
     c->pair_expert = base + p.pair_expert;
     c->pair_w = reinterpret_cast<float *>(base + p.pair_w);
     c->plist = reinterpret_cast<uint16_t *>(base + p.plist);
-    c->xs_h = reinterpret_cast<uint32_t *>(base + p.xs_h);
-    c->xs_a = reinterpret_cast<uint32_t *>(base + p.xs_a);
+    c->xs_h = reinterpret_cast<uint2 *>(base + p.xs_h);
+    c->xs_a = reinterpret_cast<uint2 *>(base + p.xs_a);
     hipError_t e = hipMemset(c->barrier, 0, 4096 + 2 * SEQ_FLAG_STRIDE * 4);
     if (e == hipSuccess) {
         int dev = 0;
@@ -1486,6 +1485,7 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
 
 // Codes per sum of activations: the groups of the zero-point term.
 static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
+static float tile_centre(const BlobLayout &b) { return b.bits == 4 ? 8.f : (b.bits == 3 ? 4.f : 1.f); }   // ZC of the format policies
 static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
 
 static bool tile_format(const moe_layer *l)
@@ -1497,10 +1497,11 @@ static bool tile_format(const moe_layer *l)
 }
 
 constexpr int TE_SMALL_TOKENS = 32;
-// token blocks of an expert: tiles of 32, up to as many per block as the kernel holds
-static int tile_blocks(const BlobLayout &b, int count, bool big)
+// token blocks of an expert: one tile of 16 or 32, or up to as many tiles of 32 per block as the kernel holds
+static int tile_blocks(const BlobLayout &b, int count, int mode)
 {
-    const int per = big ? (b.bits == 2 && b.scale_group ? TeCfg<28, true>::TOK : TeCfg<4, true>::TOK) / 32 : 1;
+    if (mode != TE_BIG) return (count + mode - 1) / mode;
+    const int per = (b.bits == 2 && b.scale_group ? TeCfg<28, TE_BIG>::TOK : TeCfg<4, TE_BIG>::TOK) / 32;
     return ((count + 31) / 32 + per - 1) / per;
 }
 
@@ -1516,39 +1517,47 @@ static void tile_plan(moe_layer *l, const int32_t *idx, int batch)
     for (int q = 0; q < pairs; ++q) cnt[idx[q]]++;
     int first = 0, blocks = 0, most = 0;
     for (int e = 0; e < E; ++e) { c->tile_first[e] = first; first += cnt[e]; most = std::max(most, cnt[e]); }
-    c->tile_big = most > TE_SMALL_TOKENS;
-    for (int e = 0; e < E; ++e) blocks += tile_blocks(b, cnt[e], c->tile_big);
-    const int n_cu = c->n_cu > 0 ? c->n_cu : 256, rows = c->tile_big ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
+    c->tile_most = most;
+    c->tile_mode = most > TE_SMALL_TOKENS ? TE_BIG : (most > 16 ? 32 : 16);
+    for (int e = 0; e < E; ++e) blocks += tile_blocks(b, cnt[e], c->tile_mode);
+    const int n_cu = c->n_cu > 0 ? c->n_cu : 256, rows = c->tile_mode == TE_BIG ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
     const int sets = (b.ffn / 64 + 3) / 4;
     const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
+    // two rounds of blocks (filling the last round better, 4 parts instead of 2 at 1024 tokens: 344 us for 344)
     int want = (2 * n_cu + rb * blocks - 1) / std::max(1, rb * blocks);
     c->tile_parts = std::max(1, std::min(std::min(want, sets), cap));
 }
 
-template <int FMT, bool W13>
-static int32_t launch_tile_fmt(moe_ctx *c, bool big, int grid, uint64_t bytes, const TeArgs &A)
+template <int FMT, bool W13, int MODE>
+static int32_t launch_tile_mode(moe_ctx *c, int grid, uint64_t bytes, const TeArgs &A)
 {
+    using C = TeCfg<FMT, MODE>;
     static bool lds_attr_set = false;      // above the default dynamic LDS limit
     if (!lds_attr_set) {
-        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tile<FMT, W13, true>), hipFuncAttributeMaxDynamicSharedMemorySize, TeCfg<FMT, true>::LDS));
-        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tile<FMT, W13, false>), hipFuncAttributeMaxDynamicSharedMemorySize, TeCfg<FMT, false>::LDS));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tile<FMT, W13, MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS));
         lds_attr_set = true;
     }
-    const int kind = W13 ? PROF_W13 : PROF_W2;
-    return big ? launch_timed(c, kind, bytes, k_tile<FMT, W13, true>, dim3(grid), dim3(TeCfg<FMT, true>::THREADS), TeCfg<FMT, true>::LDS, A)
-               : launch_timed(c, kind, bytes, k_tile<FMT, W13, false>, dim3(grid), dim3(TeCfg<FMT, false>::THREADS), TeCfg<FMT, false>::LDS, A);
+    return launch_timed(c, W13 ? PROF_W13 : PROF_W2, bytes, k_tile<FMT, W13, MODE>, dim3(grid), dim3(C::THREADS), C::LDS, A);
+}
+
+template <int FMT, bool W13>
+static int32_t launch_tile_fmt(moe_ctx *c, int mode, int grid, uint64_t bytes, const TeArgs &A)
+{
+    if (mode == 16) return launch_tile_mode<FMT, W13, 16>(c, grid, bytes, A);
+    if (mode == 32) return launch_tile_mode<FMT, W13, 32>(c, grid, bytes, A);
+    return launch_tile_mode<FMT, W13, TE_BIG>(c, grid, bytes, A);
 }
 
 template <bool W13>
-static int32_t launch_tile_half(moe_layer *l, bool big, int grid, uint64_t bytes, const TeArgs &A)
+static int32_t launch_tile_half(moe_layer *l, int mode, int grid, uint64_t bytes, const TeArgs &A)
 {
     switch (fmt_of(l->lay)) {
-    case 4: return launch_tile_fmt<4, W13>(l->ctx, big, grid, bytes, A);
-    case 48: return launch_tile_fmt<48, W13>(l->ctx, big, grid, bytes, A);
-    case 3: return launch_tile_fmt<3, W13>(l->ctx, big, grid, bytes, A);
-    case 38: return launch_tile_fmt<38, W13>(l->ctx, big, grid, bytes, A);
-    case 2: return launch_tile_fmt<2, W13>(l->ctx, big, grid, bytes, A);
-    case 28: return launch_tile_fmt<28, W13>(l->ctx, big, grid, bytes, A);
+    case 4: return launch_tile_fmt<4, W13>(l->ctx, mode, grid, bytes, A);
+    case 48: return launch_tile_fmt<48, W13>(l->ctx, mode, grid, bytes, A);
+    case 3: return launch_tile_fmt<3, W13>(l->ctx, mode, grid, bytes, A);
+    case 38: return launch_tile_fmt<38, W13>(l->ctx, mode, grid, bytes, A);
+    case 2: return launch_tile_fmt<2, W13>(l->ctx, mode, grid, bytes, A);
+    case 28: return launch_tile_fmt<28, W13>(l->ctx, mode, grid, bytes, A);
     default: return fail(MOE_EINVAL, "no tile kernel for this format");
     }
 }
@@ -1565,9 +1574,9 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
         te.first = c->tile_first[pe.expert];
         te.count = c->tile_count[pe.expert];
     }
-    const bool big = c->tile_big;
-    const int rows = big ? 256 : 128;
+    const int mode = c->tile_mode, rows = mode == TE_BIG ? 256 : 128;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
+    A.zc = tile_centre(b);
     A.top_k = K; A.part_base = batch * K;
     A.unit_shift = b.group == 128 ? 1 : 0;
     auto matrix = [&](const MatLayout &m, int Kdim, int N) {
@@ -1585,7 +1594,7 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
         const int per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
         int items = 0;
         for (int i = 0; i < A.n_exp; ++i) {
-            A.e[i].tb = tile_blocks(b, A.e[i].count, big);
+            A.e[i].tb = tile_blocks(b, A.e[i].count, mode);
             A.e[i].item0 = items;
             items += per_xcd * A.e[i].tb;
         }
@@ -1594,15 +1603,15 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     matrix(b.m13, b.hidden, b.ffn);
     A.mat_off = b.off_w13;
     A.act = c->h_buf; A.act_bytes = (uint32_t)batch * b.hidden * 2;
-    A.xs = c->xs_h; A.xs_bytes = (uint32_t)batch * A.xs_stride * 4;
+    A.xs = c->xs_h; A.xs_bytes = (uint32_t)batch * A.xs_stride * 8;
     A.xs_out = c->xs_a; A.xs_out_stride = tile_sum_stride(b.ffn, xg);
-    int32_t rc = launch_tile_half<true>(l, big, shape((2 * b.ffn + rows - 1) / rows, 1), (uint64_t)A.n_exp * 2 * b.ffn * b.m13.row_stride, A);
+    int32_t rc = launch_tile_half<true>(l, mode, shape((2 * b.ffn + rows - 1) / rows, 1), (uint64_t)A.n_exp * 2 * b.ffn * b.m13.row_stride, A);
     if (rc) return rc;
     matrix(b.m2, b.ffn, b.hidden);
     A.mat_off = b.off_w2;
     A.act = c->a_buf; A.act_bytes = (uint32_t)batch * K * b.ffn * 2;
-    A.xs = c->xs_a; A.xs_bytes = (uint32_t)batch * K * A.xs_stride * 4;
-    return launch_tile_half<false>(l, big, shape((b.hidden + rows - 1) / rows, c->tile_parts), (uint64_t)A.n_exp * b.hidden * b.m2.row_stride, A);
+    A.xs = c->xs_a; A.xs_bytes = (uint32_t)batch * K * A.xs_stride * 8;
+    return launch_tile_half<false>(l, mode, shape((b.hidden + rows - 1) / rows, c->tile_parts), (uint64_t)A.n_exp * b.hidden * b.m2.row_stride, A);
 }
 
 static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts, const float *w, int batch, bool use_tile)
@@ -1798,15 +1807,20 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     ga.x = x_in; ga.wg = l->gate_w_dev; ga.wg2 = spec ? next->gate_w_dev : nullptr;
     ga.gamma = l->gamma_dev; ga.h_out = c->h_buf; ga.h_out2 = h_out; ga.out = c->gate_out_dev;
     ga.eps = (double)cf.rms_eps; ga.H = cf.hidden; ga.E = cf.n_experts; ga.E2 = spec ? next->cfg.n_experts : 0; ga.K = cf.top_k;
-    // 4-bit group-64 layers: the tile kernels take over where an expert has more than 32 tokens, below that the 16-token
-    // kernels are the faster ones (w1/w3 + w2 of a Mixtral-shaped layer, batch 16: 88 + 50 against 130 + 65 us; batch 64:
-    // 128 + 69 against 137 + 66);
-    // which of the two it is turns on the routing, so from 33 tokens on the gate kernel prepares for both
+    // Which kernels multiply turns on the routing (never on the cache), so the gate kernel prepares for the tile kernels
+    // wherever they may be chosen.  w1/w3 + w2 of a Mixtral-shaped layer in us: 4-bit group-64 layers have 16-token kernels
+    // as well (batch 16: 88 + 50, tile kernels 106 + 55; batch 64, an expert with 17 to 32 tokens: 129 + 71 and 131 + 65,
+    // with two-level metadata 156 + 89 and 155 + 83, at 512 x 1920 33 + 24 and 25 + 19; from 33 tokens the 16-token kernels
+    // read the weights again), other formats the GEMV kernels (3-bit, batch 4, an expert with three or four tokens:
+    // 106 + 69, tile kernels 81 + 47; with one or two: 60 + 45).
     const bool tiles16 = cf.bits == 4 && cf.group == 64;
-    const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && (!tiles16 || batch > TE_SMALL_TOKENS))) && tile_format(l);
+    const int tile_above = !tiles16 ? 2 : (cf.scale_group ? 16 : TE_SMALL_TOKENS);
+    // fp16 pairs: below 16 tokens an expert on average hardly one has 33, and the sort would cost 1 % of the step (batch 64)
+    const bool likely = tile_above < TE_SMALL_TOKENS || batch * cf.top_k > 16 * cf.n_experts;
+    const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
     if (tile_ready) {
         ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
-        ga.xs = c->xs_h; ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
+        ga.xs = c->xs_h; ga.xs_zc = tile_centre(l->lay); ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
     }
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;
@@ -1864,7 +1878,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     bool use_tile = false;
     if (tile_ready) {
         tile_plan(l, idx, batch);
-        use_tile = c->mfma_form == 6 || !tiles16 || c->tile_big;
+        use_tile = c->mfma_form == 6 || c->tile_most > tile_above;
     }
     const bool use_mfma = use_tile || (batch >= c->mfma_min_batch && cf.bits == 4 && cf.group == 64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2));
     if (use_mfma && !use_tile) {
