@@ -121,16 +121,20 @@ __device__ __forceinline__ void token_w2_phase(const FusedArgs &A, float *red, i
     // a written by an earlier launch is visible to plain loads; a written inside this launch by other dies is not
     if constexpr (BARRIER && MOE_FUSED_COHERENT_A) load_act_coherent<BITS>(ac, A.a + (size_t)A.a_row[active ? e2 : 0] * A.F, cc, live2);
     else F::load_act(ac, A.a + (size_t)A.a_row[active ? e2 : 0] * A.F, cc, live2);
-    for (int rbase = row0; rbase < row_end; rbase += G2) {
+    auto trip = [&](int rbase, auto more) {              // all trips but the last request the next rows (as in k_w13)
 #pragma unroll
         for (int s = 0; s < G2; ++s) {
             const int row = rbase + s;
+            if (!more && row >= row_end) break;
             const float part = F::contrib(ring2[s], ac, live2);
-            F::load(ring2[s], base2 + (size_t)row_of(row + G2) * A.stride2, geo2, cc);
+            if constexpr (more) F::load(ring2[s], base2 + (size_t)row_of(row + G2) * A.stride2, geo2, cc);
             const float p = wave_sum_l63(part);
-            if (lane == 63 && active && row < row_end) red[(e2 * 8 + cs) * 64 + (row - row0)] = p;
+            if (lane == 63 && active) red[(e2 * 8 + cs) * 64 + (row - row0)] = p;
         }
-    }
+    };
+    int rbase = row0;
+    for (; rbase + G2 < row_end; rbase += G2) trip(rbase, std::true_type{});
+    trip(rbase, std::false_type{});
     __syncthreads();
     const int rr = threadIdx.x;
     if (rr < row_end - row0) {
