@@ -1119,7 +1119,9 @@ static int32_t launch_gate(moe_ctx *c, GateArgs ga, int32_t batch)
     if (++c->gate_seq == 0) ++c->gate_seq;             // 0 is what a fresh context holds
     ga.seq = c->gate_seq;
     const dim3 grid(batch), block(GATE_THREADS);
-    int32_t rc = ga.xs ? (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true, true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false, true>, grid, block, 0, ga))
+    const bool dense = ga.xs && !ga.wg2 && ga.E <= GATE_DENSE_EXPERTS && batch > (c->n_cu > 0 ? c->n_cu : 256);
+    int32_t rc = dense ? launch_timed(c, PROF_GATE, 0, k_gate<false, true, true>, grid, block, 0, ga)
+               : ga.xs ? (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true, true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false, true>, grid, block, 0, ga))
                        : (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false>, grid, block, 0, ga));
     if (rc) return rc;
     if (!c->sync_wait) HIPCHK(hipEventRecord(c->ev_gate, c->compute));

@@ -47,6 +47,13 @@ def test_offloaded(fmt, sg, Bn, k, m):
     run(fmt, sg, 256, 512, 8, 2, k, Bn, T=3, m=m)
 
 
+@pytest.mark.parametrize("H,E,Bn", [(4160, 8, 257), (64, 8, 300), (256, 9, 257), (128, 2, 1024)])
+def test_gate_of_large_batches(H, E, Bn):
+    """More tokens than compute units: the gate variant for up to 8 experts (and, with 9, the one for smaller batches); a
+    row that takes a second pass of the block, one that fills a single wave's lanes."""
+    run((4, 64), 0, H, 64, E, 2, E, Bn, seed=64)
+
+
 @pytest.mark.parametrize("fmt", [(4, 64), (3, 64), (2, 16)])
 @pytest.mark.parametrize("Bn", [12, 120])
 def test_result_does_not_depend_on_the_cache(fmt, Bn):
