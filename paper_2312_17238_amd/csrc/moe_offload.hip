@@ -1525,9 +1525,18 @@ static void tile_plan(moe_layer *l, const int32_t *idx, int batch)
     const int n_cu = c->n_cu > 0 ? c->n_cu : 256, rows = c->tile_mode == TE_BIG ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
     const int sets = (b.ffn / 64 + 3) / 4;
     const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
-    // two rounds of blocks (filling the last round better, 4 parts instead of 2 at 1024 tokens: 344 us for 344)
-    int want = (2 * n_cu + rb * blocks - 1) / std::max(1, rb * blocks);
-    c->tile_parts = std::max(1, std::min(std::min(want, sets), cap));
+    // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
+    // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
+    // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
+    // 226 + 14 (4).
+    const int slots = n_cu * (c->tile_mode == TE_BIG ? 1 : 2);
+    double best = 0.0;
+    c->tile_parts = 1;
+    for (int p = 1; p <= std::min(std::min(8, sets), cap); ++p) {
+        const int items = rb * blocks * p, rounds = (items + slots - 1) / slots;
+        const double eff = (double)items / ((double)rounds * slots) / (1.0 + 0.03 * p);
+        if (eff > best) { best = eff; c->tile_parts = p; }
+    }
 }
 
 template <int FMT, bool W13, int MODE>
