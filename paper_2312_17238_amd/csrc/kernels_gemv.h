@@ -402,7 +402,9 @@ __global__ __launch_bounds__(WAVES *WAVE) void k_w13(FfnArgs A)
 
     // A trip works off the ring; all but the last request the next G rows in its place.  (Requesting past the last row
     // as well, clamped to it, kept one loop but made 2 of 16 requests of a wave useless ones; 2-bit two-level token
-    // 4096 x 14336: 36.1 -> 35.6 us.)
+    // 4096 x 14336: 36.1 -> 35.6 us.)  One token only: with the activations of several, a second body costs registers
+    // that spill to accumulators (4-bit group 32, 2112 x 12224, 13 tokens: 174 us for 166).
+    constexpr bool PEEL = NT == 1;
     auto trip = [&](int it, auto more) {
 #pragma unroll
         for (int s = 0; s < G; ++s) {
@@ -430,8 +432,8 @@ __global__ __launch_bounds__(WAVES *WAVE) void k_w13(FfnArgs A)
         }
     };
     int it = 0;
-    for (; it + G < iters; it += G) trip(it, std::true_type{});
-    trip(it, std::false_type{});
+    for (; PEEL ? it + G < iters : it < iters; it += G) trip(it, std::true_type{});
+    if constexpr (PEEL) trip(it, std::false_type{});
 }
 
 // Entry of the table that tells k_combine where the contribution of one (token, expert) pair lies: `parts`
@@ -467,7 +469,8 @@ __global__ __launch_bounds__(512) void k_w2(FfnArgs A)
 #pragma unroll
     for (int t = 0; t < NT; ++t) F::load_act(ac[t], A.a + (size_t)en.pair[t < en.n_tok ? t : 0] * A.F, cc, live);
 
-    auto trip = [&](int rbase, auto more) {              // as in k_w13
+    constexpr bool PEEL = NT == 1;                       // as in k_w13
+    auto trip = [&](int rbase, auto more) {
 #pragma unroll
         for (int s = 0; s < G; ++s) {
             const int row = rbase + s;
@@ -479,13 +482,13 @@ __global__ __launch_bounds__(512) void k_w2(FfnArgs A)
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const float p = wave_sum_l63(part[t]);
-                if (lane == 63) red[((row - row0) * NT + t) * CS + cs] = p;
+                if (lane == 63 && row < row_end) red[((row - row0) * NT + t) * CS + cs] = p;
             }
         }
     };
     int rbase = row0;
-    for (; rbase + G < row_end; rbase += G) trip(rbase, std::true_type{});
-    trip(rbase, std::false_type{});
+    for (; PEEL ? rbase + G < row_end : rbase < row_end; rbase += G) trip(rbase, std::true_type{});
+    if constexpr (PEEL) trip(rbase, std::false_type{});
     __syncthreads();
     for (int i = threadIdx.x; i < (row_end - row0) * NT; i += blockDim.x) {
         const int rr = i / NT, t = i % NT;

@@ -1822,12 +1822,16 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     // wherever they may be chosen.  w1/w3 + w2 of a Mixtral-shaped layer in us: 4-bit group-64 layers have 16-token kernels
     // as well (batch 16: 88 + 50, tile kernels 106 + 55; batch 64, an expert with 17 to 32 tokens: 129 + 71 and 131 + 65,
     // with two-level metadata 156 + 89 and 155 + 83, at 512 x 1920 33 + 24 and 25 + 19; from 33 tokens the 16-token kernels
-    // read the weights again), other formats the GEMV kernels (3-bit, batch 4, an expert with three or four tokens:
-    // 106 + 69, tile kernels 81 + 47; with one or two: 60 + 45).
+    // read the weights again), other formats the GEMV kernels (2-bit, batch 16: 213 + 103, tile kernels 118 + 60;
+    // 3-bit, batch 4: 60 + 45 to 106 + 69, tile kernels 81 + 47).
     const bool tiles16 = cf.bits == 4 && cf.group == 64;
     const int tile_above = !tiles16 ? 2 : (cf.scale_group ? 16 : TE_SMALL_TOKENS);
-    // fp16 pairs: below 16 tokens an expert on average hardly one has 33, and the sort would cost 1 % of the step (batch 64)
-    const bool likely = tile_above < TE_SMALL_TOKENS || batch * cf.top_k > 16 * cf.n_experts;
+    // Whether it pays is known only after the gate, the sort is launched with it: 1 % of a batch of 64, 4 us of 30 for four
+    // tokens of a small layer.  So only where an expert has enough tokens on average (2-bit 2624 x 2496, 13 experts, batch 4:
+    // 32 us without, 37 with the sort; 3-bit 2368 x 1984, 6 tokens on 6 experts: GEMV 38, tile kernels 41; 3-bit
+    // 2304 x 704, 30 pairs on 4 experts: 43 and 37).
+    const int tile_average = !tiles16 ? 3 : (cf.scale_group ? 8 : 16);
+    const bool likely = batch * cf.top_k > tile_average * cf.n_experts;
     const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
     if (tile_ready) {
         ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
