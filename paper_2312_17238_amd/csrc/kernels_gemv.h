@@ -400,40 +400,62 @@ __global__ __launch_bounds__(WAVES *WAVE) void k_w13(FfnArgs A)
         for (int k = 0; k < KCH; ++k) F::load_act(hc[t][k], A.h + (size_t)tok * A.H, cidx[k], live[k]);
     }
 
-    // A trip works off the ring; all but the last request the next G rows in its place.  (Requesting past the last row
-    // as well, clamped to it, kept one loop but made 2 of 16 requests of a wave useless ones; 2-bit two-level token
-    // 4096 x 14336: 36.1 -> 35.6 us.)  One token only: with the activations of several, a second body costs registers
-    // that spill to accumulators (4-bit group 32, 2112 x 12224, 13 tokens: 174 us for 166).
-    constexpr bool PEEL = NT == 1;
-    auto trip = [&](int it, auto more) {
+    if constexpr (NT == 1) {
+        // A trip works off the ring; all but the last request the next G rows in its place.  (Requesting past the last row
+        // as well, clamped to it, keeps one loop but makes 2 of 16 requests of a wave useless ones; 2-bit two-level token
+        // 4096 x 14336: 36.1 -> 35.6 us.)
+        auto trip = [&](int it, auto more) {
 #pragma unroll
-        for (int s = 0; s < G; ++s) {
-            if (!more && it + s >= iters) break;
-            const int r = wave + (it + s) * n_waves;
-            float u[NT], v[NT];
+            for (int s = 0; s < G; ++s) {
+                if (!more && it + s >= iters) break;
+                const int r = wave + (it + s) * n_waves;
+                float u = 0.f, v = 0.f;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) { u[t] = 0.f; v[t] = 0.f; }
+                for (int k = 0; k < KCH; ++k) {
+                    u += F::contrib(ring[s].w1[k], hc[0][k], live[k]);
+                    v += F::contrib(ring[s].w3[k], hc[0][k], live[k]);
+                }
+                if constexpr (more) load_row(ring[s], min(r + G * n_waves, last));
+                const float us = wave_sum_l63(u), vs = wave_sum_l63(v);
+                if (lane == 63 && en.n_tok > 0 && r < A.F) {
+                    const _Float16 av = (_Float16)silu_mul(us, vs);
+                    A.a[(size_t)en.pair[0] * A.F + r] = __builtin_bit_cast(uint16_t, av);
+                }
+            }
+        };
+        int it = 0;
+        for (; it + G < iters; it += G) trip(it, std::true_type{});
+        trip(it, std::false_type{});
+    } else {
+        // Several tokens: one loop, written out.  With their activations a second body costs registers that spill to
+        // accumulators (4-bit group 32, 2112 x 12224, 13 tokens: 174 us for 166), and a loop around a lambda shared with the
+        // branch above costs scalar work per row and token (3200 x 3648, 68 tokens: 267 us for 263).
+        for (int it = 0; it < iters; it += G) {
 #pragma unroll
-            for (int k = 0; k < KCH; ++k)
+            for (int s = 0; s < G; ++s) {
+                const int r = wave + (it + s) * n_waves;
+                float u[NT], v[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) { u[t] = 0.f; v[t] = 0.f; }
+#pragma unroll
+                for (int k = 0; k < KCH; ++k)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        u[t] += F::contrib(ring[s].w1[k], hc[t][k], live[k]);
+                        v[t] += F::contrib(ring[s].w3[k], hc[t][k], live[k]);
+                    }
+                load_row(ring[s], min(r + G * n_waves, last));
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    u[t] += F::contrib(ring[s].w1[k], hc[t][k], live[k]);
-                    v[t] += F::contrib(ring[s].w3[k], hc[t][k], live[k]);
-                }
-            if constexpr (more) load_row(ring[s], min(r + G * n_waves, last));
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const float us = wave_sum_l63(u[t]), vs = wave_sum_l63(v[t]);
-                if (lane == 63 && t < en.n_tok && r < A.F) {
-                    const _Float16 av = (_Float16)silu_mul(us, vs);
-                    A.a[(size_t)en.pair[t] * A.F + r] = __builtin_bit_cast(uint16_t, av);
+                    const float us = wave_sum_l63(u[t]), vs = wave_sum_l63(v[t]);
+                    if (lane == 63 && t < en.n_tok && r < A.F) {
+                        const _Float16 av = (_Float16)silu_mul(us, vs);
+                        A.a[(size_t)en.pair[t] * A.F + r] = __builtin_bit_cast(uint16_t, av);
+                    }
                 }
             }
         }
-    };
-    int it = 0;
-    for (; PEEL ? it + G < iters : it < iters; it += G) trip(it, std::true_type{});
-    if constexpr (PEEL) trip(it, std::false_type{});
+    }
 }
 
 // Entry of the table that tells k_combine where the contribution of one (token, expert) pair lies: `parts`
@@ -469,26 +491,21 @@ __global__ __launch_bounds__(512) void k_w2(FfnArgs A)
 #pragma unroll
     for (int t = 0; t < NT; ++t) F::load_act(ac[t], A.a + (size_t)en.pair[t < en.n_tok ? t : 0] * A.F, cc, live);
 
-    constexpr bool PEEL = NT == 1;                       // as in k_w13
-    auto trip = [&](int rbase, auto more) {
+    for (int rbase = row0; rbase < row_end; rbase += G) {
 #pragma unroll
         for (int s = 0; s < G; ++s) {
             const int row = rbase + s;
-            if (!more && row >= row_end) break;
             float part[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t) part[t] = F::contrib(ring[s], ac[t], live);
-            if constexpr (more) F::load(ring[s], base + (size_t)min(row + G, last) * A.stride2, geo, cc);
+            F::load(ring[s], base + (size_t)min(row + G, last) * A.stride2, geo, cc);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const float p = wave_sum_l63(part[t]);
                 if (lane == 63 && row < row_end) red[((row - row0) * NT + t) * CS + cs] = p;
             }
         }
-    };
-    int rbase = row0;
-    for (; PEEL ? rbase + G < row_end : rbase < row_end; rbase += G) trip(rbase, std::true_type{});
-    if constexpr (PEEL) trip(rbase, std::false_type{});
+    }
     __syncthreads();
     for (int i = threadIdx.x; i < (row_end - row0) * NT; i += blockDim.x) {
         const int rr = i / NT, t = i % NT;
