@@ -1826,10 +1826,8 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     // 3-bit, batch 4: 60 + 45 to 106 + 69, tile kernels 81 + 47).
     const bool tiles16 = cf.bits == 4 && cf.group == 64;
     const int tile_above = !tiles16 ? 2 : (cf.scale_group ? 16 : TE_SMALL_TOKENS);
-    // Whether it pays is known only after the gate, the sort is launched with it: 1 % of a batch of 64, 4 us of 30 for four
-    // tokens of a small layer.  So only where an expert has enough tokens on average (2-bit 2624 x 2496, 13 experts, batch 4:
-    // 32 us without, 37 with the sort; 3-bit 2368 x 1984, 6 tokens on 6 experts: GEMV 38, tile kernels 41; 3-bit
-    // 2304 x 704, 30 pairs on 4 experts: 43 and 37).
+    // The gate kernel prepares only where an expert has enough tokens on average for the tile kernels to be likely; where it
+    // does not, they are not chosen.
     const int tile_average = !tiles16 ? 3 : (cf.scale_group ? 8 : 16);
     const bool likely = batch * cf.top_k > tile_average * cf.n_experts;
     const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
@@ -1839,15 +1837,21 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     }
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;
-    if (tile_ready) {
-        hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
-        HIPCHK(hipGetLastError());
-    }
 
     const GateHostOut *go = c->gate_out;
     int32_t idx[MOE_MAX_BATCH * MOE_MAX_TOPK];
     float w[MOE_MAX_BATCH * MOE_MAX_TOPK];
-    for (int i = 0; i < batch * cf.top_k; ++i) { idx[i] = go->idx[i]; w[i] = go->w[i]; }
+    for (int i = 0; i < batch * cf.top_k; ++i) {
+        idx[i] = go->idx[i];
+        w[i] = go->w[i];
+        if (idx[i] < 0 || idx[i] >= cf.n_experts) return fail(MOE_EINVAL, "routing index %d out of range", idx[i]);
+    }
+    if (tile_ready) tile_plan(l, idx, batch);
+    const bool use_tile = tile_ready && (c->mfma_form == 6 || c->tile_most > tile_above);
+    if (use_tile) {     // before the host's other decisions: it runs under them
+        hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
+        HIPCHK(hipGetLastError());
+    }
     double score[MOE_MAX_EXPERTS] = {0};
     if (spec)
         for (int b = 0; b < batch; ++b)
@@ -1890,11 +1894,6 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     bool spec_issued = false;          // the speculative copies went out early (prompt-sized batches, below)
     // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
     auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
-    bool use_tile = false;
-    if (tile_ready) {
-        tile_plan(l, idx, batch);
-        use_tile = c->mfma_form == 6 || c->tile_most > tile_above;
-    }
     const bool use_mfma = use_tile || (batch >= c->mfma_min_batch && cf.bits == 4 && cf.group == 64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2));
     if (use_mfma && !use_tile) {
         // How many parts the w2 launches of a window split their contraction into decides the order in which a
