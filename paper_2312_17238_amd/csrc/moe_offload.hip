@@ -1539,6 +1539,91 @@ static void tile_plan(moe_layer *l, const int32_t *idx, int batch)
     }
 }
 
+// The 16-token (streaming) kernels' windows: how many parts the w2 launches of a window split their contraction into,
+// and whether one tile of 16 tokens holds every expert's share of it.
+//
+// The number of parts decides the order in which a pair's partial sums are added, so it must not depend on how the step's
+// experts happen to be grouped into launches (which follows from what is cached, in which buffers): it is fixed here from
+// the routing alone, as if all needed experts of the window ran in one launch -- one part per block that would idle then --
+// within the rows the partial sums have.  A step's result is then the same whatever the cache held.
+//
+// Returns what the step takes with them in us (tile_us: why, and where the numbers come from).
+static double plan_windows(moe_layer *l, const int32_t *idx, int batch)
+{
+    moe_ctx *c = l->ctx;
+    const moe_layer_config_t &cf = l->cfg;
+    const int window = MF_MAX_PAIRS / cf.top_k, n_cu = c->n_cu > 0 ? c->n_cu : 256;
+    const int row_blocks = (cf.hidden + TL_ROWS - 1) / TL_ROWS, row_blocks13 = (2 * cf.ffn + TL_ROWS - 1) / TL_ROWS;
+    const int steps = (cf.ffn / 64 + TL_SG - 1) / TL_SG, steps13 = (cf.hidden / 64 + TL_SG - 1) / TL_SG;
+    const uint64_t extra_rows = c->ypart_extra_floats / cf.hidden, pairs = (uint64_t)batch * cf.top_k;
+    const int max_parts = (int)std::min<uint64_t>(255, std::max<uint64_t>(1, extra_rows / pairs));
+    const double two_level = cf.scale_group > 0 ? 1.0 : 0.0;
+    double us = 17.0 + 0.037 * batch;
+    c->w2_parts.clear();
+    c->win_small.clear();
+    for (int w0 = 0; w0 < batch; w0 += window) {
+        const int w1 = std::min(batch, w0 + window);
+        int count[MOE_MAX_EXPERTS] = {0}, entries = 0;
+        for (int q = w0 * cf.top_k; q < w1 * cf.top_k; ++q) count[idx[q]]++;
+        int most = 0;
+        for (int e = 0; e < cf.n_experts; ++e) { entries += (count[e] + 31) / 32; most = std::max(most, count[e]); }
+        const bool small = most <= 16;
+        c->win_small.push_back(small);
+        // at least four: the experts that arrive during a step are multiplied one launch each, and with fewer
+        // parts such a launch leaves most of the chip idle on the step's critical path
+        const int want = std::max(4, (2 * n_cu + entries * row_blocks - 1) / std::max(1, entries * row_blocks));
+        c->w2_parts.push_back(std::min(want, max_parts));
+        auto half = [&](int rb, int n_steps, int parts) {
+            parts = std::min(parts, n_steps);
+            const int part_steps = (n_steps + parts - 1) / parts, k_parts = (n_steps + part_steps - 1) / part_steps;
+            const double k = part_steps * TL_SG * 64 / 4096.0, x = (double)entries * rb * k_parts / (2 * n_cu);
+            return small ? k * (x * (31.0 + 5.0 * two_level) + 5.0) : k * (x * (33.0 + 8.0 * two_level) + 21.0);
+        };
+        us += 17.0 + half(row_blocks13, steps13, 1) + half(row_blocks, steps, c->w2_parts.back());
+    }
+    return us;
+}
+
+// What the step takes with the tile kernels in us, after tile_plan.
+//
+// 4-bit group-64 layers have two families of kernels for a batch, and which one is faster turns on more than the tokens:
+// the tile kernels read an expert's weights once for up to 192 tokens, but a block of the large one costs 65, 98 or 131 us
+// per 4096 columns (up to 64, 128 or 192 tokens) and there is one to a compute unit, so a round that is not full is paid in
+// whole; the 16-token kernels read them again for every 32 tokens, 37 us per round of the same work, and start again
+// for every window.  So the step's time is estimated for both from the routing, constants fitted to 548 measured steps
+// (hidden 256 to 4096, ffn 512 to 14336, 1 to 16 experts, 16 to 700 tokens, both metadata levels; standard deviation 6 %).  Of
+// the 442 steps among them that may take the tile kernels the estimates give 17 to the slower kernels by more than 2 %, at most
+// by 12 %; the tile kernels for all of them lost on 137, up to 40 % (Mixtral-shaped, 96 tokens: 425 us, 16-token kernels 261).
+static double tile_us(const moe_layer *l, int batch)
+{
+    const moe_ctx *c = l->ctx;
+    const BlobLayout &b = l->lay;
+    const int n_cu = c->n_cu > 0 ? c->n_cu : 256;
+    const bool big = c->tile_mode == TE_BIG;
+    const int rows = big ? 256 : 128, slots = n_cu * (big ? 1 : 2);
+    const double two_level = b.scale_group > 0 ? 1.0 : 0.0;
+    int blocks = 0, halves = 0;                  // token blocks; token tiles of a block's fuller half, added up over them
+    for (int e = 0; e < l->cfg.n_experts; ++e) {
+        if (!c->tile_count[e]) continue;
+        const int tb = tile_blocks(b, c->tile_count[e], c->tile_mode), tiles = (c->tile_count[e] + 31) / 32;
+        blocks += tb;
+        halves += tb * (((tiles + tb - 1) / tb + 1) / 2);
+    }
+    double rounds = 0.0, x = 0.0;                // of blocks, the last one whole or by its share, times their columns / 4096
+    auto half = [&](int n_rows, int cols, int parts) {
+        const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
+        const int items = (n_rows + rows - 1) / rows * blocks * k_parts;
+        const double k = part_sets * 256 / 4096.0;
+        rounds += (items + slots - 1) / slots * k;
+        x += (double)items / slots * k;
+    };
+    half(2 * b.ffn, b.hidden, 1);
+    half(b.hidden, b.ffn, c->tile_parts);
+    const double tiles = (double)halves / blocks;
+    return big ? 40.0 + rounds * (33.0 + 26.0 * tiles + 4.5 * two_level) + x * (24.0 - 7.6 * tiles) + 0.057 * batch
+               : 41.0 + rounds * (11.0 + 3.5 * two_level) + x * 28.0 + 0.05 * batch;
+}
+
 template <int FMT, bool W13, int MODE>
 static int32_t launch_tile_mode(moe_ctx *c, int grid, uint64_t bytes, const TeArgs &A)
 {
@@ -1821,14 +1906,17 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     // Which kernels multiply turns on the routing (never on the cache), so the gate kernel prepares for the tile kernels
     // wherever they may be chosen.  w1/w3 + w2 of a Mixtral-shaped layer in us: 4-bit group-64 layers have 16-token kernels
     // as well (batch 16: 88 + 50, tile kernels 106 + 55; batch 64, an expert with 17 to 32 tokens: 129 + 71 and 131 + 65,
-    // with two-level metadata 156 + 89 and 155 + 83, at 512 x 1920 33 + 24 and 25 + 19; from 33 tokens the 16-token kernels
-    // read the weights again), other formats the GEMV kernels (2-bit, batch 16: 213 + 103, tile kernels 118 + 60;
+    // with two-level metadata 156 + 89 and 155 + 83, at 512 x 1920 33 + 24 and 25 + 19), and above that many tokens the
+    // estimate of tile_us decides; other formats the GEMV kernels (2-bit, batch 16: 213 + 103, tile kernels 118 + 60;
     // 3-bit, batch 4: 60 + 45 to 106 + 69, tile kernels 81 + 47).
-    const bool tiles16 = cf.bits == 4 && cf.group == 64;
-    const int tile_above = !tiles16 ? 2 : (cf.scale_group ? 16 : TE_SMALL_TOKENS);
+    const bool g64 = cf.bits == 4 && cf.group == 64;
+    // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
+    auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
+    const bool tiles16 = batch >= c->mfma_min_batch && g64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2);
+    const int tile_above = !g64 ? 2 : (cf.scale_group ? 16 : TE_SMALL_TOKENS);
     // The gate kernel prepares only where an expert has enough tokens on average for the tile kernels to be likely; where it
     // does not, they are not chosen.
-    const int tile_average = !tiles16 ? 3 : (cf.scale_group ? 8 : 16);
+    const int tile_average = !g64 ? 3 : (cf.scale_group ? 8 : 16);
     const bool likely = batch * cf.top_k > tile_average * cf.n_experts;
     const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
     if (tile_ready) {
@@ -1847,7 +1935,11 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
         if (idx[i] < 0 || idx[i] >= cf.n_experts) return fail(MOE_EINVAL, "routing index %d out of range", idx[i]);
     }
     if (tile_ready) tile_plan(l, idx, batch);
-    const bool use_tile = tile_ready && (c->mfma_form == 6 || c->tile_most > tile_above);
+    bool use_tile = tile_ready && (c->mfma_form == 6 || c->tile_most > tile_above);
+    if (tiles16 && !(use_tile && c->mfma_form == 6)) {
+        const double us = plan_windows(l, idx, batch);
+        use_tile = use_tile && tile_us(l, batch) < us;
+    }
     if (use_tile) {     // before the host's other decisions: it runs under them
         hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
         HIPCHK(hipGetLastError());
@@ -1892,34 +1984,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
                            (int)plan.access.size() == cf.top_k && !plan.victim_needed;
     bool fused_done = false;
     bool spec_issued = false;          // the speculative copies went out early (prompt-sized batches, below)
-    // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
-    auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
-    const bool use_mfma = use_tile || (batch >= c->mfma_min_batch && cf.bits == 4 && cf.group == 64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2));
-    if (use_mfma && !use_tile) {
-        // How many parts the w2 launches of a window split their contraction into decides the order in which a
-        // pair's partial sums are added, so it must not depend on how the step's experts happen to be grouped into
-        // launches (which follows from what is cached, in which buffers): it is fixed here from the routing alone,
-        // as if all needed experts of the window ran in one launch -- one part per block that would idle then --
-        // within the rows the partial sums have.  A step's result is then the same whatever the cache held.
-        const int window = MF_MAX_PAIRS / cf.top_k, n_cu = c->n_cu > 0 ? c->n_cu : 256;
-        const int row_blocks = (cf.hidden + TL_ROWS - 1) / TL_ROWS;
-        const uint64_t extra_rows = c->ypart_extra_floats / cf.hidden, pairs = (uint64_t)batch * cf.top_k;
-        const int max_parts = (int)std::min<uint64_t>(255, std::max<uint64_t>(1, extra_rows / pairs));
-        c->w2_parts.clear();
-        c->win_small.clear();
-        for (int w0 = 0; w0 < batch; w0 += window) {
-            const int w1 = std::min(batch, w0 + window);
-            int count[MOE_MAX_EXPERTS] = {0}, entries = 0;
-            for (int q = w0 * cf.top_k; q < w1 * cf.top_k; ++q) count[idx[q]]++;
-            int most = 0;
-            for (int e = 0; e < cf.n_experts; ++e) { entries += (count[e] + 31) / 32; most = std::max(most, count[e]); }
-            c->win_small.push_back(most <= 16);
-            // at least four: the experts that arrive during a step are multiplied one launch each, and with fewer
-            // parts such a launch leaves most of the chip idle on the step's critical path
-            const int want = std::max(4, (2 * n_cu + entries * row_blocks - 1) / std::max(1, entries * row_blocks));
-            c->w2_parts.push_back(std::min(want, max_parts));
-        }
-    }
+    const bool use_mfma = use_tile || tiles16;
     auto pass_expert = [&](int i) {
         PassExpert pe;
         pe.blob = c->bufs[plan.access[i].buf].ptr;

@@ -74,6 +74,38 @@ def test_result_does_not_depend_on_the_cache(fmt, Bn):
         assert (y.view(np.uint32) == ys[0].view(np.uint32)).all()
 
 
+@pytest.mark.parametrize("fmt,sg,H,F,E,K,Bn,tile", [
+    # 4-bit group 64: an expert with more than 32 tokens (two-level: 16), but blocks too few or rounds too empty
+    ((4, 64), 0, 1024, 2048, 8, 2, 128, False), ((4, 64), 0, 512, 1920, 8, 2, 128, False), ((4, 64), 0, 1024, 2048, 1, 1, 200, False),
+    ((4, 64), 128, 512, 1920, 8, 2, 64, False), ((4, 64), 128, 1024, 2048, 8, 2, 128, False),
+    # ... enough of them; at most 32 (16) tokens
+    ((4, 64), 0, 512, 1920, 8, 2, 512, True), ((4, 64), 0, 2048, 4096, 8, 4, 96, True), ((4, 64), 128, 1856, 5056, 6, 3, 50, True),
+    ((4, 64), 0, 512, 1920, 8, 2, 64, False), ((4, 64), 128, 512, 1920, 8, 2, 32, False),
+    # metadata runs that the 16-token kernels cannot take: GEMV kernels or tile kernels
+    ((4, 64), 2, 512, 1920, 8, 2, 16, False), ((4, 64), 2, 512, 1920, 8, 2, 64, True),
+    # other formats: three tokens of an expert on average, and just above
+    ((3, 64), 0, 256, 512, 8, 2, 12, False), ((3, 64), 0, 256, 512, 8, 2, 13, True),
+    ((2, 16), 0, 256, 512, 8, 2, 12, False), ((2, 16), 8, 256, 512, 8, 2, 13, True), ((4, 128), 0, 256, 512, 8, 2, 13, True),
+    ((4, 32), 0, 256, 512, 8, 2, 100, False)])
+def test_which_kernels_a_step_takes(fmt, sg, H, F, E, K, Bn, tile):
+    """The default form gives the bits of the tile kernels or those of the kernels it would take without them (the order of the
+    sums tells them apart)."""
+    model = Model(1, H, F, E, K, [fmt], E, 0, 1e-5, max_batch=Bn, seed=65, scale_group=sg)
+    x = W.hidden_ar1(65, 1, Bn, H)[0].to(model.stack.device)
+    out = torch.empty_like(x)
+    torch.cuda.synchronize()
+    y = {}
+    for form in (5, 6, 0):
+        B.moe_ctx_set_option(model.stack.ctx, "mfma_form", form)
+        model.stack.step_layer(0, x, out)
+        model.stack.synchronize()
+        y[form] = model.stack.read_y(Bn, H).copy().view(np.uint32)
+    model.close()
+    if fmt != (4, 32):
+        assert (y[5] != y[6]).any()
+    assert (y[0] == y[6 if tile else 5]).all()
+
+
 @pytest.mark.parametrize("sg", [0, 8])
 @pytest.mark.parametrize("factor", [1.0, 4e4])
 def test_large_2bit_scales(sg, factor):
