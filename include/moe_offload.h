@@ -308,8 +308,9 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *   "mfma_min_batch" batches at least this large (default 3, from where on they are the faster ones on MI355X; 16
  *                is the benchmark definition's threshold) run on the matrix cores (grouped dequantize+GEMM): 4-bit
  *                group-64 experts in every form below, 4-bit group-128, 3-bit and 2-bit experts in forms 0 and 6 (2-bit
- *                layers with a scale above 32000, or two-level ones above 500, excepted); smaller batches, 4-bit
- *                group-32 experts and other formats in forms 1 to 5 use the GEMV kernels;
+ *                layers excepted with a scale above 32000 or a row of scales below 2^-14, or two-level ones with a scale
+ *                above 500 or a row 2^16 times below the largest); smaller batches, 4-bit group-32 experts and
+ *                other formats in forms 1 to 5 use the GEMV kernels;
  *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 where an expert has enough tokens of the step (4-bit group-64
  *                experts: more than 32 and 16 on average, with two-level metadata 16 and 8, and estimated from the
  *                routing to be faster than form 5; other formats: more than three on average), else form 5 (4-bit

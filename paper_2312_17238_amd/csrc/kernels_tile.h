@@ -77,6 +77,7 @@ struct TeArgs {
     int32_t units_per_part, k_parts, part_base;
     int32_t jobs;                        // row blocks * k_parts
     float zc;                            // the constant the codes are centred on
+    float lift, lower;                   // two-level 2-bit codes: what their scales are multiplied with, and its reciprocal
     uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
 };
 
@@ -156,7 +157,7 @@ template <bool META8, int ROWS, int THREADS>
 struct TeScaled {                        // the part that 4-bit and 3-bit formats share
     static constexpr bool GS = true;
     static constexpr int GPU = 1, PLANES = 1, DB = 16;                   // groups per unit; bytes of D per row and set
-    static constexpr float POST = 1.f;                                   // what the totals are multiplied with at the end
+    static constexpr bool LIFTED = false;
     static constexpr int NM = ROWS * 4 / THREADS;
     TeMeta<META8, NM> meta;
     __device__ __forceinline__ void fetch_meta(__amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
@@ -194,7 +195,7 @@ struct Te4 : TeScaled<META8, ROWS, THREADS> {
         for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) c[i] = bl128(rs, v, min(row0 + i * SLAB, n_rows - SLAB) * (int)g.stride + u * 32);
         if (h == 1) this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
     }
-    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, int tid) const
+    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, float, int tid) const
     {
         uint8_t *const to = rec + (tid / 8) * REC + (tid % 8) * 16;
 #pragma unroll
@@ -242,7 +243,7 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
             this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
         }
     }
-    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, int tid) const
+    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, float, int tid) const
     {
         if (h == 0) {
 #pragma unroll
@@ -308,8 +309,9 @@ struct Te2 {
     static constexpr bool GS = false;
     static constexpr int GPU = 4, PLANES = META8 ? 2 : 1, DB = META8 ? 80 : 0, REC = 144, SOFF = 0;   // one-level: D from the record's (scale, zero)
     static constexpr int NC = ROWS * 8 / THREADS, NA = ROWS * 4 / THREADS;
-    // two-level scales are split into two fp16: lifted by 64 the low part of any usual scale is a normal number
-    static constexpr float PRE = META8 ? 64.f : 1.f, POST = 1.f / PRE;
+    // two-level scales are split into two fp16, lifted by the layer's own power of two first (the host chooses it: the
+    // largest scale just fits, and the low part of every row's largest is a normal number), the totals lowered at the end
+    static constexpr bool LIFTED = META8;
     uint4 c[META8 ? NA : NC];
     uint2 mp[META8 ? NA : 1], quad[META8 ? NA : 1];
     struct Raw { uint4 q; };
@@ -332,7 +334,7 @@ struct Te2 {
         }
     }
     // valid: units of the set that exist; what lies behind a row's end is no scale, so those units' records are zeros
-    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int valid, int tid) const
+    __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int valid, float lift, int tid) const
     {
         if constexpr (!META8) {
             const bool in = (tid % 8) / 2 < valid;
@@ -350,7 +352,7 @@ struct Te2 {
                 for (int k = 0; k < 4; ++k) {
                     float s, z;
                     decode_meta8(pr[k], quad[i], s, z);
-                    s = in ? s * PRE : 0.f;
+                    s = in ? s * lift : 0.f;
                     z = in ? z : 0.f;
                     const _Float16 hi = (_Float16)s;
                     const h2_t p = {hi, (_Float16)(s - (float)hi)};
@@ -527,7 +529,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     };
     // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
     auto fetch_b = [&](F &f, int h, int u) __attribute__((always_inline)) { f.fetch(h, w_rs, geo, row0, n_rows, u < u1 ? u : u0, u < u1, tid); };
-    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, tid); };
+    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, A.lift, tid); };
 
     // Left alone the scheduler moves a step's loads down to just before the LDS stores that wait for them: requests stay
     // above the first mark, stores below the second; everything else may cross.
@@ -620,7 +622,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     // w1/w3: even columns hold w1's rows, odd ones w3's: SiLU(u) v, rounded to fp16, collected in LDS (put) so that rows of
     // a leave in 16-byte pieces and their sums per group are taken on the way (copy_out).  w2: put stores.
     auto put = [&](float v, int tk, int wrow) __attribute__((always_inline)) {
-        v *= F::POST;
+        if constexpr (F::LIFTED) v *= A.lower;
         if constexpr (W13) {
             const float other = dpp_f<0xB1>(v);
             if ((lane & 1) == 0)

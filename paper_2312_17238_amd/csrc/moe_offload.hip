@@ -210,7 +210,9 @@ struct moe_layer {
     uint16_t *gamma_dev = nullptr;
     uint8_t *host_blobs = nullptr;
     std::vector<uint32_t> loaded;       // bit m set: matrix m of the expert was loaded
-    std::atomic<bool> wide_scale{false};// a loaded 2-bit scale is too large for the tile kernels' fp16 products (below)
+    // 2-bit layers: the largest scale loaded, and the smallest of the rows' largest ones (rows of zeros left out), both in
+    // size and as the bit pattern of the fp32 number; tile_format decides with them
+    std::atomic<uint32_t> scale_top{0}, scale_row_low{0x7f800000u};
     std::atomic<bool> wide_meta{false}; // a loaded (scale, zero) pair is too large for the rank-1 matrix-core form (below)
     std::vector<int32_t> own_bufs;      // the k pool buffers created for this layer
     // Where each expert's blob lives on the host: buffer index into host_blobs, or -1 while it is on the device
@@ -639,6 +641,19 @@ static float half_bits_to_float(uint16_t h)
     return f;
 }
 
+static uint32_t float_bits(float f)
+{
+    uint32_t bits;
+    memcpy(&bits, &f, sizeof bits);
+    return bits;
+}
+static float bits_to_float(uint32_t bits)
+{
+    float f;
+    memcpy(&f, &bits, sizeof f);
+    return f;
+}
+
 // The rank-1 matrix-core form computes (1024 + z) * s in fp16: pairs for which that product (or anything else about
 // them) leaves the comfortable part of the fp16 range make the layer fall back to the form that subtracts first.
 static bool pair_fits_rank1(uint16_t scale, uint16_t zero)
@@ -647,13 +662,14 @@ static bool pair_fits_rank1(uint16_t scale, uint16_t zero)
     return std::isfinite(s) && std::isfinite(z) && (1024.f + std::fabs(z)) * std::fabs(s) <= 16384.f;
 }
 
-// The tile kernels multiply 2-bit codes (at most 2 in size, centred) with their scale in fp16, two-level scales lifted by
-// 64 first: layers with larger scales than that allows stay on the GEMV kernels.
-static bool scale_fits_tile(uint16_t scale) { return std::fabs(half_bits_to_float(scale)) <= 32000.f; }
-static bool run_fits_tile(const uint16_t m[4])
+// Notes a 2-bit row's largest scale, given as the bits of its size (for these, the order of the numbers; NaN is above all).
+static void note_row_scale(moe_layer *l, uint32_t top)
 {
-    const float step = std::fabs(half_bits_to_float(m[0])), zero = half_bits_to_float(m[1]);
-    return std::max(std::fabs(255.f - zero), std::fabs(zero)) * step <= 500.f;
+    if (!top) return;
+    uint32_t v = l->scale_top.load(std::memory_order_relaxed);
+    while (top > v && !l->scale_top.compare_exchange_weak(v, top, std::memory_order_relaxed)) {}
+    v = l->scale_row_low.load(std::memory_order_relaxed);
+    while (top < v && !l->scale_row_low.compare_exchange_weak(v, top, std::memory_order_relaxed)) {}
 }
 
 extern "C" int32_t moe_layer_load_expert(moe_layer_t *l, int32_t expert, int32_t matrix, const uint8_t *codes,
@@ -671,9 +687,11 @@ try {
         if (watch && !l->wide_meta.load(std::memory_order_relaxed))
             for (uint32_t g = 0; g < groups; ++g)
                 if (!pair_fits_rank1(sr[g], zr[g])) { l->wide_meta.store(true, std::memory_order_relaxed); break; }
-        if (b.bits == 2)
-            for (uint32_t g = 0; g < groups; ++g)
-                if (!scale_fits_tile(sr[g])) { l->wide_scale.store(true, std::memory_order_relaxed); break; }
+        if (b.bits == 2) {
+            uint16_t top = 0;
+            for (uint32_t g = 0; g < groups; ++g) top = std::max<uint16_t>(top, sr[g] & 0x7fffu);
+            note_row_scale(l, float_bits(half_bits_to_float(top)));
+        }
         pack_row(b, m, codes + (uint64_t)r * m.cols, sr, zr, dst);
     });
 } catch (...) {
@@ -690,9 +708,17 @@ try {
     const MatLayout &m = mat_of(b, matrix);
     const uint32_t groups = m.cols / b.group, runs = (groups + m.run_len - 1) / m.run_len;
     return load_matrix(l, expert, matrix, codes, [&](uint32_t r, uint8_t *dst) {
-        if (b.bits == 2)
-            for (uint32_t j = 0; j < runs; ++j)
-                if (!run_fits_tile(run_meta + ((uint64_t)r * runs + j) * 4)) { l->wide_scale.store(true, std::memory_order_relaxed); break; }
+        if (b.bits == 2) {
+            uint32_t top = 0;
+            for (uint32_t j = 0; j < runs; ++j) {
+                const uint16_t *q = run_meta + ((uint64_t)r * runs + j) * 4;
+                const float step = half_bits_to_float(q[0]), zero = half_bits_to_float(q[1]);
+                const uint8_t *c = scale_code + (uint64_t)r * groups;
+                for (uint32_t g = j * m.run_len; g < std::min(groups, (j + 1) * m.run_len); ++g)
+                    top = std::max(top, float_bits(((float)c[g] - zero) * step) & 0x7fffffffu);
+            }
+            note_row_scale(l, top);
+        }
         pack_row_meta8(b, m, codes + (uint64_t)r * m.cols, scale_code + (uint64_t)r * groups, zero_code + (uint64_t)r * groups,
                        run_meta + (uint64_t)r * runs * 4, dst);
     });
@@ -1490,10 +1516,29 @@ static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
 static float tile_centre(const BlobLayout &b) { return b.bits == 4 ? 8.f : (b.bits == 3 ? 4.f : 1.f); }   // ZC of the format policies
 static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
 
+// The power of two that two-level 2-bit scales are multiplied with: the layer's largest just below 32000, so that its product
+// with a code (at most 2 in size, centred) is an fp16 number.
+static float tile_lift(const moe_layer *l)
+{
+    const float top = bits_to_float(l->scale_top.load(std::memory_order_relaxed));
+    if (l->lay.bits != 2 || !l->lay.scale_group || !(top > 0.f) || !std::isfinite(top)) return 1.f;
+    int e;
+    std::frexp(32000.f / top, &e);                   // 2^(e-1) <= 32000 / top
+    return std::ldexp(1.f, std::min(e - 1, 100));
+}
+
+// 2-bit codes enter the matrix cores multiplied with their scale in fp16, so a layer whose scales fp16 does not hold stays on the
+// GEMV kernels.  Above: one-level 32000, two-level 500.  Below: fp16 numbers are subnormal from 2^-14 on, whose products the
+// matrix cores add with about 2^-40 of error (w2's scales of 2^-22: y 7e-6 off, GEMV exact), and a two-level scale's second
+// half carries all of its bits as long as the scale, lifted, is 2^-2 or more.  What counts is a row's largest scale: beside
+// it the error of a smaller one is below fp32's.
 static bool tile_format(const moe_layer *l)
 {
     const BlobLayout &b = l->lay;
-    if (b.bits == 2 && l->wide_scale.load(std::memory_order_relaxed)) return false;
+    if (b.bits == 2) {
+        const float top = bits_to_float(l->scale_top.load(std::memory_order_relaxed)), low = bits_to_float(l->scale_row_low.load(std::memory_order_relaxed));
+        if (!(top <= (b.scale_group ? 500.f : 32000.f)) || low * tile_lift(l) < (b.scale_group ? 0.25f : 0x1p-14f)) return false;
+    }
     const bool fits32 = 2ull * b.ffn * b.m13.row_stride < (1ull << 31) && (uint64_t)b.hidden * b.m2.row_stride < (1ull << 31);
     return fits32 && (b.bits != 4 || b.group >= 64);
 }
@@ -1673,6 +1718,7 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     const int mode = c->tile_mode, rows = mode == TE_BIG ? 256 : 128;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
     A.zc = tile_centre(b);
+    A.lift = tile_lift(l); A.lower = 1.f / A.lift;
     A.top_k = K; A.part_base = batch * K;
     A.unit_shift = b.group == 128 ? 1 : 0;
     auto matrix = [&](const MatLayout &m, int Kdim, int N) {

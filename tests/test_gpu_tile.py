@@ -9,7 +9,7 @@ import workload as W
 from oracle import moe_oracle as O
 from paper_2312_17238_amd import binding as B
 
-from harness import Model, run_teacher_forced, say
+from harness import Model, check_y, oracle_routing, oracle_y, run_teacher_forced, say, to_np_expert
 
 pytestmark = pytest.mark.gpu
 
@@ -106,6 +106,35 @@ def test_which_kernels_a_step_takes(fmt, sg, H, F, E, K, Bn, tile):
     assert (y[0] == y[6 if tile else 5]).all()
 
 
+def edited_layer(sg, edit, forms, x_scale=None, H=128, F=256, E=2, Bn=8, thr=3):
+    """y [Bn][H] of one 2-bit layer per form; edit(matrix, tensors, generator) changes an expert's quantized matrices.
+    x_scale: no norm, tokens of that size.  Returns ({form: y}, the oracle's y)."""
+    model = Model(1, H, F, E, 1, [(2, 16)], E, 0, 0.0 if x_scale else 1e-5, max_batch=Bn, seed=63, scale_group=sg)
+    for e in range(E):
+        mats = [list(m) for m in W.quantized_expert(63, 0, e, H, F, 2, 16, model.device, sg)]
+        for i, mat in enumerate(mats):
+            edit(i, mat, torch.Generator().manual_seed(10 * e + i))
+            model.stack.load_expert(0, e, i, *mat)
+        model.experts[(0, e)] = to_np_expert(mats)
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_min_batch", thr)
+    x = (W.hidden_ar1(63, 1, Bn, H)[0] * (x_scale or 1.0)).to(torch.float16)
+    out, xd, ys = torch.empty_like(x, device=model.stack.device), x.to(model.stack.device), {}
+    torch.cuda.synchronize()
+    for form in forms:
+        B.moe_ctx_set_option(model.stack.ctx, "mfma_form", form)
+        model.stack.step_layer(0, xd, out)
+        model.stack.synchronize()
+        ys[form] = model.stack.read_y(Bn, H).copy()
+    ref = np.stack([oracle_y(model, 0, h, idx, w, O.expert_ffn) for h, idx, w, _ in oracle_routing(model, 0, x.numpy())])
+    model.close()
+    return ys, ref
+
+
+def same_bits(a, b):
+    assert np.isfinite(a).all() and (a != 0).any()
+    return (a.view(np.uint32) == b.view(np.uint32)).all()
+
+
 @pytest.mark.parametrize("sg", [0, 8])
 @pytest.mark.parametrize("factor", [1.0, 4e4])
 def test_large_2bit_scales(sg, factor):
@@ -139,3 +168,44 @@ def test_large_2bit_scales(sg, factor):
         assert (a.view(np.uint32) == b.view(np.uint32)).all()
     else:
         assert np.linalg.norm(a - b) <= 2 ** -11 * np.linalg.norm(b)
+
+
+def test_small_2bit_scales_two_level():
+    """The tile kernels hold a two-level 2-bit scale as two fp16 numbers: w2's scales 2^14 times smaller (exactly so: their
+    steps have four bits) give a y 2^14 times smaller, bit for bit, though steps are subnormal numbers then."""
+    def scaled(f):
+        def edit(i, mat, g):
+            if i == 2:
+                m = mat[3].cpu()
+                m[..., 0] = torch.randint(1, 16, m[..., 0].shape, generator=g) * 2.0 ** -10 * f
+                m[..., 1] = -8.0 - torch.rand(m[..., 1].shape, generator=g) * 63.0
+                mat[3] = m.to(mat[3].device)
+        return edit
+    (one, _), (small, _) = (edited_layer(8, scaled(f), (5, 6)) for f in (1.0, 2.0 ** -14))
+    assert not same_bits(one[6], one[5])           # the tile kernels did run
+    for form in (5, 6):
+        assert same_bits(small[form] * np.float32(2.0 ** 14), one[form])
+
+
+@pytest.mark.parametrize("sg", [0, 8])
+def test_scales_too_small_for_two_halves(sg):
+    """One-level scales whose products are subnormal fp16 numbers in a whole row, two-level ones too far below the layer's
+    largest: the layer stays on the GEMV kernels.  Small scales among ordinary ones in their row do not matter."""
+    def whole_rows(i, mat, g):
+        if i == 2 and sg:
+            mat[3][..., 0] = 2.0 ** -24
+            mat[3][..., 1] = -8.0
+        elif i == 2:
+            mat[1] = (mat[1] * 0 + (1 + torch.randint(0, 4, mat[1].shape, generator=g) / 4).to(mat[1].device) * 2.0 ** -22).to(torch.float16)
+        elif i == 0 and sg:                       # a lift that suits w1's scales leaves w2's second halves subnormal
+            mat[3][..., 0] = 0.25
+            mat[3][..., 1] = 0.0
+    def some(i, mat, g):
+        if i == 2 and not sg:
+            mat[1][:, 1::2] = 2.0 ** -22
+    ys, _ = edited_layer(sg, whole_rows, (5, 6), x_scale=2.0 ** -6)
+    assert same_bits(ys[6], ys[5])
+    ys, ref = edited_layer(sg, some, (5, 6))
+    assert not same_bits(ys[6], ys[5])
+    for b in range(len(ref)):
+        check_y(ys[6][b], ref[b], f"b={b}")
