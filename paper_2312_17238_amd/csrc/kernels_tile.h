@@ -734,13 +734,13 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         using std::integral_constant;
         using std::false_type;
         using std::true_type;
-        const int nt = half ? n_tiles - nt0 : nt0;
+        const int nt = half ? n_tiles - nt0 : nt0;               // at most MT
         if (half == 0) {
-            if (nt == 3) body(integral_constant<int, 3>{}, false_type{});
+            if (C::MT == 3 && nt == 3) body(integral_constant<int, C::MT>{}, false_type{});
             else if (nt == 2) body(integral_constant<int, 2>{}, false_type{});
             else body(integral_constant<int, 1>{}, false_type{});
         } else {
-            if (nt == 3) body(integral_constant<int, 3>{}, true_type{});
+            if (C::MT == 3 && nt == 3) body(integral_constant<int, C::MT>{}, true_type{});
             else if (nt == 2) body(integral_constant<int, 2>{}, true_type{});
             else if (nt == 1) body(integral_constant<int, 1>{}, true_type{});
             else body(integral_constant<int, 0>{}, true_type{});
