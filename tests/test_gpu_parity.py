@@ -352,12 +352,12 @@ def test_mixtral_layer_batch16_matrix_cores(Bn, T, k, form):
     model.close()
 
 
-@pytest.mark.parametrize("form", [5, 2])
+@pytest.mark.parametrize("form", [5, 2, 6, 0])
 @pytest.mark.parametrize("Bn,k", [(16, 8), (64, 8)])
 def test_mixtral_layer_two_level_metadata_matrix_cores(Bn, k, form):
     """Mixtral-shaped layer with two-level metadata (scale group 128: one run per row of w1/w3, two per row of w2) on
-    the matrix cores, one and two token tiles, C oracle on every row: the group-scaled kernels decode scale and zero
-    in fp32 (default), form 2 dequantises to fp16 first."""
+    the matrix cores, one and two token tiles, C oracle on every row: the group-scaled and the tile kernels decode scale
+    and zero in fp32 (the default takes either), form 2 dequantises to fp16 first."""
     c = W.CONFIGS["mixtral_layer"]
     say(f"mixtral layer, two-level metadata, B={Bn} form {form}: build")
     model = Model(1, c.hidden, c.ffn, c.n_experts, c.top_k, None, k, 0, 0.0, max_batch=Bn, seed=c.seed, scale_group=128)
@@ -745,8 +745,8 @@ def test_prompt_sized_batches(Bn, k, T, form):
 
 @pytest.mark.parametrize("formats,scale_group,Bn", [([(2, 16), (3, 64)], 0, 300), ([(4, 64), (4, 64)], 256, 200)])
 def test_prompt_sized_batches_on_the_gemv_kernels(formats, scale_group, Bn):
-    """Formats the matrix-core kernels do not take (2-bit, 3-bit; and 4-bit with the threshold raised) run a large
-    batch through the GEMV kernels, four tokens per entry and sixteen entries per launch."""
+    """With the threshold of the matrix-core kernels raised every format runs a large batch through the GEMV kernels, four
+    tokens per entry and sixteen entries per launch."""
     L, H, F = 2, 256, 512
     say(f"prompt-sized batch on GEMV kernels B={Bn} formats={formats} scale_group={scale_group}")
     model = Model(L, H, F, 8, 2, formats, 4, 2, 1e-5, max_batch=Bn, seed=83, scale_group=scale_group)
@@ -785,6 +785,10 @@ def draw_configuration(seed):
     if r.rand() < 0.2:      # decode with every expert resident: the steps that do not wait for their gate
         c.update(Bn=1, T=6, k=c["E"], K=min(c["K"], 2))
         c["options"].update(token_path=1, fused=0)
+    if seed >= 40:          # the tile kernels
+        c["options"].update(mfma_form=6, mfma_min_batch=pick([2, 3]))
+        if c["Bn"] == 1:
+            c.update(Bn=pick([2, 4, 12, 33]), T=3)
     return c
 
 
@@ -797,9 +801,9 @@ def build_configuration(c, seed):
     return model
 
 
-@pytest.mark.parametrize("seed", range(40))
+@pytest.mark.parametrize("seed", range(56))
 def test_random_configurations(seed):
-    """Forty seeded combinations of shapes, per-layer formats, metadata levels, cache sizes, swap mode, warm start
+    """Forty seeded combinations (and sixteen more on the tile kernels) of shapes, per-layer formats, metadata levels, cache sizes, swap mode, warm start
     and launch options, none of them chosen by hand: every decision bit-exact and every output row in tolerance
     against the oracle, as in the hand-picked cases above.  Then the same tokens through the whole-stack entry point
     without traces (after a reset, or on a stack built anew; statistics read at seeded moments, which makes

@@ -16,12 +16,27 @@ pytestmark = pytest.mark.gpu
 FORMATS = [((4, 64), 0), ((4, 64), 256), ((4, 128), 0), ((4, 128), 2), ((3, 64), 0), ((3, 64), 1), ((2, 16), 0), ((2, 16), 8)]
 
 
-def run(fmt, sg, H, F, E, K, k, Bn, T=1, seed=61, m=0):
+def one_step(model, x, form):
+    """y of one step of layer 0 with the kernels of a form, as bits."""
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_form", form)
+    out, tr = torch.empty_like(x), B.StepTrace()      # traced: one token takes the same way as several
+    torch.cuda.synchronize()
+    model.stack.step_layer(0, x, out, None, tr)
+    model.stack.synchronize()
+    return model.stack.read_y(x.shape[0], x.shape[1]).copy().view(np.uint32)
+
+
+def run(fmt, sg, H, F, E, K, k, Bn, T=1, seed=61, m=0, rows=None):
     model = Model(2 if m else 1, H, F, E, K, [fmt] * (2 if m else 1), k, m, 1e-5, max_batch=Bn, seed=seed, scale_group=sg)
     B.moe_ctx_set_option(model.stack.ctx, "mfma_form", 6)
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_min_batch", 1)
     xs = W.hidden_ar1(seed, T, Bn, H)
-    rows = (lambda t, l: sorted({0, 1, Bn // 2, Bn - 2, Bn - 1} & set(range(Bn)))) if Bn > 40 else None
-    _, _, errs = run_teacher_forced(model, xs, O.expert_ffn, rows=rows)
+    if rows is None and Bn > 40:
+        rows = {0, 1, Bn // 2, Bn - 2, Bn - 1}
+    _, _, errs = run_teacher_forced(model, xs, O.expert_ffn, rows=(lambda t, l: sorted(rows & set(range(Bn)))) if rows else None)
+    # the tile kernels did run: the kernels a step takes without them add in another order
+    x = xs[0].to(model.stack.device)
+    assert (one_step(model, x, 6) != one_step(model, x, 5)).any()
     say(f"tile {fmt} {sg} H={H} F={F} E={E} K={K} k={k} B={Bn}: max abs {max(e[0] for e in errs):.2e} rel {max(e[1] for e in errs):.2e}")
     model.close()
 
@@ -38,6 +53,19 @@ def test_every_format(fmt, sg, H, F, Bn):
 def test_token_tiles(fmt, Bn):
     """Every token needs the one expert there is: 1 to 13 token tiles, one to three token blocks, uneven halves."""
     run(fmt, 0, 64, 192, 1, 1, 1, Bn)
+
+
+# H: 6 sets of units, the last one short; F: enough sets that every part of w2's contraction takes at least 3 of them.  Metadata
+# in several runs a row.  One expert has every token, so its number decides the kernel: 16, 32, one, two and three tiles a wave.
+STEADY = [((4, 64), 0), ((4, 64), 8), ((4, 128), 0), ((4, 128), 4), ((3, 64), 0), ((3, 64), 4), ((2, 16), 0), ((2, 16), 16)]
+
+
+@pytest.mark.parametrize("fmt,sg,Bn", [(f, s, b) for f, s in STEADY for b in (16, 32, 33)] +
+                         [(f, s, b) for f, s in (((4, 64), 0), ((3, 64), 4), ((2, 16), 0), ((2, 16), 16)) for b in (15, 17, 97, 150)])
+def test_pipelines_in_their_steady_state(fmt, sg, Bn):
+    """Contractions of several sets: buffers refilled after they were read, both halves of every double buffer."""
+    H, F = (1408, 6272) if fmt[1] == 128 else (1344, 6208)
+    run(fmt, sg, H, F, 1, 1, 1, Bn, rows={0, Bn // 2, Bn - 1})
 
 
 @pytest.mark.parametrize("fmt,sg", [((4, 64), 0), ((3, 64), 128), ((2, 16), 0)])
