@@ -1972,12 +1972,22 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;
 
+    // The sort runs under the host's work of this step, so it is queued as soon as it is known that its list will be read: at
+    // once where the average alone says so, else right behind the copy of the routing.
+    bool sorted = false;
+    auto sort_pairs = [&]() -> int32_t {
+        if (sorted) return MOE_OK;
+        sorted = true;
+        hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
+        HIPCHK(hipGetLastError());
+        return MOE_OK;
+    };
+    if (tile_ready && (c->mfma_form == 6 || (!tiles16 && batch * cf.top_k > tile_above * cf.n_experts))) { rc = sort_pairs(); if (rc) return rc; }
     const GateHostOut *go = c->gate_out;
     int32_t idx[MOE_MAX_BATCH * MOE_MAX_TOPK];
     float w[MOE_MAX_BATCH * MOE_MAX_TOPK];
     for (int i = 0; i < batch * cf.top_k; ++i) {
         idx[i] = go->idx[i];
-        w[i] = go->w[i];
         if (idx[i] < 0 || idx[i] >= cf.n_experts) return fail(MOE_EINVAL, "routing index %d out of range", idx[i]);
     }
     if (tile_ready) tile_plan(l, idx, batch);
@@ -1986,10 +1996,8 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
         const double us = plan_windows(l, idx, batch);
         use_tile = use_tile && tile_us(l, batch) < us;
     }
-    if (use_tile) {     // before the host's other decisions: it runs under them
-        hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
-        HIPCHK(hipGetLastError());
-    }
+    if (use_tile) { rc = sort_pairs(); if (rc) return rc; }
+    for (int i = 0; i < batch * cf.top_k; ++i) w[i] = go->w[i];
     double score[MOE_MAX_EXPERTS] = {0};
     if (spec)
         for (int b = 0; b < batch; ++b)
