@@ -213,13 +213,9 @@ __device__ __forceinline__ uint32_t split2(float v)
 }
 
 // What the tile kernels take of a group of activations: its sum (split in two), and minus the sum weighted with what the
-// codes' fp16 patterns add to them -- xa: sum over the elements at 0, 1, 4, 5 (mod 8), whose codes carry a bias of 1024, xb:
-// over the others, bias 64; zc: the constant the codes are centred on.
-__device__ __forceinline__ uint2 group_sums(float xa, float xb, float zc)
-{
-    const float p = -((1024.f + zc) * xa + (64.f + zc) * xb);
-    return make_uint2(split2(xa + xb), __builtin_bit_cast(uint32_t, p));
-}
+// codes' fp16 patterns and the constant they are centred on add to them -- xa: sum over the elements at 0, 1, 4, 5 (mod 8),
+// pa: what their codes carry, xb and pb: the others.
+__device__ __forceinline__ uint2 group_sums(float xa, float xb, float pa, float pb) { return make_uint2(split2(xa + xb), __builtin_bit_cast(uint32_t, -(pa * xa + pb * xb))); }
 
 // wave-uniform value as a scalar, so that addresses derived from it are computed on the scalar unit
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -44,7 +44,7 @@ struct GateArgs {
     uint8_t *pair_expert;           // [b*K + j]
     float *pair_w;                  // [b*K + j]
     uint2 *xs;                      // [b][xs_stride] (group_sums)
-    float xs_zc;
+    float xs_pa, xs_pb;             // ... their weights
     int32_t xs_stride, xs_group;
 };
 
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
                 sa += dpp_f<0x140>(sa);
                 sb += dpp_f<0x140>(sb);
             }
-            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = group_sums(sa, sb, a.xs_zc);
+            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = group_sums(sa, sb, a.xs_pa, a.xs_pb);
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e)

@@ -28,12 +28,22 @@
 // Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 684 + 351 (0.7 PFLOP/s; the
 // 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 440 + 225 (GEMV kernels 6.3 ms together); 16 tokens
 // 3-bit 116 + 62, 2-bit 119 + 62 (GEMV kernels 213 + 103); 64 tokens 4-bit 131 + 65 (two 16-token tiles 129 + 71).  What
-// bounds them: matrix and vector instructions of the waves on a SIMD overlap only in part (1024 tokens without any load
-// from memory or LDS: 478 + 231), the rest is latency between the barriers; a fetch further ahead, fewer vector
-// instructions (subnormal codes) and padded rows of activations each changed less than the runs differ.
+// bounds them: no unit is full (4-bit prompt, w1/w3: vector unit 48 %, matrix unit 32 %, LDS 9 %); a third of the waves'
+// time goes into waits, for a unit's barrier and the activations staged for it within that unit (1024 tokens without any
+// load from memory or LDS: 478 + 231), and two waves a SIMD leave nobody else to run.  A fetch further ahead, fewer vector
+// instructions (subnormal codes) and padded rows of activations each changed less than the runs differ.  2-bit, 16 tokens:
+// vector unit 54 %, of it a quarter for the metadata.
 //
-// MODE 16 and 32 (a block's tokens at most): the codes enter with the biases of their bit patterns (1024 and 64) and the
-// products start from minus what biases and ZC add up to, an fp32 number per token and group that comes with the sums
+// Error of this arithmetic alone: y of a layer against 64 bits with the activations between the halves rounded to fp16 as
+// here, 2048 x 5632 to 4096 x 14336, eight seeds, tokens as the decode workloads draw them.  BIG 2.8 to 4.0e-5 (GEMV 9 to 18e-5,
+// 16-token kernels 9 to 10e-5: their biased codes); MODE 16 and 32: 2-bit 3.6 to 4.0e-5 (GEMV 11e-5), 3-bit 14.0e-5 (17.7e-5),
+// 4-bit 3.1 to 3.4e-5 (GEMV 9.1 to 9.8e-5, 16-token kernels 9.2 to 9.4e-5).  With the rounding of a, the error of y: 4-bit 2.07 to
+// 2.08e-4 (others 2.08 to 2.10e-4), 3-bit 2.13e-4 (GEMV 2.21e-4), 2-bit 2.09e-4 (2.11e-4).  The split
+// sums show only far from such tokens: normalised ones of mean 1 and deviation 1/8 give 2-bit codes 6.4e-5 (GEMV 2.9e-5), the
+// others 8 to 9e-5 (16 to 41e-5).
+//
+// MODE 16 and 32 (a block's tokens at most): the codes enter with the biases of their bit patterns (64, with 3 bits
+// also 1024) and the products start from minus what biases and ZC add up to, an fp32 number per token and group that comes with the sums
 // X; BIG has no registers left for that and subtracts from the codes.
 //
 // BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
@@ -76,7 +86,7 @@ struct TeArgs {
     uint64_t mat_off;
     int32_t units_per_part, k_parts, part_base;
     int32_t jobs;                        // row blocks * k_parts
-    float zc;                            // the constant the codes are centred on
+    float pa, pb;                        // weights of the sums (group_sums)
     float lift, lower;                   // two-level 2-bit codes: what their scales are multiplied with, and its reciprocal
     uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
 };
@@ -119,6 +129,13 @@ __device__ __forceinline__ h8_t centred4(uint32_t w, const BiasPatterns &p, uint
     h8_t r;
     r[0] = r0.x; r[1] = r0.y; r[2] = r1.x; r[3] = r1.y; r[4] = r2.x; r[5] = r2.y; r[6] = r3.x; r[7] = r3.y;
     return r;
+}
+
+// eight codes as the fp16 numbers 64 + q, in codes_biased's slots
+__device__ __forceinline__ h8_t codes_biased64(uint32_t w, const BiasPatterns &p)
+{
+    const u32x4_t r = {((w << 4) & p.m_hi) | p.k64, (w & p.m_hi) | p.k64, ((w >> 4) & p.m_hi) | p.k64, ((w >> 8) & p.m_hi) | p.k64};
+    return __builtin_bit_cast(h8_t, r);
 }
 
 // What the format policies know of a matrix: offsets inside a row, units of a row.  Loads of codes address with one
@@ -184,6 +201,10 @@ struct TeScaled {                        // the part that 4-bit and 3-bit format
 template <bool META8, int ROWS, int THREADS>
 struct Te4 : TeScaled<META8, ROWS, THREADS> {
     static constexpr float ZC = 8.f;
+    // Bias 64 for every code.  With 1024 for half of them (two shifts per word less) the products' sums are so much larger than what
+    // is left of them that their rounding was this format's largest error: y, apart from the rounding of a, 9.5 to 10.4e-5 off, the
+    // GEMV kernels 9.1 to 9.8e-5; now 3.1 to 3.4e-5.  24 tokens, Mixtral-shaped, group 128: w1/w3 + w2 108.7 + 60.7 -> 109.7 + 60.9 us.
+    static __device__ __forceinline__ h8_t biased(uint32_t w, const BiasPatterns &p) { return codes_biased64(w, p); }
     static constexpr int SOFF = 128, REC = 144, NC = ROWS * 8 / THREADS;
     uint4 c[NC];
     struct Raw { uint4 q; };
@@ -226,6 +247,8 @@ template <int R, int T> struct Te<48, R, T> : Te4<true, R, T> {};
 template <bool META8, int ROWS, int THREADS>
 struct Te3 : TeScaled<META8, ROWS, THREADS> {
     static constexpr float ZC = 4.f;
+    // biases 1024 and 64: more exact than the GEMV kernels all the same (14.0e-5 against 17.7e-5), and 64 alone costs 2 %
+    static __device__ __forceinline__ h8_t biased(uint32_t w, const BiasPatterns &p) { return codes_biased(w, p); }
     static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS;
     static_assert(NA >= 1 && ROWS * 2 <= THREADS, "region B is one piece per thread, repeated by threads too many");
     uint4 a[NA], b;
@@ -658,7 +681,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                     if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
                     uint2 *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
                     const int g = colg / XG;
-                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = group_sums(xa, xb, A.zc);
+                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = group_sums(xa, xb, A.pa, A.pb);
                     if (c == 0 && (rb + 1) * C::ACOLS >= A.N)            // the padding behind the last group that no row block covers
                         for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
                 }
@@ -796,7 +819,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                     }
                     Acc g = p0;
 #pragma unroll
-                    for (int k = 0; k < KS; ++k) g = mm(a[k], codes_biased(t[k], bp), g);
+                    for (int k = 0; k < KS; ++k) g = mm(a[k], F::biased(t[k], bp), g);
 #pragma unroll
                     for (int i = 0; i < NR; ++i) tot[rt][i] = __builtin_fmaf(sc, g[i], tot[rt][i]);
                 }

@@ -168,14 +168,15 @@ struct moe_ctx {
     int32_t w13_blocks = 256, w2_rows = 32;
     int32_t w2_token_rows = 0;          // rows per block of the single-token w2 kernel; 0: hidden / compute units
     uint32_t gate_seq = 0;              // sequence number of the last gate launch
-    int32_t mfma_form = 0;              // matrix-core kernels: 0 the default (5); 5 streaming form with 16-token tiles (one per
+    int32_t mfma_form = 0;              // matrix-core kernels: 0 the default (6 where an expert has enough tokens and, for formats form 5 takes, 6 is
+                                        // faster; else 5 or the GEMV kernels); 6 tile kernels, every format but 4-bit g32; 5 streaming form with 16-token tiles (one per
                                         // expert while no expert of the window has more than 16 tokens, else two), codes multiplied as they are and
                                         // groups scaled in fp32; 4 the same with weights dequantised to fp16;
                                         // 3 streaming form, one fma per pair of weights plus a rank-1 correction;
                                         // 2 streaming form with an exact subtraction first; 1 row-staging form with fp32 group scaling
     int32_t mfma16_waves = 8;           // waves per block of the 16-token forms' single-tile kernels: 4 or 8 (two blocks per compute unit either
                                         // way; with two token tiles 8 waves need 194 registers, one block per unit, and measured 12 % slower)
-    int32_t mfma_min_batch = 3;         // batches at least this large use the matrix-core kernels (4-bit g64): measured, all experts of a
+    int32_t mfma_min_batch = 3;         // batches at least this large may use the matrix-core kernels (4-bit g64: do): measured, all experts of a
                                         // Mixtral-shaped layer resident, they are 9 % faster than the GEMV kernels at 3 tokens and 82 % at 12
     int32_t staged_min_batch = 0;       // matrix-core batches larger than this: resident experts first, arriving ones one by one
     uint64_t spec_head_bytes = 0;       // 0: a speculative load moves the whole expert at once (as the paper describes);
@@ -681,7 +682,7 @@ try {
     const BlobLayout &b = l->lay;
     const MatLayout &m = mat_of(b, matrix);
     const uint32_t groups = m.cols / b.group;
-    const bool watch = b.bits == 4 && b.group == 64;     // the formats the matrix cores take
+    const bool watch = b.bits == 4 && b.group == 64;     // the format of the rank-1 form
     return load_matrix(l, expert, matrix, codes, [&](uint32_t r, uint8_t *dst) {
         const uint16_t *sr = scale + (uint64_t)r * groups, *zr = zero + (uint64_t)r * groups;
         if (watch && !l->wide_meta.load(std::memory_order_relaxed))
@@ -1513,7 +1514,12 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
 
 // Codes per sum of activations: the groups of the zero-point term.
 static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
-static float tile_centre(const BlobLayout &b) { return b.bits == 4 ? 8.f : (b.bits == 3 ? 4.f : 1.f); }   // ZC of the format policies
+// What the codes' patterns (biased() of the format policies; 2-bit codes have none) and the constant they are centred on (ZC) add.
+static void tile_sum_weights(const BlobLayout &b, float &pa, float &pb)
+{
+    pa = b.bits == 4 ? 64.f + 8.f : (b.bits == 3 ? 1024.f + 4.f : 0.f);
+    pb = b.bits == 4 ? 64.f + 8.f : (b.bits == 3 ? 64.f + 4.f : 0.f);
+}
 static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
 
 // The power of two that two-level 2-bit scales are multiplied with: the layer's largest just below 32000, so that its product
@@ -1717,7 +1723,7 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     }
     const int mode = c->tile_mode, rows = mode == TE_BIG ? 256 : 128;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
-    A.zc = tile_centre(b);
+    tile_sum_weights(b, A.pa, A.pb);
     A.lift = tile_lift(l); A.lower = 1.f / A.lift;
     A.top_k = K; A.part_base = batch * K;
     A.unit_shift = b.group == 128 ? 1 : 0;
@@ -1967,7 +1973,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
     if (tile_ready) {
         ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
-        ga.xs = c->xs_h; ga.xs_zc = tile_centre(l->lay); ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
+        ga.xs = c->xs_h; tile_sum_weights(l->lay, ga.xs_pa, ga.xs_pb); ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
     }
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;

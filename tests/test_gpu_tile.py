@@ -225,6 +225,40 @@ def test_scales_too_small_for_two_halves(sg):
         check_y(ys[6][b], ref[b], f"b={b}")
 
 
+def weights64(mat, group, sg):
+    """An expert's matrix [out][in] in 64 bits."""
+    q = mat[0].astype(np.float64).reshape(mat[0].shape[0], -1, group)
+    if sg:
+        _, sc, zc, meta, run = mat
+        m = np.repeat(meta.astype(np.float64), run, axis=1)[:, : sc.shape[1]]
+        s, z = (sc - m[..., 1]) * m[..., 0], (zc - m[..., 3]) * m[..., 2]
+    else:
+        s, z = mat[1].astype(np.float64), mat[2].astype(np.float64)
+    return ((q - z[..., None]) * s[..., None]).reshape(mat[0].shape)
+
+
+@pytest.mark.parametrize("fmt,sg", [((4, 64), 8), ((4, 128), 0), ((4, 128), 4), ((3, 64), 0), ((2, 16), 0), ((2, 16), 16)])
+@pytest.mark.parametrize("Bn", [16, 32, 33])
+def test_as_exact_as_the_gemv_kernels(fmt, sg, Bn):
+    """Error against 64 bits (the activations between the halves rounded to fp16 there too) beside the GEMV kernels' on the same
+    tokens: measured at 0.15 to 0.49 of it, 3-bit up to 32 tokens at 0.77 to 0.81, whose codes enter with the GEMV kernels' biases."""
+    H, F = 1024, 2048
+    model = Model(1, H, F, 1, 1, [fmt], 1, 0, 1e-5, max_batch=Bn, seed=66, scale_group=sg)
+    xs = W.hidden_ar1(66, 1, Bn, H)[0]
+    h = np.stack([r[0] for r in oracle_routing(model, 0, xs.numpy())]).astype(np.float64)
+    w1, w3, w2 = (weights64(m, fmt[1], sg) for m in model.expert_np(0, 0))
+    u = h @ w1.T
+    y = (u / (1.0 + np.exp(-u)) * (h @ w3.T)).astype(np.float16).astype(np.float64) @ w2.T
+    x = xs.to(model.stack.device)
+    tile = one_step(model, x, 6)
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_min_batch", 1000)
+    gemv = one_step(model, x, 5)
+    model.close()
+    err = [np.linalg.norm(v.view(np.float32) - y) / np.linalg.norm(y) for v in (tile, gemv)]
+    say(f"tile {fmt} {sg} B={Bn}: {err[0]:.3g} against {err[1]:.3g}")
+    assert err[0] <= (0.95 if fmt[0] == 3 and Bn <= 32 else 0.6) * err[1]
+
+
 @pytest.mark.parametrize("sg", [0, 8])
 def test_2bit_tile_kernels_agree_with_gemv(sg):
     """Ordinary scales: within the order of the sums (fp16 activations between the halves: half an ulp, 2^-11, may fall the
