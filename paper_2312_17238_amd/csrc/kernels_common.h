@@ -212,10 +212,16 @@ __device__ __forceinline__ uint32_t split2(float v)
     return __builtin_bit_cast(uint32_t, p);
 }
 
-// What the tile kernels take of a group of activations: its sum (split in two), and minus the sum weighted with what the
-// codes' fp16 patterns and the constant they are centred on add to them -- xa: sum over the elements at 0, 1, 4, 5 (mod 8),
-// pa: what their codes carry, xb and pb: the others.
-__device__ __forceinline__ uint2 group_sums(float xa, float xb, float pa, float pb) { return make_uint2(split2(xa + xb), __builtin_bit_cast(uint32_t, -(pa * xa + pb * xb))); }
+// ... as three bf16 that together are the number, cut off one behind the other (8 bits each): x holds the first two, y the
+// third in both halves.
+__device__ __forceinline__ uint2 split3(float v)
+{
+    const uint32_t b0 = __builtin_bit_cast(uint32_t, v) & 0xffff0000u;
+    const float r1 = v - __builtin_bit_cast(float, b0);
+    const uint32_t b1 = __builtin_bit_cast(uint32_t, r1) & 0xffff0000u;
+    const uint32_t b2 = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b1));
+    return make_uint2(__builtin_amdgcn_perm(b1, b0, 0x07060302u), __builtin_amdgcn_perm(b2, b2, 0x03020302u));
+}
 
 // wave-uniform value as a scalar, so that addresses derived from it are computed on the scalar unit
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }

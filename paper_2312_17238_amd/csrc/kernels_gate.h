@@ -40,11 +40,10 @@ struct GateArgs {
     float *route_w;                 // [K] device
     int32_t *route_log;             // [K] device: this step's slot of the log ring
     // For the tile kernels (TILE): every pair's expert and combine weight in device memory, and the sums of h over
-    // groups of xs_group (16 or 64) elements, rows padded with zeros to xs_stride.
+    // groups of xs_group elements, rows padded with zeros to xs_stride (16: split2, 64: split3).
     uint8_t *pair_expert;           // [b*K + j]
     float *pair_w;                  // [b*K + j]
-    uint2 *xs;                      // [b][xs_stride] (group_sums)
-    float xs_pa, xs_pb;             // ... their weights
+    uint2 *xs;                      // [b][xs_stride]
     int32_t xs_stride, xs_group;
 };
 
@@ -133,18 +132,14 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
         const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
                      h3 = half_bits_to_f64(hv[3]);
         if constexpr (TILE) {     // 4 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
-            float sa = (float)h0 + (float)h1, sb = (float)h2 + (float)h3;
-            sa += dpp_f<0xB1>(sa);
-            sb += dpp_f<0xB1>(sb);
-            sa += dpp_f<0x4E>(sa);
-            sb += dpp_f<0x4E>(sb);
+            float s = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
+            s += dpp_f<0xB1>(s);
+            s += dpp_f<0x4E>(s);
             if (a.xs_group == 64) {
-                sa += dpp_f<0x141>(sa);
-                sb += dpp_f<0x141>(sb);
-                sa += dpp_f<0x140>(sa);
-                sb += dpp_f<0x140>(sb);
+                s += dpp_f<0x141>(s);
+                s += dpp_f<0x140>(s);
             }
-            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = group_sums(sa, sb, a.xs_pa, a.xs_pb);
+            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = a.xs_group == 64 ? split3(s) : make_uint2(split2(s), 0u);
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e)

@@ -2,7 +2,9 @@
 //
 // A block multiplies one expert's tokens (or up to TOK of them) with ROWS memory rows.  k_tile<.., TE_BIG>: 8 waves, 256
 // rows x up to 192 tokens, a wave 64 rows x up to 96 tokens (two waves share each 64 rows).  k_tile<.., 16 or 32>: 128
-// rows x up to that many tokens, the units of a set shared by the waves of 64 rows; two blocks per compute unit.
+// rows x up to that many tokens, the units of a set shared by the waves of 64 rows (32, with tiles of 32 tokens and 3 or 4 bits:
+// 8 waves a block then fit 128 registers each, four waves a SIMD; 1856 x 5056, 37 tokens, two-level: 26.7 + 19.6 -> 24.2 + 18.2 us,
+// larger layers the same as with 4 waves); two blocks per compute unit.
 //
 // A unit is 64 codes of a row, a set four units: 128 bytes of 4-bit codes, which 8 lanes read in one piece.  Weights
 // cross LDS once (v_mfma_f32_32x32x16 wants a row per lane; loaded that way from memory every 16-byte piece would be a
@@ -12,22 +14,26 @@
 //
 // Arithmetic.  A weight is s (q - z) with real z, and with any constant ZC
 //     sum_k s (q - z) x  =  sum_groups s (sum_k (q - ZC) x)  +  sum_groups s (ZC - z) X,     X = sum of the group's x.
-// q - ZC is exact in fp16.  First term, groups of 64 codes or more: the group's product comes out of the matrix cores in
-// fp32 and is scaled by the fp32 s with one fused multiply-add per accumulator register; no weight is rounded.
-// (Codes as the subnormal fp16 numbers their bits spell need no exponent and no subtraction, but the matrix cores
-// accumulate products of subnormals with fewer bits: 6 % more error in y.)
+// 3 and 4 bits (groups of 64 codes or more), ZC = -64: a code enters the matrix cores as the fp16 number 64 + q that its
+// bits spell under the exponent of 64, which costs a shift and a v_and_or_b32 per pair, no subtraction (a bias of 1024 for half of
+// the codes would save two shifts a word, but makes the sums so large that their rounding shows in y).  The group's product comes out
+// in fp32 and is scaled by the fp32 s with one fused multiply-add per accumulator register; no weight is rounded.
+// (Codes as the subnormal fp16 numbers their bits spell need no exponent, but the matrix cores accumulate products of
+// subnormals with fewer bits: 6 % more error in y.)
 // 2-bit codes (groups of 16; ZC = 1): q - 1 is one of -1, 0, 1, 2 and (q - 1) s is exact in fp16 for an fp16 s, so the
 // scaled weight goes in directly; an fp32 s (two-level metadata) goes in as two fp16 numbers, in two products.
-// Second term: a contraction over groups instead of codes.  X and D = s (ZC - z) are fp32 numbers split into two bf16
-// each (what is lost is 2^-17 of the term, itself a fraction of the result); per group the four k-slots
-// (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl) give the whole product, so one bf16 matrix instruction takes four groups; correcting
-// every group's product in the accumulators instead would double the vector work per group.  The X come from whoever
-// produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros to a multiple of
-// four groups.
+// Second term: a contraction over groups instead of codes, on the bf16 matrix instructions.  With ZC = -64 it is some twenty times
+// the result, so X and D = s (ZC - z) go in whole, cut into three bf16 each: eight k-slots a group (slots3_x, slots3_d) hold all
+// products but that of the third parts.  2-bit codes: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the
+// result), the four k-slots (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl).  Correcting every group's product in the accumulators instead
+// would double the vector work per group; starting the products from minus the biases' share takes four more LDS reads per token
+// tile and unit (that, and centred codes in the large kernel, is what these kernels did before: 1024 tokens 4-bit 684 + 351 us).
+// The X come from whoever produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros
+// to a multiple of four groups.
 //
-// Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 684 + 351 (0.7 PFLOP/s; the
-// 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 440 + 225 (GEMV kernels 6.3 ms together); 16 tokens
-// 3-bit 116 + 62, 2-bit 119 + 62 (GEMV kernels 213 + 103); 64 tokens 4-bit 131 + 65 (two 16-token tiles 129 + 71).  What
+// Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 640 + 330 (0.75 PFLOP/s; the
+// 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 430 + 220 (GEMV kernels 6.3 ms together); 16 tokens
+// 3-bit 117 + 61, 2-bit 117 + 58 (GEMV kernels 213 + 103); 64 tokens 4-bit 131 + 65 (two 16-token tiles 129 + 71).  What
 // bounds them: no unit is full (4-bit prompt, w1/w3: vector unit 48 %, matrix unit 32 %, LDS 9 %); a third of the waves'
 // time goes into waits, for a unit's barrier and the activations staged for it within that unit (1024 tokens without any
 // load from memory or LDS: 478 + 231), and two waves a SIMD leave nobody else to run.  A fetch further ahead, fewer vector
@@ -35,16 +41,10 @@
 // vector unit 54 %, of it a quarter for the metadata.
 //
 // Error of this arithmetic alone: y of a layer against 64 bits with the activations between the halves rounded to fp16 as
-// here, 2048 x 5632 to 4096 x 14336, eight seeds, tokens as the decode workloads draw them.  BIG 2.8 to 4.0e-5 (GEMV 9 to 18e-5,
-// 16-token kernels 9 to 10e-5: their biased codes); MODE 16 and 32: 2-bit 3.6 to 4.0e-5 (GEMV 11e-5), 3-bit 14.0e-5 (17.7e-5),
-// 4-bit 3.1 to 3.4e-5 (GEMV 9.1 to 9.8e-5, 16-token kernels 9.2 to 9.4e-5).  With the rounding of a, the error of y: 4-bit 2.07 to
-// 2.08e-4 (others 2.08 to 2.10e-4), 3-bit 2.13e-4 (GEMV 2.21e-4), 2-bit 2.09e-4 (2.11e-4).  The split
-// sums show only far from such tokens: normalised ones of mean 1 and deviation 1/8 give 2-bit codes 6.4e-5 (GEMV 2.9e-5), the
-// others 8 to 9e-5 (16 to 41e-5).
-//
-// MODE 16 and 32 (a block's tokens at most): the codes enter with the biases of their bit patterns (64, with 3 bits
-// also 1024) and the products start from minus what biases and ZC add up to, an fp32 number per token and group that comes with the sums
-// X; BIG has no registers left for that and subtracts from the codes.
+// here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), 1024 x 3584 to
+// 4096 x 14336, eight seeds, tokens as the decode workloads draw them.  4-bit: BIG 3.8e-5, MODE 16 and 32 4.3 to 5.2e-5 (GEMV and 16-token
+// kernels 9.1 to 9.8e-5); 3-bit 6.3e-5 (GEMV 17.7e-5); 2-bit 3.6 to 4.0e-5 (GEMV 11e-5).  With the rounding of a, the error of y: 4-bit
+// 2.07 to 2.08e-4 (others 2.08 to 2.10e-4), 3-bit 2.07e-4 (GEMV 2.21e-4), 2-bit 2.09e-4 (2.11e-4).
 //
 // BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
 // other at the end of the unit before, so that one's vector work runs under the other's matrix work.
@@ -74,7 +74,7 @@ struct TeArgs {
     const uint16_t *plist;               // pair ids (token * top_k + choice), expert by expert, ascending within one
     const float *pair_w;                 // combine weight of every pair
     const uint16_t *act;                 // w1/w3: h [B][K];  w2: a [B*top_k][K]
-    const uint2 *xs;                     // sums of act per group (group_sums): [row of act][xs_stride]
+    const uint2 *xs;                     // sums of act per group: [row of act][xs_stride]
     uint16_t *a;                         // w1/w3: SwiGLU activations [pair][N]
     uint2 *xs_out;                       // ... and their sums
     float *ypart;                        // w2: rows of N, one per pair (k_parts == 1) or per (position, part)
@@ -86,7 +86,6 @@ struct TeArgs {
     uint64_t mat_off;
     int32_t units_per_part, k_parts, part_base;
     int32_t jobs;                        // row blocks * k_parts
-    float pa, pb;                        // weights of the sums (group_sums)
     float lift, lower;                   // two-level 2-bit codes: what their scales are multiplied with, and its reciprocal
     uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
 };
@@ -108,7 +107,19 @@ __device__ __forceinline__ uint4 bl128(__amdgpu_buffer_rsrc_t r, uint32_t v, int
 }
 constexpr uint32_t TE_NONE = 0x80000000u;    // an offset past every buffer's end: zeros, no request
 
-// k-slots of two groups of the contraction over groups: X as (h l h l), D as (h h l l)
+// Contraction over groups, 3- and 4-bit codes: the eight k-slots of one group, from split3 of X and D (first, second, third
+// part): X as (0 1 0 1 0 1 2 2), D as (0 0 1 1 2 2 0 1): all products but that of the third parts.
+__device__ __forceinline__ bf8_t slots3_x(uint2 v)
+{
+    const u32x4_t r = {v.x, v.x, v.x, v.y};
+    return __builtin_bit_cast(bf8_t, r);
+}
+__device__ __forceinline__ bf8_t slots3_d(uint2 v)
+{
+    const u32x4_t r = {__builtin_amdgcn_perm(v.x, v.x, 0x01000100u), __builtin_amdgcn_perm(v.x, v.x, 0x03020302u), v.y, v.x};
+    return __builtin_bit_cast(bf8_t, r);
+}
+// 2-bit codes: the k-slots of two groups, X as (h l h l), D as (h h l l)
 __device__ __forceinline__ bf8_t slots_x(uint2 v)
 {
     const u32x4_t r = {v.x, v.x, v.y, v.y};
@@ -121,17 +132,7 @@ __device__ __forceinline__ bf8_t slots_d(uint2 v)
     return __builtin_bit_cast(bf8_t, r);
 }
 
-// eight centred codes of a word in the 4-bit layout
-__device__ __forceinline__ h8_t centred4(uint32_t w, const BiasPatterns &p, uint32_t k1024, uint32_t k64)
-{
-    const u32x4_t b = __builtin_bit_cast(u32x4_t, codes_biased(w, p));
-    const h2_t r0 = as_h2(b[0]) + as_h2(k1024), r1 = as_h2(b[1]) + as_h2(k64), r2 = as_h2(b[2]) + as_h2(k1024), r3 = as_h2(b[3]) + as_h2(k64);
-    h8_t r;
-    r[0] = r0.x; r[1] = r0.y; r[2] = r1.x; r[3] = r1.y; r[4] = r2.x; r[5] = r2.y; r[6] = r3.x; r[7] = r3.y;
-    return r;
-}
-
-// eight codes as the fp16 numbers 64 + q, in codes_biased's slots
+// eight codes of a word in the 4-bit layout as the fp16 numbers 64 + q
 __device__ __forceinline__ h8_t codes_biased64(uint32_t w, const BiasPatterns &p)
 {
     const u32x4_t r = {((w << 4) & p.m_hi) | p.k64, (w & p.m_hi) | p.k64, ((w >> 4) & p.m_hi) | p.k64, ((w >> 8) & p.m_hi) | p.k64};
@@ -173,7 +174,7 @@ template <int FMT, int ROWS, int THREADS> struct Te;
 template <bool META8, int ROWS, int THREADS>
 struct TeScaled {                        // the part that 4-bit and 3-bit formats share
     static constexpr bool GS = true;
-    static constexpr int GPU = 1, PLANES = 1, DB = 16;                   // groups per unit; bytes of D per row and set
+    static constexpr int GPU = 1, PLANES = 1, DB = 32;                   // groups per unit; bytes of D per row and set
     static constexpr bool LIFTED = false;
     static constexpr int NM = ROWS * 4 / THREADS;
     TeMeta<META8, NM> meta;
@@ -186,25 +187,20 @@ struct TeScaled {                        // the part that 4-bit and 3-bit format
         }
     }
     template <int REC, int SOFF>
-    __device__ __forceinline__ void commit_meta(uint8_t *rec, uint8_t *d, float zc, int tid) const
+    __device__ __forceinline__ void commit_meta(uint8_t *rec, uint8_t *d, int tid) const
     {
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             float s, z;
             meta.get(i, s, z);
             *reinterpret_cast<float *>(rec + (tid / 4) * REC + (tid % 4) * 4 + SOFF + i * (THREADS / 4) * REC) = s;
-            *reinterpret_cast<uint32_t *>(d + tid * 4 + i * THREADS * 4) = split2(s * (zc - z));
+            *reinterpret_cast<uint2 *>(d + tid * 8 + i * THREADS * 8) = split3(s * (-64.f - z));
         }
     }
 };
 
 template <bool META8, int ROWS, int THREADS>
 struct Te4 : TeScaled<META8, ROWS, THREADS> {
-    static constexpr float ZC = 8.f;
-    // Bias 64 for every code.  With 1024 for half of them (two shifts per word less) the products' sums are so much larger than what
-    // is left of them that their rounding was this format's largest error: y, apart from the rounding of a, 9.5 to 10.4e-5 off, the
-    // GEMV kernels 9.1 to 9.8e-5; now 3.1 to 3.4e-5.  24 tokens, Mixtral-shaped, group 128: w1/w3 + w2 108.7 + 60.7 -> 109.7 + 60.9 us.
-    static __device__ __forceinline__ h8_t biased(uint32_t w, const BiasPatterns &p) { return codes_biased64(w, p); }
     static constexpr int SOFF = 128, REC = 144, NC = ROWS * 8 / THREADS;
     uint4 c[NC];
     struct Raw { uint4 q; };
@@ -221,7 +217,7 @@ struct Te4 : TeScaled<META8, ROWS, THREADS> {
         uint8_t *const to = rec + (tid / 8) * REC + (tid % 8) * 16;
 #pragma unroll
         for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) *reinterpret_cast<uint4 *>(to + i * (THREADS / 8) * REC) = c[i];
-        if (h == 1) this->template commit_meta<REC, SOFF>(rec, d, ZC, tid);
+        if (h == 1) this->template commit_meta<REC, SOFF>(rec, d, tid);
     }
     static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u) { r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16); }
     // words of 8 codes in the 4-bit layout: the lane half's four, or those of quarter kb of the unit
@@ -231,27 +227,17 @@ struct Te4 : TeScaled<META8, ROWS, THREADS> {
         const uint2 q = *reinterpret_cast<const uint2 *>(row + u * 32 + kb * 8);
         t[0] = q.x; t[1] = q.y;
     }
-    static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[1][4])
-    {
-        constexpr uint32_t K1024 = 0xE408E408u, K64 = 0xD480D480u;       // -1032, -72
-        const BiasPatterns p = bias_patterns();
-        b[0][0] = centred4(r.q.x, p, K1024, K64);
-        b[0][1] = centred4(r.q.y, p, K1024, K64);
-        b[0][2] = centred4(r.q.z, p, K1024, K64);
-        b[0][3] = centred4(r.q.w, p, K1024, K64);
-    }
 };
 template <int R, int T> struct Te<4, R, T> : Te4<false, R, T> {};
 template <int R, int T> struct Te<48, R, T> : Te4<true, R, T> {};
 
 template <bool META8, int ROWS, int THREADS>
 struct Te3 : TeScaled<META8, ROWS, THREADS> {
-    static constexpr float ZC = 4.f;
-    // biases 1024 and 64: more exact than the GEMV kernels all the same (14.0e-5 against 17.7e-5), and 64 alone costs 2 %
-    static __device__ __forceinline__ h8_t biased(uint32_t w, const BiasPatterns &p) { return codes_biased(w, p); }
     static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS;
-    static_assert(NA >= 1 && ROWS * 2 <= THREADS, "region B is one piece per thread, repeated by threads too many");
-    uint4 a[NA], b;
+    static constexpr bool HALF = ROWS * 4 == THREADS;                    // region B: 8 or 16 bytes per thread
+    static_assert(NA >= 1 && (HALF || ROWS * 2 == THREADS), "region B is one piece per thread");
+    uint4 a[NA];
+    std::conditional_t<HALF, uint2, uint4> b;
     struct Raw { uint2 a; uint32_t b; };
     __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
     {
@@ -261,8 +247,11 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
 #pragma unroll
             for (int i = 0; i < NA; ++i) a[i] = bl128(rs, v, min(row0 + (i * THREADS / 4) + uniform(tid / 256) * 64, n_rows - 64) * (int)g.stride + u * 16);
         } else {
-            const uint32_t v = live ? (uint32_t)(tid / 2 % 64) * g.stride + (uint32_t)(tid % 2) * 16u : TE_NONE;
-            b = bl128(rs, v, min(row0 + uniform(tid % (ROWS * 2) / 128) * 64, n_rows - 64) * (int)g.stride + (int)g.b_off + u * 8);
+            constexpr int PR = HALF ? 4 : 2;                             // pieces per row
+            const uint32_t v = live ? (uint32_t)(tid / PR % 64) * g.stride + (uint32_t)(tid % PR) * (32u / PR) : TE_NONE;
+            const int at = min(row0 + uniform(tid / (PR * 64)) * 64, n_rows - 64) * (int)g.stride + (int)g.b_off + u * 8;
+            if constexpr (HALF) b = bl64(rs, v, at);
+            else b = bl128(rs, v, at);
             this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
         }
     }
@@ -272,9 +261,9 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
 #pragma unroll
             for (int i = 0; i < NA; ++i) *reinterpret_cast<uint4 *>(rec + (tid / 4) * REC + (tid % 4) * 16 + i * (THREADS / 4) * REC) = a[i];
         } else {
-            const int tb = tid % (ROWS * 2);
-            *reinterpret_cast<uint4 *>(rec + (tb / 2) * REC + (tb % 2) * 16 + 64) = b;
-            this->template commit_meta<REC, SOFF>(rec, d, ZC, tid);
+            constexpr int PR = HALF ? 4 : 2;
+            *reinterpret_cast<decltype(b) *>(rec + (tid / PR) * REC + (tid % PR) * (32 / PR) + 64) = b;
+            this->template commit_meta<REC, SOFF>(rec, d, tid);
         }
     }
     static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u)
@@ -295,17 +284,6 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
         const uint32_t b = *reinterpret_cast<const uint32_t *>(row + 64 + u * 8 + (kb >> 1) * 4) >> (2 * (kb & 1));
         t[0] = (a & 0x33333333u) | ((b << 2) & 0x44444444u);
         t[1] = ((a >> 2) & 0x33333333u) | ((b << 1) & 0x44444444u);
-    }
-    static __device__ __forceinline__ void decode(const Raw &r, h8_t (&b)[1][4])
-    {
-        constexpr uint32_t K1024 = 0xE404E404u, K64 = 0xD440D440u;       // -1028, -68
-        const BiasPatterns p = bias_patterns();
-        uint32_t t[4];
-        words(r, t);
-        b[0][0] = centred4(t[0], p, K1024, K64);
-        b[0][1] = centred4(t[1], p, K1024, K64);
-        b[0][2] = centred4(t[2], p, K1024, K64);
-        b[0][3] = centred4(t[3], p, K1024, K64);
     }
 };
 template <int R, int T> struct Te<3, R, T> : Te3<false, R, T> {};
@@ -342,7 +320,7 @@ struct Te2 {
     {
         if constexpr (!META8) {
             constexpr int SLAB = THREADS / 8;
-            const uint32_t v = live ? (uint32_t)(tid / 8) * g.stride + (uint32_t)(tid % 8) * 16u : TE_NONE;
+            const uint32_t v = live && u + (tid % 8) / 2 < g.units ? (uint32_t)(tid / 8) * g.stride + (uint32_t)(tid % 8) * 16u : TE_NONE;
 #pragma unroll
             for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) c[i] = bl128(rs, v, min(row0 + i * SLAB, n_rows - SLAB) * (int)g.stride + u * 32);
         } else {
@@ -356,14 +334,14 @@ struct Te2 {
             }
         }
     }
-    // valid: units of the set that exist; what lies behind a row's end is no scale, so those units' records are zeros
+    // What lies behind a row's end is no scale, so the records of units there are zeros: not requested (one-level), or set here;
+    // valid: units of the set that exist.
     __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int valid, float lift, int tid) const
     {
         if constexpr (!META8) {
-            const bool in = (tid % 8) / 2 < valid;
             uint8_t *const to = rec + (tid / 8) * REC + (tid % 8) * 16;
 #pragma unroll
-            for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) *reinterpret_cast<uint4 *>(to + i * (THREADS / 8) * REC) = in ? c[i] : make_uint4(0, 0, 0, 0);
+            for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) *reinterpret_cast<uint4 *>(to + i * (THREADS / 8) * REC) = c[i];
         } else {
             const bool in = tid % 4 < valid;
             uint8_t *const to = rec + (tid / 4) * REC + (tid % 4) * 32, *const dd = d + (tid / 4) * DB + (tid % 4) * 16;
@@ -449,11 +427,12 @@ constexpr int TE_BIG = 0;
 
 template <int FMT, int MODE> struct TeCfg {
     static constexpr bool BIG = MODE == TE_BIG;
-    // MODE 16: 8 waves or 4, measured (w1/w3 + w2 us, Mixtral-shaped, 16 tokens): 4-bit 106 + 55 / 112 + 57, two-level
-    // 2-bit 171 + 85 / 182 + 93; 3-bit 134 + 69 / 116 + 62, 2-bit 123 + 61 / 119 + 62.  MODE 32: 8 waves would not fit 128 registers.
-    static constexpr int THREADS = MODE == 32 || (MODE == 16 && (FMT == 3 || FMT == 38 || FMT == 2)) ? 256 : 512, RG = BIG ? 4 : 2, ROWS = RG * 64;
+    static constexpr bool SMALL2 = !BIG && (FMT == 2 || FMT == 28);      // 2-bit codes, one tile
+    static constexpr int THREADS = SMALL2 && !(MODE == 16 && FMT == 28) ? 256 : 512;
+    static constexpr int RG = BIG || (MODE == 32 && !SMALL2) ? 4 : 2, ROWS = BIG ? 256 : 128;     // row groups: RG of RGR rows
+    static constexpr int RGR = ROWS / RG;
     static constexpr int KW = THREADS / 64 / RG;                         // waves of a row group (MODE 16, 32: each a share of a set's units)
-    static constexpr int WAVES_EU = MODE == 16 && THREADS == 512 ? 4 : 2; // waves per SIMD
+    static constexpr int WAVES_EU = !BIG && THREADS == 512 ? 4 : 2;      // waves per SIMD
     using F = Te<FMT, ROWS, THREADS>;
     static constexpr int MT = BIG ? (F::PLANES == 1 ? 3 : 2) : 1;                // token tiles of 32 per wave
     static constexpr int TOK = BIG ? 2 * MT * 32 : MODE;
@@ -463,12 +442,10 @@ template <int FMT, int MODE> struct TeCfg {
     static constexpr int REC = F::REC;
     static constexpr int ABUF = TOK * PITCH, BBUF = ROWS * REC, DBUF = ROWS * F::DB;
     // sums: 16 bytes are four groups, of a set (GS) or of one unit: XQ pieces per token and staging step
-    // (8 bytes each: the split sum, and minus the sum weighted with the codes' biases, which only GS at MODE 16 and 32 takes)
-    static constexpr int XQ = F::GS ? 2 : SU * 2, XPITCH = XQ == 2 ? 16 : XQ * 8 + 16, XBUF = TOK * XPITCH;
-    static constexpr bool BIASED = F::GS && !BIG;
-    static constexpr int PBUF = BIASED ? 4 * TOK * 4 : 0;
-    static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_P = OFF_X + 2 * XBUF, OFF_END = OFF_P + 2 * PBUF;
-    static constexpr int OFF_RED = THREADS / 64 * (MODE == 16 ? 4096 : 8192);    // MODE 16, 32: behind the waves' partial sums
+    // (8 bytes each; 2-bit codes take only the first four)
+    static constexpr int XQ = F::GS ? 2 : SU * 2, XPITCH = F::GS ? 32 : (XQ == 2 ? 16 : XQ * 8 + 16), XBUF = TOK * XPITCH;
+    static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_END = OFF_X + 2 * XBUF;
+    static constexpr int OFF_RED = THREADS / 64 * (RGR * MODE * 4);    // MODE 16, 32: behind the waves' partial sums
     static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
     static constexpr int OFF_A = BIG ? 0 : OFF_RED, OFF_T = BIG || OFF_END > OFF_RED + TOK * APITCH ? OFF_END : OFF_RED + TOK * APITCH;
     static constexpr int LDS = OFF_T + TOK * 8;
@@ -522,11 +499,14 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         const int tk = tid / PPT + i * (THREADS / PPT);
         a_off[i] = tk < n_tok ? (uint32_t)act_row(tk) * (uint32_t)A.K * 2u + (uint32_t)(tid % PPT) * 16u : TE_NONE;
     }
-    // sums: piece p of a step is token p / XQ; threads too many repeat a piece (a branch less)
+    // sums: piece p of a step is token p / XQ; threads too many request nothing (a repeated piece is a visit of its line as any
+    // other), in the large kernel and with 2-bit codes they repeat one (no branch, see below)
     constexpr int XQ = C::XQ, XU = F::GS ? 1 : 4;                        // XU: groups per unit
-    static_assert(C::TOK * XQ <= THREADS && THREADS % XQ == 0, "one piece per thread");
-    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * 8;
-    const uint32_t x_off = xp / XQ < n_tok ? (uint32_t)act_row(xp / XQ) * (uint32_t)A.xs_stride * 8u + (uint32_t)(xp % XQ) * 16u : TE_NONE;
+    constexpr bool X_REPEAT = BIG || !F::GS;
+    static_assert(C::TOK * XQ <= THREADS && (!X_REPEAT || THREADS % XQ == 0), "one piece per thread");
+    const bool x_mine = X_REPEAT || tid < C::TOK * XQ;
+    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * (F::GS ? 16 : 8);
+    const uint32_t x_off = x_mine && xp / XQ < n_tok ? (uint32_t)act_row(xp / XQ) * (uint32_t)A.xs_stride * 8u + (uint32_t)(xp % XQ) * 16u : TE_NONE;
     struct Acts { uint4 a[NP], x; };                                     // activations and sums of one step on their way to LDS
     auto fetch_a = [&](Acts &t, int u) __attribute__((always_inline)) {                                          // units u .. u + SU - 1; zeros from u1 on
 #pragma unroll
@@ -543,12 +523,9 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     };
     auto fetch_x = [&](Acts &t, int u) __attribute__((always_inline)) { t.x = bl128(x_rs, (F::GS ? u : u + xp % XQ / 2) < u1 ? x_off : TE_NONE, u * (XU * 8)); };
     auto commit_x = [&](const Acts &t, int b) __attribute__((always_inline)) {
-        *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
-        if constexpr (C::BIASED) {                                       // [unit of the set][token]
-            uint32_t *const to = reinterpret_cast<uint32_t *>(lds + C::OFF_P + b * C::PBUF) + (xp % XQ) * 2 * C::TOK + xp / XQ;
-            to[0] = t.x.y;
-            to[C::TOK] = t.x.w;
-        }
+        if (!X_REPEAT && C::TOK * XQ < THREADS && !x_mine) return;
+        if constexpr (F::GS) *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = t.x;
+        else *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
     };
     // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
     auto fetch_b = [&](F &f, int h, int u) __attribute__((always_inline)) { f.fetch(h, w_rs, geo, row0, n_rows, u < u1 ? u : u0, u < u1, tid); };
@@ -560,13 +537,21 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     auto stores_below = [&]() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0x1 | 0x2 | 0x4 | 0x8 | 0x10 | 0x20 | 0x40 | 0x100); };
 
     // ---------------- multiply ----------------
-    const uint8_t *const my_rec = lds + C::OFF_B + (rg * 64 + col) * C::REC;      // + 32 rows: the wave's second tile
+    const uint8_t *const my_rec = lds + C::OFF_B + (rg * C::RGR + col) * C::REC;      // + 32 rows: the wave's second tile
+    const BiasPatterns bp = bias_patterns();
     auto unpack = [&](h8_t (&b)[2][F::PLANES][4], int bb, int u) __attribute__((always_inline)) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
             typename F::Raw raw;
             F::read(raw, my_rec + bb * C::BBUF + rt * 32 * C::REC, hh, u);
-            F::decode(raw, b[rt]);
+            if constexpr (F::GS) {
+                uint32_t t[4];
+                F::words(raw, t);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) b[rt][0][k] = codes_biased64(t[k], bp);
+            } else {
+                F::decode(raw, b[rt]);
+            }
         }
     };
     // totals of NT token tiles: plain registers where the vector unit adds to them, whole tuples where only the matrix cores do
@@ -578,7 +563,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
             if constexpr (F::GS) sc[rt] = *reinterpret_cast<const float *>(my_rec + bb * C::BBUF + rt * 32 * C::REC + F::SOFF + u * 4);
-            else d[rt] = slots_d(F::factors(my_rec + bb * C::BBUF + rt * 32 * C::REC, lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * 32 + col) * F::DB, hh, u));
+            else d[rt] = slots_d(F::factors(my_rec + bb * C::BBUF + rt * 32 * C::REC, lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * 32 + col) * F::DB, hh, u));
         }
 #pragma unroll
         for (int mt = 0; mt < NT; ++mt) {
@@ -614,20 +599,24 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     auto zero_term = [&](auto nt_tag, auto &tot, int tile, int bb) __attribute__((always_inline)) {
         if constexpr (F::GS) {
             constexpr int NT = decltype(nt_tag)::value;
-            bf8_t d[2];
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt) d[rt] = slots_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * 32 + col) * F::DB + hh * 8));
+            for (int p = 0; p < 2; ++p) {                                // two groups each
+                bf8_t d[2];
 #pragma unroll
-            for (int mt = 0; mt < NT; ++mt) {
-                const bf8_t xv = slots_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + ((tile + mt) * 32 + col) * C::XPITCH + hh * 8));
+                for (int rt = 0; rt < 2; ++rt)
+                    d[rt] = slots3_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * 32 + col) * F::DB + (p * 2 + hh) * 8));
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt) {
-                    f32x16_t z;
+                for (int mt = 0; mt < NT; ++mt) {
+                    const bf8_t xv = slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + ((tile + mt) * 32 + col) * C::XPITCH + (p * 2 + hh) * 8));
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) z[i] = 0.f;
-                    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, d[rt], z, 0, 0, 0);
+                    for (int rt = 0; rt < 2; ++rt) {
+                        f32x16_t z;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) tot[rt][mt][i] += z[i];
+                        for (int i = 0; i < 16; ++i) z[i] = tot[rt][mt][i];
+                        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, d[rt], z, 0, 0, 0);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) tot[rt][mt][i] = z[i];
+                    }
                 }
             }
         }
@@ -649,9 +638,9 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         if constexpr (W13) {
             const float other = dpp_f<0xB1>(v);
             if ((lane & 1) == 0)
-                *reinterpret_cast<uint16_t *>(lds + C::OFF_A + tk * C::APITCH + rg * 64 + wrow) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
+                *reinterpret_cast<uint16_t *>(lds + C::OFF_A + tk * C::APITCH + rg * C::RGR + wrow) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
         } else {
-            const int mrow = row0 + rg * 64 + wrow;
+            const int mrow = row0 + rg * C::RGR + wrow;
             const int row = A.k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * A.k_parts + part;
             if (tk < n_tok && mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = l_w[tk] * v;
         }
@@ -666,22 +655,20 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 const u32x4_t q = *reinterpret_cast<const u32x4_t *>(lds + C::OFF_A + tk * C::APITCH + c * 16);
                 const h2_t ones = {(_Float16)1.f, (_Float16)1.f};
                 float xa = __builtin_amdgcn_fdot2(as_h2(q[0]), ones, 0.f, false), xb = __builtin_amdgcn_fdot2(as_h2(q[1]), ones, 0.f, false);
-                xa = in ? __builtin_amdgcn_fdot2(as_h2(q[2]), ones, xa, false) : 0.f;
-                xb = in ? __builtin_amdgcn_fdot2(as_h2(q[3]), ones, xb, false) : 0.f;
-                xa += dpp_f<0xB1>(xa);                                   // two lanes: 16 columns
-                xb += dpp_f<0xB1>(xb);
+                xa = __builtin_amdgcn_fdot2(as_h2(q[2]), ones, xa, false);
+                xb = __builtin_amdgcn_fdot2(as_h2(q[3]), ones, xb, false);
+                float xs = in ? xa + xb : 0.f;
+                xs += dpp_f<0xB1>(xs);                                   // two lanes: 16 columns
                 if constexpr (XG == 64) {
-                    xa += dpp_f<0x4E>(xa);
-                    xb += dpp_f<0x4E>(xb);
-                    xa += dpp_f<0x141>(xa);
-                    xb += dpp_f<0x141>(xb);
+                    xs += dpp_f<0x4E>(xs);
+                    xs += dpp_f<0x141>(xs);
                 }
                 if (tk < n_tok) {
                     const int pr = l_pair[tk];
                     if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
                     uint2 *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
                     const int g = colg / XG;
-                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = group_sums(xa, xb, A.pa, A.pb);
+                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = XG == 64 ? split3(xs) : make_uint2(split2(xs), 0u);
                     if (c == 0 && (rb + 1) * C::ACOLS >= A.N)            // the padding behind the last group that no row block covers
                         for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
                 }
@@ -770,8 +757,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         }
     } else {
         // set by set, the units of a set shared by the waves of a row group; two sets of weights on their way
-        constexpr int RT = MODE == 32 ? 2 : 4, NR = MODE == 32 ? 16 : 4;         // row tiles of a wave, registers of a tile
-        constexpr int RROWS = 64 / RT;                                   // rows per tile: 32 or 16
+        constexpr int RROWS = MODE, RT = C::RGR / RROWS, NR = MODE == 32 ? 16 : 4;     // rows of a tile, row tiles of a wave, registers of a tile
         const int rcol = lane % RROWS, kb = lane / RROWS;                // the lane's row of a tile, its half or quarter of a unit
         using Acc = std::conditional_t<MODE == 32, f32x16_t, f32x4_t>;
         auto mm = [&](h8_t a, h8_t b, Acc c) __attribute__((always_inline)) {
@@ -787,8 +773,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int i = 0; i < NR; ++i) tot[rt][i] = 0.f;
-        const BiasPatterns bp = bias_patterns();
-        const uint8_t *const rec0 = lds + C::OFF_B + (rg * 64 + rcol) * C::REC;
+        const uint8_t *const rec0 = lds + C::OFF_B + (rg * C::RGR + rcol) * C::REC;
         // one unit of the wave's rows
         auto unit = [&](int bb, int un) __attribute__((always_inline)) {
             constexpr int KS = MODE == 32 ? 4 : 2;                       // k-steps of a unit
@@ -797,14 +782,6 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
 #pragma unroll
             for (int k = 0; k < KS; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + k * 16);
             if constexpr (F::GS) {
-                // the codes with their biases; the products start from minus what biases and centre add up to
-                Acc p0;
-                const float *const pp = reinterpret_cast<const float *>(lds + C::OFF_P + bb * C::PBUF) + un * C::TOK + 4 * kb;
-#pragma unroll
-                for (int i = 0; i < NR; i += 4) {
-                    const float4 v = *reinterpret_cast<const float4 *>(pp + 2 * i);
-                    p0[i] = v.x; p0[i + 1] = v.y; p0[i + 2] = v.z; p0[i + 3] = v.w;
-                }
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     const uint8_t *rec = rec0 + bb * C::BBUF + rt * RROWS * C::REC;
@@ -817,9 +794,11 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                     } else {
                         F::quarter(rec, kb, un, t);
                     }
-                    Acc g = p0;
+                    Acc g;
 #pragma unroll
-                    for (int k = 0; k < KS; ++k) g = mm(a[k], F::biased(t[k], bp), g);
+                    for (int i = 0; i < NR; ++i) g[i] = 0.f;
+#pragma unroll
+                    for (int k = 0; k < KS; ++k) g = mm(a[k], codes_biased64(t[k], bp), g);
 #pragma unroll
                     for (int i = 0; i < NR; ++i) tot[rt][i] = __builtin_fmaf(sc, g[i], tot[rt][i]);
                 }
@@ -835,7 +814,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     const uint8_t *rec = rec0 + bb * C::BBUF + rt * RROWS * C::REC;
-                    const uint8_t *drow = lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * RROWS + rcol) * F::DB;
+                    const uint8_t *drow = lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * RROWS + rcol) * F::DB;
                     h8_t b[F::PLANES][KS];
                     bf8_t d;
                     if constexpr (MODE == 32) {
@@ -858,14 +837,16 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 }
             }
         };
-        // GS: the zero-point term of a set (its four groups: with 16-token tiles half of the k-slots)
+        // GS: the zero-point term of a set: its four groups in one matrix instruction per row tile, or two in each of two
         auto set_term = [&](int bb) __attribute__((always_inline)) {
-            uint2 xw = *reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + (kb & 1) * 8);
-            if (MODE == 16 && kb > 1) xw = make_uint2(0u, 0u);
-            const bf8_t xv = slots_x(xw);
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                tot[rt] = mmb(xv, slots_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * 64 + rt * RROWS + rcol) * F::DB + (kb & 1) * 8)), tot[rt]);
+            for (int p = 0; p < MODE / 16; ++p) {
+                const int g = p * (64 / MODE) + kb;
+                const bf8_t xv = slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + g * 8));
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    tot[rt] = mmb(xv, slots3_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * RROWS + rcol) * F::DB + g * 8)), tot[rt]);
+            }
         };
         // Two sets are on their way, activations as well as weights (one alone takes longer to arrive than a set to multiply)
         F f0, f1;
@@ -877,8 +858,9 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         };
         auto commit = [&](const F &f, const Acts &t, int b, int u) __attribute__((always_inline)) {
             commit_a(t, b);
-            commit_x(t, b);
+            if constexpr (X_REPEAT) commit_x(t, b);
             for (int h = 0; h < 2; ++h) commit_b(f, h, b, u);
+            if constexpr (!X_REPEAT) commit_x(t, b);
         };
         fetch(f0, t0, u0);
         fetch(f1, t1, u0 + 4);
@@ -893,6 +875,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             stores_below();
             commit(fout, tout, bb ^ 1, u + 4);
             __syncthreads();
+            if constexpr (!F::GS && F::PLANES == 1) __builtin_amdgcn_sched_barrier(0);   // the next set's work stays behind its own loads: 2-bit, 16 tokens, 173 -> 160 us a step
         };
         for (int u = u0; u < u1; u += 8) {
             set(f0, t0, f1, t1, u, 0);
@@ -907,15 +890,13 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             for (int i = 0; i < NR; ++i) red[((wv * RT + rt) * NR + i) * 64 + lane] = tot[rt][i];
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < RT / C::KW; ++r)
+        for (int r = 0; r < RT * NR / C::KW; ++r) {
+            const int at = half * (RT * NR / C::KW) + r, rt = at / NR, i = at % NR;
+            float v = 0.f;
 #pragma unroll
-            for (int i = 0; i < NR; ++i) {
-                const int rt = half * (RT / C::KW) + r;
-                float v = 0.f;
-#pragma unroll
-                for (int w = 0; w < C::KW; ++w) v += red[(((w * C::RG + rg) * RT + rt) * NR + i) * 64 + lane];
-                put(v, MODE == 32 ? 8 * (i / 4) + 4 * kb + i % 4 : 4 * kb + i, rt * RROWS + rcol);
-            }
+            for (int w = 0; w < C::KW; ++w) v += red[((w * C::RG + rg) * RT * NR + at) * 64 + lane];
+            put(v, MODE == 32 ? 8 * (i / 4) + 4 * kb + i % 4 : 4 * kb + i, rt * RROWS + rcol);
+        }
         copy_out();
     }
 }

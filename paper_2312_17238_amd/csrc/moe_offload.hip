@@ -1514,12 +1514,6 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
 
 // Codes per sum of activations: the groups of the zero-point term.
 static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
-// What the codes' patterns (biased() of the format policies; 2-bit codes have none) and the constant they are centred on (ZC) add.
-static void tile_sum_weights(const BlobLayout &b, float &pa, float &pb)
-{
-    pa = b.bits == 4 ? 64.f + 8.f : (b.bits == 3 ? 1024.f + 4.f : 0.f);
-    pb = b.bits == 4 ? 64.f + 8.f : (b.bits == 3 ? 64.f + 4.f : 0.f);
-}
 static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
 
 // The power of two that two-level 2-bit scales are multiplied with: the layer's largest just below 32000, so that its product
@@ -1723,7 +1717,6 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     }
     const int mode = c->tile_mode, rows = mode == TE_BIG ? 256 : 128;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
-    tile_sum_weights(b, A.pa, A.pb);
     A.lift = tile_lift(l); A.lower = 1.f / A.lift;
     A.top_k = K; A.part_base = batch * K;
     A.unit_shift = b.group == 128 ? 1 : 0;
@@ -1973,7 +1966,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
     if (tile_ready) {
         ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
-        ga.xs = c->xs_h; tile_sum_weights(l->lay, ga.xs_pa, ga.xs_pb); ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
+        ga.xs = c->xs_h; ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
     }
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;
