@@ -142,7 +142,7 @@ typedef struct {
     uint64_t bytes_h2d_spec;
     uint64_t bytes_d2h_writeback; /* MOE_LAYER_SWAP: evicted experts written back to host buffers    */
     uint64_t steps_device_routed; /* ... of `steps`, those enqueued without waiting for the gate (every
-                                     expert resident, one token; option "device_routing")            */
+                                     expert resident; option "device_routing")                       */
 } moe_stats_t;                /* "expert recall" (Sec. 4.1) = (hits + prefetch_hits) / needed    */
 
 /* ---- sizes ---------------------------------------------------------------------------------- */
@@ -298,7 +298,7 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
 
 /* Launch-shape tuning knobs (defaults are the measured best for Mixtral shapes on MI355X):
  *   "w13_blocks" total thread blocks of the w1/w3 kernel (default 256: one per compute unit);
- *   "w2_rows"    output rows per block of the w2 kernel (default 32);
+ *   "w2_rows"    output rows per block of the w2 kernel at most (default 32; fewer where the blocks would not fill the chip);
  *   "w2_token_rows" output rows per block of the single-token w2 kernel, at most 64 (default 0: hidden size /
  *                compute units, 16 for Mixtral's width);
  *   "sync_wait"  1: wait for the gate result with hipStreamSynchronize instead of polling host-mapped memory;
@@ -311,15 +311,15 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                layers excepted with a scale above 32000 or a row of scales below 2^-14, or two-level ones with a scale
  *                above 500 or a row 2^16 times below the largest); smaller batches, 4-bit group-32 experts and
  *                other formats in forms 1 to 5 use the GEMV kernels;
- *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 where an expert has enough tokens of the step (4-bit group-64
- *                experts: more than 32 and 16 on average, with two-level metadata 16 and 8, and estimated from the
- *                routing to be faster than form 5; other formats: more than three on average), else form 5 (4-bit
- *                group-64) or the GEMV kernels.  6: tile kernels,
+ *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 where it is the faster one for the layer's size and the tokens an
+ *                expert has on average (4-bit group-64 layers of middle size, and larger ones with more than 32, two-level 16;
+ *                other formats: more than three, or more than one in all but the smallest layers), else form 5 (4-bit
+ *                group-64) or the GEMV kernels.  The choice, like all that decides the order of a result's sums, follows
+ *                from the layer, the batch and the options, never from the routing or the cache.  6: tile kernels,
  *                every format, up to 192 tokens of one expert multiplied per pass over its weights, codes
  *                exact and groups scaled in fp32 (2-bit: exact fp16 products of code and scale).  4: persistent streaming kernels with
- *                tiles of 16 tokens -- one tile per expert while no expert has more than 16 tokens of a window of up to
- *                256 / top_k tokens of the step, else two, decided per window from its routing alone, so that a token's
- *                result does not depend on which experts share a launch -- each dequantised weight rounded once to fp16
+ *                tiles of 16 tokens -- one, or two where an expert has more than 14 tokens of a window of up to 256 / top_k
+ *                tokens of the step on average, and as many entries of those as an expert needs -- each dequantised weight rounded once to fp16
  *                before the multiply, as Sec. 4.2's fp16 experts do; fp16 metadata only (form 2 runs otherwise).  5: the
  *                kernels of form 4 with the weights not dequantised at all: the codes enter the matrix cores as they are
  *                and a group's product is corrected for the zero-point and scaled in fp32 (no rounding of a weight; any
@@ -346,10 +346,12 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                into a buffer that launch reads waits for it alone), then the arriving experts are multiplied one by
  *                one as their copies land.  Otherwise, and below the threshold, a step whose buffers are used twice
  *                runs in passes, a pass's copies waiting for all kernels of the pass before;
- *   "device_routing" 1 (default): a single-token step of a layer whose experts are ALL on the device (cache_slots ==
- *                n_experts, every slot filled) and whose caller asks for no trace is enqueued without waiting for
- *                its gate kernel: no cache decision depends on the routing then, so the FFN kernels read the selection
- *                and the combine weights the gate kernel left in device memory, and moe_layer_step returns at once.
+ *   "device_routing" 1 (default): a step of a layer whose experts are ALL on the device (cache_slots == n_experts, every
+ *                slot filled) and whose caller asks for no trace is enqueued without waiting for its gate kernel: no
+ *                cache decision depends on the routing then, so the FFN kernels read the selection and the combine
+ *                weights the gate kernel left in device memory, and moe_layer_step returns at once.  That takes one token
+ *                with top_k <= 2, and batches in forms 0, 5 and 6: of any size on the tile kernels, up to 256 / top_k tokens on form
+ *                5's, up to 64 (token, expert) pairs on the GEMV kernels; other steps wait.
  *                Outputs are bit-identical to a waiting step's.  The recency stamps and counters such steps owe are
  *                caught up from a log of the selections in device memory (copied back after waiting for the compute
  *                stream) before any call reads or changes them: moe_layer_stats, moe_layer_cache_state, moe_layer_reset, a waiting step,

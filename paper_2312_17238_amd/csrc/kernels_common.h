@@ -223,6 +223,49 @@ __device__ __forceinline__ uint2 split3(float v)
     return make_uint2(__builtin_amdgcn_perm(b1, b0, 0x07060302u), __builtin_amdgcn_perm(b2, b2, 0x03020302u));
 }
 
+// A word that an earlier launch left in memory, at an address all lanes share, through the scalar cache (empty at a launch's start).
+__device__ __forceinline__ int scalar_word(const int32_t *p) { return *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)p; }
+
+// The routing of a step of at most 256 pairs as a wave holds it: the expert of pair 64 c + lane in e[c].  Its kernels find an
+// expert's pairs with ballots, so such a step needs no sorted list (a launch of 6 us, more than all this takes).
+constexpr int FEW_PAIRS = 256;
+struct FewPairs {
+    uint32_t e[FEW_PAIRS / 64];
+    int n;
+    __device__ __forceinline__ void load(const uint8_t *expert, int pairs)
+    {
+        n = pairs;
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int c = 0; c < FEW_PAIRS / 64; ++c) e[c] = c * 64 + lane < n ? (uint32_t)expert[c * 64 + lane] : 255u;
+    }
+    __device__ __forceinline__ uint64_t mask(int c, int expert) const { return __ballot(e[c] == (uint32_t)expert); }
+    // lane e: the pairs of expert e, for the first `experts` lanes (at most 16); 0 in the others
+    __device__ __forceinline__ int counts(int experts) const
+    {
+        const int lane = threadIdx.x & 63;
+        int own = 0;
+        for (int x = 0; x < experts; ++x) {
+            int k = __popcll(mask(0, x));
+            if (n > 64) {
+#pragma unroll
+                for (int c = 1; c < FEW_PAIRS / 64; ++c) k += __popcll(mask(c, x));
+            }
+            own = lane == x ? k : own;
+        }
+        return own;
+    }
+};
+// lanes 0 .. 15: sum of v over the lanes up to the own one
+__device__ __forceinline__ int prefix16(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    return v;
+}
+
 // wave-uniform value as a scalar, so that addresses derived from it are computed on the scalar unit
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 

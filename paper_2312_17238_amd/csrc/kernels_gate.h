@@ -39,12 +39,13 @@ struct GateArgs {
     int32_t *route_idx;             // [K] device, or null
     float *route_w;                 // [K] device
     int32_t *route_log;             // [K] device: this step's slot of the log ring
-    // For the tile kernels (TILE): every pair's expert and combine weight in device memory, and the sums of h over
-    // groups of xs_group elements, rows padded with zeros to xs_stride (16: split2, 64: split3).
+    // For kernels that find the routing in device memory (TILE): every pair's expert and combine weight; where xs is set the
+    // sums of h over groups of xs_group elements for the tile kernels, rows padded with zeros to xs_stride (16: split2, 64:
+    // split3).  quiet: nobody waits for this launch, nothing is published in `out`.
     uint8_t *pair_expert;           // [b*K + j]
     float *pair_w;                  // [b*K + j]
     uint2 *xs;                      // [b][xs_stride]
-    int32_t xs_stride, xs_group;
+    int32_t xs_stride, xs_group, quiet;
 };
 
 constexpr int GATE_THREADS = 1024;
@@ -58,7 +59,7 @@ constexpr int GATE_DENSE_EXPERTS = 8;
 // are not needed and the registers go to this thread's first slice of W_g instead, requested before the norm's
 // reduction so that its memory latency overlaps the norm rather than following it (after the thread's slice of x:
 // loads return in order, and the norm waits for x).
-// TILE: also leaves what the tile kernels need in device memory -- every pair's expert and weight, the sums of h.
+// TILE: also leaves the routing in device memory -- every pair's expert and weight, the tile kernels' sums of h.
 // DENSE: for more tokens than compute units and at most 8 experts.  A token's block waits most of its time (memory, then
 // the barriers' serial ends), so what counts is how many run at once: without slices requested up front and with 8
 // accumulators the kernel fits 64 registers, two blocks a compute unit.  The order of the sums is the same.
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
         if (a.yacc) *reinterpret_cast<float4 *>(a.yacc + (size_t)b * a.H + i) = make_float4(0.f, 0.f, 0.f, 0.f);
         const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
                      h3 = half_bits_to_f64(hv[3]);
-        if constexpr (TILE) {     // 4 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
+        if (TILE && a.xs) {       // 4 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
             float s = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
             s += dpp_f<0xB1>(s);
             s += dpp_f<0x4E>(s);
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
                 }
         }
     }
-    if (TILE && a.H / a.xs_group + tid < a.xs_stride) a.xs[(size_t)b * a.xs_stride + a.H / a.xs_group + tid] = make_uint2(0u, 0u);
+    if (TILE && a.xs && a.H / a.xs_group + tid < a.xs_stride) a.xs[(size_t)b * a.xs_stride + a.H / a.xs_group + tid] = make_uint2(0u, 0u);
     // all logits' wave sums at once; accumulators of experts that do not exist hold zeros
     if constexpr (SPEC) {
         wave_sum_many_f64<32>(acc, lane);
@@ -224,13 +225,16 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
             return;
         }
         if (lane < a.K) {
-            o->idx[b * a.K + lane] = mine;
-            o->w[b * a.K + lane] = wgt;
             if constexpr (TILE) {
                 a.pair_expert[b * a.K + lane] = (uint8_t)mine;
                 a.pair_w[b * a.K + lane] = wgt;
             }
+            if (!TILE || !a.quiet) {
+                o->idx[b * a.K + lane] = mine;
+                o->w[b * a.K + lane] = wgt;
+            }
         }
+        if (TILE && a.quiet) return;
         if (lane < n1) o->logits[b * n1 + lane] = t;
     }
     if constexpr (SPEC) {
@@ -251,6 +255,54 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
         }
     }
     if (lane == 0) __hip_atomic_store(&o->done[b], a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The pairs of a step of more than FEW_PAIRS sorted by expert, ascending within one expert: a counting sort in one block of 16 waves.  Expert e has
+// positions first[e] .. first[e + 1] - 1 of plist.
+constexpr int SORT_THREADS = 1024;
+__global__ __launch_bounds__(SORT_THREADS) void k_sort_pairs(const uint8_t *expert, int n, uint16_t *plist, int32_t *first)
+{
+    constexpr int CHUNKS = GATE_MAX_TOKENS * 4 / 64;                     // chunks of 64 pairs (64)
+    __shared__ int32_t cnt[16][CHUNKS];
+    __shared__ int32_t wave_tot[SORT_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint64_t below = (1ull << lane) - 1;
+    for (int c = wv; c < CHUNKS; c += SORT_THREADS / 64) {
+        const int q = c * 64 + lane, e = q < n ? (int)expert[q] : -1;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint64_t m = __ballot(e == k);
+            if (lane == 0) cnt[k][c] = __popcll(m);
+        }
+    }
+    __syncthreads();
+    // exclusive prefix sum over (expert, chunk): one entry per thread
+    static_assert(16 * CHUNKS == SORT_THREADS, "one entry per thread");
+    const int own = cnt[tid / CHUNKS][tid % CHUNKS];
+    int inc = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int v = __shfl_up(inc, d);
+        if (lane >= d) inc += v;
+    }
+    if (lane == 63) wave_tot[wv] = inc;
+    __syncthreads();
+    int base = inc - own;
+    for (int w = 0; w < wv; ++w) base += wave_tot[w];
+    cnt[tid / CHUNKS][tid % CHUNKS] = base;
+    if (tid % CHUNKS == 0) first[tid / CHUNKS] = base;
+    if (tid == 0) first[16] = n;
+    __syncthreads();
+    for (int c = wv; c < CHUNKS; c += SORT_THREADS / 64) {
+        const int q = c * 64 + lane, e = q < n ? (int)expert[q] : -1;
+        int pos = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint64_t m = __ballot(e == k);
+            if (e == k) pos = cnt[k][c] + __popcll(m & below);
+        }
+        if (e >= 0) plist[pos] = (uint16_t)q;
+    }
 }
 
 }  // namespace moe

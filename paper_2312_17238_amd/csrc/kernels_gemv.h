@@ -42,7 +42,47 @@ struct FfnArgs {
     // route_idx[j]; its weights are in table[id].  Null: the entries carry their blob pointers themselves.
     const int32_t *route_idx;
     const uint8_t *table[16];       // device buffer of every expert of the layer (all resident)
+    // ... for several tokens (kernels of more than one token per entry, at most 64 pairs): every pair's expert and weight, an
+    // entry is up to NT of an expert's pairs.  Null: the entries above.
+    const uint8_t *pair_expert;
+    const float *pair_w;
+    int32_t n_pairs, n_experts, top_k;
 };
+
+// Entries of such a step, and the j-th of them (there is one); e: the expert of pair `lane`, 255 past the last.
+template <int NT>
+__device__ __forceinline__ int route_entries(const FfnArgs &A, uint32_t e)
+{
+    int n = 0;
+    for (int k = 0; k < A.n_experts; ++k) n += (__popcll(__ballot(e == (uint32_t)k)) + NT - 1) / NT;
+    return n;
+}
+template <int NT>
+__device__ __forceinline__ FfnEntry route_entry(const FfnArgs &A, uint32_t e, int j)
+{
+    uint64_t mine = 0;
+    int expert = 0;
+    for (int k = 0; k < A.n_experts; ++k) {
+        const uint64_t m = __ballot(e == (uint32_t)k);
+        const int n = (__popcll(m) + NT - 1) / NT;
+        if (j >= 0 && j < n) { mine = m; expert = k; }
+        if (j >= 0) j = j < n ? -1 - j : j - n;          // found: minus one minus the entries of this expert before it
+    }
+    for (int s = (-1 - j) * NT; s > 0; --s) mine &= mine - 1;
+    FfnEntry en;
+    en.blob = A.table[expert];
+    en.n_tok = min(NT, (int)__popcll(mine));
+    int p = 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (mine) p = (int)__builtin_ctzll(mine);        // tokens that do not exist repeat the last
+        mine &= mine - 1;
+        en.pair[t] = p;
+        en.tok[t] = p / A.top_k;
+        en.w[t] = A.pair_w[p];
+    }
+    return en;
+}
 
 // Geometry of one matrix row as the format policies see it.
 struct RowGeom {
@@ -362,9 +402,23 @@ template <int BITS, int KCH, int NT, int G, int WAVES>
 __global__ __launch_bounds__(WAVES *WAVE) void k_w13(FfnArgs A)
 {
     using F = Fmt<BITS>;
-    const FfnEntry &en = A.e[blockIdx.y];
     const int lane = threadIdx.x & 63;
-    const int wave = uniform(blockIdx.x * WAVES + (threadIdx.x >> 6)), n_waves = gridDim.x * WAVES;
+    int entry = blockIdx.y, block = blockIdx.x, blocks = gridDim.x;
+    uint32_t pair_e = 255u;
+    if (NT > 1 && A.pair_expert) {         // one row of blocks, shared evenly by the entries there are
+        if (lane < A.n_pairs) pair_e = A.pair_expert[lane];
+        const int n = route_entries<NT>(A, pair_e);
+        blocks = max((int)gridDim.x / max(n, 1), 1);
+        entry = blockIdx.x / blocks;
+        block = blockIdx.x % blocks;
+        if (entry >= n) return;
+    }
+    auto pick = [&]() -> std::conditional_t<(NT > 1), FfnEntry, const FfnEntry &> {
+        if constexpr (NT > 1) { if (A.pair_expert) return route_entry<NT>(A, pair_e, entry); }
+        return A.e[entry];
+    };
+    const auto &en = pick();
+    const int wave = uniform(block * WAVES + (threadIdx.x >> 6)), n_waves = blocks * WAVES;
     const int n_chunks = A.H / F::CODES;
     const RowGeom geo = row_geom<BITS>(A.meta13, A.H, A.group, A.scale_group);
     const uint8_t *base = A.route_idx ? A.table[uniform(A.route_idx[blockIdx.y]) & 15] : en.blob;
@@ -470,7 +524,16 @@ __global__ __launch_bounds__(512) void k_w2(FfnArgs A)
 {
     using F = Fmt<BITS>;
     extern __shared__ float red[];                       // [rows_per_block][NT][CS]
-    const FfnEntry &en = A.e[blockIdx.y];
+    uint32_t pair_e = 255u;
+    if (NT > 1 && A.pair_expert) {
+        if ((int)(threadIdx.x & 63) < A.n_pairs) pair_e = A.pair_expert[threadIdx.x & 63];
+        if ((int)blockIdx.y >= route_entries<NT>(A, pair_e)) return;                   // the grid covers the most there can be
+    }
+    auto pick = [&]() -> std::conditional_t<(NT > 1), FfnEntry, const FfnEntry &> {
+        if constexpr (NT > 1) { if (A.pair_expert) return route_entry<NT>(A, pair_e, blockIdx.y); }
+        return A.e[blockIdx.y];
+    };
+    const auto &en = pick();
     const int lane = threadIdx.x & 63, cs = uniform(threadIdx.x >> 6), CS = blockDim.x >> 6;
     const int n_chunks = A.F / F::CODES;
     const int c = cs * 64 + lane;
@@ -522,9 +585,17 @@ __global__ __launch_bounds__(512) void k_w2(FfnArgs A)
 // pair's rows of ypart (parts of a split contraction in ascending order); x_out = fp16(x + y); y is kept (fp32) for
 // diagnostics.  One thread per four elements; the order of the additions is fixed, so the result is reproducible
 // bit for bit whatever order the w2 blocks finished in.
+// log (may be null): one bit per expert that has pairs, for the host's bookkeeping.
 __global__ __launch_bounds__(256) void k_combine(const uint16_t *x, const float *ypart, const uint32_t *ytab, float *y, uint16_t *x_out,
-                                                 int H, int K, uint32_t cap_rows)
+                                                 int H, int K, uint32_t cap_rows, const uint8_t *pair_expert, int32_t *log)
 {
+    if (log && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64) {
+        uint32_t used = 0;
+        for (int q = threadIdx.x; q < (int)gridDim.y * K; q += 64) used |= 1u << pair_expert[q];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) used |= __shfl_xor(used, d);
+        if (threadIdx.x == 0) *log = (int32_t)used;
+    }
     const int b = blockIdx.y, i = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= H) return;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);

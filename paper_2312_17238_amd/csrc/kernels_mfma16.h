@@ -84,10 +84,67 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
     const int n_rows = W13 ? 2 * A.N : A.N;
     const int groups = A.K / 64, n_seg = (groups + TL_SG - 1) / TL_SG;
 
+    float *l_w = reinterpret_cast<float *>(lds + 2 * TL_BUF_BYTES);
+    uint8_t *l_tok = reinterpret_cast<uint8_t *>(l_w + MF_MAX_PAIRS), *l_pair = l_tok + MF_MAX_PAIRS;
+    MfmaEntry *const l_e = reinterpret_cast<MfmaEntry *>(l_pair + MF_MAX_PAIRS);
+    int32_t *const l_n = reinterpret_cast<int32_t *>(l_e + 32);
+    static_assert(sizeof(MfmaEntry) == 16 && (2 * TL_BUF_BYTES + MF_MAX_PAIRS * 6) % 16 == 0, "entries are 16 bytes of the table");
+    static_assert(FEW_PAIRS == MF_MAX_PAIRS, "the tables hold a step's pairs");
+    if (A.pair_expert) {
+        // the first wave cuts every expert's pairs into entries and puts them into the tables, expert by expert
+        if (tid < 64) {
+            FewPairs few;
+            few.load(A.pair_expert, A.n_pairs);
+            const int count = few.counts(A.n_experts), first = prefix16(count) - count;      // lane e: expert e's pairs, its first place
+            const int tiles = lane < 16 ? (count + A.tile_tokens - 1) / A.tile_tokens : 0, end = prefix16(tiles);
+            const uint8_t *const blob = A.table[lane & 15];
+            for (int k = 0; k < tiles; ++k)
+                if (end - tiles + k < 32) l_e[end - tiles + k] = {blob, min(A.tile_tokens, count - k * A.tile_tokens), first + k * A.tile_tokens};
+            const int n = __builtin_amdgcn_readlane(end, 15);
+            uint32_t before[FEW_PAIRS / 64] = {0};                       // pairs of the same expert before the lane's own
+            for (int x = 0; x < A.n_experts; ++x) {
+                int k = 0;
+#pragma unroll
+                for (int c = 0; c < FEW_PAIRS / 64; ++c) {
+                    const uint64_t m = few.mask(c, x);
+                    if (few.e[c] == (uint32_t)x) before[c] = k + __popcll(m & ((1ull << lane) - 1));
+                    k += __popcll(m);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < FEW_PAIRS / 64; ++c) {
+                const int p = c * 64 + lane, at = __shfl(first, (int)few.e[c] & 15) + (int)before[c];
+                if (p < A.n_pairs) {
+                    l_pair[at] = (uint8_t)p;
+                    l_tok[at] = (uint8_t)(p / A.top_k);
+                    l_w[at] = A.pair_w[p];
+                }
+            }
+            if (lane == 0) *l_n = min(n, 32);
+        }
+    } else {
+        if (tid < MF_MAX_PAIRS) {
+            l_w[tid] = A.w[tid];
+            l_tok[tid] = A.tok[tid];
+            l_pair[tid] = A.pair[tid];
+        }
+        if (tid < 32) l_e[tid] = A.e[tid];
+    }
+    __syncthreads();
+    const int n_items = A.pair_expert ? uniform(*l_n) * A.row_blocks * A.k_parts : A.n_items;
+    auto entry = [&](int e) -> MfmaEntry {
+        MfmaEntry en = l_e[e];
+        const uint64_t b = (uint64_t)en.blob;
+        en.blob = (const uint8_t *)(((uint64_t)(uint32_t)uniform((int)(b >> 32)) << 32) | (uint32_t)uniform((int)(uint32_t)b));
+        en.n_tok = uniform(en.n_tok);
+        en.first = uniform(en.first);
+        return en;
+    };
+
     auto first_step = [&](int it) -> TileStep {
         TileStep s;
         s.it = it;
-        s.valid = it < A.n_items;
+        s.valid = it < n_items;
         const int part = it % A.k_parts, t = it / A.k_parts;
         s.rb = t % A.row_blocks;
         s.e = s.valid ? t / A.row_blocks : 0;
@@ -100,17 +157,8 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
         return first_step(s.it + (int)gridDim.x);
     };
     auto seg_groups = [&](const TileStep &s) { return min(TL_SG, groups - s.seg * TL_SG); };
-
     TileStep cur = first_step(blockIdx.x);
-    if (!cur.valid) return;                                          // whole block, before any barrier
-    float *l_w = reinterpret_cast<float *>(lds + 2 * TL_BUF_BYTES);
-    uint8_t *l_tok = reinterpret_cast<uint8_t *>(l_w + MF_MAX_PAIRS), *l_pair = l_tok + MF_MAX_PAIRS;
-    if (tid < MF_MAX_PAIRS) {
-        l_w[tid] = A.w[tid];
-        l_tok[tid] = A.tok[tid];
-        l_pair[tid] = A.pair[tid];
-    }
-    __syncthreads();
+    if (!cur.valid) return;                                          // whole block, before the next barrier
     TileStep nxt = next(cur);
     int buf = 0;
 
@@ -118,7 +166,7 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
     int addr_it = -1;
     // the item's matrix as a buffer: a load's address is this scalar descriptor, a scalar offset and ONE 32-bit vector
     // register, instead of 64-bit arithmetic in vector registers per load (a matrix is far below 4 GB)
-    __amdgpu_buffer_rsrc_t mat_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(A.e[0].blob), 0, 0, 0x00020000);
+    __amdgpu_buffer_rsrc_t mat_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(A.act), 0, 0, 0x00020000);
     // The activations as a buffer too: a lane whose token does not exist carries an offset past the buffer's end, for
     // which the hardware returns zeros without a request -- at four tokens per expert three quarters of the A operand's
     // lanes, whose 16 bytes each would otherwise cross the compute unit's path to memory like any others.
@@ -128,7 +176,7 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
     auto enter_item = [&](const TileStep &s) {
         if (s.it == addr_it) return;
         addr_it = s.it;
-        const MfmaEntry &en = A.e[s.e];
+        const MfmaEntry en = entry(s.e);
         mat_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(en.blob + A.mat_off), 0, n_rows * (int)A.stride, 0x00020000);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -303,7 +351,7 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
     static_assert(WAVES * RS * 4 * 64 * 4 <= TL_BUF_BYTES && NI * WAVES == RS * 4 && 4 % (NI < 4 ? NI : 4) == 0, "one reduction round must fit a staging buffer");
     auto finish_item = [&](const TileStep &s, int b) {
         float *red = reinterpret_cast<float *>(lds + b * TL_BUF_BYTES);   // [wave][sub-tile of the round][4][64]
-        const MfmaEntry &en = A.e[s.e];
+        const MfmaEntry en = entry(s.e);
         const int part = s.it % A.k_parts;
         if (!W13 && s.rb == 0 && part == 0 && tid < en.n_tok) {      // one block per entry tells k_combine where the rows are
             const int tk = en.first + tid;

@@ -57,7 +57,7 @@ constexpr int TL_GPW = TL_SG / TL_WAVES;                 // groups per wave and 
 constexpr int TL_CODE_PITCH = TL_SG * 32 + 16;           // bytes per staged row of codes (+16: bank spread)
 constexpr int TL_META_PITCH = TL_SG + 1;                 // words per staged row of pairs (odd: bank spread)
 constexpr int TL_BUF_BYTES = TL_ROWS * TL_CODE_PITCH + TL_ROWS * TL_META_PITCH * 4;
-constexpr int TL_TABLE_BYTES = MF_MAX_PAIRS * 6;         // token, pair (bytes) and combine weight (float) of every pair
+constexpr int TL_TABLE_BYTES = MF_MAX_PAIRS * 6 + 32 * 16 + 16;  // token, pair (bytes) and combine weight (float) of every pair; entries, their number
 constexpr int TL_LDS_BYTES = 2 * TL_BUF_BYTES + TL_TABLE_BYTES;
 constexpr int TL_CPR = TL_SG * 2, TL_MPR = TL_SG / 4;    // 16-byte code / pair pieces per staged row
 constexpr int TL_CP = TL_ROWS * TL_CPR / TL_THREADS;     // code pieces per thread and step (8)
@@ -84,6 +84,12 @@ struct TileArgs {
     int32_t run_shift;                       // ... log2(groups per run), 31 when a row is one run
     uint64_t mat_off;
     int32_t row_blocks, k_parts, seg_per_part, n_items;   // item = ((entry * row_blocks) + row block) * k_parts + part
+    // The 16-token kernels may find the routing in device memory: every pair's expert (at most FEW_PAIRS pairs) and weight,
+    // expert e's blob in table[e]; an entry is up to tile_tokens of an expert's pairs.  Null: the entries and pairs above.
+    const uint8_t *pair_expert;
+    const float *pair_w;
+    const uint8_t *table[16];
+    int32_t n_pairs, n_experts, top_k, tile_tokens;
 };
 
 struct TileStep { int it, seg, seg_hi, rb, e; bool valid; };

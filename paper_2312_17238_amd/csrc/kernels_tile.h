@@ -61,16 +61,11 @@ typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 
 constexpr int TE_XCD = 8;                // blocks of one row block go to one XCD, whose L2 then serves its token blocks
 
-struct TileExpert {
-    const uint8_t *blob;
-    int32_t first, count;                // its pairs: positions first .. first + count - 1 of plist
-    int32_t tb;                          // token blocks
-    int32_t item0;                       // its first item in every XCD's sequence
-};
-
 struct TeArgs {
-    TileExpert e[16];
-    int32_t n_exp;
+    const uint8_t *blob[16];             // device buffers of the launch's experts
+    uint32_t experts;                    // ... one bit for each of them
+    const uint8_t *pair_expert;          // at most FEW_PAIRS pairs: every pair's expert, and null else
+    const int32_t *first;                // k_sort_pairs: expert e's pairs are positions first[e] .. first[e + 1] - 1 of plist
     const uint16_t *plist;               // pair ids (token * top_k + choice), expert by expert, ascending within one
     const float *pair_w;                 // combine weight of every pair
     const uint16_t *act;                 // w1/w3: h [B][K];  w2: a [B*top_k][K]
@@ -79,13 +74,13 @@ struct TeArgs {
     uint2 *xs_out;                       // ... and their sums
     float *ypart;                        // w2: rows of N, one per pair (k_parts == 1) or per (position, part)
     uint32_t *ytab;
-    int32_t K, N, top_k;
+    int32_t K, N, top_k, n_pairs, n_experts;
     int32_t xs_stride, xs_out_stride;
     uint32_t stride, meta_off, meta2_off, b_off;
     int32_t unit_shift, run_shift;       // group of unit u: u >> unit_shift; run of group g: g >> run_shift
     uint64_t mat_off;
     int32_t units_per_part, k_parts, part_base;
-    int32_t jobs;                        // row blocks * k_parts
+    int32_t jobs, per_xcd;               // row blocks * k_parts, and an XCD's share of them
     float lift, lower;                   // two-level 2-bit codes: what their scales are multiplied with, and its reciprocal
     uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
 };
@@ -453,6 +448,10 @@ template <int FMT, int MODE> struct TeCfg {
     static_assert(OFF_X >= TOK * APITCH && LDS <= (BIG || F::PLANES == 2 ? 160 : 80) * 1024, "the epilogue reuses the staging buffers");
 };
 
+// token blocks of an expert: one tile of 16 or 32, or up to as many tiles of 32 per block as the large kernel holds
+template <int TOK, bool BIG>
+__host__ __device__ constexpr int te_token_blocks(int count) { return BIG ? ((count + 31) / 32 + TOK / 32 - 1) / (TOK / 32) : (count + TOK - 1) / TOK; }
+
 template <int FMT, bool W13, int MODE>
 __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAVES_EU)) void k_tile(TeArgs A)
 {
@@ -467,12 +466,32 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     const int rg = wv % C::RG, half = wv / C::RG;                        // rows of the wave; token half (BIG) or unit parity
 
     // ---------------- the item ----------------
-    int j = (int)blockIdx.x / TE_XCD, e = 0;
-    while (e + 1 < A.n_exp && j >= A.e[e + 1].item0) ++e;
-    const TileExpert ex = A.e[e];
-    j -= ex.item0;
+    // Items of an XCD: expert by expert, its jobs, each job's token blocks next to each other.  How many token blocks an expert
+    // has is worked out here, from the sorted list's table, so that the launch need not know the routing (its grid then
+    // covers the most there can be; the blocks too many end here).
+    // Lane e works it out for expert e (a chain of sixteen scalar steps, each behind a load of its arguments, cost 3 us a block).
+    FewPairs few;
+    int j = (int)blockIdx.x / TE_XCD;
+    struct { const uint8_t *blob; int expert, first, count, tb; } ex;
+    {
+        int count, first;
+        if (A.pair_expert) {
+            few.load(A.pair_expert, A.n_pairs);
+            count = few.counts(A.n_experts);
+            first = prefix16(count) - count;
+        } else {
+            first = A.first[lane & 15];
+            count = A.first[(lane & 15) + 1] - first;
+        }
+        const int tb = lane < 16 && (A.experts >> lane & 1u) ? te_token_blocks<C::TOK, BIG>(count) : 0, items = tb * A.per_xcd, end = prefix16(items);
+        const uint64_t mine = __ballot(lane < 16 && j >= end - items && j < end);
+        if (!mine) return;                                               // whole block, before any barrier
+        const int e = (int)__builtin_ctzll(mine);
+        ex = {A.blob[e], e, __builtin_amdgcn_readlane(first, e), __builtin_amdgcn_readlane(count, e), __builtin_amdgcn_readlane(tb, e)};
+        j -= __builtin_amdgcn_readlane(end - items, e);
+    }
     const int job = (j / ex.tb) * TE_XCD + (int)blockIdx.x % TE_XCD, t = j % ex.tb;
-    if (job >= A.jobs) return;                                           // whole block, before any barrier
+    if (job >= A.jobs) return;                                           // ... this one too
     const int rb = job / A.k_parts, part = job % A.k_parts;
     constexpr int TILE = BIG ? 32 : MODE;                                // tokens per tile
     const int tiles = (ex.count + TILE - 1) / TILE;
@@ -480,7 +499,33 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     const int tok0 = tile0 * TILE, n_tok = min(ex.count - tok0, n_tiles * TILE);
     const int n_rows = W13 ? 2 * A.N : A.N, row0 = rb * ROWS;
     const int u0 = part * A.units_per_part, u1 = min(A.K / 64, u0 + A.units_per_part);
-    if (tid < C::TOK) {
+    // The first sets of weights need no routing: they are requested before the pairs are known.
+    const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(ex.blob + A.mat_off), 0, n_rows * (int)A.stride, 0x00020000);
+    const TeGeom geo = {A.stride, A.meta_off, A.meta2_off, A.b_off, A.unit_shift, A.run_shift, A.K / 64};
+    auto fetch_b = [&](F &f, int h, int u) __attribute__((always_inline)) { f.fetch(h, w_rs, geo, row0, n_rows, u < u1 ? u : u0, u < u1, tid); };
+    F f0, f1;                                                            // weights on their way to LDS (BIG: f0)
+    fetch_b(f0, 0, u0);
+    fetch_b(f0, 1, u0);
+    if constexpr (!BIG) {
+        fetch_b(f1, 0, u0 + 4);
+        fetch_b(f1, 1, u0 + 4);
+    }
+    if (A.pair_expert) {
+        if (tid < C::TOK && tid >= n_tok) l_pair[tid] = -1;
+        if (wv == 0) {
+            int at = -tok0;                                              // a pair's place among its expert's, from the block's first token
+#pragma unroll
+            for (int c = 0; c < FEW_PAIRS / 64; ++c) {
+                const uint64_t m = few.mask(c, ex.expert);
+                const int k = at + __popcll(m & ((1ull << lane) - 1)), p = c * 64 + lane;
+                if (few.e[c] == (uint32_t)ex.expert && k >= 0 && k < n_tok) {
+                    l_pair[k] = p;
+                    l_w[k] = W13 ? 0.f : A.pair_w[p];
+                }
+                at += __popcll(m);
+            }
+        }
+    } else if (tid < C::TOK) {
         const int p = tid < n_tok ? (int)A.plist[ex.first + tok0 + tid] : -1;
         l_pair[tid] = p;
         l_w[tid] = p >= 0 && !W13 ? A.pair_w[p] : 0.f;
@@ -488,10 +533,8 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     __syncthreads();
 
     // ---------------- staging ----------------
-    const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(ex.blob + A.mat_off), 0, n_rows * (int)A.stride, 0x00020000);
     const __amdgpu_buffer_rsrc_t a_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(A.act), 0, (int)A.act_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint2 *>(A.xs), 0, (int)A.xs_bytes, 0x00020000);
-    const TeGeom geo = {A.stride, A.meta_off, A.meta2_off, A.b_off, A.unit_shift, A.run_shift, A.K / 64};
     auto act_row = [&](int tk) __attribute__((always_inline)) { const int p = l_pair[tk]; return W13 ? p / A.top_k : p; };
     uint32_t a_off[NP];
 #pragma unroll
@@ -500,7 +543,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         a_off[i] = tk < n_tok ? (uint32_t)act_row(tk) * (uint32_t)A.K * 2u + (uint32_t)(tid % PPT) * 16u : TE_NONE;
     }
     // sums: piece p of a step is token p / XQ; threads too many request nothing (a repeated piece is a visit of its line as any
-    // other), in the large kernel and with 2-bit codes they repeat one (no branch, see below)
+    // other), in the large kernel and with 2-bit codes they repeat one (a branch costs those more: 2-bit, 16 tokens, 120 -> 129 us)
     constexpr int XQ = C::XQ, XU = F::GS ? 1 : 4;                        // XU: groups per unit
     constexpr bool X_REPEAT = BIG || !F::GS;
     static_assert(C::TOK * XQ <= THREADS && (!X_REPEAT || THREADS % XQ == 0), "one piece per thread");
@@ -528,7 +571,6 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         else *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
     };
     // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
-    auto fetch_b = [&](F &f, int h, int u) __attribute__((always_inline)) { f.fetch(h, w_rs, geo, row0, n_rows, u < u1 ? u : u0, u < u1, tid); };
     auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, A.lift, tid); };
 
     // Left alone the scheduler moves a step's loads down to just before the LDS stores that wait for them: requests stay
@@ -684,16 +726,13 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         // units one by one: activations double buffered per unit, weights per set
         const int nt0 = (n_tiles + 1) / 2;
         {
-            F f;
             Acts t;
             fetch_a(t, u0);
             fetch_x(t, u0);
-            fetch_b(f, 0, u0);
-            fetch_b(f, 1, u0);
             commit_a(t, 0);
             commit_x(t, 0);
-            commit_b(f, 0, 0, u0);
-            commit_b(f, 1, 0, u0);
+            commit_b(f0, 0, 0, u0);
+            commit_b(f0, 1, 0, u0);
         }
         __syncthreads();
         auto body = [&](auto nt_tag, auto late_tag) __attribute__((always_inline)) {
@@ -849,7 +888,6 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             }
         };
         // Two sets are on their way, activations as well as weights (one alone takes longer to arrive than a set to multiply)
-        F f0, f1;
         Acts t0, t1;
         auto fetch = [&](F &f, Acts &t, int u) __attribute__((always_inline)) {
             fetch_a(t, u);
@@ -862,8 +900,10 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             for (int h = 0; h < 2; ++h) commit_b(f, h, b, u);
             if constexpr (!X_REPEAT) commit_x(t, b);
         };
-        fetch(f0, t0, u0);
-        fetch(f1, t1, u0 + 4);
+        fetch_a(t0, u0);
+        fetch_x(t0, u0);
+        fetch_a(t1, u0 + 4);
+        fetch_x(t1, u0 + 4);
         commit(f0, t0, 0, u0);
         __syncthreads();
         auto set = [&](F &fin, Acts &tin, const F &fout, const Acts &tout, int u, int bb) __attribute__((always_inline)) {
@@ -898,51 +938,6 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             put(v, MODE == 32 ? 8 * (i / 4) + 4 * kb + i % 4 : 4 * kb + i, rt * RROWS + rcol);
         }
         copy_out();
-    }
-}
-
-// The pairs of a step sorted by expert, ascending within one expert: a counting sort in one block of 16 waves.
-constexpr int SORT_THREADS = 1024;
-__global__ __launch_bounds__(SORT_THREADS) void k_sort_pairs(const uint8_t *expert, int n, uint16_t *plist)
-{
-    constexpr int CHUNKS = GATE_MAX_TOKENS * 4 / 64;                     // chunks of 64 pairs (64)
-    __shared__ int32_t cnt[16][CHUNKS];
-    __shared__ int32_t wave_tot[SORT_THREADS / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const uint64_t below = (1ull << lane) - 1;
-    for (int c = wv; c < CHUNKS; c += SORT_THREADS / 64) {
-        const int q = c * 64 + lane, e = q < n ? (int)expert[q] : -1;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint64_t m = __ballot(e == k);
-            if (lane == 0) cnt[k][c] = __popcll(m);
-        }
-    }
-    __syncthreads();
-    // exclusive prefix sum over (expert, chunk): one entry per thread
-    static_assert(16 * CHUNKS == SORT_THREADS, "one entry per thread");
-    const int own = cnt[tid / CHUNKS][tid % CHUNKS];
-    int inc = own;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int v = __shfl_up(inc, d);
-        if (lane >= d) inc += v;
-    }
-    if (lane == 63) wave_tot[wv] = inc;
-    __syncthreads();
-    int base = inc - own;
-    for (int w = 0; w < wv; ++w) base += wave_tot[w];
-    cnt[tid / CHUNKS][tid % CHUNKS] = base;
-    __syncthreads();
-    for (int c = wv; c < CHUNKS; c += SORT_THREADS / 64) {
-        const int q = c * 64 + lane, e = q < n ? (int)expert[q] : -1;
-        int pos = 0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint64_t m = __ballot(e == k);
-            if (e == k) pos = cnt[k][c] + __popcll(m & below);
-        }
-        if (e >= 0) plist[pos] = (uint16_t)q;
     }
 }
 

@@ -150,16 +150,13 @@ struct moe_ctx {
     uint32_t *ytab = nullptr;
     uint64_t ypart_extra_floats = 0;    // capacity behind the first B*K rows
     uint64_t ypart_extra_used = 0;      // floats of it taken by the launches of the current step
-    std::vector<int32_t> w2_parts;      // per window of the current step: parts the matrix-core w2 launches split their contraction into
-    std::vector<uint8_t> win_small;     // ... and whether no expert has more than 16 tokens of the window (the 16-token tile form fits)
-    // Tile kernels: what the gate kernel leaves in device memory (expert and combine weight of every pair, sums of h per
-    // group), the pairs sorted by expert, and the sums of a per group; per step, from its routing: each expert's first
-    // position in that list and its pairs, and the parts the w2 launches split their contraction into.
+    // What the gate kernel leaves in device memory (expert and combine weight of every pair, the tile kernels' sums of h per
+    // group), the pairs sorted by expert with each expert's first position, and the sums of a per group.
     uint8_t *pair_expert = nullptr;
     float *pair_w = nullptr;
     uint16_t *plist = nullptr;
+    int32_t *pair_first = nullptr;
     uint2 *xs_h = nullptr, *xs_a = nullptr;
-    int32_t tile_first[MOE_MAX_EXPERTS] = {}, tile_count[MOE_MAX_EXPERTS] = {}, tile_parts = 1, tile_mode = TE_BIG, tile_most = 0;
     uint8_t *noalloc_scratch = nullptr; // this device's copy of the file-scope scratch array (moe_layer_step_noalloc)
     GateHostOut *gate_out = nullptr;    // host pointer
     GateHostOut *gate_out_dev = nullptr;// the same memory as the device sees it
@@ -196,7 +193,7 @@ struct moe_ctx {
     float *route_w = nullptr;           // device: ... and combine weights
     int32_t *route_log = nullptr;       // pinned host copy of the ring below, refreshed when the bookkeeping catches up
     int32_t *route_log_dev = nullptr;   // device ring of ROUTE_LOG entries of MOE_MAX_TOPK selections, written by the gate kernel
-    struct PendingStep { moe_layer *layer; uint32_t slot; };
+    struct PendingStep { moe_layer *layer; uint32_t slot; bool batch; };   // batch: the slot's first word has one bit per expert needed
     std::vector<PendingStep> pending;   // steps enqueued that way whose bookkeeping is still to be done, oldest first
     static constexpr uint32_t ROUTE_LOG = ROUTE_LOG_ENTRIES;
 };
@@ -255,7 +252,7 @@ static bool layer_cfg_ok(const moe_layer_config_t *c)
            c->scale_group >= 0 && blob_layout(c->hidden, c->ffn, c->bits, c->group, c->scale_group).ok;
 }
 
-struct ScratchPlan { uint64_t staging, h, a, yacc, ypart, ytab, ypart_extra_floats, x0, x1, barrier, route, route_log, pair_expert, pair_w, plist, xs_h, xs_a, total; };
+struct ScratchPlan { uint64_t staging, h, a, yacc, ypart, ytab, ypart_extra_floats, x0, x1, barrier, route, route_log, pair_expert, pair_w, plist, pair_first, xs_h, xs_a, total; };
 
 static ScratchPlan plan_scratch(const moe_ctx_config_t *c)
 {
@@ -279,6 +276,7 @@ static ScratchPlan plan_scratch(const moe_ctx_config_t *c)
     p.pair_expert = off; off += align_u64(pairs, 256);
     p.pair_w = off; off += align_u64(pairs * 4, 256);
     p.plist = off; off += align_u64(pairs * 2, 256);
+    p.pair_first = off; off += 256;
     // sums of activations per group, 8 bytes each: room for the smallest groups (16) and rows padded to multiples of 4
     p.xs_h = off; off += align_u64((uint64_t)c->max_batch * (c->max_hidden / 16) * 8, 256);
     p.xs_a = off; off += align_u64(pairs * (c->max_ffn / 16) * 8, 256);
@@ -369,6 +367,7 @@ try {
     c->pair_expert = base + p.pair_expert;
     c->pair_w = reinterpret_cast<float *>(base + p.pair_w);
     c->plist = reinterpret_cast<uint16_t *>(base + p.plist);
+    c->pair_first = reinterpret_cast<int32_t *>(base + p.pair_first);
     c->xs_h = reinterpret_cast<uint2 *>(base + p.xs_h);
     c->xs_a = reinterpret_cast<uint2 *>(base + p.xs_a);
     hipError_t e = hipMemset(c->barrier, 0, 4096 + 2 * SEQ_FLAG_STRIDE * 4);
@@ -1146,14 +1145,16 @@ static int32_t launch_gate(moe_ctx *c, GateArgs ga, int32_t batch)
     if (++c->gate_seq == 0) ++c->gate_seq;             // 0 is what a fresh context holds
     ga.seq = c->gate_seq;
     const dim3 grid(batch), block(GATE_THREADS);
-    const bool dense = ga.xs && !ga.wg2 && ga.E <= GATE_DENSE_EXPERTS && batch > (c->n_cu > 0 ? c->n_cu : 256);
+    const bool dense = ga.pair_expert && !ga.wg2 && ga.E <= GATE_DENSE_EXPERTS && batch > (c->n_cu > 0 ? c->n_cu : 256);
     int32_t rc = dense ? launch_timed(c, PROF_GATE, 0, k_gate<false, true, true>, grid, block, 0, ga)
-               : ga.xs ? (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true, true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false, true>, grid, block, 0, ga))
+               : ga.pair_expert ? (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true, true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false, true>, grid, block, 0, ga))
                        : (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false>, grid, block, 0, ga));
-    if (rc) return rc;
+    if (rc || ga.quiet) return rc;
     if (!c->sync_wait) HIPCHK(hipEventRecord(c->ev_gate, c->compute));
     return wait_gate(c, batch, ga.seq);
 }
+
+static int n_cu_of(const moe_ctx *c) { return c->n_cu > 0 ? c->n_cu : 256; }
 
 // Rows each wave keeps in flight (ring depth) in the w1/w3 and the w2 kernel.
 #ifndef MOE_W13_G
@@ -1204,7 +1205,9 @@ static int32_t launch_w13_t(moe_ctx *c, uint64_t bytes, int n_entries, const Ffn
 {
     if constexpr (KCH * NT * act_regs<BITS>() <= ACT_REG_BUDGET) {
         constexpr int WAVES = w13_waves<BITS, KCH, NT>();
-        const dim3 grid(std::max(1, std::min((A.F + WAVES - 1) / WAVES, c->w13_blocks / n_entries)), n_entries);
+        const int per_entry = std::max(1, std::min((A.F + WAVES - 1) / WAVES, c->w13_blocks / n_entries));
+        // entries the kernels find themselves: at least a block for each there can be, more for each there is where they are fewer
+        const dim3 grid = A.pair_expert ? dim3(std::max(n_entries, std::min((A.F + WAVES - 1) / WAVES * n_entries, c->w13_blocks))) : dim3(per_entry, n_entries);
         return launch_timed(c, PROF_W13, bytes, k_w13<BITS, KCH, NT, MOE_W13_G, WAVES>, grid, dim3(WAVES * WAVE), 0, A);
     } else {
         return fail(MOE_EINVAL, "no w1/w3 kernel for %d chunks per lane and %d tokens per entry", KCH, NT);
@@ -1220,31 +1223,38 @@ static int32_t launch_w13_k(moe_ctx *c, int nt, uint64_t bytes, int n_entries, c
 }
 
 // table (device-side routing): the layer's expert -> device buffer map; entry j then serves the j-th selected expert
+// ... or, for a batch (routed = its pairs), entries of up to nt tokens that the kernels find themselves; `entries` is
+// empty then.
 template <int BITS>
-static int32_t launch_ffn_fmt(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only, const uint8_t *const *table)
+static int32_t launch_ffn_fmt(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only, const uint8_t *const *table, int routed)
 {
     moe_ctx *c = l->ctx;
     const BlobLayout &b = l->lay;
     const int kch = chunks_per_lane(b.hidden, BITS);                          // per w1/w3 row
     const int cs = (b.ffn / Fmt<BITS>::CODES + 63) / 64;                      // waves per block for w2
     if (kch == 0 || cs > 8) return fail(MOE_EINVAL, "shape too large for the GEMV kernels");
-    for (size_t first = 0; first < entries.size(); first += MAX_ENTRIES) {
-        const int n = (int)std::min<size_t>(MAX_ENTRIES, entries.size() - first);
+    for (size_t first = 0; first < (routed ? 1 : entries.size()); first += MAX_ENTRIES) {
+        const int own = std::min(routed, l->cfg.n_experts);
+        const int n = routed ? own + (routed - own) / nt : (int)std::min<size_t>(MAX_ENTRIES, entries.size() - first);   // routed: the most there can be
         FfnArgs A{};
-        for (int i = 0; i < n; ++i) A.e[i] = entries[first + i];
+        for (int i = 0; i < n && !routed; ++i) A.e[i] = entries[first + i];
         A.h = c->h_buf; A.a = c->a_buf; A.ypart = c->ypart; A.ytab = c->ytab;
         A.H = b.hidden; A.F = b.ffn; A.group = b.group; A.scale_group = b.scale_group;
         A.stride13 = b.m13.row_stride; A.meta13 = b.m13.meta_off;
         A.stride2 = b.m2.row_stride; A.meta2 = b.m2.meta_off;
         A.off_w2 = b.off_w2;
+        // Rows of a w2 block: w2_rows where that fills the chip with two waves a SIMD, fewer in smaller layers, whose blocks would
+        // otherwise be few and each a long chain of rows (704 x 768, 3 tokens, 32 rows a block: 13 to 18 us).
         A.rows_per_block = c->w2_rows;
+        while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < n_cu_of(c) * 8) A.rows_per_block = (A.rows_per_block + 1) / 2;
         if (table) {
-            A.route_idx = c->route_idx;
+            if (routed) { A.pair_expert = c->pair_expert; A.pair_w = c->pair_w; A.n_pairs = routed; A.n_experts = l->cfg.n_experts; A.top_k = l->cfg.top_k; }
+            else A.route_idx = c->route_idx;
             for (int e = 0; e < 16; ++e) A.table[e] = table[e];
         }
         // algorithmic bytes: every distinct expert of the launch is read once
-        uint64_t n_distinct = 0;
-        for (int i = 0; i < n; ++i) {
+        uint64_t n_distinct = routed ? own : 0;
+        for (int i = 0; i < n && !routed; ++i) {
             bool seen = false;
             for (int j = 0; j < i && !table; ++j) seen |= (A.e[j].blob == A.e[i].blob);
             n_distinct += !seen;
@@ -1372,11 +1382,231 @@ static int32_t launch_token(moe_layer *l, const FusedArgs &A, bool one_launch, b
 
 // Matrix-core path for one pass: every expert of the pass with all its tokens, two launches (w1/w3, w2)
 // plus the group-sum tables of their activation operands.
+
 struct PassExpert { const uint8_t *blob; std::vector<int> pairs; int32_t expert; };
 
+// ---- which kernels a step takes ----
+
+// Codes per sum of activations: the groups of the zero-point term.
+static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
+static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
+
+// The power of two that two-level 2-bit scales are multiplied with: the layer's largest just below 32000, so that its product
+// with a code (at most 2 in size, centred) is an fp16 number.
+static float tile_lift(const moe_layer *l)
+{
+    const float top = bits_to_float(l->scale_top.load(std::memory_order_relaxed));
+    if (l->lay.bits != 2 || !l->lay.scale_group || !(top > 0.f) || !std::isfinite(top)) return 1.f;
+    int e;
+    std::frexp(32000.f / top, &e);                   // 2^(e-1) <= 32000 / top
+    return std::ldexp(1.f, std::min(e - 1, 100));
+}
+
+// 2-bit codes enter the matrix cores multiplied with their scale in fp16, so a layer whose scales fp16 does not hold stays on the
+// GEMV kernels.  Above: one-level 32000, two-level 500.  Below: fp16 numbers are subnormal from 2^-14 on, whose products the
+// matrix cores add with about 2^-40 of error (w2's scales of 2^-22: y 7e-6 off, GEMV exact), and a two-level scale's second
+// half carries all of its bits as long as the scale, lifted, is 2^-2 or more.  What counts is a row's largest scale: beside
+// it the error of a smaller one is below fp32's.
+static bool tile_format(const moe_layer *l)
+{
+    const BlobLayout &b = l->lay;
+    if (b.bits == 2) {
+        const float top = bits_to_float(l->scale_top.load(std::memory_order_relaxed)), low = bits_to_float(l->scale_row_low.load(std::memory_order_relaxed));
+        if (!(top <= (b.scale_group ? 500.f : 32000.f)) || low * tile_lift(l) < (b.scale_group ? 0.25f : 0x1p-14f)) return false;
+    }
+    const bool fits32 = 2ull * b.ffn * b.m13.row_stride < (1ull << 31) && (uint64_t)b.hidden * b.m2.row_stride < (1ull << 31);
+    return fits32 && (b.bits != 4 || b.group >= 64);
+}
+
+// token blocks of an expert with `count` tokens
+static int tile_blocks(const BlobLayout &b, int count, int mode)
+{
+    if (mode != TE_BIG) return (count + mode - 1) / mode;
+    return b.bits == 2 && b.scale_group ? te_token_blocks<TeCfg<28, TE_BIG>::TOK, true>(count) : te_token_blocks<TeCfg<4, TE_BIG>::TOK, true>(count);
+}
+
+constexpr int TILE_MODE32_AVERAGE = 26;                              // tokens of an expert on average up to which the 32-token tile kernel runs
+constexpr int STREAM_SMALL_AVERAGE = 14;                              // ... up to which the 16-token kernels' entries are one tile of 16
+constexpr int64_t TILE_MIDDLE_LOW = 1 << 21, TILE_MIDDLE_HIGH = 11 << 20, TILE_TWO_TILES_HIGH = 18 << 20;    // hidden * ffn, tile_may
+
+// How a step of several tokens runs.  All of it follows from the layer, the batch and the options, nothing from the routing or
+// the cache: the kernels add in different orders, so that is what makes a result depend on neither, and it lets a step
+// whose experts are all resident be queued before anybody has seen its routing.  Where the tokens of an expert matter the
+// plan goes by a nominal routing, the pairs dealt out evenly; an expert with more than that takes another token block.
+struct BatchPlan {
+    enum Kind { GEMV, STREAM, TILE } kind = GEMV;
+    int mode = TE_BIG, parts = 1;         // TILE: tokens per block; parts that w2 splits its contraction into
+    struct Window { int parts; bool small; };
+    std::vector<Window> win;              // STREAM: per window of 256 / top_k tokens, w2's parts and whether one tile of 16 tokens is enough
+};
+
+// Pairs of expert e when `pairs` of them are dealt out evenly.
+static int nominal_count(const moe_layer *l, int pairs, int e) { return pairs / l->cfg.n_experts + (e < pairs % l->cfg.n_experts); }
+
+// Tile kernels: tokens per block, and into how many parts w2 splits its contraction.
+static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
+{
+    const moe_ctx *c = l->ctx;
+    const BlobLayout &b = l->lay;
+    const int E = l->cfg.n_experts, pairs = batch * l->cfg.top_k;
+    // Where every token needs every expert the tokens of one are known.  Otherwise they spread around the average, and a kernel
+    // for more tokens than that on average is the better one before experts that need a second block of the smaller become many.
+    const bool exact = l->cfg.top_k == E;
+    const double avg = (double)pairs / E;
+    p.mode = avg > (exact ? 32 : TILE_MODE32_AVERAGE) ? TE_BIG : (avg > (exact ? 16 : 12) ? 32 : 16);
+    int blocks = 0;
+    for (int e = 0; e < E; ++e) blocks += tile_blocks(b, nominal_count(l, pairs, e), p.mode);
+    const int rows = p.mode == TE_BIG ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
+    const int sets = (b.ffn / 64 + 3) / 4;
+    const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
+    // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
+    // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
+    // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
+    // 226 + 14 (4).
+    const int slots = n_cu_of(c) * (p.mode == TE_BIG ? 1 : 2);
+    double best = 0.0;
+    p.parts = 1;
+    for (int n = 1; n <= std::min(std::min(8, sets), cap); ++n) {
+        const int items = rb * blocks * n, rounds = (items + slots - 1) / slots;
+        const double eff = (double)items / ((double)rounds * slots) / (1.0 + 0.03 * n);
+        if (eff > best) { best = eff; p.parts = n; }
+    }
+}
+
+// The 16-token (streaming) kernels' windows: how many parts the w2 launches of a window split their contraction into, and
+// whether their entries are tiles of 16 tokens or of 32.  One tile of 16 costs 88 us where two cost 129 (w1/w3, Mixtral-shaped), so
+// it is the better one as long as less than about four experts in ten need a second entry: up to an average of 14.
+//
+// Returns what the step takes with them in us (tile_us: why, and where the numbers come from).
+static double plan_windows(const moe_layer *l, int batch, BatchPlan &p)
+{
+    const moe_ctx *c = l->ctx;
+    const moe_layer_config_t &cf = l->cfg;
+    const int window = MF_MAX_PAIRS / cf.top_k, n_cu = n_cu_of(c);
+    const int row_blocks = (cf.hidden + TL_ROWS - 1) / TL_ROWS, row_blocks13 = (2 * cf.ffn + TL_ROWS - 1) / TL_ROWS;
+    const int steps = (cf.ffn / 64 + TL_SG - 1) / TL_SG, steps13 = (cf.hidden / 64 + TL_SG - 1) / TL_SG;
+    const uint64_t extra_rows = c->ypart_extra_floats / cf.hidden, pairs = (uint64_t)batch * cf.top_k;
+    const int max_parts = (int)std::min<uint64_t>(255, std::max<uint64_t>(1, extra_rows / pairs));
+    const double two_level = cf.scale_group > 0 ? 1.0 : 0.0;
+    double us = 17.0 + 0.037 * batch;
+    p.win.clear();
+    for (int w0 = 0; w0 < batch; w0 += window) {
+        const int mine = (std::min(batch, w0 + window) - w0) * cf.top_k;
+        const bool small = mine <= (cf.top_k == cf.n_experts ? 16 : STREAM_SMALL_AVERAGE) * cf.n_experts;
+        int entries = 0;
+        for (int e = 0; e < cf.n_experts; ++e) entries += (nominal_count(l, mine, e) + 31) / 32;
+        // at least four: the experts that arrive during a step are multiplied one launch each, and with fewer
+        // parts such a launch leaves most of the chip idle on the step's critical path
+        const int want = std::max(4, (2 * n_cu + entries * row_blocks - 1) / std::max(1, entries * row_blocks));
+        p.win.push_back({std::min(want, max_parts), small});
+        auto half = [&](int rb, int n_steps, int parts) {
+            parts = std::min(parts, n_steps);
+            const int part_steps = (n_steps + parts - 1) / parts, k_parts = (n_steps + part_steps - 1) / part_steps;
+            const double k = part_steps * TL_SG * 64 / 4096.0, x = (double)entries * rb * k_parts / (2 * n_cu);
+            return small ? k * (x * (31.0 + 5.0 * two_level) + 5.0) : k * (x * (33.0 + 8.0 * two_level) + 21.0);
+        };
+        us += 17.0 + half(row_blocks13, steps13, 1) + half(row_blocks, steps, p.win.back().parts);
+    }
+    return us;
+}
+
+// What the step takes with the tile kernels in us, after plan_tile.
+//
+// 4-bit group-64 layers have two families of kernels for a batch, and which one is faster turns on more than the tokens:
+// the tile kernels read an expert's weights once for up to 192 tokens, but a block of the large one costs 65, 98 or 131 us
+// per 4096 columns (up to 64, 128 or 192 tokens) and there is one to a compute unit, so a round that is not full is paid in
+// whole; the 16-token kernels read them again for every 32 tokens, 37 us per round of the same work, and start again
+// for every window.  So the step's time is estimated for both, constants fitted to 548 measured steps
+// (hidden 256 to 4096, ffn 512 to 14336, 1 to 16 experts, 16 to 700 tokens, both metadata levels; standard deviation 6 %).
+static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
+{
+    const BlobLayout &b = l->lay;
+    const int n_cu = n_cu_of(l->ctx), pairs = batch * l->cfg.top_k;
+    const bool big = p.mode == TE_BIG;
+    const int rows = big ? 256 : 128, slots = n_cu * (big ? 1 : 2);
+    const double two_level = b.scale_group > 0 ? 1.0 : 0.0;
+    int blocks = 0, halves = 0;                  // token blocks; token tiles of a block's fuller half, added up over them
+    for (int e = 0; e < l->cfg.n_experts; ++e) {
+        const int count = nominal_count(l, pairs, e);
+        if (!count) continue;
+        const int tb = tile_blocks(b, count, p.mode), tiles = (count + 31) / 32;
+        blocks += tb;
+        halves += tb * (((tiles + tb - 1) / tb + 1) / 2);
+    }
+    double rounds = 0.0, x = 0.0;                // of blocks, the last one whole or by its share, times their columns / 4096
+    auto half = [&](int n_rows, int cols, int parts) {
+        const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
+        const int items = (n_rows + rows - 1) / rows * blocks * k_parts;
+        const double k = part_sets * 256 / 4096.0;
+        rounds += (items + slots - 1) / slots * k;
+        x += (double)items / slots * k;
+    };
+    half(2 * b.ffn, b.hidden, 1);
+    half(b.hidden, b.ffn, p.parts);
+    const double tiles = (double)halves / blocks;
+    return big ? 40.0 + rounds * (33.0 + 26.0 * tiles + 4.5 * two_level) + x * (24.0 - 7.6 * tiles) + 0.057 * batch
+               : 41.0 + rounds * (11.0 + 3.5 * two_level) + x * 28.0 + 0.05 * batch;
+}
+
+// Whether the tile kernels may run a step.  Times of a step in us, everything resident, GEMV kernels / tile kernels.
+//
+// Formats without 16-token kernels: more than one token of an expert on average (4096 x 14336, 3-bit: 6 tokens 202 / 163, 8
+// tokens 214 / 174; 2-bit 216 / 172; 2-bit two-level, 8 tokens 251 / 247), or a row that fills at most half of the GEMV kernels' lanes,
+// a quarter with two-level 2-bit codes (4 tokens, 1024 x 4096, 3-bit 44 / 30, 4-bit group 128 34 / 29; 320 x 8384, 13 experts 59 / 29;
+// rows twice as long, 2048 x 12032: 3-bit 86 / 74, 2-bit 73 / 76, two-level 95 / 100).  In the smallest layers the two are within
+// 10 % of each other (256 x 512), so there it takes the three tokens of an expert at which a step's time no longer
+// counts in launches alone.
+//
+// 4-bit group 64: beside the 16-token kernels' steps.  Layers of middle size are faster on the tile kernels at any batch
+// (16-token / tile kernels: 1024 x 4096, 16 tokens 37 / 32, 64 tokens 46 / 37; 4096 x 1792 46 / 42 and 59 / 49; two-level 40 / 34 and 49 / 38), larger ones only
+// where the 16-token kernels need tiles of 32 (16 tokens: 2048 x 5056 50 / 49, 2048 x 7168 60 / 62, 4096 x 14336 148 / 167; 64 tokens: 2048 x 7168
+// 78 / 74, 1024 x 16384 88 / 87, 4096 x 14336 205 / 210), the smallest gain little (512 x 1024 23 / 22).  Elsewhere with more than 32 (two-level: 16) tokens of an expert on average, if the estimates say so.
+static bool tile_may(const moe_layer *l, int batch, bool stream, bool *surely)
+{
+    const moe_layer_config_t &cf = l->cfg;
+    const int pairs = batch * cf.top_k;
+    const int64_t size = (int64_t)cf.hidden * cf.ffn;
+    *surely = true;
+    if (stream) {
+        const bool two_tiles = pairs > STREAM_SMALL_AVERAGE * cf.n_experts;
+        if (size > TILE_MIDDLE_LOW && size <= (two_tiles ? TILE_TWO_TILES_HIGH : TILE_MIDDLE_HIGH) && pairs <= TILE_MODE32_AVERAGE * cf.n_experts) return true;
+        *surely = false;
+        return pairs > (cf.scale_group ? 16 : 32) * cf.n_experts;
+    }
+    const bool g64 = cf.bits == 4 && cf.group == 64;         // with runs of metadata that the 16-token kernels do not take
+    if (pairs > (g64 ? 8 : 3) * cf.n_experts) return true;
+    if (size <= (g64 ? 1 << 20 : 1 << 17)) return false;
+    const int fmt = fmt_of(l->lay);
+    return pairs > cf.n_experts || cf.hidden / codes_per_chunk(fmt) <= (fmt == 28 ? 16 : 32);
+}
+
+static BatchPlan plan_batch(const moe_layer *l, int batch)
+{
+    BatchPlan p;
+    const moe_ctx *c = l->ctx;
+    const moe_layer_config_t &cf = l->cfg;
+    if (batch < c->mfma_min_batch) return p;
+    const bool g64 = cf.bits == 4 && cf.group == 64;
+    // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
+    auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
+    const bool stream = g64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2);
+    bool surely = false;
+    const bool may = tile_may(l, batch, stream, &surely);
+    const bool tile = (c->mfma_form == 6 || (c->mfma_form == 0 && may)) && tile_format(l);
+    if (tile) plan_tile(l, batch, p);
+    double stream_us = 0.0;
+    const bool chosen = tile && (surely || !stream || c->mfma_form == 6);
+    if (stream && !chosen) stream_us = plan_windows(l, batch, p);
+    if (chosen || (tile && tile_us(l, batch, p) < stream_us)) p.kind = BatchPlan::TILE;
+    else if (stream) p.kind = BatchPlan::STREAM;
+    return p;
+}
+
 // Streaming matrix-core form: persistent blocks over (entry, 128-row block, K part) items.
-// An expert with more than 32 tokens becomes two entries (token tiles) that read the same weights.
-static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &experts, const float *w, int batch)
+// An expert with more tokens than a tile takes becomes several entries (token tiles) that read the same weights.
+// w: the step's combine weights; null: nobody has seen the routing yet, the kernels find it in device memory (batches of one
+// window, the default form).
+static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &experts, const float *w, int batch, const BatchPlan &plan)
 {
     moe_ctx *c = l->ctx;
     const BlobLayout &b = l->lay;
@@ -1414,15 +1644,26 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
         const int w1 = std::min(batch, w0 + window);
         TileArgs A{};
         int n = 0, first = 0, n_distinct = 0;
-        for (const PassExpert &pe : experts) {
+        // Which kernels multiply a window (one or two token tiles of 16): the plan's choice.  The other forms have tiles of 32 only.
+        const bool small = plan.win.at(w0 / window).small;
+        const size_t tile_tokens = small && (c->mfma_form == 4 || c->mfma_form == 5 || c->mfma_form == 0) ? 16 : 32;
+        if (!w) {
+            A.pair_expert = c->pair_expert; A.pair_w = c->pair_w;
+            A.n_pairs = batch * K; A.n_experts = l->cfg.n_experts; A.top_k = K; A.tile_tokens = (int32_t)tile_tokens;
+            for (const PassExpert &pe : experts) A.table[pe.expert] = pe.blob;
+            const int own = std::min(l->cfg.n_experts, batch * K);
+            n = own + (batch * K - own) / (int)tile_tokens;          // the most entries there can be
+            first = batch * K;
+            n_distinct = own;
+        } else for (const PassExpert &pe : experts) {
             std::vector<int> mine;
             for (int q : pe.pairs)
                 if (q / K >= w0 && q / K < w1) mine.push_back(q);
             if (mine.empty()) continue;
             ++n_distinct;
-            for (size_t t0 = 0; t0 < mine.size(); t0 += 32) {
+            for (size_t t0 = 0; t0 < mine.size(); t0 += tile_tokens) {
                 if (n >= 32) return fail(MOE_EINVAL, "more than 32 (expert, token tile) entries in one launch");
-                const size_t t1 = std::min(mine.size(), t0 + 32);
+                const size_t t1 = std::min(mine.size(), t0 + tile_tokens);
                 A.e[n].blob = pe.blob;
                 A.e[n].n_tok = (int32_t)(t1 - t0);
                 A.e[n].first = first;
@@ -1442,9 +1683,8 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
             A.row_blocks = (rows + TL_ROWS - 1) / TL_ROWS;
             int parts = 1;
             if (may_split) {
-                // the step fixed the number of parts per window from its routing alone; the rows for the parts'
-                // partial sums were budgeted there, the check below only guards the buffer
-                parts = std::min(n_seg, std::max<int>(1, c->w2_parts.at(w0 / window)));
+                // the rows for the parts' partial sums were budgeted by the plan, the check below only guards the buffer
+                parts = std::min(n_seg, std::max<int>(1, plan.win.at(w0 / window).parts));
                 const uint64_t left = (c->ypart_extra_floats - c->ypart_extra_used) / ((uint64_t)first * b.hidden);
                 if (parts > 1 && (uint64_t)parts > left) parts = 1;
             }
@@ -1461,10 +1701,6 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
         A.act = c->h_buf + (size_t)w0 * b.hidden;
         const bool meta8 = b.scale_group > 0;
         const bool r1 = (c->mfma_form == 3 || c->mfma_form == 0) && !meta8 && !l->wide_meta.load(std::memory_order_relaxed);
-        // Which kernels multiply a window (one or two token tiles of 16) is decided from the window's routing, never from
-        // the experts that happen to share a launch: they add in different orders, and a token's result must not depend
-        // on what the cache held.
-        const bool small = c->win_small.at(w0 / window) != 0;
         // (the 16-token kernels address a matrix with 32-bit offsets)
         const bool fits32 = 2ull * b.ffn * b.m13.row_stride < (1ull << 31) && (uint64_t)b.hidden * b.m2.row_stride < (1ull << 31);
         const bool t16 = (c->mfma_form == 4 || c->mfma_form == 5 || c->mfma_form == 0) && !meta8 && fits32;
@@ -1512,163 +1748,6 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
 
 // ---- tile kernels ----
 
-// Codes per sum of activations: the groups of the zero-point term.
-static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
-static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
-
-// The power of two that two-level 2-bit scales are multiplied with: the layer's largest just below 32000, so that its product
-// with a code (at most 2 in size, centred) is an fp16 number.
-static float tile_lift(const moe_layer *l)
-{
-    const float top = bits_to_float(l->scale_top.load(std::memory_order_relaxed));
-    if (l->lay.bits != 2 || !l->lay.scale_group || !(top > 0.f) || !std::isfinite(top)) return 1.f;
-    int e;
-    std::frexp(32000.f / top, &e);                   // 2^(e-1) <= 32000 / top
-    return std::ldexp(1.f, std::min(e - 1, 100));
-}
-
-// 2-bit codes enter the matrix cores multiplied with their scale in fp16, so a layer whose scales fp16 does not hold stays on the
-// GEMV kernels.  Above: one-level 32000, two-level 500.  Below: fp16 numbers are subnormal from 2^-14 on, whose products the
-// matrix cores add with about 2^-40 of error (w2's scales of 2^-22: y 7e-6 off, GEMV exact), and a two-level scale's second
-// half carries all of its bits as long as the scale, lifted, is 2^-2 or more.  What counts is a row's largest scale: beside
-// it the error of a smaller one is below fp32's.
-static bool tile_format(const moe_layer *l)
-{
-    const BlobLayout &b = l->lay;
-    if (b.bits == 2) {
-        const float top = bits_to_float(l->scale_top.load(std::memory_order_relaxed)), low = bits_to_float(l->scale_row_low.load(std::memory_order_relaxed));
-        if (!(top <= (b.scale_group ? 500.f : 32000.f)) || low * tile_lift(l) < (b.scale_group ? 0.25f : 0x1p-14f)) return false;
-    }
-    const bool fits32 = 2ull * b.ffn * b.m13.row_stride < (1ull << 31) && (uint64_t)b.hidden * b.m2.row_stride < (1ull << 31);
-    return fits32 && (b.bits != 4 || b.group >= 64);
-}
-
-constexpr int TE_SMALL_TOKENS = 32;
-// token blocks of an expert: one tile of 16 or 32, or up to as many tiles of 32 per block as the kernel holds
-static int tile_blocks(const BlobLayout &b, int count, int mode)
-{
-    if (mode != TE_BIG) return (count + mode - 1) / mode;
-    const int per = (b.bits == 2 && b.scale_group ? TeCfg<28, TE_BIG>::TOK : TeCfg<4, TE_BIG>::TOK) / 32;
-    return ((count + 31) / 32 + per - 1) / per;
-}
-
-// The step's pairs per expert, where they lie in the sorted list, which kernel runs and into how many parts w2 splits
-// its contraction -- all from the routing alone, so that a result does not depend on which experts share a launch.
-static void tile_plan(moe_layer *l, const int32_t *idx, int batch)
-{
-    moe_ctx *c = l->ctx;
-    const BlobLayout &b = l->lay;
-    const int E = l->cfg.n_experts, pairs = batch * l->cfg.top_k;
-    int32_t *cnt = c->tile_count;
-    for (int e = 0; e < E; ++e) cnt[e] = 0;
-    for (int q = 0; q < pairs; ++q) cnt[idx[q]]++;
-    int first = 0, blocks = 0, most = 0;
-    for (int e = 0; e < E; ++e) { c->tile_first[e] = first; first += cnt[e]; most = std::max(most, cnt[e]); }
-    c->tile_most = most;
-    c->tile_mode = most > TE_SMALL_TOKENS ? TE_BIG : (most > 16 ? 32 : 16);
-    for (int e = 0; e < E; ++e) blocks += tile_blocks(b, cnt[e], c->tile_mode);
-    const int n_cu = c->n_cu > 0 ? c->n_cu : 256, rows = c->tile_mode == TE_BIG ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
-    const int sets = (b.ffn / 64 + 3) / 4;
-    const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
-    // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
-    // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
-    // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
-    // 226 + 14 (4).
-    const int slots = n_cu * (c->tile_mode == TE_BIG ? 1 : 2);
-    double best = 0.0;
-    c->tile_parts = 1;
-    for (int p = 1; p <= std::min(std::min(8, sets), cap); ++p) {
-        const int items = rb * blocks * p, rounds = (items + slots - 1) / slots;
-        const double eff = (double)items / ((double)rounds * slots) / (1.0 + 0.03 * p);
-        if (eff > best) { best = eff; c->tile_parts = p; }
-    }
-}
-
-// The 16-token (streaming) kernels' windows: how many parts the w2 launches of a window split their contraction into,
-// and whether one tile of 16 tokens holds every expert's share of it.
-//
-// The number of parts decides the order in which a pair's partial sums are added, so it must not depend on how the step's
-// experts happen to be grouped into launches (which follows from what is cached, in which buffers): it is fixed here from
-// the routing alone, as if all needed experts of the window ran in one launch -- one part per block that would idle then --
-// within the rows the partial sums have.  A step's result is then the same whatever the cache held.
-//
-// Returns what the step takes with them in us (tile_us: why, and where the numbers come from).
-static double plan_windows(moe_layer *l, const int32_t *idx, int batch)
-{
-    moe_ctx *c = l->ctx;
-    const moe_layer_config_t &cf = l->cfg;
-    const int window = MF_MAX_PAIRS / cf.top_k, n_cu = c->n_cu > 0 ? c->n_cu : 256;
-    const int row_blocks = (cf.hidden + TL_ROWS - 1) / TL_ROWS, row_blocks13 = (2 * cf.ffn + TL_ROWS - 1) / TL_ROWS;
-    const int steps = (cf.ffn / 64 + TL_SG - 1) / TL_SG, steps13 = (cf.hidden / 64 + TL_SG - 1) / TL_SG;
-    const uint64_t extra_rows = c->ypart_extra_floats / cf.hidden, pairs = (uint64_t)batch * cf.top_k;
-    const int max_parts = (int)std::min<uint64_t>(255, std::max<uint64_t>(1, extra_rows / pairs));
-    const double two_level = cf.scale_group > 0 ? 1.0 : 0.0;
-    double us = 17.0 + 0.037 * batch;
-    c->w2_parts.clear();
-    c->win_small.clear();
-    for (int w0 = 0; w0 < batch; w0 += window) {
-        const int w1 = std::min(batch, w0 + window);
-        int count[MOE_MAX_EXPERTS] = {0}, entries = 0;
-        for (int q = w0 * cf.top_k; q < w1 * cf.top_k; ++q) count[idx[q]]++;
-        int most = 0;
-        for (int e = 0; e < cf.n_experts; ++e) { entries += (count[e] + 31) / 32; most = std::max(most, count[e]); }
-        const bool small = most <= 16;
-        c->win_small.push_back(small);
-        // at least four: the experts that arrive during a step are multiplied one launch each, and with fewer
-        // parts such a launch leaves most of the chip idle on the step's critical path
-        const int want = std::max(4, (2 * n_cu + entries * row_blocks - 1) / std::max(1, entries * row_blocks));
-        c->w2_parts.push_back(std::min(want, max_parts));
-        auto half = [&](int rb, int n_steps, int parts) {
-            parts = std::min(parts, n_steps);
-            const int part_steps = (n_steps + parts - 1) / parts, k_parts = (n_steps + part_steps - 1) / part_steps;
-            const double k = part_steps * TL_SG * 64 / 4096.0, x = (double)entries * rb * k_parts / (2 * n_cu);
-            return small ? k * (x * (31.0 + 5.0 * two_level) + 5.0) : k * (x * (33.0 + 8.0 * two_level) + 21.0);
-        };
-        us += 17.0 + half(row_blocks13, steps13, 1) + half(row_blocks, steps, c->w2_parts.back());
-    }
-    return us;
-}
-
-// What the step takes with the tile kernels in us, after tile_plan.
-//
-// 4-bit group-64 layers have two families of kernels for a batch, and which one is faster turns on more than the tokens:
-// the tile kernels read an expert's weights once for up to 192 tokens, but a block of the large one costs 65, 98 or 131 us
-// per 4096 columns (up to 64, 128 or 192 tokens) and there is one to a compute unit, so a round that is not full is paid in
-// whole; the 16-token kernels read them again for every 32 tokens, 37 us per round of the same work, and start again
-// for every window.  So the step's time is estimated for both from the routing, constants fitted to 548 measured steps
-// (hidden 256 to 4096, ffn 512 to 14336, 1 to 16 experts, 16 to 700 tokens, both metadata levels; standard deviation 6 %).  Of
-// the 442 steps among them that may take the tile kernels the estimates give 17 to the slower kernels by more than 2 %, at most
-// by 12 %; the tile kernels for all of them lost on 137, up to 40 % (Mixtral-shaped, 96 tokens: 425 us, 16-token kernels 261).
-static double tile_us(const moe_layer *l, int batch)
-{
-    const moe_ctx *c = l->ctx;
-    const BlobLayout &b = l->lay;
-    const int n_cu = c->n_cu > 0 ? c->n_cu : 256;
-    const bool big = c->tile_mode == TE_BIG;
-    const int rows = big ? 256 : 128, slots = n_cu * (big ? 1 : 2);
-    const double two_level = b.scale_group > 0 ? 1.0 : 0.0;
-    int blocks = 0, halves = 0;                  // token blocks; token tiles of a block's fuller half, added up over them
-    for (int e = 0; e < l->cfg.n_experts; ++e) {
-        if (!c->tile_count[e]) continue;
-        const int tb = tile_blocks(b, c->tile_count[e], c->tile_mode), tiles = (c->tile_count[e] + 31) / 32;
-        blocks += tb;
-        halves += tb * (((tiles + tb - 1) / tb + 1) / 2);
-    }
-    double rounds = 0.0, x = 0.0;                // of blocks, the last one whole or by its share, times their columns / 4096
-    auto half = [&](int n_rows, int cols, int parts) {
-        const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
-        const int items = (n_rows + rows - 1) / rows * blocks * k_parts;
-        const double k = part_sets * 256 / 4096.0;
-        rounds += (items + slots - 1) / slots * k;
-        x += (double)items / slots * k;
-    };
-    half(2 * b.ffn, b.hidden, 1);
-    half(b.hidden, b.ffn, c->tile_parts);
-    const double tiles = (double)halves / blocks;
-    return big ? 40.0 + rounds * (33.0 + 26.0 * tiles + 4.5 * two_level) + x * (24.0 - 7.6 * tiles) + 0.057 * batch
-               : 41.0 + rounds * (11.0 + 3.5 * two_level) + x * 28.0 + 0.05 * batch;
-}
-
 template <int FMT, bool W13, int MODE>
 static int32_t launch_tile_mode(moe_ctx *c, int grid, uint64_t bytes, const TeArgs &A)
 {
@@ -1703,22 +1782,31 @@ static int32_t launch_tile_half(moe_layer *l, int mode, int grid, uint64_t bytes
     }
 }
 
-static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts, int batch)
+// idx: the step's routing, for a grid that fits it; null: nobody has seen it yet, the grid covers the most token blocks there can be.
+static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts, const int32_t *idx, int batch, const BatchPlan &plan)
 {
     moe_ctx *c = l->ctx;
     const BlobLayout &b = l->lay;
-    const int K = l->cfg.top_k, xg = tile_sum_group(b);
+    const int K = l->cfg.top_k, E = l->cfg.n_experts, pairs = batch * K, xg = tile_sum_group(b);
     TeArgs A{};
-    for (const PassExpert &pe : experts) {
-        TileExpert &te = A.e[A.n_exp++];
-        te.blob = pe.blob;
-        te.first = c->tile_first[pe.expert];
-        te.count = c->tile_count[pe.expert];
+    for (const PassExpert &pe : experts) { A.blob[pe.expert] = pe.blob; A.experts |= 1u << pe.expert; }
+    const int mode = plan.mode, rows = mode == TE_BIG ? 256 : 128;
+    int token_blocks = 0;
+    if (idx) {
+        int count[MOE_MAX_EXPERTS] = {0};
+        for (int q = 0; q < pairs; ++q) count[idx[q]]++;
+        for (const PassExpert &pe : experts) token_blocks += tile_blocks(b, count[pe.expert], mode);
+    } else {
+        // every expert's first token opens a block, and from then on it takes a block's worth of further ones to open another
+        const int own = std::min(E, pairs), per = mode == TE_BIG ? (tile_blocks(b, 192, mode) == 1 ? 192 : 128) : mode;
+        token_blocks = K == E ? E * tile_blocks(b, batch, mode) : own + (pairs - own) / per;
     }
-    const int mode = c->tile_mode, rows = mode == TE_BIG ? 256 : 128;
+    A.n_pairs = pairs; A.n_experts = E;
+    if (pairs <= FEW_PAIRS) A.pair_expert = c->pair_expert;
+    A.first = c->pair_first;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
     A.lift = tile_lift(l); A.lower = 1.f / A.lift;
-    A.top_k = K; A.part_base = batch * K;
+    A.top_k = K; A.part_base = pairs;
     A.unit_shift = b.group == 128 ? 1 : 0;
     auto matrix = [&](const MatLayout &m, int Kdim, int N) {
         A.K = Kdim; A.N = N;
@@ -1732,37 +1820,32 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
         A.units_per_part = sp * 4;
         A.k_parts = (sets + sp - 1) / sp;
         A.jobs = row_blocks * A.k_parts;
-        const int per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
-        int items = 0;
-        for (int i = 0; i < A.n_exp; ++i) {
-            A.e[i].tb = tile_blocks(b, A.e[i].count, mode);
-            A.e[i].item0 = items;
-            items += per_xcd * A.e[i].tb;
-        }
-        return items * TE_XCD;
+        A.per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
+        return A.per_xcd * token_blocks * TE_XCD;
     };
+    const uint64_t n_exp = experts.size();
     matrix(b.m13, b.hidden, b.ffn);
     A.mat_off = b.off_w13;
     A.act = c->h_buf; A.act_bytes = (uint32_t)batch * b.hidden * 2;
     A.xs = c->xs_h; A.xs_bytes = (uint32_t)batch * A.xs_stride * 8;
     A.xs_out = c->xs_a; A.xs_out_stride = tile_sum_stride(b.ffn, xg);
-    int32_t rc = launch_tile_half<true>(l, mode, shape((2 * b.ffn + rows - 1) / rows, 1), (uint64_t)A.n_exp * 2 * b.ffn * b.m13.row_stride, A);
+    int32_t rc = launch_tile_half<true>(l, mode, shape((2 * b.ffn + rows - 1) / rows, 1), n_exp * 2 * b.ffn * b.m13.row_stride, A);
     if (rc) return rc;
     matrix(b.m2, b.ffn, b.hidden);
     A.mat_off = b.off_w2;
-    A.act = c->a_buf; A.act_bytes = (uint32_t)batch * K * b.ffn * 2;
-    A.xs = c->xs_a; A.xs_bytes = (uint32_t)batch * K * A.xs_stride * 8;
-    return launch_tile_half<false>(l, mode, shape((b.hidden + rows - 1) / rows, c->tile_parts), (uint64_t)A.n_exp * b.hidden * b.m2.row_stride, A);
+    A.act = c->a_buf; A.act_bytes = (uint32_t)pairs * b.ffn * 2;
+    A.xs = c->xs_a; A.xs_bytes = (uint32_t)pairs * A.xs_stride * 8;
+    return launch_tile_half<false>(l, mode, shape((b.hidden + rows - 1) / rows, plan.parts), n_exp * b.hidden * b.m2.row_stride, A);
 }
 
-static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts, const float *w, int batch, bool use_tile)
+static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts, const int32_t *idx, const float *w, int batch, const BatchPlan &plan)
 {
     moe_ctx *c = l->ctx;
     const BlobLayout &b = l->lay;
     const int K = l->cfg.top_k;
     // the row-staging form takes up to 64 tokens per expert, indexes pairs with one byte and reads fp16 pairs only
-    if (use_tile) return launch_tile(l, experts, batch);
-    if (c->mfma_form != 1 || batch > 64 || batch * K > MF_MAX_PAIRS || b.scale_group > 0) return launch_mfma_stream(l, experts, w, batch);
+    if (plan.kind == BatchPlan::TILE) return launch_tile(l, experts, idx, batch, plan);
+    if (c->mfma_form != 1 || batch > 64 || batch * K > MF_MAX_PAIRS || b.scale_group > 0) return launch_mfma_stream(l, experts, w, batch, plan);
     MfmaArgs A{};
     int n = 0, first = 0, max_tok = 0;
     for (const PassExpert &pe : experts) {
@@ -1807,15 +1890,15 @@ static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts,
 }
 
 static int32_t launch_ffn(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only = false,
-                          const uint8_t *const *table = nullptr)
+                          const uint8_t *const *table = nullptr, int routed = 0)
 {
     switch (fmt_of(l->lay)) {
-    case 4: return launch_ffn_fmt<4>(l, entries, nt, w13_only, table);
-    case 3: return launch_ffn_fmt<3>(l, entries, nt, w13_only, table);
-    case 2: return launch_ffn_fmt<2>(l, entries, nt, w13_only, table);
-    case 48: return launch_ffn_fmt<48>(l, entries, nt, w13_only, table);
-    case 38: return launch_ffn_fmt<38>(l, entries, nt, w13_only, table);
-    case 28: return launch_ffn_fmt<28>(l, entries, nt, w13_only, table);
+    case 4: return launch_ffn_fmt<4>(l, entries, nt, w13_only, table, routed);
+    case 3: return launch_ffn_fmt<3>(l, entries, nt, w13_only, table, routed);
+    case 2: return launch_ffn_fmt<2>(l, entries, nt, w13_only, table, routed);
+    case 48: return launch_ffn_fmt<48>(l, entries, nt, w13_only, table, routed);
+    case 38: return launch_ffn_fmt<38>(l, entries, nt, w13_only, table, routed);
+    case 28: return launch_ffn_fmt<28>(l, entries, nt, w13_only, table, routed);
     default: return fail(MOE_EINVAL, "unsupported bit width %d", l->lay.bits);
     }
 }
@@ -1843,7 +1926,14 @@ static int32_t fold_pending(moe_ctx *c)
     for (const moe_ctx::PendingStep &p : c->pending) {
         moe_layer *l = p.layer;
         const int32_t *idx = c->route_log + (size_t)p.slot * MOE_MAX_TOPK;
-        needed.assign(idx, idx + l->cfg.top_k);
+        if (p.batch) {
+            needed.clear();
+            for (int e = 0; e < 32; ++e)
+                if ((uint32_t)idx[0] >> e & 1u) needed.push_back(e);
+            if (needed.empty()) needed.push_back(-1);
+        } else {
+            needed.assign(idx, idx + l->cfg.top_k);
+        }
         std::sort(needed.begin(), needed.end());
         needed.erase(std::unique(needed.begin(), needed.end()), needed.end());
         if (needed.front() < 0 || needed.back() >= l->cfg.n_experts) { c->pending.clear(); return fail(MOE_ESTATE, "device-routed step logged expert %d", needed.front() < 0 ? needed.front() : needed.back()); }
@@ -1901,7 +1991,7 @@ static int32_t device_routed_step(moe_layer *l, const uint16_t *x_in, uint16_t *
     ga.route_idx = c->route_idx; ga.route_w = c->route_w; ga.route_log = c->route_log_dev + (size_t)slot * MOE_MAX_TOPK;
     int32_t rc = launch_timed(c, PROF_GATE, 0, k_gate<false>, dim3(1), dim3(GATE_THREADS), 0, ga);
     if (rc) return rc;
-    c->pending.push_back({l, slot});
+    c->pending.push_back({l, slot, false});
     l->steps_device_routed++;
 
     const uint8_t *table[16];
@@ -1924,6 +2014,95 @@ static int32_t device_routed_step(moe_layer *l, const uint16_t *x_in, uint16_t *
     return rc;
 }
 
+// The tile kernels' sorted list, for steps of more pairs than they look through themselves.
+static int32_t launch_sort(moe_ctx *c, int pairs)
+{
+    if (pairs <= FEW_PAIRS) return MOE_OK;
+    hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, pairs, c->plist, c->pair_first);
+    HIPCHK(hipGetLastError());
+    return MOE_OK;
+}
+
+static void tile_gate_args(const moe_layer *l, GateArgs &ga)
+{
+    const moe_ctx *c = l->ctx;
+    ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
+    ga.xs = c->xs_h; ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(l->cfg.hidden, ga.xs_group);
+}
+
+// S7: the pairs' rows added per token in a fixed order, then the residual
+static int32_t launch_combine(moe_layer *l, const uint16_t *x_in, uint16_t *x_out, int batch, int32_t *log)
+{
+    moe_ctx *c = l->ctx;
+    const moe_layer_config_t &cf = l->cfg;
+    const uint64_t cap_rows = ((uint64_t)batch * cf.top_k * cf.hidden + c->ypart_extra_floats) / cf.hidden;
+    hipLaunchKernelGGL(k_combine, dim3((cf.hidden / 4 + 255) / 256, batch), dim3(256), 0, c->compute, x_in, c->ypart, c->ytab, c->yacc,
+                       x_out, cf.hidden, cf.top_k, (uint32_t)cap_rows, c->pair_expert, log);
+    HIPCHK(hipGetLastError());
+    return MOE_OK;
+}
+
+// Several tokens through a layer whose experts are all on the device: nothing the host would decide depends on the routing, so
+// gate, w1/w3, w2 and the sum are enqueued back to back, the kernels reading the routing from device memory.
+// Waiting for the gate costs a step about 15 us, all of it for a small layer (512 x 1024, 3 tokens: 28.7 us a step before).
+static bool device_routed_batch_fits(moe_layer *l, const moe_layer *next, int32_t batch, const moe_step_trace_t *trace, bool spec)
+{
+    moe_ctx *c = l->ctx;
+    if (!c->device_routing || batch <= 1 || trace || c->gate_out->ffn_error) return false;
+    return all_resident(l) && (!spec || all_resident(next));
+}
+
+// Tokens per entry of such a step's GEMV kernels (0: it takes the waiting path).
+static int routed_nt(const moe_layer *l, int batch)
+{
+    const int pairs = batch * l->cfg.top_k, most = max_tokens_per_entry(l->cfg.hidden, fmt_of(l->lay));
+    return most < 2 ? 0 : (batch == 2 || pairs <= l->cfg.n_experts ? 2 : most);
+}
+
+static bool device_routed_plan_fits(const moe_layer *l, int batch, const BatchPlan &p)
+{
+    const moe_ctx *c = l->ctx;
+    const int pairs = batch * l->cfg.top_k;
+    if (p.kind == BatchPlan::TILE) return true;
+    // one window; the other forms and matrices the 16-token kernels do not address find no routing in device memory
+    const bool fits32 = 2ull * l->lay.ffn * l->lay.m13.row_stride < (1ull << 31) && (uint64_t)l->lay.hidden * l->lay.m2.row_stride < (1ull << 31);
+    if (p.kind == BatchPlan::STREAM) return (c->mfma_form == 0 || c->mfma_form == 5) && p.win.size() == 1 && fits32;
+    // GEMV kernels: a block for every entry there can be, so a few dozen pairs at most
+    return pairs <= 64 && routed_nt(l, batch) > 0 && chunks_per_lane(l->lay.hidden, fmt_of(l->lay)) > 0 &&
+           (l->lay.ffn / codes_per_chunk(fmt_of(l->lay)) + 63) / 64 <= 8;
+}
+
+static int32_t device_routed_batch(moe_layer *l, const uint16_t *x_in, int32_t batch, uint16_t *x_out, uint16_t *h_out, const BatchPlan &p)
+{
+    moe_ctx *c = l->ctx;
+    const moe_layer_config_t &cf = l->cfg;
+    const int pairs = batch * cf.top_k;
+    if (c->pending.size() >= moe_ctx::ROUTE_LOG) { int32_t rc = fold_pending(c); if (rc) return rc; }
+    uint32_t slot = c->pending.empty() ? 0 : (c->pending.back().slot + 1) % moe_ctx::ROUTE_LOG;
+    GateArgs ga{};
+    ga.x = x_in; ga.wg = l->gate_w_dev; ga.gamma = l->gamma_dev; ga.h_out = c->h_buf; ga.h_out2 = h_out; ga.out = c->gate_out_dev;
+    ga.eps = (double)cf.rms_eps; ga.H = cf.hidden; ga.E = cf.n_experts; ga.K = cf.top_k;
+    if (p.kind == BatchPlan::TILE) tile_gate_args(l, ga);
+    ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w; ga.quiet = 1;
+    int32_t rc = launch_gate(c, ga, batch);
+    if (rc) return rc;
+    if (p.kind == BatchPlan::TILE) { rc = launch_sort(c, pairs); if (rc) return rc; }
+    c->pending.push_back({l, slot, true});
+    l->steps_device_routed++;
+    c->ypart_extra_used = 0;
+    std::vector<PassExpert> all(cf.n_experts);
+    const uint8_t *table[16];
+    for (int e = 0; e < 16; ++e) {
+        table[e] = c->bufs[l->cache.slot_buf[l->cache.find(e < cf.n_experts ? e : 0)]].ptr;
+        if (e < cf.n_experts) { all[e].blob = table[e]; all[e].expert = e; }
+    }
+    rc = p.kind == BatchPlan::TILE ? launch_tile(l, all, nullptr, batch, p)
+       : p.kind == BatchPlan::STREAM ? launch_mfma_stream(l, all, nullptr, batch, p)
+       : launch_ffn(l, {}, routed_nt(l, batch), false, table, pairs);
+    if (rc) return rc;
+    return launch_combine(l, x_in, x_out, batch, c->route_log_dev + (size_t)slot * MOE_MAX_TOPK);
+}
+
 // One decode step of one layer.  plain: the variant for callers that cannot allocate -- the host waits for the gate
 // (no selection log in the arena) and the one-launch kernel with its barrier flags in the arena is not used.
 static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, int32_t batch, uint16_t *x_out, uint16_t *h_out,
@@ -1941,6 +2120,10 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     l->stepped = true;
     if (spec) next->stepped = true;
     if (!plain && device_routed_step_fits(l, next, batch, trace, spec)) return device_routed_step(l, x_in, x_out, h_out);
+    if (!plain && device_routed_batch_fits(l, next, batch, trace, spec)) {
+        const BatchPlan p = plan_batch(l, batch);
+        if (device_routed_plan_fits(l, batch, p)) return device_routed_batch(l, x_in, batch, x_out, h_out, p);
+    }
     rc = fold_pending(c);
     if (rc) return rc;
 
@@ -1948,40 +2131,13 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     ga.x = x_in; ga.wg = l->gate_w_dev; ga.wg2 = spec ? next->gate_w_dev : nullptr;
     ga.gamma = l->gamma_dev; ga.h_out = c->h_buf; ga.h_out2 = h_out; ga.out = c->gate_out_dev;
     ga.eps = (double)cf.rms_eps; ga.H = cf.hidden; ga.E = cf.n_experts; ga.E2 = spec ? next->cfg.n_experts : 0; ga.K = cf.top_k;
-    // Which kernels multiply turns on the routing (never on the cache), so the gate kernel prepares for the tile kernels
-    // wherever they may be chosen.  w1/w3 + w2 of a Mixtral-shaped layer in us: 4-bit group-64 layers have 16-token kernels
-    // as well (batch 16: 88 + 50, tile kernels 106 + 55; batch 64, an expert with 17 to 32 tokens: 129 + 71 and 131 + 65,
-    // with two-level metadata 156 + 89 and 155 + 83, at 512 x 1920 33 + 24 and 25 + 19), and above that many tokens the
-    // estimate of tile_us decides; other formats the GEMV kernels (2-bit, batch 16: 213 + 103, tile kernels 118 + 60;
-    // 3-bit, batch 4: 60 + 45 to 106 + 69, tile kernels 81 + 47).
-    const bool g64 = cf.bits == 4 && cf.group == 64;
-    // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
-    auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
-    const bool tiles16 = batch >= c->mfma_min_batch && g64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2);
-    const int tile_above = !g64 ? 2 : (cf.scale_group ? 16 : TE_SMALL_TOKENS);
-    // The gate kernel prepares only where an expert has enough tokens on average for the tile kernels to be likely; where it
-    // does not, they are not chosen.
-    const int tile_average = !g64 ? 3 : (cf.scale_group ? 8 : 16);
-    const bool likely = batch * cf.top_k > tile_average * cf.n_experts;
-    const bool tile_ready = batch >= c->mfma_min_batch && (c->mfma_form == 6 || (c->mfma_form == 0 && batch > tile_above && likely)) && tile_format(l);
-    if (tile_ready) {
-        ga.pair_expert = c->pair_expert; ga.pair_w = c->pair_w;
-        ga.xs = c->xs_h; ga.xs_group = tile_sum_group(l->lay); ga.xs_stride = tile_sum_stride(cf.hidden, ga.xs_group);
-    }
+    const BatchPlan bp = plan_batch(l, batch);
+    const bool use_tile = bp.kind == BatchPlan::TILE;
+    if (use_tile) tile_gate_args(l, ga);
     rc = launch_gate(c, ga, batch);
     if (rc) return rc;
 
-    // The sort runs under the host's work of this step, so it is queued as soon as it is known that its list will be read: at
-    // once where the average alone says so, else right behind the copy of the routing.
-    bool sorted = false;
-    auto sort_pairs = [&]() -> int32_t {
-        if (sorted) return MOE_OK;
-        sorted = true;
-        hipLaunchKernelGGL(k_sort_pairs, dim3(1), dim3(SORT_THREADS), 0, c->compute, c->pair_expert, batch * cf.top_k, c->plist);
-        HIPCHK(hipGetLastError());
-        return MOE_OK;
-    };
-    if (tile_ready && (c->mfma_form == 6 || (!tiles16 && batch * cf.top_k > tile_above * cf.n_experts))) { rc = sort_pairs(); if (rc) return rc; }
+    if (use_tile) { rc = launch_sort(c, batch * cf.top_k); if (rc) return rc; }      // runs under the host's work of this step
     const GateHostOut *go = c->gate_out;
     int32_t idx[MOE_MAX_BATCH * MOE_MAX_TOPK];
     float w[MOE_MAX_BATCH * MOE_MAX_TOPK];
@@ -1989,13 +2145,6 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
         idx[i] = go->idx[i];
         if (idx[i] < 0 || idx[i] >= cf.n_experts) return fail(MOE_EINVAL, "routing index %d out of range", idx[i]);
     }
-    if (tile_ready) tile_plan(l, idx, batch);
-    bool use_tile = tile_ready && (c->mfma_form == 6 || c->tile_most > tile_above);
-    if (tiles16 && !(use_tile && c->mfma_form == 6)) {
-        const double us = plan_windows(l, idx, batch);
-        use_tile = use_tile && tile_us(l, batch) < us;
-    }
-    if (use_tile) { rc = sort_pairs(); if (rc) return rc; }
     for (int i = 0; i < batch * cf.top_k; ++i) w[i] = go->w[i];
     double score[MOE_MAX_EXPERTS] = {0};
     if (spec)
@@ -2037,7 +2186,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
                            (int)plan.access.size() == cf.top_k && !plan.victim_needed;
     bool fused_done = false;
     bool spec_issued = false;          // the speculative copies went out early (prompt-sized batches, below)
-    const bool use_mfma = use_tile || tiles16;
+    const bool use_mfma = bp.kind != BatchPlan::GEMV;
     auto pass_expert = [&](int i) {
         PassExpert pe;
         pe.blob = c->bufs[plan.access[i].buf].ptr;
@@ -2053,7 +2202,7 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
         if (use_mfma) {
             std::vector<PassExpert> g;
             for (int i : set) g.push_back(pass_expert(i));
-            return launch_mfma(l, g, w, batch, use_tile);
+            return launch_mfma(l, g, idx, w, batch, bp);
         }
         std::vector<FfnEntry> entries;
         for (int i : set) {
@@ -2141,14 +2290,14 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
                 group.push_back(pass_expert(i));
             }
             if (!group.empty()) {
-                rc = launch_mfma(l, group, w, batch, use_tile);
+                rc = launch_mfma(l, group, idx, w, batch, bp);
                 if (rc) return rc;
             }
             for (int i : in_flight) {
                 PoolBuf &pb = c->bufs[plan.access[i].buf];
                 HIPCHK(hipStreamWaitEvent(c->compute, pb.ready, 0));
                 pb.pending = false;
-                rc = launch_mfma(l, std::vector<PassExpert>{pass_expert(i)}, w, batch, use_tile);
+                rc = launch_mfma(l, std::vector<PassExpert>{pass_expert(i)}, idx, w, batch, bp);
                 if (rc) return rc;
             }
             continue;
@@ -2196,10 +2345,8 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
         for (const CopyOp &op : plan.spec) { rc = issue_copy(c, next, op); if (rc) return rc; }
     }
     if (!fused_done) {      // S7: the pairs' rows added per token in a fixed order, then the residual
-        const uint64_t cap_rows = ((uint64_t)batch * cf.top_k * cf.hidden + c->ypart_extra_floats) / cf.hidden;
-        hipLaunchKernelGGL(k_combine, dim3((cf.hidden / 4 + 255) / 256, batch), dim3(256), 0, c->compute, x_in, c->ypart, c->ytab, c->yacc,
-                           x_out, cf.hidden, cf.top_k, (uint32_t)cap_rows);
-        HIPCHK(hipGetLastError());
+        rc = launch_combine(l, x_in, x_out, batch, nullptr);
+        if (rc) return rc;
     }
     return MOE_OK;
 }
