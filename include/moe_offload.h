@@ -307,10 +307,10 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                0: the general kernels also for one token;
  *   "mfma_min_batch" batches at least this large (default 3, from where on they are the faster ones on MI355X; 16
  *                is the benchmark definition's threshold) run on the matrix cores (grouped dequantize+GEMM): 4-bit
- *                group-64 experts in every form below, 4-bit group-128, 3-bit and 2-bit experts in forms 0 and 6 (2-bit
- *                layers excepted with a scale above 32000 or a row of scales below 2^-14, or two-level ones with a scale
- *                above 500 or a row 2^16 times below the largest); smaller batches, 4-bit group-32 experts and
- *                other formats in forms 1 to 5 use the GEMV kernels;
+ *                group-64 experts in every form below, 4-bit group-128 and group-32, 3-bit and 2-bit experts in forms 0 and 6
+ *                (2-bit layers excepted with a scale above 32000 or a row of scales below 2^-14, or two-level ones with a
+ *                scale above 500 or a row 2^16 times below the largest; group-32 layers excepted less than 128 wide or
+ *                with metadata runs of one group); smaller batches and these formats in forms 1 to 5 use the GEMV kernels;
  *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 where it is the faster one for the layer's size and the tokens an
  *                expert has on average (4-bit group-64 layers of middle size, and larger ones with more than 32, two-level 16;
  *                other formats: more than three, or more than one in all but the smallest layers), else form 5 (4-bit

@@ -40,7 +40,7 @@ struct GateArgs {
     float *route_w;                 // [K] device
     int32_t *route_log;             // [K] device: this step's slot of the log ring
     // For kernels that find the routing in device memory (TILE): every pair's expert and combine weight; where xs is set the
-    // sums of h over groups of xs_group elements for the tile kernels, rows padded with zeros to xs_stride (16: split2, 64:
+    // sums of h over groups of xs_group elements for the tile kernels, rows padded with zeros to xs_stride (16: split2, else
     // split3).  quiet: nobody waits for this launch, nothing is published in `out`.
     uint8_t *pair_expert;           // [b*K + j]
     float *pair_w;                  // [b*K + j]
@@ -132,15 +132,13 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
         if (a.yacc) *reinterpret_cast<float4 *>(a.yacc + (size_t)b * a.H + i) = make_float4(0.f, 0.f, 0.f, 0.f);
         const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
                      h3 = half_bits_to_f64(hv[3]);
-        if (TILE && a.xs) {       // 4 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
+        if (TILE && a.xs) {       // 4, 8 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
             float s = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
             s += dpp_f<0xB1>(s);
             s += dpp_f<0x4E>(s);
-            if (a.xs_group == 64) {
-                s += dpp_f<0x141>(s);
-                s += dpp_f<0x140>(s);
-            }
-            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = a.xs_group == 64 ? split3(s) : make_uint2(split2(s), 0u);
+            if (a.xs_group >= 32) s += dpp_f<0x141>(s);
+            if (a.xs_group == 64) s += dpp_f<0x140>(s);
+            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = a.xs_group >= 32 ? split3(s) : make_uint2(split2(s), 0u);
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e)

@@ -20,6 +20,7 @@
 // in fp32 and is scaled by the fp32 s with one fused multiply-add per accumulator register; no weight is rounded.
 // (Codes as the subnormal fp16 numbers their bits spell need no exponent, but the matrix cores accumulate products of
 // subnormals with fewer bits: 6 % more error in y.)
+// Groups of 32 (4 bits, tiles of 16 and 32 tokens): two products of half the length per unit, a lane half or quarter holding its share of either group.
 // 2-bit codes (groups of 16; ZC = 1): q - 1 is one of -1, 0, 1, 2 and (q - 1) s is exact in fp16 for an fp16 s, so the
 // scaled weight goes in directly; an fp32 s (two-level metadata) goes in as two fp16 numbers, in two products.
 // Second term: a contraction over groups instead of codes, on the bf16 matrix instructions.  With ZC = -64 it is some twenty times
@@ -127,10 +128,18 @@ __device__ __forceinline__ bf8_t slots_d(uint2 v)
     return __builtin_bit_cast(bf8_t, r);
 }
 
-// eight codes of a word in the 4-bit layout as the fp16 numbers 64 + q
-__device__ __forceinline__ h8_t codes_biased64(uint32_t w, const BiasPatterns &p)
+// Eight codes of a word in the 4-bit layout as the fp16 numbers 64 + q, in codes_biased's slots.  m: the bits of a code, 0x00F000F0, or
+// 0x00700070 where bit 3 of a field is not the code's.
+struct Bias64 { uint32_t m, k; };
+__device__ __forceinline__ Bias64 bias64(uint32_t m)
 {
-    const u32x4_t r = {((w << 4) & p.m_hi) | p.k64, (w & p.m_hi) | p.k64, ((w >> 4) & p.m_hi) | p.k64, ((w >> 8) & p.m_hi) | p.k64};
+    Bias64 p = {m, 0x54005400u};
+    asm("" : "+s"(p.m), "+v"(p.k));
+    return p;
+}
+__device__ __forceinline__ h8_t codes_biased64(uint32_t w, const Bias64 &p)
+{
+    const u32x4_t r = {((w << 4) & p.m) | p.k, (w & p.m) | p.k, ((w >> 4) & p.m) | p.k, ((w >> 8) & p.m) | p.k};
     return __builtin_bit_cast(h8_t, r);
 }
 
@@ -159,6 +168,24 @@ template <int N> struct TeMeta<true, N> {
     __device__ __forceinline__ void get(int i, float &s, float &z) const { decode_meta8(m[i], quad[i], s, z); }
 };
 
+// Groups of 32: two (scale, zero) per unit; with two-level metadata both lie in one run (tile_format).
+template <bool META8, int N> struct TeMeta2;
+template <int N> struct TeMeta2<false, N> {
+    uint2 m[N];
+    __device__ __forceinline__ void fetch(int i, __amdgpu_buffer_rsrc_t r, uint32_t row, int u, const TeGeom &g) { m[i] = bl64(r, row + g.meta_off + 8u * (uint32_t)u); }
+    __device__ __forceinline__ void get(int i, int j, float &s, float &z) const { const uint32_t w = j ? m[i].y : m[i].x; s = lo_half(w); z = hi_half(w); }
+};
+template <int N> struct TeMeta2<true, N> {
+    uint32_t m[N];
+    uint2 quad[N];
+    __device__ __forceinline__ void fetch(int i, __amdgpu_buffer_rsrc_t r, uint32_t row, int u, const TeGeom &g)
+    {
+        m[i] = bl32(r, row + g.meta_off + 4u * (uint32_t)u);
+        quad[i] = bl64(r, row + g.meta2_off + 8u * (2u * (uint32_t)u >> g.run_shift));
+    }
+    __device__ __forceinline__ void get(int i, int j, float &s, float &z) const { decode_meta8(m[i] >> (16 * j), quad[i], s, z); }
+};
+
 // ---------------------------------------------------------------------------------------------
 // format policies.  Stage: what a thread holds of one set on its way to LDS; a row's record in LDS: CODES bytes of
 // codes, then (GS) four fp32 scales; D: split zero-point factors, DB bytes per row.  GS: scaled in the accumulators.
@@ -166,13 +193,13 @@ template <int N> struct TeMeta<true, N> {
 
 template <int FMT, int ROWS, int THREADS> struct Te;
 
-template <bool META8, int ROWS, int THREADS>
+template <bool META8, int ROWS, int THREADS, int G = 1>
 struct TeScaled {                        // the part that 4-bit and 3-bit formats share
     static constexpr bool GS = true;
-    static constexpr int GPU = 1, PLANES = 1, DB = 32;                   // groups per unit; bytes of D per row and set
+    static constexpr int GPU = G, PLANES = 1, DB = 32 * G;               // groups per unit; bytes of D per row and set
     static constexpr bool LIFTED = false;
     static constexpr int NM = ROWS * 4 / THREADS;
-    TeMeta<META8, NM> meta;
+    std::conditional_t<G == 1, TeMeta<META8, NM>, TeMeta2<META8, NM>> meta;
     __device__ __forceinline__ void fetch_meta(__amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
     {
 #pragma unroll
@@ -187,16 +214,26 @@ struct TeScaled {                        // the part that 4-bit and 3-bit format
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             float s, z;
-            meta.get(i, s, z);
-            *reinterpret_cast<float *>(rec + (tid / 4) * REC + (tid % 4) * 4 + SOFF + i * (THREADS / 4) * REC) = s;
-            *reinterpret_cast<uint2 *>(d + tid * 8 + i * THREADS * 8) = split3(s * (-64.f - z));
+            if constexpr (G == 1) {
+                meta.get(i, s, z);
+                *reinterpret_cast<float *>(rec + (tid / 4) * REC + (tid % 4) * 4 + SOFF + i * (THREADS / 4) * REC) = s;
+                *reinterpret_cast<uint2 *>(d + tid * 8 + i * THREADS * 8) = split3(s * (-64.f - z));
+            } else {
+                float s1, z1;
+                meta.get(i, 0, s, z);
+                meta.get(i, 1, s1, z1);
+                *reinterpret_cast<float2 *>(rec + (tid / 4) * REC + (tid % 4) * 8 + SOFF + i * (THREADS / 4) * REC) = make_float2(s, s1);
+                const uint2 d0 = split3(s * (-64.f - z)), d1 = split3(s1 * (-64.f - z1));
+                *reinterpret_cast<uint4 *>(d + tid * 16 + i * THREADS * 16) = make_uint4(d0.x, d0.y, d1.x, d1.y);
+            }
         }
     }
 };
 
-template <bool META8, int ROWS, int THREADS>
-struct Te4 : TeScaled<META8, ROWS, THREADS> {
-    static constexpr int SOFF = 128, REC = 144, NC = ROWS * 8 / THREADS;
+template <bool META8, int ROWS, int THREADS, int G = 1>
+struct Te4 : TeScaled<META8, ROWS, THREADS, G> {
+    static constexpr uint32_t FIELD = 0x00F000F0u;
+    static constexpr int SOFF = 128, REC = G == 1 ? 144 : 176, NC = ROWS * 8 / THREADS;
     uint4 c[NC];
     struct Raw { uint4 q; };
     __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
@@ -214,20 +251,37 @@ struct Te4 : TeScaled<META8, ROWS, THREADS> {
         for (int i = h * NC / 2; i < (h + 1) * NC / 2; ++i) *reinterpret_cast<uint4 *>(to + i * (THREADS / 8) * REC) = c[i];
         if (h == 1) this->template commit_meta<REC, SOFF>(rec, d, tid);
     }
-    static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u) { r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16); }
+    // (groups of 32: a lane half takes half of either group)
+    static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u)
+    {
+        if constexpr (G == 1) {
+            r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16);
+        } else {
+            const uint2 p = *reinterpret_cast<const uint2 *>(row + u * 32 + hh * 8), q = *reinterpret_cast<const uint2 *>(row + u * 32 + 16 + hh * 8);
+            r.q = make_uint4(p.x, p.y, q.x, q.y);
+        }
+    }
     // words of 8 codes in the 4-bit layout: the lane half's four, or those of quarter kb of the unit
     static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4]) { t[0] = r.q.x; t[1] = r.q.y; t[2] = r.q.z; t[3] = r.q.w; }
     static __device__ __forceinline__ void quarter(const uint8_t *row, int kb, int u, uint32_t (&t)[2])
     {
-        const uint2 q = *reinterpret_cast<const uint2 *>(row + u * 32 + kb * 8);
-        t[0] = q.x; t[1] = q.y;
+        if constexpr (G == 1) {
+            const uint2 q = *reinterpret_cast<const uint2 *>(row + u * 32 + kb * 8);
+            t[0] = q.x; t[1] = q.y;
+        } else {                                                         // a quarter of either group
+            t[0] = *reinterpret_cast<const uint32_t *>(row + u * 32 + kb * 4);
+            t[1] = *reinterpret_cast<const uint32_t *>(row + u * 32 + 16 + kb * 4);
+        }
     }
 };
 template <int R, int T> struct Te<4, R, T> : Te4<false, R, T> {};
 template <int R, int T> struct Te<48, R, T> : Te4<true, R, T> {};
+template <int R, int T> struct Te<5, R, T> : Te4<false, R, T, 2> {};      // 4-bit codes in groups of 32, and with two-level metadata
+template <int R, int T> struct Te<58, R, T> : Te4<true, R, T, 2> {};
 
 template <bool META8, int ROWS, int THREADS>
 struct Te3 : TeScaled<META8, ROWS, THREADS> {
+    static constexpr uint32_t FIELD = 0x00700070u;
     static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS;
     static constexpr bool HALF = ROWS * 4 == THREADS;                    // region B: 8 or 16 bytes per thread
     static_assert(NA >= 1 && (HALF || ROWS * 2 == THREADS), "region B is one piece per thread");
@@ -268,17 +322,18 @@ struct Te3 : TeScaled<META8, ROWS, THREADS> {
     }
     static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4])
     {
-        t[0] = (r.a.x & 0x33333333u) | ((r.b << 2) & 0x44444444u);
-        t[1] = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & 0x44444444u);
-        t[2] = (r.a.y & 0x33333333u) | (r.b & 0x44444444u);
-        t[3] = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & 0x44444444u);
+        // one v_bfi each; bit 3 of a field is another word's
+        t[0] = (r.a.x & 0x33333333u) | ((r.b << 2) & ~0x33333333u);
+        t[1] = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & ~0x33333333u);
+        t[2] = (r.a.y & 0x33333333u) | (r.b & ~0x33333333u);
+        t[3] = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & ~0x33333333u);
     }
     static __device__ __forceinline__ void quarter(const uint8_t *row, int kb, int u, uint32_t (&t)[2])
     {
         const uint32_t a = *reinterpret_cast<const uint32_t *>(row + u * 16 + kb * 4);
         const uint32_t b = *reinterpret_cast<const uint32_t *>(row + 64 + u * 8 + (kb >> 1) * 4) >> (2 * (kb & 1));
-        t[0] = (a & 0x33333333u) | ((b << 2) & 0x44444444u);
-        t[1] = ((a >> 2) & 0x33333333u) | ((b << 1) & 0x44444444u);
+        t[0] = (a & 0x33333333u) | ((b << 2) & ~0x33333333u);
+        t[1] = ((a >> 2) & 0x33333333u) | ((b << 1) & ~0x33333333u);
     }
 };
 template <int R, int T> struct Te<3, R, T> : Te3<false, R, T> {};
@@ -303,6 +358,7 @@ __device__ __forceinline__ void centred2(uint32_t w, const Patterns2 &p, h2_t (&
 template <bool META8, int ROWS, int THREADS>
 struct Te2 {
     static constexpr bool GS = false;
+    static constexpr uint32_t FIELD = 0;
     static constexpr int GPU = 4, PLANES = META8 ? 2 : 1, DB = META8 ? 80 : 0, REC = 144, SOFF = 0;   // one-level: D from the record's (scale, zero)
     static constexpr int NC = ROWS * 8 / THREADS, NA = ROWS * 4 / THREADS;
     // two-level scales are split into two fp16, lifted by the layer's own power of two first (the host chooses it: the
@@ -427,7 +483,7 @@ template <int FMT, int MODE> struct TeCfg {
     static constexpr int RG = BIG || (MODE == 32 && !SMALL2) ? 4 : 2, ROWS = BIG ? 256 : 128;     // row groups: RG of RGR rows
     static constexpr int RGR = ROWS / RG;
     static constexpr int KW = THREADS / 64 / RG;                         // waves of a row group (MODE 16, 32: each a share of a set's units)
-    static constexpr int WAVES_EU = !BIG && THREADS == 512 ? 4 : 2;      // waves per SIMD
+    static constexpr int WAVES_EU = !BIG && THREADS == 512 && !((FMT == 5 || FMT == 58) && MODE == 32) ? 4 : 2;   // waves per SIMD (groups of 32: LDS for one block a compute unit)
     using F = Te<FMT, ROWS, THREADS>;
     static constexpr int MT = BIG ? (F::PLANES == 1 ? 3 : 2) : 1;                // token tiles of 32 per wave
     static constexpr int TOK = BIG ? 2 * MT * 32 : MODE;
@@ -438,14 +494,14 @@ template <int FMT, int MODE> struct TeCfg {
     static constexpr int ABUF = TOK * PITCH, BBUF = ROWS * REC, DBUF = ROWS * F::DB;
     // sums: 16 bytes are four groups, of a set (GS) or of one unit: XQ pieces per token and staging step
     // (8 bytes each; 2-bit codes take only the first four)
-    static constexpr int XQ = F::GS ? 2 : SU * 2, XPITCH = F::GS ? 32 : (XQ == 2 ? 16 : XQ * 8 + 16), XBUF = TOK * XPITCH;
+    static constexpr int XQ = F::GS ? 2 * F::GPU : SU * 2, XPITCH = F::GS ? 32 * F::GPU : (XQ == 2 ? 16 : XQ * 8 + 16), XBUF = TOK * XPITCH;
     static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_END = OFF_X + 2 * XBUF;
     static constexpr int OFF_RED = THREADS / 64 * (RGR * MODE * 4);    // MODE 16, 32: behind the waves' partial sums
     static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
     static constexpr int OFF_A = BIG ? 0 : OFF_RED, OFF_T = BIG || OFF_END > OFF_RED + TOK * APITCH ? OFF_END : OFF_RED + TOK * APITCH;
     static constexpr int LDS = OFF_T + TOK * 8;
     using Tot = std::conditional_t<F::GS, float[16], f32x16_t>;
-    static_assert(OFF_X >= TOK * APITCH && LDS <= (BIG || F::PLANES == 2 ? 160 : 80) * 1024, "the epilogue reuses the staging buffers");
+    static_assert(OFF_X >= TOK * APITCH && LDS <= (BIG || F::PLANES == 2 || (F::GPU == 2 && MODE == 32) ? 160 : 80) * 1024, "the epilogue reuses the staging buffers");
 };
 
 // token blocks of an expert: one tile of 16 or 32, or up to as many tiles of 32 per block as the large kernel holds
@@ -544,7 +600,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     }
     // sums: piece p of a step is token p / XQ; threads too many request nothing (a repeated piece is a visit of its line as any
     // other), in the large kernel and with 2-bit codes they repeat one (a branch costs those more: 2-bit, 16 tokens, 120 -> 129 us)
-    constexpr int XQ = C::XQ, XU = F::GS ? 1 : 4;                        // XU: groups per unit
+    constexpr int XQ = C::XQ, XU = F::GPU;                               // XU: groups per unit
     constexpr bool X_REPEAT = BIG || !F::GS;
     static_assert(C::TOK * XQ <= THREADS && (!X_REPEAT || THREADS % XQ == 0), "one piece per thread");
     const bool x_mine = X_REPEAT || tid < C::TOK * XQ;
@@ -580,7 +636,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
 
     // ---------------- multiply ----------------
     const uint8_t *const my_rec = lds + C::OFF_B + (rg * C::RGR + col) * C::REC;      // + 32 rows: the wave's second tile
-    const BiasPatterns bp = bias_patterns();
+    const Bias64 bp = bias64(F::FIELD);
     auto unpack = [&](h8_t (&b)[2][F::PLANES][4], int bb, int u) __attribute__((always_inline)) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
@@ -690,7 +746,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     auto copy_out = [&]() __attribute__((always_inline)) {
         if constexpr (W13) {
             __syncthreads();
-            constexpr int CPT = C::ACOLS / 8, XG = F::GPU == 1 ? 64 : 16;         // 16-byte pieces per token, columns per sum
+            constexpr int CPT = C::ACOLS / 8, XG = 64 / F::GPU;         // 16-byte pieces per token, columns per sum
             for (int p = tid; p < n_tiles * TILE * CPT; p += THREADS) {
                 const int tk = p / CPT, c = p % CPT, colg = rb * C::ACOLS + c * 8;
                 const bool in = colg < A.N;                              // N is a multiple of 64: a piece is in or out as a whole
@@ -701,16 +757,14 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 xb = __builtin_amdgcn_fdot2(as_h2(q[3]), ones, xb, false);
                 float xs = in ? xa + xb : 0.f;
                 xs += dpp_f<0xB1>(xs);                                   // two lanes: 16 columns
-                if constexpr (XG == 64) {
-                    xs += dpp_f<0x4E>(xs);
-                    xs += dpp_f<0x141>(xs);
-                }
+                if constexpr (XG >= 32) xs += dpp_f<0x4E>(xs);
+                if constexpr (XG == 64) xs += dpp_f<0x141>(xs);
                 if (tk < n_tok) {
                     const int pr = l_pair[tk];
                     if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
                     uint2 *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
                     const int g = colg / XG;
-                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = XG == 64 ? split3(xs) : make_uint2(split2(xs), 0u);
+                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = F::GS ? split3(xs) : make_uint2(split2(xs), 0u);
                     if (c == 0 && (rb + 1) * C::ACOLS >= A.N)            // the padding behind the last group that no row block covers
                         for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
                 }
@@ -816,15 +870,19 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         // one unit of the wave's rows
         auto unit = [&](int bb, int un) __attribute__((always_inline)) {
             constexpr int KS = MODE == 32 ? 4 : 2;                       // k-steps of a unit
-            const uint8_t *src = lds + bb * C::ABUF + rcol * C::PITCH + un * 128 + kb * (KS * 16);
+            // k-steps in the order of the lane's codes: its share of the unit, or (groups of 32) of either group
+            constexpr int KG = KS / (F::GS ? F::GPU : 1);                // k-steps of a group's product
+            const uint8_t *src = lds + bb * C::ABUF + rcol * C::PITCH + un * 128 + kb * (KG * 16);
             h8_t a[KS];
 #pragma unroll
-            for (int k = 0; k < KS; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + k * 16);
+            for (int k = 0; k < KS; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + k / KG * 64 + k % KG * 16);
             if constexpr (F::GS) {
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     const uint8_t *rec = rec0 + bb * C::BBUF + rt * RROWS * C::REC;
-                    const float sc = *reinterpret_cast<const float *>(rec + F::SOFF + un * 4);
+                    float sc[F::GPU];
+#pragma unroll
+                    for (int j = 0; j < F::GPU; ++j) sc[j] = *reinterpret_cast<const float *>(rec + F::SOFF + (un * F::GPU + j) * 4);
                     uint32_t t[KS];
                     if constexpr (MODE == 32) {
                         typename F::Raw raw;
@@ -833,13 +891,16 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                     } else {
                         F::quarter(rec, kb, un, t);
                     }
-                    Acc g;
 #pragma unroll
-                    for (int i = 0; i < NR; ++i) g[i] = 0.f;
+                    for (int j = 0; j < F::GPU; ++j) {
+                        Acc g;
 #pragma unroll
-                    for (int k = 0; k < KS; ++k) g = mm(a[k], codes_biased64(t[k], bp), g);
+                        for (int i = 0; i < NR; ++i) g[i] = 0.f;
 #pragma unroll
-                    for (int i = 0; i < NR; ++i) tot[rt][i] = __builtin_fmaf(sc, g[i], tot[rt][i]);
+                        for (int k = j * KG; k < (j + 1) * KG; ++k) g = mm(a[k], codes_biased64(t[k], bp), g);
+#pragma unroll
+                        for (int i = 0; i < NR; ++i) tot[rt][i] = __builtin_fmaf(sc[j], g[i], tot[rt][i]);
+                    }
                 }
             } else {
                 const uint8_t *const xp0 = lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + un * 16;
@@ -876,10 +937,10 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 }
             }
         };
-        // GS: the zero-point term of a set: its four groups in one matrix instruction per row tile, or two in each of two
+        // GS: the zero-point term of a set: four groups in one matrix instruction per row tile, or two with tiles of 32
         auto set_term = [&](int bb) __attribute__((always_inline)) {
 #pragma unroll
-            for (int p = 0; p < MODE / 16; ++p) {
+            for (int p = 0; p < MODE / 16 * F::GPU; ++p) {
                 const int g = p * (64 / MODE) + kb;
                 const bf8_t xv = slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + g * 8));
 #pragma unroll

@@ -166,7 +166,7 @@ struct moe_ctx {
     int32_t w2_token_rows = 0;          // rows per block of the single-token w2 kernel; 0: hidden / compute units
     uint32_t gate_seq = 0;              // sequence number of the last gate launch
     int32_t mfma_form = 0;              // matrix-core kernels: 0 the default (6 where an expert has enough tokens and, for formats form 5 takes, 6 is
-                                        // faster; else 5 or the GEMV kernels); 6 tile kernels, every format but 4-bit g32; 5 streaming form with 16-token tiles (one per
+                                        // faster; else 5 or the GEMV kernels); 6 tile kernels, every format; 5 streaming form with 16-token tiles (one per
                                         // expert while no expert of the window has more than 16 tokens, else two), codes multiplied as they are and
                                         // groups scaled in fp32; 4 the same with weights dequantised to fp16;
                                         // 3 streaming form, one fma per pair of weights plus a rank-1 correction;
@@ -1388,8 +1388,9 @@ struct PassExpert { const uint8_t *blob; std::vector<int> pairs; int32_t expert;
 // ---- which kernels a step takes ----
 
 // Codes per sum of activations: the groups of the zero-point term.
-static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : 64; }
-static int tile_sum_stride(int cols, int group) { return (cols / group + 3) / 4 * 4; }
+static int tile_sum_group(const BlobLayout &b) { return b.bits == 2 ? 16 : (b.group == 32 ? 32 : 64); }
+// ... rows of them padded to a staging step's (a unit of 64 codes with 2 bits, else a set of four)
+static int tile_sum_stride(int cols, int group) { const int step = group == 32 ? 8 : 4; return (cols / group + step - 1) / step * step; }
 
 // The power of two that two-level 2-bit scales are multiplied with: the layer's largest just below 32000, so that its product
 // with a code (at most 2 in size, centred) is an fp16 number.
@@ -1415,7 +1416,9 @@ static bool tile_format(const moe_layer *l)
         if (!(top <= (b.scale_group ? 500.f : 32000.f)) || low * tile_lift(l) < (b.scale_group ? 0.25f : 0x1p-14f)) return false;
     }
     const bool fits32 = 2ull * b.ffn * b.m13.row_stride < (1ull << 31) && (uint64_t)b.hidden * b.m2.row_stride < (1ull << 31);
-    return fits32 && (b.bits != 4 || b.group >= 64);
+    // groups of 32: rows of sums no longer than the arena's, and metadata runs of whole units
+    const bool g32 = b.bits == 4 && b.group == 32;
+    return fits32 && (!g32 || (b.hidden >= 128 && b.ffn >= 128 && (!b.scale_group || b.scale_group >= 2)));
 }
 
 // token blocks of an expert with `count` tokens
@@ -1453,7 +1456,8 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     // for more tokens than that on average is the better one before experts that need a second block of the smaller become many.
     const bool exact = l->cfg.top_k == E;
     const double avg = (double)pairs / E;
-    p.mode = avg > (exact ? 32 : TILE_MODE32_AVERAGE) ? TE_BIG : (avg > (exact ? 16 : 12) ? 32 : 16);
+    // (groups of 32 have no large kernel: twice the metadata does not fit beside its tokens)
+    p.mode = avg > (exact ? 32 : TILE_MODE32_AVERAGE) && !(b.bits == 4 && b.group == 32) ? TE_BIG : (avg > (exact ? 16 : 12) ? 32 : 16);
     int blocks = 0;
     for (int e = 0; e < E; ++e) blocks += tile_blocks(b, nominal_count(l, pairs, e), p.mode);
     const int rows = p.mode == TE_BIG ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
@@ -1463,7 +1467,8 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
     // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
     // 226 + 14 (4).
-    const int slots = n_cu_of(c) * (p.mode == TE_BIG ? 1 : 2);
+    const bool alone = p.mode == TE_BIG || (p.mode == 32 && b.bits == 4 && b.group == 32);       // one block a compute unit
+    const int slots = n_cu_of(c) * (alone ? 1 : 2);
     double best = 0.0;
     p.parts = 1;
     for (int n = 1; n <= std::min(std::min(8, sets), cap); ++n) {
@@ -1555,7 +1560,8 @@ static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
 // a quarter with two-level 2-bit codes (4 tokens, 1024 x 4096, 3-bit 44 / 30, 4-bit group 128 34 / 29; 320 x 8384, 13 experts 59 / 29;
 // rows twice as long, 2048 x 12032: 3-bit 86 / 74, 2-bit 73 / 76, two-level 95 / 100).  In the smallest layers the two are within
 // 10 % of each other (256 x 512), so there it takes the three tokens of an expert at which a step's time no longer
-// counts in launches alone.
+// counts in launches alone (groups of 32 stay on the GEMV kernels there).  Groups of 32, GEMV / tile kernels: 1024 x 4096, 8 tokens 42 / 31, 64 tokens
+// 148 / 44; 4096 x 14336, 8 tokens 220 / 189, 16 tokens 273 / 197, 64 tokens 948 / 301.
 //
 // 4-bit group 64: beside the 16-token kernels' steps.  Layers of middle size are faster on the tile kernels at any batch
 // (16-token / tile kernels: 1024 x 4096, 16 tokens 37 / 32, 64 tokens 46 / 37; 4096 x 1792 46 / 42 and 59 / 49; two-level 40 / 34 and 49 / 38), larger ones only
@@ -1574,7 +1580,7 @@ static bool tile_may(const moe_layer *l, int batch, bool stream, bool *surely)
         return pairs > (cf.scale_group ? 16 : 32) * cf.n_experts;
     }
     const bool g64 = cf.bits == 4 && cf.group == 64;         // with runs of metadata that the 16-token kernels do not take
-    if (pairs > (g64 ? 8 : 3) * cf.n_experts) return true;
+    if (pairs > (g64 ? 8 : 3) * cf.n_experts && (cf.bits != 4 || cf.group != 32 || size > 1 << 17)) return true;
     if (size <= (g64 ? 1 << 20 : 1 << 17)) return false;
     const int fmt = fmt_of(l->lay);
     return pairs > cf.n_experts || cf.hidden / codes_per_chunk(fmt) <= (fmt == 28 ? 16 : 32);
@@ -1765,13 +1771,17 @@ static int32_t launch_tile_fmt(moe_ctx *c, int mode, int grid, uint64_t bytes, c
 {
     if (mode == 16) return launch_tile_mode<FMT, W13, 16>(c, grid, bytes, A);
     if (mode == 32) return launch_tile_mode<FMT, W13, 32>(c, grid, bytes, A);
-    return launch_tile_mode<FMT, W13, TE_BIG>(c, grid, bytes, A);
+    if constexpr (FMT != 5 && FMT != 58) return launch_tile_mode<FMT, W13, TE_BIG>(c, grid, bytes, A);
+    return fail(MOE_EINVAL, "no large tile kernel for groups of 32");
 }
 
 template <bool W13>
 static int32_t launch_tile_half(moe_layer *l, int mode, int grid, uint64_t bytes, const TeArgs &A)
 {
-    switch (fmt_of(l->lay)) {
+    const int g32 = l->lay.bits == 4 && l->lay.group == 32;
+    switch (g32 ? (l->lay.scale_group ? 58 : 5) : fmt_of(l->lay)) {
+    case 5: return launch_tile_fmt<5, W13>(l->ctx, mode, grid, bytes, A);
+    case 58: return launch_tile_fmt<58, W13>(l->ctx, mode, grid, bytes, A);
     case 4: return launch_tile_fmt<4, W13>(l->ctx, mode, grid, bytes, A);
     case 48: return launch_tile_fmt<48, W13>(l->ctx, mode, grid, bytes, A);
     case 3: return launch_tile_fmt<3, W13>(l->ctx, mode, grid, bytes, A);
