@@ -26,8 +26,9 @@ struct FfnEntry {
     float w[MAX_NT];                // combine weight of each
 };
 
-struct FfnArgs {
-    FfnEntry e[MAX_ENTRIES];
+// The arguments of a launch are copied by the host and fetched over the link, about 1 us per 700 bytes: a launch that needs no entries
+// does not carry them.
+struct FfnCommon {
     const uint16_t *h;              // [B][H] fp16 gate input
     uint16_t *a;                    // [B*K][F] fp16 SwiGLU activations
     float *ypart;                   // [B*K][H] fp32: row `pair` receives w * (W2^ a[pair]); k_combine adds a token's rows
@@ -38,12 +39,16 @@ struct FfnArgs {
     uint32_t stride2, meta2;        // w2 row
     uint64_t off_w2;
     int32_t rows_per_block;         // w2 kernel
-    // Device-side routing: entry j serves the j-th selected expert, whose id the gate kernel of the same step left in
-    // route_idx[j]; its weights are in table[id].  Null: the entries carry their blob pointers themselves.
-    const int32_t *route_idx;
+};
+struct FfnArgs : FfnCommon {
+    FfnEntry e[MAX_ENTRIES];
+};
+// Device-side routing.  One token: entry j serves the j-th selected expert, whose id the gate kernel of the same step left in
+// route_idx[j].  Several tokens (kernels of more than one token per entry, at most 64 pairs): every pair's expert and weight; an
+// entry is up to NT of an expert's pairs.
+struct FfnRouted : FfnCommon {
     const uint8_t *table[16];       // device buffer of every expert of the layer (all resident)
-    // ... for several tokens (kernels of more than one token per entry, at most 64 pairs): every pair's expert and weight, an
-    // entry is up to NT of an expert's pairs.  Null: the entries above.
+    const int32_t *route_idx;
     const uint8_t *pair_expert;
     const float *pair_w;
     int32_t n_pairs, n_experts, top_k;
@@ -51,14 +56,14 @@ struct FfnArgs {
 
 // Entries of such a step, and the j-th of them (there is one); e: the expert of pair `lane`, 255 past the last.
 template <int NT>
-__device__ __forceinline__ int route_entries(const FfnArgs &A, uint32_t e)
+__device__ __forceinline__ int route_entries(const FfnRouted &A, uint32_t e)
 {
     int n = 0;
     for (int k = 0; k < A.n_experts; ++k) n += (__popcll(__ballot(e == (uint32_t)k)) + NT - 1) / NT;
     return n;
 }
 template <int NT>
-__device__ __forceinline__ FfnEntry route_entry(const FfnArgs &A, uint32_t e, int j)
+__device__ __forceinline__ FfnEntry route_entry(const FfnRouted &A, uint32_t e, int j)
 {
     uint64_t mine = 0;
     int expert = 0;
@@ -398,14 +403,15 @@ __device__ __forceinline__ RowGeom row_geom(uint32_t meta_off, int cols, int gro
 
 // K2: a[pair][r] = silu(W1^ h)[r] * (W3^ h)[r].  grid = (row blocks, entries), WAVES waves per block; a wave
 // walks rows r = wave_id, wave_id + n_waves, ... with G of them in flight; KCH = chunks per lane per row.
-template <int BITS, int KCH, int NT, int G, int WAVES>
-__global__ __launch_bounds__(WAVES *WAVE) void k_w13(FfnArgs A)
+template <int BITS, int KCH, int NT, int G, int WAVES, class ARGS = FfnArgs>
+__global__ __launch_bounds__(WAVES *WAVE) void k_w13(ARGS A)
 {
     using F = Fmt<BITS>;
+    constexpr bool ROUTED = std::is_same_v<ARGS, FfnRouted>;
     const int lane = threadIdx.x & 63;
     int entry = blockIdx.y, block = blockIdx.x, blocks = gridDim.x;
     uint32_t pair_e = 255u;
-    if (NT > 1 && A.pair_expert) {         // one row of blocks, shared evenly by the entries there are
+    if constexpr (ROUTED && NT > 1) {      // one row of blocks, shared evenly by the entries there are
         if (lane < A.n_pairs) pair_e = A.pair_expert[lane];
         const int n = route_entries<NT>(A, pair_e);
         blocks = max((int)gridDim.x / max(n, 1), 1);
@@ -413,15 +419,16 @@ __global__ __launch_bounds__(WAVES *WAVE) void k_w13(FfnArgs A)
         block = blockIdx.x % blocks;
         if (entry >= n) return;
     }
-    auto pick = [&]() -> std::conditional_t<(NT > 1), FfnEntry, const FfnEntry &> {
-        if constexpr (NT > 1) { if (A.pair_expert) return route_entry<NT>(A, pair_e, entry); }
-        return A.e[entry];
+    auto pick = [&]() -> std::conditional_t<ROUTED, FfnEntry, const FfnEntry &> {
+        if constexpr (ROUTED && NT > 1) return route_entry<NT>(A, pair_e, entry);
+        else if constexpr (ROUTED) return {A.table[uniform(A.route_idx[entry]) & 15], 1, {0}, {entry}, {0.f}};
+        else return A.e[entry];
     };
     const auto &en = pick();
     const int wave = uniform(block * WAVES + (threadIdx.x >> 6)), n_waves = blocks * WAVES;
     const int n_chunks = A.H / F::CODES;
     const RowGeom geo = row_geom<BITS>(A.meta13, A.H, A.group, A.scale_group);
-    const uint8_t *base = A.route_idx ? A.table[uniform(A.route_idx[blockIdx.y]) & 15] : en.blob;
+    const uint8_t *base = en.blob;
 
     int cidx[KCH];
     bool live[KCH];
@@ -519,19 +526,21 @@ __host__ __device__ __forceinline__ uint32_t y_rows(uint32_t row, uint32_t parts
 // K3: ypart[pair][r] = w * (W2^ a[pair])[r].  grid = (row blocks, entries); block = CS waves, wave cs owns
 // column chunk cs*64 + lane of every row of the block (G rows in flight); partial sums meet in LDS.  No atomics:
 // every element of ypart has one writer, and k_combine adds the rows of a token in a fixed order.
-template <int BITS, int NT, int G>
-__global__ __launch_bounds__(512) void k_w2(FfnArgs A)
+template <int BITS, int NT, int G, class ARGS = FfnArgs>
+__global__ __launch_bounds__(512) void k_w2(ARGS A)
 {
     using F = Fmt<BITS>;
+    constexpr bool ROUTED = std::is_same_v<ARGS, FfnRouted>;
+    static_assert(!ROUTED || NT > 1, "one token has a kernel of its own");
     extern __shared__ float red[];                       // [rows_per_block][NT][CS]
     uint32_t pair_e = 255u;
-    if (NT > 1 && A.pair_expert) {
+    if constexpr (ROUTED) {
         if ((int)(threadIdx.x & 63) < A.n_pairs) pair_e = A.pair_expert[threadIdx.x & 63];
         if ((int)blockIdx.y >= route_entries<NT>(A, pair_e)) return;                   // the grid covers the most there can be
     }
-    auto pick = [&]() -> std::conditional_t<(NT > 1), FfnEntry, const FfnEntry &> {
-        if constexpr (NT > 1) { if (A.pair_expert) return route_entry<NT>(A, pair_e, blockIdx.y); }
-        return A.e[blockIdx.y];
+    auto pick = [&]() -> std::conditional_t<ROUTED, FfnEntry, const FfnEntry &> {
+        if constexpr (ROUTED) return route_entry<NT>(A, pair_e, blockIdx.y);
+        else return A.e[blockIdx.y];
     };
     const auto &en = pick();
     const int lane = threadIdx.x & 63, cs = uniform(threadIdx.x >> 6), CS = blockDim.x >> 6;

@@ -68,9 +68,10 @@ __device__ __forceinline__ h8_t codes_biased(uint32_t w, const BiasPatterns &p)
 // META8 (GS only): two-level metadata (Sec. 4.2 "scale group size").  A step then stages, per row, 16 bytes of (scale
 // code, zero code) byte pairs and the fp16 quad of the run the step lies in, and a unit decodes scale and zero in fp32
 // -- which is where the group-scaled arithmetic wants them anyway.
-template <bool W13, int MT, int WAVES, bool GS = false, bool META8 = false>
-__global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void k_mfma_stream16_q4(TileArgs A)
+template <bool W13, int MT, int WAVES, bool GS = false, bool META8 = false, class ARGS = TileArgs>
+__global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void k_mfma_stream16_q4(ARGS A)
 {
+    constexpr bool ROUTED = std::is_same_v<ARGS, TileRouted>;
     static_assert(GS || !META8, "two-level metadata is decoded in fp32: group-scaled arithmetic only");
     static_assert(MT == 1 || MT == 2, "one or two token tiles of 16");
     static_assert(WAVES == 4 || WAVES == 8, "four or eight waves per block");
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
     int32_t *const l_n = reinterpret_cast<int32_t *>(l_e + 32);
     static_assert(sizeof(MfmaEntry) == 16 && (2 * TL_BUF_BYTES + MF_MAX_PAIRS * 6) % 16 == 0, "entries are 16 bytes of the table");
     static_assert(FEW_PAIRS == MF_MAX_PAIRS, "the tables hold a step's pairs");
-    if (A.pair_expert) {
+    if constexpr (ROUTED) {
         // the first wave cuts every expert's pairs into entries and puts them into the tables, expert by expert
         if (tid < 64) {
             FewPairs few;
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
         if (tid < 32) l_e[tid] = A.e[tid];
     }
     __syncthreads();
-    const int n_items = A.pair_expert ? uniform(*l_n) * A.row_blocks * A.k_parts : A.n_items;
+    const int n_items = ROUTED ? uniform(*l_n) * A.row_blocks * A.k_parts : A.n_items;
     auto entry = [&](int e) -> MfmaEntry {
         MfmaEntry en = l_e[e];
         const uint64_t b = (uint64_t)en.blob;

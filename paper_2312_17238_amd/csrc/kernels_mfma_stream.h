@@ -67,11 +67,7 @@ static_assert(TL_WAVES * 2 * 16 * 64 * 4 <= TL_BUF_BYTES, "one reduction round (
 static_assert(TL_CP * TL_THREADS == TL_ROWS * TL_CPR && TL_MP * TL_THREADS == TL_ROWS * TL_MPR, "pieces must divide evenly");
 static_assert(TL_SG % 4 == 0 && (TL_CPR & (TL_CPR - 1)) == 0 && (TL_MPR & (TL_MPR - 1)) == 0, "pieces per row must be powers of two");
 
-struct TileArgs {
-    MfmaEntry e[32];                         // (expert, token tile) entries
-    uint8_t tok[MF_MAX_PAIRS];
-    uint8_t pair[MF_MAX_PAIRS];
-    float w[MF_MAX_PAIRS];
+struct TileCommon {
     const uint16_t *act;                     // w1/w3: h [B][H];   w2: a [B*K][F]
     uint16_t *a;                             // w1/w3 output
     float *ypart;                            // w2 output: fp32 rows of H, one per pair (and per part of a split contraction)
@@ -84,8 +80,16 @@ struct TileArgs {
     int32_t run_shift;                       // ... log2(groups per run), 31 when a row is one run
     uint64_t mat_off;
     int32_t row_blocks, k_parts, seg_per_part, n_items;   // item = ((entry * row_blocks) + row block) * k_parts + part
-    // The 16-token kernels may find the routing in device memory: every pair's expert (at most FEW_PAIRS pairs) and weight,
-    // expert e's blob in table[e]; an entry is up to tile_tokens of an expert's pairs.  Null: the entries and pairs above.
+};
+struct TileArgs : TileCommon {
+    MfmaEntry e[32];                         // (expert, token tile) entries
+    uint8_t tok[MF_MAX_PAIRS];
+    uint8_t pair[MF_MAX_PAIRS];
+    float w[MF_MAX_PAIRS];
+};
+// The 16-token kernels may find the routing in device memory: every pair's expert (at most FEW_PAIRS pairs) and weight, expert e's
+// blob in table[e]; an entry is up to tile_tokens of an expert's pairs.
+struct TileRouted : TileCommon {
     const uint8_t *pair_expert;
     const float *pair_w;
     const uint8_t *table[16];

@@ -1200,81 +1200,94 @@ static int max_tokens_per_entry(int hidden, int fmt)
 #endif
 template <int BITS, int KCH, int NT> constexpr int w13_waves() { return KCH * NT * act_regs<BITS>() <= 80 ? MOE_W13_WAVES : 4; }
 
-template <int BITS, int KCH, int NT>
-static int32_t launch_w13_t(moe_ctx *c, uint64_t bytes, int n_entries, const FfnArgs &A)
+template <int BITS, int KCH, int NT, class ARGS>
+static int32_t launch_w13_t(moe_ctx *c, uint64_t bytes, int n_entries, const ARGS &A)
 {
     if constexpr (KCH * NT * act_regs<BITS>() <= ACT_REG_BUDGET) {
         constexpr int WAVES = w13_waves<BITS, KCH, NT>();
         const int per_entry = std::max(1, std::min((A.F + WAVES - 1) / WAVES, c->w13_blocks / n_entries));
         // entries the kernels find themselves: at least a block for each there can be, more for each there is where they are fewer
-        const dim3 grid = A.pair_expert ? dim3(std::max(n_entries, std::min((A.F + WAVES - 1) / WAVES * n_entries, c->w13_blocks))) : dim3(per_entry, n_entries);
-        return launch_timed(c, PROF_W13, bytes, k_w13<BITS, KCH, NT, MOE_W13_G, WAVES>, grid, dim3(WAVES * WAVE), 0, A);
+        const dim3 grid = std::is_same_v<ARGS, FfnRouted> && NT > 1 ? dim3(std::max(n_entries, std::min((A.F + WAVES - 1) / WAVES * n_entries, c->w13_blocks))) : dim3(per_entry, n_entries);
+        return launch_timed(c, PROF_W13, bytes, k_w13<BITS, KCH, NT, MOE_W13_G, WAVES, ARGS>, grid, dim3(WAVES * WAVE), 0, A);
     } else {
         return fail(MOE_EINVAL, "no w1/w3 kernel for %d chunks per lane and %d tokens per entry", KCH, NT);
     }
 }
 
-template <int BITS, int KCH>
-static int32_t launch_w13_k(moe_ctx *c, int nt, uint64_t bytes, int n_entries, const FfnArgs &A)
+template <int BITS, int KCH, class ARGS>
+static int32_t launch_w13_k(moe_ctx *c, int nt, uint64_t bytes, int n_entries, const ARGS &A)
 {
     if (nt == 1) return launch_w13_t<BITS, KCH, 1>(c, bytes, n_entries, A);
     if (nt == 2) return launch_w13_t<BITS, KCH, 2>(c, bytes, n_entries, A);
     return launch_w13_t<BITS, KCH, 4>(c, bytes, n_entries, A);
 }
 
-// table (device-side routing): the layer's expert -> device buffer map; entry j then serves the j-th selected expert
-// ... or, for a batch (routed = its pairs), entries of up to nt tokens that the kernels find themselves; `entries` is
-// empty then.
-template <int BITS>
-static int32_t launch_ffn_fmt(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only, const uint8_t *const *table, int routed)
+template <int BITS, class ARGS>
+static int32_t launch_ffn_args(moe_layer *l, ARGS &A, int n, int nt, bool w13_only, uint64_t n_distinct)
 {
     moe_ctx *c = l->ctx;
     const BlobLayout &b = l->lay;
     const int kch = chunks_per_lane(b.hidden, BITS);                          // per w1/w3 row
     const int cs = (b.ffn / Fmt<BITS>::CODES + 63) / 64;                      // waves per block for w2
     if (kch == 0 || cs > 8) return fail(MOE_EINVAL, "shape too large for the GEMV kernels");
-    for (size_t first = 0; first < (routed ? 1 : entries.size()); first += MAX_ENTRIES) {
-        const int own = std::min(routed, l->cfg.n_experts);
-        const int n = routed ? own + (routed - own) / nt : (int)std::min<size_t>(MAX_ENTRIES, entries.size() - first);   // routed: the most there can be
+    A.h = c->h_buf; A.a = c->a_buf; A.ypart = c->ypart; A.ytab = c->ytab;
+    A.H = b.hidden; A.F = b.ffn; A.group = b.group; A.scale_group = b.scale_group;
+    A.stride13 = b.m13.row_stride; A.meta13 = b.m13.meta_off;
+    A.stride2 = b.m2.row_stride; A.meta2 = b.m2.meta_off;
+    A.off_w2 = b.off_w2;
+    // Rows of a w2 block: w2_rows where that fills the chip with two waves a SIMD, fewer in smaller layers, whose blocks would
+    // otherwise be few and each a long chain of rows (704 x 768, 3 tokens, 32 rows a block: 13 to 18 us).
+    A.rows_per_block = c->w2_rows;
+    while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < n_cu_of(c) * 8) A.rows_per_block = (A.rows_per_block + 1) / 2;
+    const uint64_t bytes13 = n_distinct * 2 * (uint64_t)b.ffn * b.m13.row_stride;
+    const uint64_t bytes2 = n_distinct * (uint64_t)b.hidden * b.m2.row_stride;
+    int32_t rc;
+    if (kch == 1) rc = launch_w13_k<BITS, 1>(c, nt, bytes13, n, A);
+    else if (kch == 2) rc = launch_w13_k<BITS, 2>(c, nt, bytes13, n, A);
+    else rc = launch_w13_k<BITS, 4>(c, nt, bytes13, n, A);
+    if (rc || w13_only) return rc;
+    const dim3 g2((b.hidden + A.rows_per_block - 1) / A.rows_per_block, n), blk(cs * WAVE);
+    const size_t shm = (size_t)A.rows_per_block * nt * cs * sizeof(float);
+    if (nt == 2) return launch_timed(c, PROF_W2, bytes2, k_w2<BITS, 2, MOE_W2_G, ARGS>, g2, blk, shm, A);
+    if (nt > 2) return launch_timed(c, PROF_W2, bytes2, k_w2<BITS, 4, MOE_W2_G, ARGS>, g2, blk, shm, A);
+    if constexpr (std::is_same_v<ARGS, FfnArgs>) return launch_timed(c, PROF_W2, bytes2, k_w2<BITS, 1, MOE_W2_G, ARGS>, g2, blk, shm, A);
+    return fail(MOE_EINVAL, "one token routed on the device: w2 has a kernel of its own");
+}
+
+template <int BITS>
+static int32_t launch_ffn_fmt(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only)
+{
+    for (size_t first = 0; first < entries.size(); first += MAX_ENTRIES) {
+        const int n = (int)std::min<size_t>(MAX_ENTRIES, entries.size() - first);
         FfnArgs A{};
-        for (int i = 0; i < n && !routed; ++i) A.e[i] = entries[first + i];
-        A.h = c->h_buf; A.a = c->a_buf; A.ypart = c->ypart; A.ytab = c->ytab;
-        A.H = b.hidden; A.F = b.ffn; A.group = b.group; A.scale_group = b.scale_group;
-        A.stride13 = b.m13.row_stride; A.meta13 = b.m13.meta_off;
-        A.stride2 = b.m2.row_stride; A.meta2 = b.m2.meta_off;
-        A.off_w2 = b.off_w2;
-        // Rows of a w2 block: w2_rows where that fills the chip with two waves a SIMD, fewer in smaller layers, whose blocks would
-        // otherwise be few and each a long chain of rows (704 x 768, 3 tokens, 32 rows a block: 13 to 18 us).
-        A.rows_per_block = c->w2_rows;
-        while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < n_cu_of(c) * 8) A.rows_per_block = (A.rows_per_block + 1) / 2;
-        if (table) {
-            if (routed) { A.pair_expert = c->pair_expert; A.pair_w = c->pair_w; A.n_pairs = routed; A.n_experts = l->cfg.n_experts; A.top_k = l->cfg.top_k; }
-            else A.route_idx = c->route_idx;
-            for (int e = 0; e < 16; ++e) A.table[e] = table[e];
-        }
+        for (int i = 0; i < n; ++i) A.e[i] = entries[first + i];
         // algorithmic bytes: every distinct expert of the launch is read once
-        uint64_t n_distinct = routed ? own : 0;
-        for (int i = 0; i < n && !routed; ++i) {
+        uint64_t n_distinct = 0;
+        for (int i = 0; i < n; ++i) {
             bool seen = false;
-            for (int j = 0; j < i && !table; ++j) seen |= (A.e[j].blob == A.e[i].blob);
+            for (int j = 0; j < i; ++j) seen |= (A.e[j].blob == A.e[i].blob);
             n_distinct += !seen;
         }
-        const uint64_t bytes13 = n_distinct * 2 * (uint64_t)b.ffn * b.m13.row_stride;
-        const uint64_t bytes2 = n_distinct * (uint64_t)b.hidden * b.m2.row_stride;
-        int32_t rc;
-        if (kch == 1) rc = launch_w13_k<BITS, 1>(c, nt, bytes13, n, A);
-        else if (kch == 2) rc = launch_w13_k<BITS, 2>(c, nt, bytes13, n, A);
-        else rc = launch_w13_k<BITS, 4>(c, nt, bytes13, n, A);
-        if (rc) return rc;
-        if (w13_only) continue;
-        const dim3 g2((b.hidden + A.rows_per_block - 1) / A.rows_per_block, n), blk(cs * WAVE);
-        const size_t shm = (size_t)A.rows_per_block * nt * cs * sizeof(float);
-        if (nt == 1) rc = launch_timed(c, PROF_W2, bytes2, k_w2<BITS, 1, MOE_W2_G>, g2, blk, shm, A);
-        else if (nt == 2) rc = launch_timed(c, PROF_W2, bytes2, k_w2<BITS, 2, MOE_W2_G>, g2, blk, shm, A);
-        else rc = launch_timed(c, PROF_W2, bytes2, k_w2<BITS, 4, MOE_W2_G>, g2, blk, shm, A);
+        int32_t rc = launch_ffn_args<BITS>(l, A, n, nt, w13_only, n_distinct);
         if (rc) return rc;
     }
     return MOE_OK;
+}
+
+// Device-side routing.  table: the layer's expert -> device buffer map.  pairs == 0: one token, entry j serves the j-th selected
+// expert (w1/w3 only); else a batch of that many pairs, whose entries of up to nt tokens the kernels find themselves.
+template <int BITS>
+static int32_t launch_ffn_routed_fmt(moe_layer *l, int nt, const uint8_t *const *table, int pairs)
+{
+    moe_ctx *c = l->ctx;
+    const int own = std::min(pairs, l->cfg.n_experts);
+    const int n = pairs ? own + (pairs - own) / nt : l->cfg.top_k;              // the most entries there can be
+    FfnRouted A{};
+    for (int e = 0; e < 16; ++e) A.table[e] = table[e];
+    A.route_idx = c->route_idx;
+    A.pair_expert = c->pair_expert; A.pair_w = c->pair_w;
+    A.n_pairs = pairs; A.n_experts = l->cfg.n_experts; A.top_k = l->cfg.top_k;
+    return launch_ffn_args<BITS>(l, A, n, nt, pairs == 0, pairs ? own : n);
 }
 
 // Ring depths of the expert-after-expert one-launch kernel.
@@ -1639,6 +1652,14 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<true, 2, 4, true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<false, 2, 4, true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<false, 2, 4, true>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<true, 1, 8, true, false, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<true, 1, 8, true, true, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<true, 2, 4, true, false, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<true, 2, 4, true, true, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<false, 1, 8, true, false, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<false, 1, 8, true, true, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<false, 2, 4, true, false, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mfma_stream16_q4<false, 2, 4, true, true, TileRouted>), hipFuncAttributeMaxDynamicSharedMemorySize, TL_LDS_BYTES));
         lds_attr_set = true;
     }
     const int n_cu = c->n_cu > 0 ? c->n_cu : 256;
@@ -1648,20 +1669,25 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
     const int window = MF_MAX_PAIRS / K;
     for (int w0 = 0; w0 < batch; w0 += window) {
         const int w1 = std::min(batch, w0 + window);
-        TileArgs A{};
+        TileArgs A;                          // what every launch carries, and a waiting step's entries and pairs
+        static_cast<TileCommon &>(A) = {};
+        TileRouted routed{};
         int n = 0, first = 0, n_distinct = 0;
         // Which kernels multiply a window (one or two token tiles of 16): the plan's choice.  The other forms have tiles of 32 only.
         const bool small = plan.win.at(w0 / window).small;
         const size_t tile_tokens = small && (c->mfma_form == 4 || c->mfma_form == 5 || c->mfma_form == 0) ? 16 : 32;
         if (!w) {
-            A.pair_expert = c->pair_expert; A.pair_w = c->pair_w;
-            A.n_pairs = batch * K; A.n_experts = l->cfg.n_experts; A.top_k = K; A.tile_tokens = (int32_t)tile_tokens;
-            for (const PassExpert &pe : experts) A.table[pe.expert] = pe.blob;
+            routed.pair_expert = c->pair_expert; routed.pair_w = c->pair_w;
+            routed.n_pairs = batch * K; routed.n_experts = l->cfg.n_experts; routed.top_k = K; routed.tile_tokens = (int32_t)tile_tokens;
+            for (const PassExpert &pe : experts) routed.table[pe.expert] = pe.blob;
             const int own = std::min(l->cfg.n_experts, batch * K);
             n = own + (batch * K - own) / (int)tile_tokens;          // the most entries there can be
             first = batch * K;
             n_distinct = own;
-        } else for (const PassExpert &pe : experts) {
+        } else {
+            memset(A.e, 0, sizeof A.e); memset(A.tok, 0, sizeof A.tok); memset(A.pair, 0, sizeof A.pair); memset(A.w, 0, sizeof A.w);
+        }
+        if (w) for (const PassExpert &pe : experts) {
             std::vector<int> mine;
             for (int q : pe.pairs)
                 if (q / K >= w0 && q / K < w1) mine.push_back(q);
@@ -1718,7 +1744,17 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
         A.K = b.hidden; A.N = b.ffn; A.stride = b.m13.row_stride; A.meta_off = b.m13.meta_off; A.mat_off = b.off_w13;
         A.meta2_off = b.m13.meta2_off; A.run_shift = run_shift(b.m13);
         const dim3 g13 = shape(2 * b.ffn, b.hidden, false);
-        int32_t rc = gs8 ? (max_tok <= 16 ? launch_timed(c, PROF_W13, bytes13, k_mfma_stream16_q4<true, 1, 8, true, true>, g13, dim3(512), TL_LDS_BYTES, A)
+        auto launch_routed = [&](auto w13_tag, uint64_t bytes, dim3 grid) -> int32_t {
+            constexpr bool W13 = decltype(w13_tag)::value;
+            const int kind = W13 ? PROF_W13 : PROF_W2;
+            static_cast<TileCommon &>(routed) = A;
+            if (meta8) return max_tok <= 16 ? launch_timed(c, kind, bytes, k_mfma_stream16_q4<W13, 1, 8, true, true, TileRouted>, grid, dim3(512), TL_LDS_BYTES, routed)
+                                            : launch_timed(c, kind, bytes, k_mfma_stream16_q4<W13, 2, 4, true, true, TileRouted>, grid, dim3(TL_THREADS), TL_LDS_BYTES, routed);
+            return max_tok <= 16 ? launch_timed(c, kind, bytes, k_mfma_stream16_q4<W13, 1, 8, true, false, TileRouted>, grid, dim3(512), TL_LDS_BYTES, routed)
+                                 : launch_timed(c, kind, bytes, k_mfma_stream16_q4<W13, 2, 4, true, false, TileRouted>, grid, dim3(TL_THREADS), TL_LDS_BYTES, routed);
+        };
+        int32_t rc = !w ? launch_routed(std::true_type{}, bytes13, g13)
+                   : gs8 ? (max_tok <= 16 ? launch_timed(c, PROF_W13, bytes13, k_mfma_stream16_q4<true, 1, 8, true, true>, g13, dim3(512), TL_LDS_BYTES, A)
                                           : launch_timed(c, PROF_W13, bytes13, k_mfma_stream16_q4<true, 2, 4, true, true>, g13, dim3(TL_THREADS), TL_LDS_BYTES, A))
                    : t16 && gs ? (max_tok <= 16 ? launch_timed(c, PROF_W13, bytes13, k_mfma_stream16_q4<true, 1, 8, true>, g13, dim3(512), TL_LDS_BYTES, A)
                                                 : launch_timed(c, PROF_W13, bytes13, k_mfma_stream16_q4<true, 2, 4, true>, g13, dim3(TL_THREADS), TL_LDS_BYTES, A))
@@ -1737,7 +1773,8 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
             A.part_base = (int32_t)((uint64_t)batch * K + c->ypart_extra_used / b.hidden) - w0 * K;
             c->ypart_extra_used += (uint64_t)first * A.k_parts * b.hidden;
         }
-        rc = gs8 ? (max_tok <= 16 ? launch_timed(c, PROF_W2, bytes2, k_mfma_stream16_q4<false, 1, 8, true, true>, g2, dim3(512), TL_LDS_BYTES, A)
+        rc = !w ? launch_routed(std::false_type{}, bytes2, g2)
+           : gs8 ? (max_tok <= 16 ? launch_timed(c, PROF_W2, bytes2, k_mfma_stream16_q4<false, 1, 8, true, true>, g2, dim3(512), TL_LDS_BYTES, A)
                                   : launch_timed(c, PROF_W2, bytes2, k_mfma_stream16_q4<false, 2, 4, true, true>, g2, dim3(TL_THREADS), TL_LDS_BYTES, A))
            : t16 && gs ? (max_tok <= 16 ? launch_timed(c, PROF_W2, bytes2, k_mfma_stream16_q4<false, 1, 8, true>, g2, dim3(512), TL_LDS_BYTES, A)
                                         : launch_timed(c, PROF_W2, bytes2, k_mfma_stream16_q4<false, 2, 4, true>, g2, dim3(TL_THREADS), TL_LDS_BYTES, A))
@@ -1899,16 +1936,28 @@ static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts,
                    : launch_timed(c, PROF_W2, bytes2, k_mfma_rows_q4<false, 1>, gr2, blkr, rows_lds(b.ffn, 1), A);
 }
 
-static int32_t launch_ffn(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only = false,
-                          const uint8_t *const *table = nullptr, int routed = 0)
+static int32_t launch_ffn(moe_layer *l, const std::vector<FfnEntry> &entries, int nt, bool w13_only = false)
 {
     switch (fmt_of(l->lay)) {
-    case 4: return launch_ffn_fmt<4>(l, entries, nt, w13_only, table, routed);
-    case 3: return launch_ffn_fmt<3>(l, entries, nt, w13_only, table, routed);
-    case 2: return launch_ffn_fmt<2>(l, entries, nt, w13_only, table, routed);
-    case 48: return launch_ffn_fmt<48>(l, entries, nt, w13_only, table, routed);
-    case 38: return launch_ffn_fmt<38>(l, entries, nt, w13_only, table, routed);
-    case 28: return launch_ffn_fmt<28>(l, entries, nt, w13_only, table, routed);
+    case 4: return launch_ffn_fmt<4>(l, entries, nt, w13_only);
+    case 3: return launch_ffn_fmt<3>(l, entries, nt, w13_only);
+    case 2: return launch_ffn_fmt<2>(l, entries, nt, w13_only);
+    case 48: return launch_ffn_fmt<48>(l, entries, nt, w13_only);
+    case 38: return launch_ffn_fmt<38>(l, entries, nt, w13_only);
+    case 28: return launch_ffn_fmt<28>(l, entries, nt, w13_only);
+    default: return fail(MOE_EINVAL, "unsupported bit width %d", l->lay.bits);
+    }
+}
+
+static int32_t launch_ffn_routed(moe_layer *l, int nt, const uint8_t *const *table, int pairs)
+{
+    switch (fmt_of(l->lay)) {
+    case 4: return launch_ffn_routed_fmt<4>(l, nt, table, pairs);
+    case 3: return launch_ffn_routed_fmt<3>(l, nt, table, pairs);
+    case 2: return launch_ffn_routed_fmt<2>(l, nt, table, pairs);
+    case 48: return launch_ffn_routed_fmt<48>(l, nt, table, pairs);
+    case 38: return launch_ffn_routed_fmt<38>(l, nt, table, pairs);
+    case 28: return launch_ffn_routed_fmt<28>(l, nt, table, pairs);
     default: return fail(MOE_EINVAL, "unsupported bit width %d", l->lay.bits);
     }
 }
@@ -2006,12 +2055,7 @@ static int32_t device_routed_step(moe_layer *l, const uint16_t *x_in, uint16_t *
 
     const uint8_t *table[16];
     for (int e = 0; e < 16; ++e) table[e] = c->bufs[l->cache.slot_buf[l->cache.find(e < cf.n_experts ? e : 0)]].ptr;
-    std::vector<FfnEntry> entries(cf.top_k);
-    for (int j = 0; j < cf.top_k; ++j) {
-        entries[j] = FfnEntry{};
-        entries[j].n_tok = 1; entries[j].tok[0] = 0; entries[j].pair[0] = j;
-    }
-    rc = launch_ffn(l, entries, 1, true, table);
+    rc = launch_ffn_routed(l, 1, table, 0);
     if (rc) return rc;
     FusedArgs fa = token_args(l, x_in, x_out);
     fa.n_exp = cf.top_k;
@@ -2108,7 +2152,7 @@ static int32_t device_routed_batch(moe_layer *l, const uint16_t *x_in, int32_t b
     }
     rc = p.kind == BatchPlan::TILE ? launch_tile(l, all, nullptr, batch, p)
        : p.kind == BatchPlan::STREAM ? launch_mfma_stream(l, all, nullptr, batch, p)
-       : launch_ffn(l, {}, routed_nt(l, batch), false, table, pairs);
+       : launch_ffn_routed(l, routed_nt(l, batch), table, pairs);
     if (rc) return rc;
     return launch_combine(l, x_in, x_out, batch, c->route_log_dev + (size_t)slot * MOE_MAX_TOPK);
 }
