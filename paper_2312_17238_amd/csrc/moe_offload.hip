@@ -1451,13 +1451,41 @@ constexpr int64_t TILE_MIDDLE_LOW = 1 << 21, TILE_MIDDLE_HIGH = 11 << 20, TILE_T
 // plan goes by a nominal routing, the pairs dealt out evenly; an expert with more than that takes another token block.
 struct BatchPlan {
     enum Kind { GEMV, STREAM, TILE } kind = GEMV;
-    int mode = TE_BIG, parts = 1;         // TILE: tokens per block; parts that w2 splits its contraction into
+    int mode13 = TE_BIG, mode2 = TE_BIG;  // TILE: tokens per block, of w1/w3 and of w2
+    int parts = 1;                        // ... and the parts that w2 splits its contraction into
     struct Window { int parts; bool small; };
     std::vector<Window> win;              // STREAM: per window of 256 / top_k tokens, w2's parts and whether one tile of 16 tokens is enough
 };
 
 // Pairs of expert e when `pairs` of them are dealt out evenly.
 static int nominal_count(const moe_layer *l, int pairs, int e) { return pairs / l->cfg.n_experts + (e < pairs % l->cfg.n_experts); }
+
+static int tile_rows(int mode) { return mode == TE_BIG ? 256 : 128; }
+// blocks a compute unit runs at a time
+static int tile_per_cu(const BlobLayout &b, int mode) { return mode == TE_BIG || (mode == 32 && b.bits == 4 && b.group == 32) ? 1 : 2; }
+
+// One launch of a tile kernel in us: rounds of blocks, a block's start and end and its units of 64 columns.  The large kernel's
+// rounds are paid in whole (one block a compute unit), but with few blocks their tiles run faster; of the others' last round what
+// is in it counts.  An expert has more or less than its share of the pairs, in about half of the cases a 32-token tile more.
+// Fitted to which of the two ran faster, each half by itself, over 38 layers and batches.  w1/w3 and w2 at 32 tokens / at the
+// large kernel, us a step: 8 experts 4096x14336, 4-bit, top 2, 128 tokens 305 / 392, 192 370 / 429, 256 449 / 420, 512 778 / 578;
+// 2-bit, 160 tokens 359 / 507, 300 527 / 561, 512 816 / 645; 3-bit 960x960, 352 tokens 37 / 51, 3136x1792, 503 tokens 144 / 97;
+// 4-bit 256x12288, 6 experts, 306 tokens 87 / 88, with w1/w3 alone at the large one 62.  Two-level 2-bit costs the 32-token
+// kernel about twice: 2048x4096, 160 tokens 130 / 97.
+static double tile_half_us(const moe_layer *l, int batch, int mode, int n_rows, int cols, int parts)
+{
+    const BlobLayout &b = l->lay;
+    const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs), avg = pairs / n_exp;
+    const double spread = l->cfg.top_k == l->cfg.n_experts ? 0.0 : 0.45;
+    const double tiles = spread > 0.0 ? std::max(1.0, avg / 32 + spread) : std::ceil(avg / 32);        // of 32 tokens, an expert's
+    const double blocks = mode == TE_BIG ? tile_blocks(b, (int)std::ceil(avg), mode) : tiles;
+    const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
+    const int row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
+    const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
+    if (mode != TE_BIG) return std::max(1.0, rounds) * (2.5 + units * 0.54 * (b.bits != 2 ? 1.0 : b.scale_group ? 2.1 : 0.86));
+    const double half_tiles = std::max(1.0, tiles / blocks / 2 + 0.25), whole = std::ceil(rounds);     // tiles of a block's fuller half
+    return whole * 3.7 + units * 0.52 * (whole + half_tiles * std::max(rounds, 0.32 * whole));
+}
 
 // Tile kernels: tokens per block, and into how many parts w2 splits its contraction.
 static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
@@ -1467,28 +1495,35 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     const int E = l->cfg.n_experts, pairs = batch * l->cfg.top_k;
     // Where every token needs every expert the tokens of one are known.  Otherwise they spread around the average, and a kernel
     // for more tokens than that on average is the better one before experts that need a second block of the smaller become many.
+    // (groups of 32 have no large kernel: twice the metadata does not fit beside its tokens)
     const bool exact = l->cfg.top_k == E;
     const double avg = (double)pairs / E;
-    // (groups of 32 have no large kernel: twice the metadata does not fit beside its tokens)
-    p.mode = avg > (exact ? 32 : TILE_MODE32_AVERAGE) && !(b.bits == 4 && b.group == 32) ? TE_BIG : (avg > (exact ? 16 : 12) ? 32 : 16);
-    int blocks = 0;
-    for (int e = 0; e < E; ++e) blocks += tile_blocks(b, nominal_count(l, pairs, e), p.mode);
-    const int rows = p.mode == TE_BIG ? 256 : 128, rb = (b.hidden + rows - 1) / rows;
+    const bool many = avg > (exact ? 32 : TILE_MODE32_AVERAGE) && !(b.bits == 4 && b.group == 32);
     const int sets = (b.ffn / 64 + 3) / 4;
     const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
     // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
     // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
     // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
     // 226 + 14 (4).
-    const bool alone = p.mode == TE_BIG || (p.mode == 32 && b.bits == 4 && b.group == 32);       // one block a compute unit
-    const int slots = n_cu_of(c) * (alone ? 1 : 2);
-    double best = 0.0;
-    p.parts = 1;
-    for (int n = 1; n <= std::min(std::min(8, sets), cap); ++n) {
-        const int items = rb * blocks * n, rounds = (items + slots - 1) / slots;
-        const double eff = (double)items / ((double)rounds * slots) / (1.0 + 0.03 * n);
-        if (eff > best) { best = eff; p.parts = n; }
-    }
+    auto best_parts = [&](int mode) {
+        int blocks = 0, parts = 1;
+        for (int e = 0; e < E; ++e) blocks += tile_blocks(b, nominal_count(l, pairs, e), mode);
+        const int rb = (b.hidden + tile_rows(mode) - 1) / tile_rows(mode), slots = n_cu_of(c) * tile_per_cu(b, mode);
+        double best = 0.0;
+        for (int n = 1; n <= std::min(std::min(8, sets), cap); ++n) {
+            const int items = rb * blocks * n, rounds = (items + slots - 1) / slots;
+            const double eff = (double)items / ((double)rounds * slots) / (1.0 + 0.03 * n);
+            if (eff > best) { best = eff; parts = n; }
+        }
+        return parts;
+    };
+    p.mode13 = p.mode2 = avg > (exact ? 16 : 12) ? 32 : 16;
+    p.parts = best_parts(p.mode2);
+    if (!many) return;
+    // (the 32-token kernel where it is faster by more than the fit's error)
+    const int big_parts = best_parts(TE_BIG);
+    if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < 1.05 * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
+    if (tile_half_us(l, batch, TE_BIG, b.hidden, b.ffn, big_parts) < 1.05 * tile_half_us(l, batch, 32, b.hidden, b.ffn, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
 }
 
 // The 16-token (streaming) kernels' windows: how many parts the w2 launches of a window split their contraction into, and
@@ -1540,30 +1575,27 @@ static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
 {
     const BlobLayout &b = l->lay;
     const int n_cu = n_cu_of(l->ctx), pairs = batch * l->cfg.top_k;
-    const bool big = p.mode == TE_BIG;
-    const int rows = big ? 256 : 128, slots = n_cu * (big ? 1 : 2);
+    const bool big = p.mode13 == TE_BIG;
     const double two_level = b.scale_group > 0 ? 1.0 : 0.0;
-    int blocks = 0, halves = 0;                  // token blocks; token tiles of a block's fuller half, added up over them
-    for (int e = 0; e < l->cfg.n_experts; ++e) {
-        const int count = nominal_count(l, pairs, e);
-        if (!count) continue;
-        const int tb = tile_blocks(b, count, p.mode), tiles = (count + 31) / 32;
-        blocks += tb;
-        halves += tb * (((tiles + tb - 1) / tb + 1) / 2);
-    }
-    double rounds = 0.0, x = 0.0;                // of blocks, the last one whole or by its share, times their columns / 4096
-    auto half = [&](int n_rows, int cols, int parts) {
+    double us = big ? 40.0 + 0.057 * batch : 41.0 + 0.05 * batch;
+    auto half = [&](int mode, int n_rows, int cols, int parts) {
+        int blocks = 0, halves = 0;              // token blocks; token tiles of a block's fuller half, added up over them
+        for (int e = 0; e < l->cfg.n_experts; ++e) {
+            const int count = nominal_count(l, pairs, e);
+            if (!count) continue;
+            const int tb = tile_blocks(b, count, mode), tiles = (count + 31) / 32;
+            blocks += tb;
+            halves += tb * (((tiles + tb - 1) / tb + 1) / 2);
+        }
         const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
-        const int items = (n_rows + rows - 1) / rows * blocks * k_parts;
-        const double k = part_sets * 256 / 4096.0;
-        rounds += (items + slots - 1) / slots * k;
-        x += (double)items / slots * k;
+        const int items = (n_rows + tile_rows(mode) - 1) / tile_rows(mode) * blocks * k_parts, slots = n_cu * tile_per_cu(b, mode);
+        // rounds of blocks, the last one whole (rounds) or by its share (x), times their columns / 4096
+        const double k = part_sets * 256 / 4096.0, rounds = (items + slots - 1) / slots * k, x = (double)items / slots * k, tiles = (double)halves / blocks;
+        us += mode == TE_BIG ? rounds * (33.0 + 26.0 * tiles + 4.5 * two_level) + x * (24.0 - 7.6 * tiles) : rounds * (11.0 + 3.5 * two_level) + x * 28.0;
     };
-    half(2 * b.ffn, b.hidden, 1);
-    half(b.hidden, b.ffn, p.parts);
-    const double tiles = (double)halves / blocks;
-    return big ? 40.0 + rounds * (33.0 + 26.0 * tiles + 4.5 * two_level) + x * (24.0 - 7.6 * tiles) + 0.057 * batch
-               : 41.0 + rounds * (11.0 + 3.5 * two_level) + x * 28.0 + 0.05 * batch;
+    half(p.mode13, 2 * b.ffn, b.hidden, 1);
+    half(p.mode2, b.hidden, b.ffn, p.parts);
+    return us;
 }
 
 // Whether the tile kernels may run a step.  Times of a step in us, everything resident, GEMV kernels / tile kernels.
@@ -1579,7 +1611,10 @@ static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
 // 4-bit group 64: beside the 16-token kernels' steps.  Layers of middle size are faster on the tile kernels at any batch
 // (16-token / tile kernels: 1024 x 4096, 16 tokens 37 / 32, 64 tokens 46 / 37; 4096 x 1792 46 / 42 and 59 / 49; two-level 40 / 34 and 49 / 38), larger ones only
 // where the 16-token kernels need tiles of 32 (16 tokens: 2048 x 5056 50 / 49, 2048 x 7168 60 / 62, 4096 x 14336 148 / 167; 64 tokens: 2048 x 7168
-// 78 / 74, 1024 x 16384 88 / 87, 4096 x 14336 205 / 210), the smallest gain little (512 x 1024 23 / 22).  Elsewhere with more than 32 (two-level: 16) tokens of an expert on average, if the estimates say so.
+// 78 / 74, 1024 x 16384 88 / 87, 4096 x 14336 205 / 210), the smallest gain little (512 x 1024 23 / 22).  From the average at
+// which many experts need a second tile of 32 they take the tile kernels whatever their size (28 tokens of an expert: 1024 x 4096
+// 54 / 42, 2048 x 7168 92 / 85, 4096 x 14336 265 / 254, 6144 x 16384 399 / 398; 36: 4096 x 14336 445 / 329; two-level 314 / 292
+// and 541 / 372).  Elsewhere with more than 32 (two-level: 16) tokens of an expert on average, if the estimates say so.
 static bool tile_may(const moe_layer *l, int batch, bool stream, bool *surely)
 {
     const moe_layer_config_t &cf = l->cfg;
@@ -1589,6 +1624,7 @@ static bool tile_may(const moe_layer *l, int batch, bool stream, bool *surely)
     if (stream) {
         const bool two_tiles = pairs > STREAM_SMALL_AVERAGE * cf.n_experts;
         if (size > TILE_MIDDLE_LOW && size <= (two_tiles ? TILE_TWO_TILES_HIGH : TILE_MIDDLE_HIGH) && pairs <= TILE_MODE32_AVERAGE * cf.n_experts) return true;
+        if (size > TILE_MIDDLE_LOW && pairs > TILE_MODE32_AVERAGE * cf.n_experts) return true;
         *surely = false;
         return pairs > (cf.scale_group ? 16 : 32) * cf.n_experts;
     }
@@ -1837,19 +1873,18 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     const int K = l->cfg.top_k, E = l->cfg.n_experts, pairs = batch * K, xg = tile_sum_group(b);
     TeArgs A{};
     for (const PassExpert &pe : experts) { A.blob[pe.expert] = pe.blob; A.experts |= 1u << pe.expert; }
-    const int mode = plan.mode, rows = mode == TE_BIG ? 256 : 128;
-    int token_blocks = 0;
-    if (idx) {
-        int count[MOE_MAX_EXPERTS] = {0};
-        for (int q = 0; q < pairs; ++q) count[idx[q]]++;
-        for (const PassExpert &pe : experts) token_blocks += tile_blocks(b, count[pe.expert], mode);
-    } else {
+    int count[MOE_MAX_EXPERTS] = {0};
+    for (int q = 0; q < pairs && idx; ++q) count[idx[q]]++;
+    auto token_blocks = [&](int mode) {
+        int n = 0;
+        for (const PassExpert &pe : experts) n += tile_blocks(b, count[pe.expert], mode);
+        if (idx) return n;
         // every expert's first token opens a block, and from then on it takes a block's worth of further ones to open another
         const int own = std::min(E, pairs), per = mode == TE_BIG ? (tile_blocks(b, 192, mode) == 1 ? 192 : 128) : mode;
-        token_blocks = K == E ? E * tile_blocks(b, batch, mode) : own + (pairs - own) / per;
-    }
+        return K == E ? E * tile_blocks(b, batch, mode) : own + (pairs - own) / per;
+    };
     A.n_pairs = pairs; A.n_experts = E;
-    if (pairs <= FEW_PAIRS) A.pair_expert = c->pair_expert;
+    if (pairs <= FEW_PAIRS) A.pair_expert = c->pair_expert;          // else k_sort_pairs' list (launch_sort)
     A.first = c->pair_first;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
     A.lift = tile_lift(l); A.lower = 1.f / A.lift;
@@ -1861,14 +1896,16 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
         A.run_shift = (m.run_len == 0 || m.run_len >= m.cols / (uint32_t)b.group) ? 31 : __builtin_ctz(m.run_len);
         A.xs_stride = tile_sum_stride(Kdim, xg);
     };
-    // items: (row block, part) jobs dealt to the XCDs round robin, an expert's token blocks of one job next to each other
-    auto shape = [&](int row_blocks, int parts) {
+    // (parts: of w2; 0: w1/w3) items: (row block, part) jobs dealt to the XCDs round robin, an expert's token blocks of one job next to each other
+    auto shape = [&](int mode, int parts) {
+        const int n_rows = parts ? A.N : 2 * A.N, row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
+        parts = std::max(parts, 1);
         const int sets = (A.K / 64 + 3) / 4, sp = (sets + parts - 1) / parts;
         A.units_per_part = sp * 4;
         A.k_parts = (sets + sp - 1) / sp;
         A.jobs = row_blocks * A.k_parts;
         A.per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
-        return A.per_xcd * token_blocks * TE_XCD;
+        return A.per_xcd * token_blocks(mode) * TE_XCD;
     };
     const uint64_t n_exp = experts.size();
     matrix(b.m13, b.hidden, b.ffn);
@@ -1876,13 +1913,13 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     A.act = c->h_buf; A.act_bytes = (uint32_t)batch * b.hidden * 2;
     A.xs = c->xs_h; A.xs_bytes = (uint32_t)batch * A.xs_stride * 8;
     A.xs_out = c->xs_a; A.xs_out_stride = tile_sum_stride(b.ffn, xg);
-    int32_t rc = launch_tile_half<true>(l, mode, shape((2 * b.ffn + rows - 1) / rows, 1), n_exp * 2 * b.ffn * b.m13.row_stride, A);
+    int32_t rc = launch_tile_half<true>(l, plan.mode13, shape(plan.mode13, 0), n_exp * 2 * b.ffn * b.m13.row_stride, A);
     if (rc) return rc;
     matrix(b.m2, b.ffn, b.hidden);
     A.mat_off = b.off_w2;
     A.act = c->a_buf; A.act_bytes = (uint32_t)pairs * b.ffn * 2;
     A.xs = c->xs_a; A.xs_bytes = (uint32_t)pairs * A.xs_stride * 8;
-    return launch_tile_half<false>(l, mode, shape((b.hidden + rows - 1) / rows, plan.parts), n_exp * b.hidden * b.m2.row_stride, A);
+    return launch_tile_half<false>(l, plan.mode2, shape(plan.mode2, plan.parts), n_exp * b.hidden * b.m2.row_stride, A);
 }
 
 static int32_t launch_mfma(moe_layer *l, const std::vector<PassExpert> &experts, const int32_t *idx, const float *w, int batch, const BatchPlan &plan)
