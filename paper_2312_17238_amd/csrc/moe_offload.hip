@@ -1494,7 +1494,8 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     const BlobLayout &b = l->lay;
     const int E = l->cfg.n_experts, pairs = batch * l->cfg.top_k;
     // Where every token needs every expert the tokens of one are known.  Otherwise they spread around the average, and a kernel
-    // for more tokens than that on average is the better one before experts that need a second block of the smaller become many.
+    // for more tokens than that on average is the better one before experts that need a second block of the smaller become many;
+    // from there on the estimates decide, each half by itself.
     // (groups of 32 have no large kernel: twice the metadata does not fit beside its tokens)
     const bool exact = l->cfg.top_k == E;
     const double avg = (double)pairs / E;
@@ -1623,8 +1624,8 @@ static bool tile_may(const moe_layer *l, int batch, bool stream, bool *surely)
     *surely = true;
     if (stream) {
         const bool two_tiles = pairs > STREAM_SMALL_AVERAGE * cf.n_experts;
-        if (size > TILE_MIDDLE_LOW && size <= (two_tiles ? TILE_TWO_TILES_HIGH : TILE_MIDDLE_HIGH) && pairs <= TILE_MODE32_AVERAGE * cf.n_experts) return true;
-        if (size > TILE_MIDDLE_LOW && pairs > TILE_MODE32_AVERAGE * cf.n_experts) return true;
+        const bool middle = size <= (two_tiles ? TILE_TWO_TILES_HIGH : TILE_MIDDLE_HIGH);
+        if (size > TILE_MIDDLE_LOW && (middle || pairs > TILE_MODE32_AVERAGE * cf.n_experts)) return true;
         *surely = false;
         return pairs > (cf.scale_group ? 16 : 32) * cf.n_experts;
     }
@@ -2158,7 +2159,17 @@ static bool device_routed_plan_fits(const moe_layer *l, int batch, const BatchPl
     // one window; the other forms and matrices the 16-token kernels do not address find no routing in device memory
     const bool fits32 = 2ull * l->lay.ffn * l->lay.m13.row_stride < (1ull << 31) && (uint64_t)l->lay.hidden * l->lay.m2.row_stride < (1ull << 31);
     if (p.kind == BatchPlan::STREAM) return (c->mfma_form == 0 || c->mfma_form == 5) && p.win.size() == 1 && fits32;
-    // GEMV kernels: a block for every entry there can be, so a few dozen pairs at most
+    // GEMV kernels: a block for every entry there can be, so a few dozen pairs at most.  Their entries take two tokens or more, and a
+    // host that has seen that no expert has two launches the one-token kernels instead: in large layers, where that is likely, those
+    // are worth the wait.  us a step, 8 experts, waiting / queued: 2 tokens top 2 4-bit 2048x8192 37 / 35, 3072x8192 44 / 50, 4096x14336
+    // 70 / 77; 3-bit 2048x4096 34 / 32, 2048x8192 43 / 46, 4096x14336 72 / 79; two-level 2-bit 2048x4096 34 / 35, 2048x8192 44 / 50; 2 tokens top 1
+    // 3-bit 4096x14336 43 / 51; 3 tokens top 2 (one in nine steps without a shared expert) 3-bit 4096x14336 121 / 100.
+    double apart = 1.0;                          // probability that no expert has two tokens, all sets of top_k alike
+    for (int t = 1; t < batch && apart > 0.0; ++t)
+        for (int k = 0; k < l->cfg.top_k; ++k)
+            apart *= std::max(0.0, (double)(l->cfg.n_experts - t * l->cfg.top_k - k) / (l->cfg.n_experts - k));
+    const bool heavy = l->lay.bits == 3 || (l->lay.bits == 2 && l->lay.scale_group);         // a second token costs these more
+    if (apart > 0.3 && (int64_t)l->cfg.hidden * l->cfg.ffn > (heavy ? 8 << 20 : 16 << 20)) return false;
     return pairs <= 64 && routed_nt(l, batch) > 0 && chunks_per_lane(l->lay.hidden, fmt_of(l->lay)) > 0 &&
            (l->lay.ffn / codes_per_chunk(fmt_of(l->lay)) + 63) / 64 <= 8;
 }
