@@ -212,15 +212,14 @@ __device__ __forceinline__ uint32_t split2(float v)
     return __builtin_bit_cast(uint32_t, p);
 }
 
-// ... as three bf16 that together are the number, cut off one behind the other (8 bits each): x holds the first two, y the
-// third in both halves.
+// ... as three bf16 that together are the number: x holds split2's, y the third in both halves.
 __device__ __forceinline__ uint2 split3(float v)
 {
-    const uint32_t b0 = __builtin_bit_cast(uint32_t, v) & 0xffff0000u;
-    const float r1 = v - __builtin_bit_cast(float, b0);
-    const uint32_t b1 = __builtin_bit_cast(uint32_t, r1) & 0xffff0000u;
-    const uint32_t b2 = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b1));
-    return make_uint2(__builtin_amdgcn_perm(b1, b0, 0x07060302u), __builtin_amdgcn_perm(b2, b2, 0x03020302u));
+    const __bf16 h = (__bf16)v;
+    const float r = v - (float)h;
+    const __bf16 l = (__bf16)r, t = (__bf16)(r - (float)l);
+    const bf2_t p = {h, l}, q = {t, t};
+    return make_uint2(__builtin_bit_cast(uint32_t, p), __builtin_bit_cast(uint32_t, q));
 }
 
 // A word that an earlier launch left in memory, at an address all lanes share, through the scalar cache (empty at a launch's start).

@@ -14,21 +14,23 @@
 //
 // Arithmetic.  A weight is s (q - z) with real z, and with any constant ZC
 //     sum_k s (q - z) x  =  sum_groups s (sum_k (q - ZC) x)  +  sum_groups s (ZC - z) X,     X = sum of the group's x.
-// 3 and 4 bits (groups of 64 codes or more), ZC = -64: a code enters the matrix cores as the fp16 number 64 + q that its
-// bits spell under the exponent of 64, which costs a shift and a v_and_or_b32 per pair, no subtraction (a bias of 1024 for half of
-// the codes would save two shifts a word, but makes the sums so large that their rounding shows in y).  The group's product comes out
+// 3 and 4 bits, ZC = 4 and 8: a code's bits under the exponent of 64 or 1024 are the fp16 numbers 64 + q and 1024 + q, bias and ZC are
+// subtracted packed (codes_centred, nine instructions a word of eight).  q - ZC is exact.  The group's product comes out
 // in fp32 and is scaled by the fp32 s with one fused multiply-add per accumulator register; no weight is rounded.
+// The subtraction is there for the error.  Codes that enter as 64 + q make the products some fourteen times as large, and the matrix
+// cores' roundings with them, which have one sign where the tokens have a mean: the error then grows with the length of the
+// contraction (4096 x 14336, 4-bit, below: 4.8e-5, and 24e-5 at a mean of eight deviations; minus the bias's share as a product's
+// start, one more matrix instruction, leaves 2.3 to 2.9e-5).  It costs 1 to 3 %: 1024 tokens 4-bit 1042 -> 1073 us a step, 512 tokens 3-bit
+// 605 -> 616, 37 tokens two-level 49.6 -> 50.3, 16 tokens 3-bit 183.4 -> 184.3.
 // (Codes as the subnormal fp16 numbers their bits spell need no exponent, but the matrix cores accumulate products of
 // subnormals with fewer bits: 6 % more error in y.)
 // Groups of 32 (4 bits, tiles of 16 and 32 tokens): two products of half the length per unit, a lane half or quarter holding its share of either group.
 // 2-bit codes (groups of 16; ZC = 1): q - 1 is one of -1, 0, 1, 2 and (q - 1) s is exact in fp16 for an fp16 s, so the
 // scaled weight goes in directly; an fp32 s (two-level metadata) goes in as two fp16 numbers, in two products.
-// Second term: a contraction over groups instead of codes, on the bf16 matrix instructions.  With ZC = -64 it is some twenty times
-// the result, so X and D = s (ZC - z) go in whole, cut into three bf16 each: eight k-slots a group (slots3_x, slots3_d) hold all
-// products but that of the third parts.  2-bit codes: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the
-// result), the four k-slots (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl).  Correcting every group's product in the accumulators instead
-// would double the vector work per group; starting the products from minus the biases' share takes four more LDS reads per token
-// tile and unit (that, and centred codes in the large kernel, is what these kernels did before: 1024 tokens 4-bit 684 + 351 us).
+// Second term: a contraction over groups instead of codes, on the bf16 matrix instructions.  3 and 4 bits: X and D = s (ZC - z) go in
+// whole, cut into three bf16 each: eight k-slots a group (slots3_x, slots3_d) hold all products but that of the third parts.  2-bit
+// codes: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the result), the four k-slots
+// (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl).  Correcting every group's product in the accumulators instead would double the vector work per group.
 // The X come from whoever produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros
 // to a multiple of four groups.
 //
@@ -42,10 +44,11 @@
 // vector unit 54 %, of it a quarter for the metadata.
 //
 // Error of this arithmetic alone: y of a layer against 64 bits with the activations between the halves rounded to fp16 as
-// here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), 1024 x 3584 to
-// 4096 x 14336, eight seeds, tokens as the decode workloads draw them.  4-bit: BIG 3.8e-5, MODE 16 and 32 4.3 to 5.2e-5 (GEMV and 16-token
-// kernels 9.1 to 9.8e-5); 3-bit 6.3e-5 (GEMV 17.7e-5); 2-bit 3.6 to 4.0e-5 (GEMV 11e-5).  With the rounding of a, the error of y: 4-bit
-// 2.07 to 2.08e-4 (others 2.08 to 2.10e-4), 3-bit 2.07e-4 (GEMV 2.21e-4), 2-bit 2.09e-4 (2.11e-4).
+// here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), one expert of 1024 x 4096
+// and of 4096 x 14336, every format, 16, 32 and 192 tokens, two seeds.  Normalised tokens of mean 0, as the decode workloads draw them / of a
+// mean of a tenth of the deviation / of mean 1 and deviation 1/8, in 1e-5: 4-bit 0.5 to 2.4 / 0.6 to 1.5 / 0.8 to 2.2 (GEMV kernels 8.6 to 10 /
+// 8.6 to 10 / 14 to 17), 3-bit 0.5 to 1.4 / 0.4 to 1.4 / 1.1 to 2.8 (GEMV 17 to 18 / 19 / 41), 2-bit 3.7 to 4.3 / 3.7 to 4.4 / 6.3 to 7.3
+// (GEMV 11 / 11 / 2.9: the two bf16 of X and D).  With the rounding of a, the error of y at mean 0 is 2.07 to 2.1e-4 (GEMV 2.08 to 2.2e-4).
 //
 // BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
 // other at the end of the unit before, so that one's vector work runs under the other's matrix work.
@@ -104,7 +107,7 @@ __device__ __forceinline__ uint4 bl128(__amdgpu_buffer_rsrc_t r, uint32_t v, int
 constexpr uint32_t TE_NONE = 0x80000000u;    // an offset past every buffer's end: zeros, no request
 
 // Contraction over groups, 3- and 4-bit codes: the eight k-slots of one group, from split3 of X and D (first, second, third
-// part): X as (0 1 0 1 0 1 2 2), D as (0 0 1 1 2 2 0 1): all products but that of the third parts.
+// part): X as (0 1 0 1 0 1 2 2), D as (0 0 1 1 2 2 0 1): all products but that of the third parts.  (Or the other way round.)
 __device__ __forceinline__ bf8_t slots3_x(uint2 v)
 {
     const u32x4_t r = {v.x, v.x, v.x, v.y};
@@ -128,19 +131,25 @@ __device__ __forceinline__ bf8_t slots_d(uint2 v)
     return __builtin_bit_cast(bf8_t, r);
 }
 
-// Eight codes of a word in the 4-bit layout as the fp16 numbers 64 + q, in codes_biased's slots.  m: the bits of a code, 0x00F000F0, or
-// 0x00700070 where bit 3 of a field is not the code's.
-struct Bias64 { uint32_t m, k; };
-__device__ __forceinline__ Bias64 bias64(uint32_t m)
+// Eight codes of a word in the 4-bit layout as the fp16 numbers q - ZC, in codes_biased's slots: their bits under the exponent of 1024
+// or of 64, and the bias and ZC subtracted.  With 3 bits, bit 3 of a field is not the code's.
+struct CentredPatterns { uint32_t m_lo, m_hi, k1024, k64; };
+template <int BITS> __device__ __forceinline__ CentredPatterns centred_patterns()
 {
-    Bias64 p = {m, 0x54005400u};
-    asm("" : "+s"(p.m), "+v"(p.k));
+    constexpr uint32_t F = (1u << BITS) - 1u;
+    CentredPatterns p = {F * 0x00010001u, F * 0x00100010u, 0x64006400u, 0x54005400u};
+    asm("" : "+s"(p.m_lo), "+s"(p.m_hi), "+v"(p.k1024), "+v"(p.k64));
     return p;
 }
-__device__ __forceinline__ h8_t codes_biased64(uint32_t w, const Bias64 &p)
+template <int BITS> __device__ __forceinline__ h8_t codes_centred(uint32_t w, const CentredPatterns &p)
 {
-    const u32x4_t r = {((w << 4) & p.m) | p.k, (w & p.m) | p.k, ((w >> 4) & p.m) | p.k, ((w >> 8) & p.m) | p.k};
-    return __builtin_bit_cast(h8_t, r);
+    constexpr uint32_t C1024 = BITS == 4 ? 0xE408E408u : 0xE404E404u, C64 = BITS == 4 ? 0xD480D480u : 0xD440D440u;      // -1024 - ZC, -64 - ZC
+    const uint32_t hi = w >> 8;
+    const h2_t r0 = as_h2((w & p.m_lo) | p.k1024) + as_h2(C1024), r1 = as_h2((w & p.m_hi) | p.k64) + as_h2(C64);
+    const h2_t r2 = as_h2((hi & p.m_lo) | p.k1024) + as_h2(C1024), r3 = as_h2((hi & p.m_hi) | p.k64) + as_h2(C64);
+    h8_t r;
+    r[0] = r0.x; r[1] = r0.y; r[2] = r1.x; r[3] = r1.y; r[4] = r2.x; r[5] = r2.y; r[6] = r3.x; r[7] = r3.y;
+    return r;
 }
 
 // What the format policies know of a matrix: offsets inside a row, units of a row.  Loads of codes address with one
@@ -193,8 +202,9 @@ template <int N> struct TeMeta2<true, N> {
 
 template <int FMT, int ROWS, int THREADS> struct Te;
 
-template <bool META8, int ROWS, int THREADS, int G = 1>
+template <bool META8, int ROWS, int THREADS, int BITS, int G = 1>
 struct TeScaled {                        // the part that 4-bit and 3-bit formats share
+    static constexpr float ZC = float(1 << (BITS - 1));                  // what the codes are centred on
     static constexpr bool GS = true;
     static constexpr int GPU = G, PLANES = 1, DB = 32 * G;               // groups per unit; bytes of D per row and set
     static constexpr bool LIFTED = false;
@@ -217,13 +227,13 @@ struct TeScaled {                        // the part that 4-bit and 3-bit format
             if constexpr (G == 1) {
                 meta.get(i, s, z);
                 *reinterpret_cast<float *>(rec + (tid / 4) * REC + (tid % 4) * 4 + SOFF + i * (THREADS / 4) * REC) = s;
-                *reinterpret_cast<uint2 *>(d + tid * 8 + i * THREADS * 8) = split3(s * (-64.f - z));
+                *reinterpret_cast<uint2 *>(d + tid * 8 + i * THREADS * 8) = split3(s * (ZC - z));
             } else {
                 float s1, z1;
                 meta.get(i, 0, s, z);
                 meta.get(i, 1, s1, z1);
                 *reinterpret_cast<float2 *>(rec + (tid / 4) * REC + (tid % 4) * 8 + SOFF + i * (THREADS / 4) * REC) = make_float2(s, s1);
-                const uint2 d0 = split3(s * (-64.f - z)), d1 = split3(s1 * (-64.f - z1));
+                const uint2 d0 = split3(s * (ZC - z)), d1 = split3(s1 * (ZC - z1));
                 *reinterpret_cast<uint4 *>(d + tid * 16 + i * THREADS * 16) = make_uint4(d0.x, d0.y, d1.x, d1.y);
             }
         }
@@ -231,8 +241,8 @@ struct TeScaled {                        // the part that 4-bit and 3-bit format
 };
 
 template <bool META8, int ROWS, int THREADS, int G = 1>
-struct Te4 : TeScaled<META8, ROWS, THREADS, G> {
-    static constexpr uint32_t FIELD = 0x00F000F0u;
+struct Te4 : TeScaled<META8, ROWS, THREADS, 4, G> {
+    static constexpr uint32_t BITS = 4;
     static constexpr int SOFF = 128, REC = G == 1 ? 144 : 176, NC = ROWS * 8 / THREADS;
     uint4 c[NC];
     struct Raw { uint4 q; };
@@ -280,8 +290,8 @@ template <int R, int T> struct Te<5, R, T> : Te4<false, R, T, 2> {};      // 4-b
 template <int R, int T> struct Te<58, R, T> : Te4<true, R, T, 2> {};
 
 template <bool META8, int ROWS, int THREADS>
-struct Te3 : TeScaled<META8, ROWS, THREADS> {
-    static constexpr uint32_t FIELD = 0x00700070u;
+struct Te3 : TeScaled<META8, ROWS, THREADS, 3> {
+    static constexpr uint32_t BITS = 3;
     static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS;
     static constexpr bool HALF = ROWS * 4 == THREADS;                    // region B: 8 or 16 bytes per thread
     static_assert(NA >= 1 && (HALF || ROWS * 2 == THREADS), "region B is one piece per thread");
@@ -358,7 +368,7 @@ __device__ __forceinline__ void centred2(uint32_t w, const Patterns2 &p, h2_t (&
 template <bool META8, int ROWS, int THREADS>
 struct Te2 {
     static constexpr bool GS = false;
-    static constexpr uint32_t FIELD = 0;
+    static constexpr uint32_t BITS = 2;
     static constexpr int GPU = 4, PLANES = META8 ? 2 : 1, DB = META8 ? 80 : 0, REC = 144, SOFF = 0;   // one-level: D from the record's (scale, zero)
     static constexpr int NC = ROWS * 8 / THREADS, NA = ROWS * 4 / THREADS;
     // two-level scales are split into two fp16, lifted by the layer's own power of two first (the host chooses it: the
@@ -626,8 +636,10 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         if constexpr (F::GS) *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = t.x;
         else *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
     };
+    // (the large kernel works the address of its 4-bit records out for every set: kept, it does not fit the registers; 1024 tokens 1082 -> 1073 us)
+    auto again = [&](int v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); return v; };
     // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
-    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, A.lift, tid); };
+    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, A.lift, BIG && F::BITS == 4 ? again(tid) : tid); };
 
     // Left alone the scheduler moves a step's loads down to just before the LDS stores that wait for them: requests stay
     // above the first mark, stores below the second; everything else may cross.
@@ -636,7 +648,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
 
     // ---------------- multiply ----------------
     const uint8_t *const my_rec = lds + C::OFF_B + (rg * C::RGR + col) * C::REC;      // + 32 rows: the wave's second tile
-    const Bias64 bp = bias64(F::FIELD);
+    const CentredPatterns cp = centred_patterns<F::BITS>();
     auto unpack = [&](h8_t (&b)[2][F::PLANES][4], int bb, int u) __attribute__((always_inline)) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
@@ -646,7 +658,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 uint32_t t[4];
                 F::words(raw, t);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) b[rt][0][k] = codes_biased64(t[k], bp);
+                for (int k = 0; k < 4; ++k) b[rt][0][k] = codes_centred<F::BITS>(t[k], cp);
             } else {
                 F::decode(raw, b[rt]);
             }
@@ -897,7 +909,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
 #pragma unroll
                         for (int i = 0; i < NR; ++i) g[i] = 0.f;
 #pragma unroll
-                        for (int k = j * KG; k < (j + 1) * KG; ++k) g = mm(a[k], codes_biased64(t[k], bp), g);
+                        for (int k = j * KG; k < (j + 1) * KG; ++k) g = mm(a[k], codes_centred<F::BITS>(t[k], cp), g);
 #pragma unroll
                         for (int i = 0; i < NR; ++i) tot[rt][i] = __builtin_fmaf(sc[j], g[i], tot[rt][i]);
                     }
@@ -939,13 +951,14 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         };
         // GS: the zero-point term of a set: four groups in one matrix instruction per row tile, or two with tiles of 32
         auto set_term = [&](int bb) __attribute__((always_inline)) {
+            constexpr int PER = MODE / 16 * F::GPU / (MODE == 32 ? 2 : 1);
 #pragma unroll
-            for (int p = 0; p < MODE / 16 * F::GPU; ++p) {
-                const int g = p * (64 / MODE) + kb;
-                const bf8_t xv = slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + g * 8));
+            for (int p = 0; p < PER; ++p) {
+                const int g = MODE == 32 ? (half * PER + p) * 2 + kb : p * 4 + kb;
+                const bf8_t xv = slots3_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + g * 8));
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
-                    tot[rt] = mmb(xv, slots3_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * RROWS + rcol) * F::DB + g * 8)), tot[rt]);
+                    tot[rt] = mmb(xv, slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * RROWS + rcol) * F::DB + g * 8)), tot[rt]);
             }
         };
         // Two sets are on their way, activations as well as weights (one alone takes longer to arrive than a set to multiply)
@@ -972,7 +985,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             loads_above();
 #pragma unroll
             for (int un = 0; un < 4; un += C::KW) unit(bb, un + half);
-            if constexpr (F::GS) if (half == bb) set_term(bb);
+            if constexpr (F::GS) if (MODE == 32 || half == bb) set_term(bb);
             stores_below();
             commit(fout, tout, bb ^ 1, u + 4);
             __syncthreads();
