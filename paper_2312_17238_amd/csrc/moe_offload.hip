@@ -2189,8 +2189,6 @@ static int32_t device_routed_batch(moe_layer *l, const uint16_t *x_in, int32_t b
     int32_t rc = launch_gate(c, ga, batch);
     if (rc) return rc;
     if (p.kind == BatchPlan::TILE) { rc = launch_sort(c, pairs); if (rc) return rc; }
-    c->pending.push_back({l, slot, true});
-    l->steps_device_routed++;
     c->ypart_extra_used = 0;
     std::vector<PassExpert> all(cf.n_experts);
     const uint8_t *table[16];
@@ -2202,7 +2200,11 @@ static int32_t device_routed_batch(moe_layer *l, const uint16_t *x_in, int32_t b
        : p.kind == BatchPlan::STREAM ? launch_mfma_stream(l, all, nullptr, batch, p)
        : launch_ffn_routed(l, routed_nt(l, batch), table, pairs);
     if (rc) return rc;
-    return launch_combine(l, x_in, x_out, batch, c->route_log_dev + (size_t)slot * MOE_MAX_TOPK);
+    rc = launch_combine(l, x_in, x_out, batch, c->route_log_dev + (size_t)slot * MOE_MAX_TOPK);
+    if (rc) return rc;
+    c->pending.push_back({l, slot, true});          // not before the launch that writes its log word is queued
+    l->steps_device_routed++;
+    return MOE_OK;
 }
 
 // One decode step of one layer.  plain: the variant for callers that cannot allocate -- the host waits for the gate
