@@ -193,7 +193,8 @@ struct moe_ctx {
     float *route_w = nullptr;           // device: ... and combine weights
     int32_t *route_log = nullptr;       // pinned host copy of the ring below, refreshed when the bookkeeping catches up
     int32_t *route_log_dev = nullptr;   // device ring of ROUTE_LOG entries of MOE_MAX_TOPK selections, written by the gate kernel
-    struct PendingStep { moe_layer *layer; uint32_t slot; bool batch; };   // batch: the slot's first word has one bit per expert needed
+    // batch: the slot's first word has one bit per expert needed; timed: its launches' bytes are still to be counted (moe_profile_t)
+    struct PendingStep { moe_layer *layer; uint32_t slot; bool batch, timed; };
     std::vector<PendingStep> pending;   // steps enqueued that way whose bookkeeping is still to be done, oldest first
     static constexpr uint32_t ROUTE_LOG = ROUTE_LOG_ENTRIES;
 };
@@ -823,6 +824,8 @@ extern "C" int32_t moe_ctx_profile_enable(moe_ctx_t *c, int32_t on)
 try {
     if (!c) return fail(MOE_EINVAL, "moe_ctx_profile_enable: ctx is null");
     if (c->host_only) return fail(MOE_ESTATE, "moe_ctx_profile_enable: host-only context");
+    int32_t rc = fold_pending(c);
+    if (rc) return rc;
     HIPCHK(hipStreamSynchronize(c->compute));
     HIPCHK(hipStreamSynchronize(c->copy));
     if (c->writeback) HIPCHK(hipStreamSynchronize(c->writeback));
@@ -875,12 +878,14 @@ extern "C" int32_t moe_ctx_profile_read(moe_ctx_t *c, moe_profile_t *out)
 try {
     if (!c || !out) return fail(MOE_EINVAL, "moe_ctx_profile_read: null argument");
     if (c->host_only) return fail(MOE_ESTATE, "moe_ctx_profile_read: host-only context");
+    int32_t rc = fold_pending(c);                      // queued batches' bytes follow from their log
+    if (rc) return rc;
     HIPCHK(hipStreamSynchronize(c->compute));
     HIPCHK(hipStreamSynchronize(c->copy));
     if (c->writeback) HIPCHK(hipStreamSynchronize(c->writeback));
     moe_profile_entry_t *dst[PROF_KINDS] = {&out->gate, &out->w13, &out->w2, &out->copy, &out->ffn, &out->writeback};
     for (int k = 0; k < PROF_KINDS; ++k) {
-        int32_t rc = prof_drain(c, k);
+        rc = prof_drain(c, k);
         if (rc) return rc;
         dst[k]->launches = c->prof.kind[k].launches;
         dst[k]->bytes = c->prof.kind[k].bytes;
@@ -1287,7 +1292,7 @@ static int32_t launch_ffn_routed_fmt(moe_layer *l, int nt, const uint8_t *const 
     A.route_idx = c->route_idx;
     A.pair_expert = c->pair_expert; A.pair_w = c->pair_w;
     A.n_pairs = pairs; A.n_experts = l->cfg.n_experts; A.top_k = l->cfg.top_k;
-    return launch_ffn_args<BITS>(l, A, n, nt, pairs == 0, pairs ? own : n);
+    return launch_ffn_args<BITS>(l, A, n, nt, pairs == 0, pairs ? 0 : n);        // (a batch's bytes: fold_pending)
 }
 
 // Ring depths of the expert-after-expert one-launch kernel.
@@ -1720,7 +1725,6 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
             const int own = std::min(l->cfg.n_experts, batch * K);
             n = own + (batch * K - own) / (int)tile_tokens;          // the most entries there can be
             first = batch * K;
-            n_distinct = own;
         } else {
             memset(A.e, 0, sizeof A.e); memset(A.tok, 0, sizeof A.tok); memset(A.pair, 0, sizeof A.pair); memset(A.w, 0, sizeof A.w);
         }
@@ -1908,7 +1912,7 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
         A.per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
         return A.per_xcd * token_blocks(mode) * TE_XCD;
     };
-    const uint64_t n_exp = experts.size();
+    const uint64_t n_exp = idx ? experts.size() : 0;                 // whose bytes the launches count (nobody has seen the routing: fold_pending)
     matrix(b.m13, b.hidden, b.ffn);
     A.mat_off = b.off_w13;
     A.act = c->h_buf; A.act_bytes = (uint32_t)batch * b.hidden * 2;
@@ -2028,6 +2032,10 @@ static int32_t fold_pending(moe_ctx *c)
             for (int e = 0; e < 32; ++e)
                 if ((uint32_t)idx[0] >> e & 1u) needed.push_back(e);
             if (needed.empty()) needed.push_back(-1);
+            if (p.timed) {
+                c->prof.kind[PROF_W13].bytes += needed.size() * 2 * (uint64_t)l->lay.ffn * l->lay.m13.row_stride;
+                c->prof.kind[PROF_W2].bytes += needed.size() * (uint64_t)l->lay.hidden * l->lay.m2.row_stride;
+            }
         } else {
             needed.assign(idx, idx + l->cfg.top_k);
         }
@@ -2088,7 +2096,7 @@ static int32_t device_routed_step(moe_layer *l, const uint16_t *x_in, uint16_t *
     ga.route_idx = c->route_idx; ga.route_w = c->route_w; ga.route_log = c->route_log_dev + (size_t)slot * MOE_MAX_TOPK;
     int32_t rc = launch_timed(c, PROF_GATE, 0, k_gate<false>, dim3(1), dim3(GATE_THREADS), 0, ga);
     if (rc) return rc;
-    c->pending.push_back({l, slot, false});
+    c->pending.push_back({l, slot, false, false});
     l->steps_device_routed++;
 
     const uint8_t *table[16];
@@ -2202,7 +2210,7 @@ static int32_t device_routed_batch(moe_layer *l, const uint16_t *x_in, int32_t b
     if (rc) return rc;
     rc = launch_combine(l, x_in, x_out, batch, c->route_log_dev + (size_t)slot * MOE_MAX_TOPK);
     if (rc) return rc;
-    c->pending.push_back({l, slot, true});          // not before the launch that writes its log word is queued
+    c->pending.push_back({l, slot, true, c->prof.on});          // not before the launch that writes its log word is queued
     l->steps_device_routed++;
     return MOE_OK;
 }

@@ -14,6 +14,10 @@ static hipError_t launch_result() { return g_launches - 1 == g_fail_at ? hipErro
 #define hipGetLastError() launch_result()
 #define hipStreamSynchronize(s) ((void)(s), hipSuccess)
 #define hipFuncSetAttribute(...) hipSuccess
+#define hipEventCreate(e) (*(e) = nullptr, hipSuccess)
+#define hipEventSynchronize(e) hipSuccess
+#define hipEventRecord(e, s) hipSuccess
+#define hipEventElapsedTime(ms, a, b) (*(ms) = 1.f, hipSuccess)
 #define hipMemcpy(d, s, n, k) (memcpy(d, s, n), hipSuccess)
 #include "../../paper_2312_17238_amd/csrc/moe_offload.hip"
 
@@ -108,12 +112,38 @@ static void failed_launches(int bits, int group, int batch, int min_batch, Batch
     CHECK(s.steps == 2 && s.steps_device_routed == 2 && s.needed == 4 && s.hits == 4);
 }
 
+// Algorithmic bytes: the experts that a step turned out to need, once each.
+static void profiled_bytes(int bits, int group, int batch, int min_batch)
+{
+    Layer l(256, 512, 8, 2, bits, group, batch);
+    CHECK(moe_ctx_set_option(l.ctx, "mfma_min_batch", min_batch) == MOE_OK);
+    CHECK(l.step(batch) == MOE_OK);              // not timed
+    l.selected(0xff);
+    CHECK(moe_ctx_profile_enable(l.ctx, 1) == MOE_OK);
+    const uint32_t masks[3] = {0x01, 0x90, 0xff};
+    for (uint32_t m : masks) { CHECK(l.step(batch) == MOE_OK); l.selected(m); }
+    const MatLayout &m13 = l.layer->lay.m13, &m2 = l.layer->lay.m2;
+    moe_profile_t p;
+    CHECK(moe_ctx_profile_read(l.ctx, &p) == MOE_OK);
+    CHECK(p.w13.launches == 3 && p.w13.bytes == 11ull * 2 * 512 * m13.row_stride);
+    CHECK(p.w2.launches == 3 && p.w2.bytes == 11ull * 256 * m2.row_stride);
+    CHECK(l.step(batch) == MOE_OK);
+    l.selected(0x03);
+    CHECK(moe_ctx_profile_enable(l.ctx, 1) == MOE_OK);       // clears
+    CHECK(moe_ctx_profile_read(l.ctx, &p) == MOE_OK && p.w13.bytes == 0 && p.w2.bytes == 0);
+    const moe_stats_t s = l.stats();
+    CHECK(s.steps == 5 && s.needed == 8 + 11 + 2);
+}
+
 int main()
 {
     failed_launches(3, 64, 4, 1000, BatchPlan::GEMV);
     failed_launches(4, 64, 8, 3, BatchPlan::STREAM);
     failed_launches(3, 64, 40, 3, BatchPlan::TILE);
     failed_launches(3, 64, 200, 3, BatchPlan::TILE);          // ... with the sorted list
+    profiled_bytes(3, 64, 4, 1000);
+    profiled_bytes(4, 64, 8, 3);
+    profiled_bytes(3, 64, 40, 3);
     std::printf("ok\n");
     return 0;
 }

@@ -84,3 +84,22 @@ def test_stacks_of_batches_and_tokens():
         model.close()
     assert runs[0][0] == runs[1][0] and runs[0][1] == runs[1][1]
     assert all((a == b).all() for a, b in zip(runs[0][2], runs[1][2]))
+
+
+@pytest.mark.parametrize("fmt,Bn,low", [((3, 64), 4, 1000), ((4, 64), 8, 3), ((3, 64), 40, 3)])
+@pytest.mark.parametrize("kind", ["spread", "alike"])
+def test_profiled_bytes_are_the_waiting_steps(fmt, Bn, low, kind):
+    """Every expert a launch touches counts once: GEMV, 16-token and tile kernels."""
+    model = Model(1, 256, 512, 8, 2, [fmt], 8, 0, 1e-5, max_batch=Bn, seed=74, init_policy=1)
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_min_batch", low)
+    x = tokens(kind, Bn, 256, 74).to(model.stack.device)
+    out, got = torch.empty_like(x), []
+    for routed in (1, 0):
+        B.moe_ctx_set_option(model.stack.ctx, "device_routing", routed)
+        B.moe_ctx_profile_enable(model.stack.ctx, True)
+        torch.cuda.synchronize()
+        model.stack.step_layer(0, x, out)
+        p = B.moe_ctx_profile_read(model.stack.ctx)
+        got.append([(k.launches, k.bytes) for k in (p.w13, p.w2)])
+    model.close()
+    assert got[0] == got[1] and all(b > 0 for _, b in got[0])
