@@ -1241,9 +1241,13 @@ static int32_t launch_ffn_args(moe_layer *l, ARGS &A, int n, int nt, bool w13_on
     A.stride2 = b.m2.row_stride; A.meta2 = b.m2.meta_off;
     A.off_w2 = b.off_w2;
     // Rows of a w2 block: w2_rows where that fills the chip with two waves a SIMD, fewer in smaller layers, whose blocks would
-    // otherwise be few and each a long chain of rows (704 x 768, 3 tokens, 32 rows a block: 13 to 18 us).
+    // otherwise be few and each a long chain of rows.  us a step, 32 rows / fewer: 704 x 768 3 tokens 21.5 / 16.6, 1024 x 2048 two-level
+    // 2-bit 2 tokens 30.2 / 22.0, 1024 x 4096 two-level 3-bit 34.1 / 27.0; over 120 steps of layers up to 2048 x 4096 whose rows one or two waves
+    // share 0.88 of the time.  Larger layers and longer rows gain nothing on average, and some lose: 2048 x 8192 3-bit 2 tokens 40.8 / 42.6,
+    // 3776 x 11456 two-level 3-bit 64.0 / 67.4, 512 x 14336 3-bit 3 tokens 48.1 / 51.6.
     A.rows_per_block = c->w2_rows;
-    while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < n_cu_of(c) * 8) A.rows_per_block = (A.rows_per_block + 1) / 2;
+    if (cs <= 2 && (int64_t)b.hidden * b.ffn <= 8 << 20)
+        while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < n_cu_of(c) * 8) A.rows_per_block = (A.rows_per_block + 1) / 2;
     const uint64_t bytes13 = n_distinct * 2 * (uint64_t)b.ffn * b.m13.row_stride;
     const uint64_t bytes2 = n_distinct * (uint64_t)b.hidden * b.m2.row_stride;
     int32_t rc;
