@@ -330,6 +330,8 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                the form computes that product in fp16 -- form 2 runs).  1: row-staging kernels that keep the codes
  *                exact and scale every group's product in fp32 (batches of at most 64 tokens, fp16 metadata; otherwise
  *                form 2 runs).  All meet the output tolerance;
+ *   "tile_tokens" tokens of an expert per block of form 6's kernels in both halves of a layer: 16, 32, or 192 for the large kernel
+ *                (128 with two-level 2-bit codes; group-32 layers, which have none, take 32); 0 (default): from layer and batch;
  *   "mfma16_waves" waves per block of the kernels of forms 4 and 5 for up to 16 tokens per expert: 8 (default; 128
  *                registers, four waves per SIMD) or 4 (two groups of a step per wave; form 4 only); with two token tiles
  *                they always run 4;

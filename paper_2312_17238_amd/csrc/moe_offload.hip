@@ -175,6 +175,7 @@ struct moe_ctx {
                                         // way; with two token tiles 8 waves need 194 registers, one block per unit, and measured 12 % slower)
     int32_t mfma_min_batch = 3;         // batches at least this large may use the matrix-core kernels (4-bit g64: do): measured, all experts of a
                                         // Mixtral-shaped layer resident, they are 9 % faster than the GEMV kernels at 3 tokens and 82 % at 12
+    int32_t tile_tokens = 0;            // tokens per block of the tile kernels: 16, 32, 192 (the large kernel), or 0: by layer and batch
     int32_t staged_min_batch = 0;       // matrix-core batches larger than this: resident experts first, arriving ones one by one
     uint64_t spec_head_bytes = 0;       // 0: a speculative load moves the whole expert at once (as the paper describes);
                                         // > 0: only this many leading bytes, the rest when the guess is confirmed
@@ -1508,7 +1509,7 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     // (groups of 32 have no large kernel: twice the metadata does not fit beside its tokens)
     const bool exact = l->cfg.top_k == E;
     const double avg = (double)pairs / E;
-    const bool many = avg > (exact ? 32 : TILE_MODE32_AVERAGE) && !(b.bits == 4 && b.group == 32);
+    const bool g32 = b.bits == 4 && b.group == 32, many = avg > (exact ? 32 : TILE_MODE32_AVERAGE) && !g32;
     const int sets = (b.ffn / 64 + 3) / 4;
     const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
     // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
@@ -1527,9 +1528,9 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
         }
         return parts;
     };
-    p.mode13 = p.mode2 = avg > (exact ? 16 : 12) ? 32 : 16;
+    p.mode13 = p.mode2 = c->tile_tokens ? (c->tile_tokens <= 32 ? c->tile_tokens : g32 ? 32 : TE_BIG) : avg > (exact ? 16 : 12) ? 32 : 16;
     p.parts = best_parts(p.mode2);
-    if (!many) return;
+    if (!many || c->tile_tokens) return;
     // (the 32-token kernel where it is faster by more than the fit's error)
     const int big_parts = best_parts(TE_BIG);
     if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < 1.05 * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
@@ -2664,6 +2665,7 @@ try {
     else if (n == "spec_head_mb" && value >= 0) c->spec_head_bytes = (uint64_t)value << 20;
     else if (n == "mfma_min_batch" && value >= 1) c->mfma_min_batch = value;
     else if (n == "mfma_form" && value >= 0 && value <= 6) c->mfma_form = value;
+    else if (n == "tile_tokens" && (value == 0 || value == 16 || value == 32 || value == 192)) c->tile_tokens = value;
     else if (n == "mfma16_waves" && (value == 4 || value == 8)) c->mfma16_waves = value;
     else if (n == "device_routing") c->device_routing = value != 0;
     else if (n == "staged_min_batch" && value >= 0) c->staged_min_batch = value;
