@@ -40,8 +40,8 @@ struct GateArgs {
     float *route_w;                 // [K] device
     int32_t *route_log;             // [K] device: this step's slot of the log ring
     // For kernels that find the routing in device memory (TILE): every pair's expert and combine weight; where xs is set the
-    // sums of h over groups of xs_group elements for the tile kernels, rows padded with zeros to xs_stride (16: split2, else
-    // split3).  quiet: nobody waits for this launch, nothing is published in `out`.
+    // sums of h over groups of xs_group elements for the tile kernels, rows padded with zeros to xs_stride
+    // (split3).  quiet: nobody waits for this launch, nothing is published in `out`.
     uint8_t *pair_expert;           // [b*K + j]
     float *pair_w;                  // [b*K + j]
     uint2 *xs;                      // [b][xs_stride]
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
             s += dpp_f<0x4E>(s);
             if (a.xs_group >= 32) s += dpp_f<0x141>(s);
             if (a.xs_group == 64) s += dpp_f<0x140>(s);
-            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = a.xs_group >= 32 ? split3(s) : make_uint2(split2(s), 0u);
+            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = split3(s);
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e)
