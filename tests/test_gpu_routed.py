@@ -12,9 +12,9 @@ from harness import Model, check_y, oracle_routing, oracle_y, say
 
 pytestmark = pytest.mark.gpu
 
-# (format, scale group, H, F, E, K, tokens): GEMV kernels with entries of two and of four tokens, up to 64 pairs; 16-token kernels
-# with tiles of 16 and 32, up to 256 pairs; tile kernels of each size, with the pairs found by ballots (one chunk of 64 pairs and
-# more, up to 256) and sorted (more); an odd number of experts, sixteen of them, three choices; a layer where all are needed.
+# (format, scale group, H, F, E, K, tokens): GEMV kernels with entries of two and of four tokens; 16-token kernels with tiles of 16 and 32, up
+# to 256 pairs; tile kernels of each size, with the pairs found by ballots (one chunk of 64 pairs and more, up to 256) and sorted
+# (more); an odd number of experts, sixteen of them, three choices; a layer where all are needed.
 CASES = [((4, 64), 0, 256, 512, 8, 2, 2), ((3, 64), 0, 256, 512, 16, 3, 5), ((2, 16), 8, 256, 512, 8, 2, 12), ((4, 32), 0, 320, 640, 13, 2, 32),
          ((4, 64), 0, 256, 512, 8, 2, 3), ((4, 64), 4, 512, 640, 13, 3, 21), ((4, 64), 0, 256, 512, 8, 2, 64), ((4, 64), 0, 256, 512, 8, 2, 128),
          ((3, 64), 0, 512, 640, 6, 2, 32), ((3, 64), 2, 512, 640, 6, 2, 33), ((2, 16), 0, 512, 640, 6, 1, 64), ((2, 16), 16, 512, 640, 6, 1, 65),
@@ -22,17 +22,51 @@ CASES = [((4, 64), 0, 256, 512, 8, 2, 2), ((3, 64), 0, 256, 512, 16, 3, 5), ((2,
          ((4, 64), 0, 1600, 1408, 8, 2, 20), ((2, 16), 0, 256, 640, 4, 2, 400)]
 
 
+# GEMV kernels only: every format with entries of two tokens (two tokens, or no more pairs than experts, or rows of two and of four chunks a
+# lane) and of four, rows of w1/w3 of one, two and four chunks a lane, of w2 of one wave and of two, and as many pairs as are queued.
+GEMV = [((4, 64), 0, 4096, 2304, 8, 2, 2), ((4, 64), 0, 4096, 2304, 8, 2, 3), ((4, 64), 0, 4096, 2304, 8, 2, 5), ((4, 64), 0, 8192, 640, 8, 2, 7),
+        ((4, 64), 0, 1024, 2304, 13, 2, 32), ((4, 64), 8, 4096, 2304, 8, 2, 2), ((4, 64), 8, 4096, 2304, 8, 2, 5), ((4, 32), 0, 1024, 2304, 16, 4, 16),
+        ((3, 64), 0, 1920, 4160, 8, 2, 2), ((3, 64), 0, 8192, 640, 8, 2, 6), ((3, 64), 0, 1024, 4416, 16, 3, 21), ((3, 64), 128, 1920, 4160, 8, 2, 2),
+        ((3, 64), 4, 4096, 640, 8, 2, 5), ((2, 16), 0, 4096, 1984, 8, 2, 2), ((2, 16), 0, 4096, 2304, 8, 2, 5), ((2, 16), 0, 1024, 640, 13, 2, 32),
+        ((2, 16), 16, 1920, 4160, 8, 2, 2), ((2, 16), 16, 4096, 4160, 8, 2, 5), ((2, 16), 128, 8192, 640, 8, 2, 6)]
+
+
 def tokens(kind, Bn, H, seed):
     x = W.hidden_ar1(seed, 1, Bn, H)[0]
     return x if kind == "spread" else x[:1].expand(Bn, H).contiguous()
+
+
+def apart(model, Bn):
+    """Tokens of which no two take the same expert."""
+    pool, picked, taken = W.hidden_ar1(75, 1, 64, model.H)[0], [], set()
+    for i, (_, idx, _, _) in enumerate(oracle_routing(model, 0, pool.numpy())):
+        if len(picked) < Bn and not taken & set(idx):
+            picked.append(i)
+            taken |= set(idx)
+    assert len(picked) == Bn
+    return pool[picked].contiguous()
 
 
 @pytest.mark.parametrize("fmt,sg,H,F,E,K,Bn", CASES)
 @pytest.mark.parametrize("kind", ["spread", "alike"])
 def test_batches_queued_without_their_routing(fmt, sg, H, F, E, K, Bn, kind):
     """alike: every token takes the same experts, so a few have all pairs and the others none."""
+    queued_and_waiting(fmt, sg, H, F, E, K, Bn, kind)
+
+
+@pytest.mark.parametrize("fmt,sg,H,F,E,K,Bn", GEMV)
+@pytest.mark.parametrize("kind", ["spread", "alike", "apart"])
+def test_gemv_batches_queued_without_their_routing(fmt, sg, H, F, E, K, Bn, kind):
+    """apart: no two tokens share an expert, where a waiting step takes the kernels of one token."""
+    if kind == "apart" and Bn * K > E:
+        Bn = E // K // 2 + 1
+    queued_and_waiting(fmt, sg, H, F, E, K, Bn, kind, 1000)
+
+
+def queued_and_waiting(fmt, sg, H, F, E, K, Bn, kind, mfma_min_batch=3):
     model = Model(1, H, F, E, K, [fmt], E, 0, 1e-5, max_batch=Bn, seed=71, scale_group=sg, init_policy=1)
-    x = tokens(kind, Bn, H, 71).to(model.stack.device)
+    B.moe_ctx_set_option(model.stack.ctx, "mfma_min_batch", mfma_min_batch)
+    x = (apart(model, Bn) if kind == "apart" else tokens(kind, Bn, H, 71)).to(model.stack.device)
     out, h, ys, hs = torch.empty_like(x), torch.empty_like(x), [], []
     for routed in (1, 0, 1):
         B.moe_ctx_set_option(model.stack.ctx, "device_routing", routed)
