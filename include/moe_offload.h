@@ -210,14 +210,15 @@ int32_t moe_layer_peek_run_meta(const moe_layer_t *layer, int32_t expert, int32_
 /* One decode step of one layer for `batch` tokens (Sec. 3: token-by-token, layer-by-layer).
  *   x_in_dev  [batch][H] fp16, device: the block's input (residual stream).
  *   x_out_dev [batch][H] fp16, device: x_in + sum_j w_j expert_j(h); may alias x_in_dev.
- *   h_out_dev nullable, [batch][H] fp16: receives the gate input h (x, or RMSNorm(x)).
+ *   h_out_dev nullable, [batch][H] fp16: receives the gate input h (x, or RMSNorm(x)), valid like x_out.
  *   next      nullable: the following layer.  If given and next->prefetch_m > 0 the step also applies
  *             next's gate to h and stages its guesses (Sec. 3.2), right after this layer's own loads
  *             were issued (Sec. 3.3).
  *   trace     nullable, host: what was decided.
- * The gate runs on the compute stream and the call waits for its result (the cache table lives on the
- * host); copies and the expert kernels are then enqueued and the call returns without waiting for
- * them: x_out is valid once the compute stream reaches this point. */
+ * The gate runs on the compute stream.  Where copies or evictions may follow from its result the call waits for that
+ * (the cache table lives on the host); where every expert is on the device the whole step may be enqueued without it
+ * (option "device_routing").  The call then returns without waiting for what it enqueued: x_out and h_out are valid once
+ * the compute stream reaches this point. */
 int32_t moe_layer_step(moe_layer_t *layer, moe_layer_t *next, const uint16_t *x_in_dev, int32_t batch,
                        uint16_t *x_out_dev, uint16_t *h_out_dev, moe_step_trace_t *trace);
 
