@@ -222,9 +222,6 @@ __device__ __forceinline__ uint2 split3(float v)
     return make_uint2(__builtin_bit_cast(uint32_t, p), __builtin_bit_cast(uint32_t, q));
 }
 
-// A word that an earlier launch left in memory, at an address all lanes share, through the scalar cache (empty at a launch's start).
-__device__ __forceinline__ int scalar_word(const int32_t *p) { return *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)p; }
-
 // The routing of a step of at most 256 pairs as a wave holds it: the expert of pair 64 c + lane in e[c].  Its kernels find an
 // expert's pairs with ballots, so such a step needs no sorted list (a launch of 6 us, more than all this takes).
 constexpr int FEW_PAIRS = 256;
