@@ -3,7 +3,7 @@
 //
 // At batch 16 with top-2 an expert sees four tokens on average: a 32-token tile is seven eighths padding, costs 64
 // accumulator registers per wave and two 16-byte A-operand loads per token row and group that touch 32 cache lines
-// each.  Here the tile is MT x 16 tokens (MT = 1 while no expert of the launch has more than 16 tokens, else 2):
+// each.  Here the tile is MT x 16 tokens (MT = 1 where an expert has few tokens of the window on average, else 2):
 // 8 x MT x 4 accumulator registers for the same 128 memory rows of an item, one A operand of 16 bytes per lane,
 // k-step and token tile (lanes of one token read 64 consecutive bytes), and half the matrix instructions' work.
 //

@@ -165,10 +165,10 @@ struct moe_ctx {
     int32_t w13_blocks = 256, w2_rows = 32;
     int32_t w2_token_rows = 0;          // rows per block of the single-token w2 kernel; 0: hidden / compute units
     uint32_t gate_seq = 0;              // sequence number of the last gate launch
-    int32_t mfma_form = 0;              // matrix-core kernels: 0 the default (6 where an expert has enough tokens and, for formats form 5 takes, 6 is
-                                        // faster; else 5 or the GEMV kernels); 6 tile kernels, every format; 5 streaming form with 16-token tiles (one per
-                                        // expert while no expert of the window has more than 16 tokens, else two), codes multiplied as they are and
-                                        // groups scaled in fp32; 4 the same with weights dequantised to fp16;
+    int32_t mfma_form = 0;              // matrix-core kernels: 0 the default (plan_batch: 6 where it is the faster one for the layer's size and an expert's
+                                        // tokens on average, else 5 or the GEMV kernels); 6 tile kernels, every format; 5 streaming form with 16-token tiles (one
+                                        // an entry up to an average of STREAM_SMALL_AVERAGE tokens of an expert in a window, else two), codes multiplied as they
+                                        // are and groups scaled in fp32; 4 the same with weights dequantised to fp16;
                                         // 3 streaming form, one fma per pair of weights plus a rank-1 correction;
                                         // 2 streaming form with an exact subtraction first; 1 row-staging form with fp32 group scaling
     int32_t mfma16_waves = 8;           // waves per block of the 16-token forms' single-tile kernels: 4 or 8 (two blocks per compute unit either
@@ -186,14 +186,14 @@ struct moe_ctx {
     uint32_t *barrier = nullptr;        // device counter of its grid barrier
     uint32_t barrier_count = 0;         // value it reaches after all launches enqueued so far
     bool sync_wait = false;
-    // Device-side routing: steps of one token through a layer whose experts are all resident need no decision of the
-    // host, so they are enqueued without waiting for the gate; the cache bookkeeping (recency stamps, counters) is
-    // caught up from a log of the selections (a ring in device memory, copied back then) before anything reads or changes it.
+    // Device-side routing: steps through a layer whose experts are all resident need no decision of the host, so they are
+    // enqueued without waiting for the gate; the cache bookkeeping (recency stamps, counters) is caught up from a log of the
+    // selections (a ring in device memory, copied back then) before anything reads or changes it.
     bool device_routing = true;
-    int32_t *route_idx = nullptr;       // device: the current step's selection, written by its gate kernel
+    int32_t *route_idx = nullptr;       // device: the selection of a step of one token, written by its gate kernel
     float *route_w = nullptr;           // device: ... and combine weights
     int32_t *route_log = nullptr;       // pinned host copy of the ring below, refreshed when the bookkeeping catches up
-    int32_t *route_log_dev = nullptr;   // device ring of ROUTE_LOG entries of MOE_MAX_TOPK selections, written by the gate kernel
+    int32_t *route_log_dev = nullptr;   // device ring of ROUTE_LOG entries of MOE_MAX_TOPK selections, written by the gate kernel of one token, by a batch's k_combine
     // batch: the slot's first word has one bit per expert needed; timed: its launches' bytes are still to be counted (moe_profile_t)
     struct PendingStep { moe_layer *layer; uint32_t slot; bool batch, timed; };
     std::vector<PendingStep> pending;   // steps enqueued that way whose bookkeeping is still to be done, oldest first
@@ -1451,7 +1451,7 @@ static int tile_blocks(const BlobLayout &b, int count, int mode)
     return b.bits == 2 && b.scale_group ? te_token_blocks<TeCfg<28, TE_BIG>::TOK, true>(count) : te_token_blocks<TeCfg<4, TE_BIG>::TOK, true>(count);
 }
 
-constexpr int TILE_MODE32_AVERAGE = 26;                              // tokens of an expert on average up to which the 32-token tile kernel runs
+constexpr int TILE_MODE32_AVERAGE = 26;                              // tokens of an expert on average from where on the large tile kernel is considered
 constexpr int STREAM_SMALL_AVERAGE = 14;                              // ... up to which the 16-token kernels' entries are one tile of 16
 constexpr int64_t TILE_MIDDLE_LOW = 1 << 21, TILE_MIDDLE_HIGH = 11 << 20, TILE_TWO_TILES_HIGH = 18 << 20;    // hidden * ffn, tile_may
 
