@@ -29,10 +29,10 @@
 // scaled weight goes in directly; an fp32 s (two-level metadata) goes in as two fp16 numbers, in two products.
 // Second term: a contraction over groups instead of codes, on the bf16 matrix instructions.  X and D = s (ZC - z) go in
 // whole, cut into three bf16 each: eight k-slots a group (slots3_x, slots3_d) hold all products but that of the third parts.  2-bit
-// codes in the large kernel: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the result unless the tokens have a
-// mean), the four k-slots (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl); tiles of 16 and 32 take steps that the GEMV kernels, whose term is in fp32,
-// would else take, and go in whole too (D staged as fp32, cut where it is used: 2-bit, 16 tokens, 167.6 -> 168.4 us a step).  Correcting
-// every group's product in the accumulators instead would double the vector work per group.
+// codes in the large kernel and in tiles of 32: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the result unless the
+// tokens have a mean), the four k-slots (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl).  Tiles of 16 take steps that the GEMV kernels, whose term is in
+// fp32, would else take, and have the slots: whole too (D staged as fp32, cut where it is used; 2-bit, 16 tokens, 167.6 -> 168.4 us a
+// step; with tiles of 32 it takes an instruction more, 64 tokens 224 -> 231).  Correcting every group's product in the accumulators instead would double the vector work per group.
 // The X come from whoever produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros
 // to a multiple of four groups.
 //
@@ -49,8 +49,8 @@
 // here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), one expert of 1024 x 4096
 // and of 4096 x 14336, every format, 16, 32 and 192 tokens, two seeds.  Normalised tokens of mean 0, as the decode workloads draw them / of a
 // mean of a tenth of the deviation / of mean 1 and deviation 1/8, in 1e-5: 4-bit 0.5 to 2.4 / 0.6 to 1.5 / 0.8 to 2.2 (GEMV kernels 8.6 to 10 /
-// 8.6 to 10 / 14 to 17), 3-bit 0.5 to 1.4 / 0.4 to 1.4 / 1.1 to 2.8 (GEMV 17 to 18 / 19 / 41), 2-bit 0.7 to 2.2 / 1.3
-// to 1.6 / 1.2 to 1.8, large kernel 3.7 to 4.3 / 3.7 to 4.6 / 6.3 to 7.3 (GEMV 11 to 12 / 11 / 2.9 to 3.3; the two bf16 of X and D).  With the rounding of a, the error of y at mean 0 is 2.07 to 2.1e-4 (GEMV 2.08 to 2.2e-4).
+// 8.6 to 10 / 14 to 17), 3-bit 0.5 to 1.4 / 0.4 to 1.4 / 1.1 to 2.8 (GEMV 17 to 18 / 19 / 41), 2-bit tiles
+// of 16 0.7 to 2.2 / 1.5 to 1.6 / 1.2 to 1.8, others 3.5 to 4.3 / 3.7 to 4.6 / 6.3 to 7.3 (GEMV 11 to 12 / 11 / 2.9 to 3.3; the two bf16 of X and D).  With the rounding of a, the error of y at mean 0 is 2.07 to 2.1e-4 (GEMV 2.08 to 2.2e-4).
 //
 // BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
 // other at the end of the unit before, so that one's vector work runs under the other's matrix work.
@@ -376,8 +376,8 @@ struct Te2 {
     // two-level scales are split into two fp16, lifted by the layer's own power of two first (the host chooses it: the
     // largest scale just fits, and the low part of every row's largest is a normal number), the totals lowered at the end
     static constexpr bool LIFTED = META8;
-    // D: one word a group, the large kernel's two bf16 or, with tiles of 16 and 32, the fp32 number
-    static constexpr bool D2 = ROWS == 256;
+    // D (two-level): one word a group, two bf16 or, with tiles of 16, the fp32 number
+    static constexpr bool D2 = ROWS == 256 || THREADS == 256;
     uint4 c[META8 ? NA : NC];
     uint2 mp[META8 ? NA : 1], quad[META8 ? NA : 1];
     struct Raw { uint4 q; };
@@ -432,15 +432,14 @@ struct Te2 {
         }
     }
     static __device__ __forceinline__ void read(Raw &r, const uint8_t *row, int hh, int u) { r.q = *reinterpret_cast<const uint4 *>(row + u * 32 + hh * 16); }
-    // the two groups' D, as the words above
+    // the two groups' D, split in two
     static __device__ __forceinline__ uint2 factors(const uint8_t *row, const uint8_t *drow, int hh, int u)
     {
         if constexpr (META8) return *reinterpret_cast<const uint2 *>(drow + u * 16 + hh * 8);
         Raw r;
         read(r, row, hh, u);
         const float s0 = lo_half(r.q.y), s1 = lo_half(r.q.w);
-        const float d0 = s0 - s0 * hi_half(r.q.y), d1 = s1 - s1 * hi_half(r.q.w);
-        return D2 ? make_uint2(split2(d0), split2(d1)) : make_uint2(__builtin_bit_cast(uint32_t, d0), __builtin_bit_cast(uint32_t, d1));
+        return make_uint2(split2(s0 - s0 * hi_half(r.q.y)), split2(s1 - s1 * hi_half(r.q.w)));
     }
     // a quarter of a unit is one group: its two words of weights per plane
     static __device__ __forceinline__ uint2 quarter(const uint8_t *row, int kb, int u, h8_t (&b)[PLANES][2])
@@ -508,8 +507,9 @@ template <int FMT, int MODE> struct TeCfg {
     static constexpr int REC = F::REC;
     static constexpr int ABUF = TOK * PITCH, BBUF = ROWS * REC, DBUF = ROWS * F::DB;
     // sums: 16 bytes are four groups, of a set (GS) or of one unit: XQ pieces per token and staging step
-    // (8 bytes each; the large kernel takes only the first four of 2-bit codes)
-    static constexpr int XQ = F::GS ? 2 * F::GPU : SU * 2, XPITCH = F::GS ? 32 * F::GPU : (BIG ? 16 : XQ * 16 + 16), XBUF = TOK * XPITCH;
+    // (8 bytes each; 2-bit codes take only the first four but with tiles of 16)
+    static constexpr bool XWHOLE = F::GS || MODE == 16;
+    static constexpr int XQ = F::GS ? 2 * F::GPU : SU * 2, XPITCH = F::GS ? 32 * F::GPU : (BIG ? 16 : XQ * (XWHOLE ? 16 : 8) + 16), XBUF = TOK * XPITCH;
     static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_END = OFF_X + 2 * XBUF;
     static constexpr int OFF_RED = THREADS / 64 * (RGR * MODE * 4);    // MODE 16, 32: behind the waves' partial sums
     static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
@@ -619,7 +619,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     constexpr bool X_REPEAT = BIG || !F::GS;
     static_assert(C::TOK * XQ <= THREADS && (!X_REPEAT || THREADS % XQ == 0), "one piece per thread");
     const bool x_mine = X_REPEAT || tid < C::TOK * XQ;
-    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * (F::GS || !BIG ? 16 : 8);
+    const int xp = tid % (C::TOK * XQ), x_to = C::OFF_X + (xp / XQ) * C::XPITCH + (xp % XQ) * (C::XWHOLE ? 16 : 8);
     const uint32_t x_off = x_mine && xp / XQ < n_tok ? (uint32_t)act_row(xp / XQ) * (uint32_t)A.xs_stride * 8u + (uint32_t)(xp % XQ) * 16u : TE_NONE;
     struct Acts { uint4 a[NP], x; };                                     // activations and sums of one step on their way to LDS
     auto fetch_a = [&](Acts &t, int u) __attribute__((always_inline)) {                                          // units u .. u + SU - 1; zeros from u1 on
@@ -638,7 +638,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     auto fetch_x = [&](Acts &t, int u) __attribute__((always_inline)) { t.x = bl128(x_rs, (F::GS ? u : u + xp % XQ / 2) < u1 ? x_off : TE_NONE, u * (XU * 8)); };
     auto commit_x = [&](const Acts &t, int b) __attribute__((always_inline)) {
         if (!X_REPEAT && C::TOK * XQ < THREADS && !x_mine) return;
-        if constexpr (F::GS || !BIG) *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = t.x;
+        if constexpr (C::XWHOLE) *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = t.x;
         else *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
     };
     // (the large kernel works the address of its 4-bit records out for every set: kept, it does not fit the registers; 1024 tokens 1082 -> 1073 us)
@@ -920,36 +920,33 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                     }
                 }
             } else {
-                // one group per lane and bf16 instruction: the quarter's, or the half's two in turn
-                constexpr int NX = MODE == 32 ? 2 : 1;
-                bf8_t xv[NX];
-#pragma unroll
-                for (int j = 0; j < NX; ++j)
-                    xv[j] = slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH + un * 32 + (kb * NX + j) * 8));
+                const uint8_t *const xp0 = lds + C::OFF_X + bb * C::XBUF + rcol * C::XPITCH;
+                bf8_t xv;
+                if constexpr (MODE == 32) xv = slots_x(*reinterpret_cast<const uint2 *>(xp0 + un * 16 + kb * 8));
+                else xv = slots3_x(*reinterpret_cast<const uint2 *>(xp0 + un * 32 + kb * 8));          // one group per lane: all of its slots
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     const uint8_t *rec = rec0 + bb * C::BBUF + rt * RROWS * C::REC;
                     const uint8_t *drow = lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * RROWS + rcol) * F::DB;
                     h8_t b[F::PLANES][KS];
-                    uint32_t d[NX];
+                    bf8_t d;
                     if constexpr (MODE == 32) {
                         typename F::Raw raw;
                         F::read(raw, rec, kb, un);
                         F::decode(raw, b);
-                        const uint2 v = F::factors(rec, drow, kb, un);
-                        d[0] = v.x;
-                        d[NX - 1] = v.y;
+                        d = slots_d(F::factors(rec, drow, kb, un));
                     } else {
                         const uint2 q = F::quarter(rec, kb, un, b);
-                        if constexpr (F::DB > 0) d[0] = *reinterpret_cast<const uint32_t *>(drow + un * 16 + kb * 4);
-                        else d[0] = __builtin_bit_cast(uint32_t, lo_half(q.y) - lo_half(q.y) * hi_half(q.y));
+                        float v;
+                        if constexpr (F::DB > 0) v = *reinterpret_cast<const float *>(drow + un * 16 + kb * 4);
+                        else v = lo_half(q.y) - lo_half(q.y) * hi_half(q.y);
+                        d = slots3_d(split3(v));
                     }
 #pragma unroll
                     for (int k = 0; k < KS; ++k)
 #pragma unroll
                         for (int pl = 0; pl < F::PLANES; ++pl) tot[rt] = mm(a[k], b[pl][k], tot[rt]);
-#pragma unroll
-                    for (int j = 0; j < NX; ++j) tot[rt] = mmb(xv[j], slots3_d(split3(__builtin_bit_cast(float, d[j]))), tot[rt]);
+                    tot[rt] = mmb(xv, d, tot[rt]);
                 }
             }
         };

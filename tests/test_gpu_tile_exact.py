@@ -49,4 +49,4 @@ def test_2bit_tiles_no_less_exact_than_the_gemv_kernels(sg, mean, deviation):
     """Steps of two and three tokens of an expert take tiles of 16 where smaller ones take the GEMV kernels, whose zero-point term
     is in fp32: a step's error does not grow with its tokens."""
     err = errors((2, 16), sg, mean, deviation)
-    assert max(err["16"], err["32"]) <= err["gemv"]
+    assert err["16"] <= err["gemv"]
