@@ -1470,9 +1470,32 @@ struct BatchPlan {
 // Pairs of expert e when `pairs` of them are dealt out evenly.
 static int nominal_count(const moe_layer *l, int pairs, int e) { return pairs / l->cfg.n_experts + (e < pairs % l->cfg.n_experts); }
 
+// The tile kernels' formats: groups of 32 have their own.
+static int tile_fmt(const BlobLayout &b) { return b.bits == 4 && b.group == 32 ? (b.scale_group ? 58 : 5) : fmt_of(b); }
+
 static int tile_rows(int mode) { return mode == TE_BIG ? 256 : 128; }
-// blocks a compute unit runs at a time
-static int tile_per_cu(const BlobLayout &b, int mode) { return mode == TE_BIG || (mode == 32 && b.bits == 4 && b.group == 32) ? 1 : 2; }
+// blocks a compute unit runs at a time: what its LDS holds, two at most (their waves' registers)
+template <int FMT> static int tile_lds(int mode)
+{
+    if (mode == 16) return TeCfg<FMT, 16>::LDS;
+    if constexpr (FMT != 5 && FMT != 58) { if (mode == TE_BIG) return TeCfg<FMT, TE_BIG>::LDS; }
+    return TeCfg<FMT, 32>::LDS;
+}
+static int tile_per_cu(const BlobLayout &b, int mode)
+{
+    int lds;
+    switch (tile_fmt(b)) {
+    case 5: lds = tile_lds<5>(mode); break;
+    case 58: lds = tile_lds<58>(mode); break;
+    case 48: lds = tile_lds<48>(mode); break;
+    case 3: lds = tile_lds<3>(mode); break;
+    case 38: lds = tile_lds<38>(mode); break;
+    case 2: lds = tile_lds<2>(mode); break;
+    case 28: lds = tile_lds<28>(mode); break;
+    default: lds = tile_lds<4>(mode);
+    }
+    return std::min(2, 160 * 1024 / lds);
+}
 
 // One launch of a tile kernel in us: rounds of blocks, a block's start and end and its units of 64 columns.  The large kernel's
 // rounds are paid in whole (one block a compute unit), but with few blocks their tiles run faster; of the others' last round what
@@ -1480,8 +1503,9 @@ static int tile_per_cu(const BlobLayout &b, int mode) { return mode == TE_BIG ||
 // Fitted to which of the two ran faster, each half by itself, over 38 layers and batches.  w1/w3 and w2 at 32 tokens / at the
 // large kernel, us a step: 8 experts 4096x14336, 4-bit, top 2, 128 tokens 305 / 392, 192 370 / 429, 256 449 / 420, 512 778 / 578;
 // 2-bit, 160 tokens 359 / 507, 300 527 / 561, 512 816 / 645; 3-bit 960x960, 352 tokens 37 / 51, 3136x1792, 503 tokens 144 / 97;
-// 4-bit 256x12288, 6 experts, 306 tokens 87 / 88, with w1/w3 alone at the large one 62.  Two-level 2-bit costs the 32-token
-// kernel about twice: 2048x4096, 160 tokens 130 / 97.
+// 4-bit 256x12288, 6 experts, 306 tokens 87 / 88, with w1/w3 alone at the large one 62.  Two-level 2-bit scales go in as two numbers,
+// which costs the large kernel's units 1.3 times the matrix work, and the 32-token one has a compute unit to itself: one launch
+// each, 32 tokens / large kernel, w1/w3 of 4096x14336, 160 tokens 513 / 397, 384 tokens 862 / 489; w2 of 256x12288, 6 experts, 306 tokens 28 / 91.
 static double tile_half_us(const moe_layer *l, int batch, int mode, int n_rows, int cols, int parts)
 {
     const BlobLayout &b = l->lay;
@@ -1492,9 +1516,9 @@ static double tile_half_us(const moe_layer *l, int batch, int mode, int n_rows, 
     const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
     const int row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
     const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
-    if (mode != TE_BIG) return std::max(1.0, rounds) * (2.5 + units * 0.54 * (b.bits != 2 ? 1.0 : b.scale_group ? 2.1 : 0.86));
+    if (mode != TE_BIG) return std::max(1.0, rounds) * (2.5 + units * 0.54 * (b.bits != 2 ? 1.0 : b.scale_group ? 1.05 : 0.86));
     const double half_tiles = std::max(1.0, tiles / blocks / 2 + 0.25), whole = std::ceil(rounds);     // tiles of a block's fuller half
-    return whole * 3.7 + units * 0.52 * (whole + half_tiles * std::max(rounds, 0.32 * whole));
+    return whole * 3.7 + units * (b.bits == 2 && b.scale_group ? 0.68 : 0.52) * (whole + half_tiles * std::max(rounds, 0.32 * whole));
 }
 
 // Tile kernels: tokens per block, and into how many parts w2 splits its contraction.
@@ -1861,8 +1885,7 @@ static int32_t launch_tile_fmt(moe_ctx *c, int mode, int grid, uint64_t bytes, c
 template <bool W13>
 static int32_t launch_tile_half(moe_layer *l, int mode, int grid, uint64_t bytes, const TeArgs &A)
 {
-    const int g32 = l->lay.bits == 4 && l->lay.group == 32;
-    switch (g32 ? (l->lay.scale_group ? 58 : 5) : fmt_of(l->lay)) {
+    switch (tile_fmt(l->lay)) {
     case 5: return launch_tile_fmt<5, W13>(l->ctx, mode, grid, bytes, A);
     case 58: return launch_tile_fmt<58, W13>(l->ctx, mode, grid, bytes, A);
     case 4: return launch_tile_fmt<4, W13>(l->ctx, mode, grid, bytes, A);
