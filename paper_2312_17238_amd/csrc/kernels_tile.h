@@ -85,8 +85,11 @@ struct TeArgs {
     uint32_t stride, meta_off, meta2_off, b_off;
     int32_t unit_shift, run_shift;       // group of unit u: u >> unit_shift; run of group g: g >> run_shift
     uint64_t mat_off;
-    int32_t units_per_part, k_parts, part_base;
-    int32_t jobs, per_xcd;               // row blocks * k_parts, and an XCD's share of them
+    int32_t units_per_part, k_parts, part_base, row_blocks;
+    // w2, other parts where the step's token blocks, all experts' together, turn out fewer than few_below: four bits for every number of
+    // blocks, from one up
+    int32_t few_below;
+    uint64_t few;
     float lift, lower;                   // two-level 2-bit codes: what their scales are multiplied with, and its reciprocal
     uint32_t act_bytes, xs_bytes;        // sizes of the two tables, for the bounds of their loads
 };
@@ -523,6 +526,14 @@ template <int FMT, int MODE> struct TeCfg {
 template <int TOK, bool BIG>
 __host__ __device__ constexpr int te_token_blocks(int count) { return BIG ? ((count + 31) / 32 + TOK / 32 - 1) / (TOK / 32) : (count + TOK - 1) / TOK; }
 
+// a contraction of `sets` sets in at most `parts` parts
+__host__ __device__ inline void te_split(int sets, int parts, int32_t &k_parts, int32_t &units_per_part)
+{
+    const int per = (sets + parts - 1) / parts;
+    units_per_part = per * 4;
+    k_parts = (sets + per - 1) / per;
+}
+
 template <int FMT, bool W13, int MODE>
 __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAVES_EU)) void k_tile(TeArgs A)
 {
@@ -544,6 +555,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     FewPairs few;
     int j = (int)blockIdx.x / TE_XCD;
     struct { const uint8_t *blob; int expert, first, count, tb; } ex;
+    int k_parts = A.k_parts, units_per_part = A.units_per_part, jobs;
     {
         int count, first;
         if (A.pair_expert) {
@@ -554,7 +566,20 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             first = A.first[lane & 15];
             count = A.first[(lane & 15) + 1] - first;
         }
-        const int tb = lane < 16 && (A.experts >> lane & 1u) ? te_token_blocks<C::TOK, BIG>(count) : 0, items = tb * A.per_xcd, end = prefix16(items);
+        const int blocks = te_token_blocks<C::TOK, BIG>(count);
+        // tokens that crowd to a few experts: w2's contraction in as many parts as fill the chip then (of the whole step's
+        // experts, not the launch's: the order of the sums must not depend on the cache)
+        if (!W13 && A.few_below) {
+            const int n = __builtin_amdgcn_readlane(prefix16(blocks), 15);
+            if (n > 0 && n < A.few_below) {
+                te_split((A.K / 64 + 3) / 4, (int)(A.few >> 4 * (n - 1) & 15u), k_parts, units_per_part);
+                k_parts = uniform(k_parts);
+                units_per_part = uniform(units_per_part);
+            }
+        }
+        jobs = A.row_blocks * k_parts;
+        const int per_xcd = (jobs + TE_XCD - 1) / TE_XCD;
+        const int tb = lane < 16 && (A.experts >> lane & 1u) ? blocks : 0, items = tb * per_xcd, end = prefix16(items);
         const uint64_t mine = __ballot(lane < 16 && j >= end - items && j < end);
         if (!mine) return;                                               // whole block, before any barrier
         const int e = (int)__builtin_ctzll(mine);
@@ -562,14 +587,14 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         j -= __builtin_amdgcn_readlane(end - items, e);
     }
     const int job = (j / ex.tb) * TE_XCD + (int)blockIdx.x % TE_XCD, t = j % ex.tb;
-    if (job >= A.jobs) return;                                           // ... this one too
-    const int rb = job / A.k_parts, part = job % A.k_parts;
+    if (job >= jobs) return;                                             // ... this one too
+    const int rb = job / k_parts, part = job % k_parts;
     constexpr int TILE = BIG ? 32 : MODE;                                // tokens per tile
     const int tiles = (ex.count + TILE - 1) / TILE;
     const int tile0 = t * tiles / ex.tb, n_tiles = (t + 1) * tiles / ex.tb - tile0;
     const int tok0 = tile0 * TILE, n_tok = min(ex.count - tok0, n_tiles * TILE);
     const int n_rows = W13 ? 2 * A.N : A.N, row0 = rb * ROWS;
-    const int u0 = part * A.units_per_part, u1 = min(A.K / 64, u0 + A.units_per_part);
+    const int u0 = part * units_per_part, u1 = min(A.K / 64, u0 + units_per_part);
     // The first sets of weights need no routing: they are requested before the pairs are known.
     const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(ex.blob + A.mat_off), 0, n_rows * (int)A.stride, 0x00020000);
     const TeGeom geo = {A.stride, A.meta_off, A.meta2_off, A.b_off, A.unit_shift, A.run_shift, A.K / 64};
@@ -756,7 +781,8 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 *reinterpret_cast<uint16_t *>(lds + C::OFF_A + tk * C::APITCH + rg * C::RGR + wrow) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
         } else {
             const int mrow = row0 + rg * C::RGR + wrow;
-            const int row = A.k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * A.k_parts + part;
+            // (the argument asked as well: without it the large kernel's totals go through scratch here, 1024 tokens 1073 -> 1491 us)
+            const int row = A.k_parts == 1 && k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * k_parts + part;
             if (tk < n_tok && mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = l_w[tk] * v;
         }
     };
@@ -788,8 +814,8 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             }
         } else if (rb == 0 && part == 0 && tid < n_tok) {                // one block per token block tells k_combine where the rows are
             const int pr = l_pair[tid];
-            const int row = A.k_parts == 1 ? pr : A.part_base + (ex.first + tok0 + tid) * A.k_parts;
-            A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)A.k_parts);
+            const int row = A.k_parts == 1 && k_parts == 1 ? pr : A.part_base + (ex.first + tok0 + tid) * k_parts;
+            A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)k_parts);
         }
     };
 

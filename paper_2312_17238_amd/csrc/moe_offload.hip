@@ -1458,11 +1458,14 @@ constexpr int64_t TILE_MIDDLE_LOW = 1 << 21, TILE_MIDDLE_HIGH = 11 << 20, TILE_T
 // How a step of several tokens runs.  All of it follows from the layer, the batch and the options, nothing from the routing or
 // the cache: the kernels add in different orders, so that is what makes a result depend on neither, and it lets a step
 // whose experts are all resident be queued before anybody has seen its routing.  Where the tokens of an expert matter the
-// plan goes by a nominal routing, the pairs dealt out evenly; an expert with more than that takes another token block.
+// plan goes by a nominal routing, the pairs dealt out evenly; an expert with more than that takes another token block.  The tile
+// kernels' w2 alone looks at the step's own routing, all of it and on the device (few).
 struct BatchPlan {
     enum Kind { GEMV, STREAM, TILE } kind = GEMV;
     int mode13 = TE_BIG, mode2 = TE_BIG;  // TILE: tokens per block, of w1/w3 and of w2
     int parts = 1;                        // ... and the parts that w2 splits its contraction into
+    int few_below = 0;                    // ... other parts for steps of fewer token blocks than this,
+    uint8_t few[16] = {};                 // few[n - 1] where they are n
     struct Window { int parts; bool small; };
     std::vector<Window> win;              // STREAM: per window of 256 / top_k tokens, w2's parts and whether one tile of 16 tokens is enough
 };
@@ -1540,9 +1543,13 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
     // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
     // 226 + 14 (4).
-    auto best_parts = [&](int mode) {
-        int blocks = 0, parts = 1;
+    auto nominal_blocks = [&](int mode) {
+        int blocks = 0;
         for (int e = 0; e < E; ++e) blocks += tile_blocks(b, nominal_count(l, pairs, e), mode);
+        return blocks;
+    };
+    auto best_parts = [&](int mode, int blocks) {
+        int parts = 1;
         const int rb = (b.hidden + tile_rows(mode) - 1) / tile_rows(mode), slots = n_cu_of(c) * tile_per_cu(b, mode);
         double best = 0.0;
         for (int n = 1; n <= std::min(std::min(8, sets), cap); ++n) {
@@ -1553,12 +1560,22 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
         return parts;
     };
     p.mode13 = p.mode2 = c->tile_tokens ? (c->tile_tokens <= 32 ? c->tile_tokens : g32 ? 32 : TE_BIG) : avg > (exact ? 16 : 12) ? 32 : 16;
-    p.parts = best_parts(p.mode2);
-    if (!many || c->tile_tokens) return;
-    // (the 32-token kernel where it is faster by more than the fit's error)
-    const int big_parts = best_parts(TE_BIG);
-    if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < 1.05 * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
-    if (tile_half_us(l, batch, TE_BIG, b.hidden, b.ffn, big_parts) < 1.05 * tile_half_us(l, batch, 32, b.hidden, b.ffn, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
+    p.parts = best_parts(p.mode2, nominal_blocks(p.mode2));
+    if (many && !c->tile_tokens) {
+        // (the 32-token kernel where it is faster by more than the fit's error)
+        const int big_parts = best_parts(TE_BIG, nominal_blocks(TE_BIG));
+        if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < 1.05 * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
+        if (tile_half_us(l, batch, TE_BIG, b.hidden, b.ffn, big_parts) < 1.05 * tile_half_us(l, batch, 32, b.hidden, b.ffn, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
+    }
+    // Tokens that crowd to few experts leave fewer token blocks than the nominal routing's, and its parts would leave part of the
+    // chip idle.  Half as many at most: nearer to the nominal number the better of the two is a matter of a few percent either way
+    // (2944 x 1088, 4-bit groups of 32, 16 experts, 108 tokens, w2 42.7 / 47.5; 2304 x 1216, 21 tokens 26.7 / 23.0).  4096 x 14336, 16 tokens that all choose the same two of eight experts, w2 in us, nominal parts / these: 3-bit 28.9 / 22.2,
+    // 2-bit 34.4 / 21.3, two-level 44.0 / 27.9; 64 such tokens 38.5 / 34.2, 39.4 / 36.8.
+    const int most = std::min(16, nominal_blocks(p.mode2) / 2);
+    for (int n = 1; n <= most && !exact; ++n) {
+        p.few[n - 1] = (uint8_t)best_parts(p.mode2, n);
+        if (p.few[n - 1] != p.parts) p.few_below = n + 1;
+    }
 }
 
 // The 16-token (streaming) kernels' windows: how many parts the w2 launches of a window split their contraction into, and
@@ -1640,13 +1657,17 @@ static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
 // a quarter with two-level 2-bit codes (4 tokens, 1024 x 4096, 3-bit 44 / 30, 4-bit group 128 34 / 29; 320 x 8384, 13 experts 59 / 29;
 // rows twice as long, 2048 x 12032: 3-bit 86 / 74, 2-bit 73 / 76, two-level 95 / 100).  In the smallest layers the two are within
 // 10 % of each other (256 x 512), so there it takes the three tokens of an expert at which a step's time no longer
-// counts in launches alone (groups of 32 stay on the GEMV kernels there).  Groups of 32, GEMV / tile kernels: 1024 x 4096, 8 tokens 42 / 31, 64 tokens
-// 148 / 44; 4096 x 14336, 8 tokens 220 / 189, 16 tokens 273 / 197, 64 tokens 948 / 301.
+// counts in launches alone.  Groups of 32, GEMV / tile kernels: 1024 x 4096, 8 tokens 42 / 31, 64 tokens
+// 148 / 44; 4096 x 14336, 8 tokens 220 / 189, 16 tokens 273 / 197, 64 tokens 948 / 301.  (The smallest layers of these groups stay on the GEMV
+// kernels at any number of tokens, as before they had tile kernels; those would be faster from four tokens of an expert on: 256 x 512, 32
+// tokens 31 / 26, 100 tokens 86 / 29; 320 x 640, the smallest that takes them, 34 / 26 and 96 / 30.)
 //
 // 4-bit group 64: beside the 16-token kernels' steps.  Layers of middle size are faster on the tile kernels at any batch
 // (16-token / tile kernels: 1024 x 4096, 16 tokens 37 / 32, 64 tokens 46 / 37; 4096 x 1792 46 / 42 and 59 / 49; two-level 40 / 34 and 49 / 38), larger ones only
 // where the 16-token kernels need tiles of 32 (16 tokens: 2048 x 5056 50 / 49, 2048 x 7168 60 / 62, 4096 x 14336 148 / 167; 64 tokens: 2048 x 7168
-// 78 / 74, 1024 x 16384 88 / 87, 4096 x 14336 205 / 210), the smallest gain little (512 x 1024 23 / 22).  From the average at
+// 78 / 74, 1024 x 16384 88 / 87, 4096 x 14336 205 / 210), the smallest gain little.  The line lies at 1024 x 2048, from where on few
+// tokens gain too (16 tokens / 64 tokens: 512 x 1024 26.3 / 24.9 and 33.3 / 27.9, 768 x 1536 28.6 / 29.9 and 36.4 / 34.2, 1024 x 2048 29.8 / 32.5 and
+// 38.2 / 36.8, 1024 x 2560 36.5 / 35.3 and 48.1 / 40.2; two-level 32.2 / 34.9 and 40.7 / 39.3 there, 39.4 / 36.2 and 50.4 / 41.2 beyond).  From the average at
 // which many experts need a second tile of 32 they take the tile kernels whatever their size (28 tokens of an expert: 1024 x 4096
 // 54 / 42, 2048 x 7168 92 / 85, 4096 x 14336 265 / 254, 6144 x 16384 399 / 398; 36: 4096 x 14336 445 / 329; two-level 314 / 292
 // and 541 / 372).  Elsewhere with more than 32 (two-level: 16) tokens of an expert on average, if the estimates say so.
@@ -1931,14 +1952,26 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
     };
     // (parts: of w2; 0: w1/w3) items: (row block, part) jobs dealt to the XCDs round robin, an expert's token blocks of one job next to each other
     auto shape = [&](int mode, int parts) {
-        const int n_rows = parts ? A.N : 2 * A.N, row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
+        const bool w2 = parts > 0;
+        const int n_rows = w2 ? A.N : 2 * A.N, row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
         parts = std::max(parts, 1);
-        const int sets = (A.K / 64 + 3) / 4, sp = (sets + parts - 1) / parts;
-        A.units_per_part = sp * 4;
-        A.k_parts = (sets + sp - 1) / sp;
-        A.jobs = row_blocks * A.k_parts;
-        A.per_xcd = (A.jobs + TE_XCD - 1) / TE_XCD;
-        return A.per_xcd * token_blocks(mode) * TE_XCD;
+        const int sets = (A.K / 64 + 3) / 4;
+        te_split(sets, parts, A.k_parts, A.units_per_part);
+        A.row_blocks = row_blocks;
+        auto items = [&](int blocks, int k_parts) { return (row_blocks * k_parts + TE_XCD - 1) / TE_XCD * blocks * TE_XCD; };
+        const int blocks = token_blocks(mode);
+        if (!w2 || !plan.few_below) return items(blocks, A.k_parts);
+        A.few_below = plan.few_below;
+        int all = 0, most = 0, own[16];                  // all: the step's token blocks
+        for (int n = 1; n < plan.few_below; ++n) {
+            int32_t units;
+            te_split(sets, plan.few[n - 1], own[n - 1], units);
+            A.few |= (uint64_t)plan.few[n - 1] << 4 * (n - 1);
+            most = std::max(most, items(n, own[n - 1]));
+        }
+        if (!idx) return std::max(most, items(blocks, A.k_parts));
+        for (int e = 0; e < E; ++e) all += tile_blocks(b, count[e], mode);
+        return items(blocks, all < plan.few_below ? own[all - 1] : A.k_parts);
     };
     const uint64_t n_exp = idx ? experts.size() : 0;                 // whose bytes the launches count (nobody has seen the routing: fold_pending)
     matrix(b.m13, b.hidden, b.ffn);
