@@ -1241,14 +1241,15 @@ static int32_t launch_ffn_args(moe_layer *l, ARGS &A, int n, int nt, bool w13_on
     A.stride13 = b.m13.row_stride; A.meta13 = b.m13.meta_off;
     A.stride2 = b.m2.row_stride; A.meta2 = b.m2.meta_off;
     A.off_w2 = b.off_w2;
-    // Rows of a w2 block: w2_rows where that fills the chip with two waves a SIMD, fewer in smaller layers, whose blocks would
-    // otherwise be few and each a long chain of rows.  us a step, 32 rows / fewer: 704 x 768 3 tokens 21.5 / 16.6, 1024 x 2048 two-level
-    // 2-bit 2 tokens 30.2 / 22.0, 1024 x 4096 two-level 3-bit 34.1 / 27.0; over 120 steps of layers up to 2048 x 4096 whose rows one or two waves
-    // share 0.88 of the time.  Larger layers and longer rows gain nothing on average, and some lose: 2048 x 8192 3-bit 2 tokens 40.8 / 42.6,
-    // 3776 x 11456 two-level 3-bit 64.0 / 67.4, 512 x 14336 3-bit 3 tokens 48.1 / 51.6.
+    // Rows of a w2 block: w2_rows where that gives a compute unit eight waves (five where a lane's chunk has 64 codes, whose rows
+    // cost more to start), fewer in layers whose blocks would otherwise be few and each a long chain of rows.  w2 in us, 32 / 16 / 8 / 4 rows (waves
+    // with 32), 2 or 3 tokens: 4-bit 1280 x 7680 15.1 / 10.0 / 9.0 / 9.3 (480), 4096 x 4096 14.5 / 11.3 / 9.0 / 11.0 (768) and 18.4 / 12.2 / 12.8 / 15.6
+    // (1024), 2048 x 8192 20.3 / 17.8 / 21.1 / 26.1 (1536); two-level 3-bit 4096 x 4096 18.2 / 11.4 / 11.1 / 13.9 (512), 3776 x 11456
+    // 21.9 / 23.0 / 26.5 / 35.1 (1416).  Over 168 steps of ten layers, every format, the step takes 0.88 and 0.89 of its time with 32 rows and never more;
+    // one line for all, at five 0.89 and 0.89, at eight 0.88 and 0.90 and up to 1.05.
     A.rows_per_block = c->w2_rows;
-    if (cs <= 2 && (int64_t)b.hidden * b.ffn <= 8 << 20)
-        while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < n_cu_of(c) * 8) A.rows_per_block = (A.rows_per_block + 1) / 2;
+    const int enough = n_cu_of(c) * (Fmt<BITS>::CODES == 32 ? 8 : 5);
+    while (A.rows_per_block > 4 && (b.hidden + A.rows_per_block - 1) / A.rows_per_block * n * cs < enough) A.rows_per_block = (A.rows_per_block + 1) / 2;
     const uint64_t bytes13 = n_distinct * 2 * (uint64_t)b.ffn * b.m13.row_stride;
     const uint64_t bytes2 = n_distinct * (uint64_t)b.hidden * b.m2.row_stride;
     int32_t rc;
