@@ -36,14 +36,14 @@
 // The X come from whoever produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros
 // to a multiple of four groups.
 //
-// Measured, Mixtral-shaped layer, all 8 experts resident, w1/w3 + w2 us: 1024 tokens 4-bit 640 + 330 (0.75 PFLOP/s; the
-// 16-token kernels' eight windows 8 x (193 + 104)); 512 tokens 3-bit 430 + 220 (GEMV kernels 6.3 ms together); 16 tokens
-// 3-bit 117 + 61, 2-bit 117 + 58 (GEMV kernels 213 + 103); 64 tokens 4-bit 131 + 65 (two 16-token tiles 129 + 71).  What
-// bounds them: no unit is full (4-bit prompt, w1/w3: vector unit 48 %, matrix unit 32 %, LDS 9 %); a third of the waves'
-// time goes into waits, for a unit's barrier and the activations staged for it within that unit (1024 tokens without any
-// load from memory or LDS: 478 + 231), and two waves a SIMD leave nobody else to run.  A fetch further ahead, fewer vector
+// Measured, Mixtral-shaped layer, all 8 experts resident, one step at a time, median (shortest) us of w1/w3 + w2: 1024 tokens 4-bit 766 + 380
+// (734 + 359; passes behind each other, at higher clocks, 1079 the step, 0.66 PFLOP/s; the 16-token kernels' eight windows 8 x (193 + 104)); 512
+// tokens 3-bit 478 + 235 (444 + 212; GEMV kernels 6.3 ms together); 16 tokens 3-bit 115 + 60, 2-bit 116 + 62 (GEMV kernels 213 + 103).  What
+// bounds them: no unit is full (4-bit prompt, w1/w3: vector unit 47 %, matrix unit 34 %, LDS 9 %); a third of the waves'
+// time goes into waits, for a unit's barrier and the activations staged for it within that unit, and two waves a SIMD leave
+// nobody else to run.  A fetch further ahead, fewer vector
 // instructions (subnormal codes) and padded rows of activations each changed less than the runs differ.  2-bit, 16 tokens:
-// vector unit 54 %, of it a quarter for the metadata.
+// vector unit 59 %, of it a quarter for the metadata.
 //
 // Error of this arithmetic alone: y of a layer against 64 bits with the activations between the halves rounded to fp16 as
 // here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), one expert of 1024 x 4096
