@@ -8,3 +8,4 @@
 #include "kernels_mfma_stream.h"
 #include "kernels_mfma16.h"
 #include "kernels_tile.h"
+#include "kernels_big.h"

@@ -1,7 +1,7 @@
 // Grouped dequantize+GEMM on the matrix cores for batches and prompts, every weight format.
 //
-// A block multiplies one expert's tokens (or up to TOK of them) with ROWS memory rows.  k_tile<.., TE_BIG>: 8 waves, 256
-// rows x up to 192 tokens, a wave 64 rows x up to 96 tokens (two waves share each 64 rows).  k_tile<.., 16 or 32>: 128
+// A block multiplies one expert's tokens (or up to TOK of them) with ROWS memory rows.  k_tile<.., TE_BIG>, 2-bit codes (the others have a large
+// kernel of their own, kernels_big.h): 8 waves, 256 rows x up to 192 tokens, a wave 64 rows x up to 96 tokens (two waves share each 64 rows).  k_tile<.., 16 or 32>: 128
 // rows x up to that many tokens, the units of a set shared by the waves of 64 rows (32, with tiles of 32 tokens and 3 or 4 bits:
 // 8 waves a block then fit 128 registers each, four waves a SIMD; 1856 x 5056, 37 tokens, two-level: 26.7 + 19.6 -> 24.2 + 18.2 us,
 // larger layers the same as with 4 waves); two blocks per compute unit.
@@ -29,21 +29,16 @@
 // scaled weight goes in directly; an fp32 s (two-level metadata) goes in as two fp16 numbers, in two products.
 // Second term: a contraction over groups instead of codes, on the bf16 matrix instructions.  X and D = s (ZC - z) go in
 // whole, cut into three bf16 each: eight k-slots a group (slots3_x, slots3_d) hold all products but that of the third parts.  2-bit
-// codes in the large kernel and in tiles of 32: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the result unless the
+// codes in their large kernel and in tiles of 32: two bf16 each (what is lost is 2^-17 of the term, itself a fraction of the result unless the
 // tokens have a mean), the four k-slots (Xh, Xl, Xh, Xl) x (Dh, Dh, Dl, Dl).  Tiles of 16 take steps that the GEMV kernels, whose term is in
 // fp32, would else take, and have the slots: whole too (D staged as fp32, cut where it is used; 2-bit, 16 tokens, 167.6 -> 168.4 us a
 // step; with tiles of 32 it takes an instruction more, 64 tokens 224 -> 231).  Correcting every group's product in the accumulators instead would double the vector work per group.
 // The X come from whoever produced the activations (the gate kernel for h, the w1/w3 epilogue for a), rows padded with zeros
 // to a multiple of four groups.
 //
-// Measured, Mixtral-shaped layer, all 8 experts resident, one step at a time, median (shortest) us of w1/w3 + w2: 1024 tokens 4-bit 766 + 380
-// (734 + 359; passes behind each other, at higher clocks, 1079 the step, 0.66 PFLOP/s; the 16-token kernels' eight windows 8 x (193 + 104)); 512
-// tokens 3-bit 478 + 235 (444 + 212; GEMV kernels 6.3 ms together); 16 tokens 3-bit 115 + 60, 2-bit 116 + 62 (GEMV kernels 213 + 103).  What
-// bounds them: no unit is full (4-bit prompt, w1/w3: vector unit 47 %, matrix unit 34 %, LDS 9 %); a third of the waves'
-// time goes into waits, for a unit's barrier and the activations staged for it within that unit, and two waves a SIMD leave
-// nobody else to run.  A fetch further ahead, fewer vector
-// instructions (subnormal codes) and padded rows of activations each changed less than the runs differ.  2-bit, 16 tokens:
-// vector unit 59 %, of it a quarter for the metadata.
+// Measured, Mixtral-shaped layer, all 8 experts resident, one step at a time, w1/w3 + w2 in us: 16 tokens 3-bit 115 + 60, 2-bit 116 + 62 (GEMV kernels
+// 213 + 103).  What bounds them: no unit is full; a third of the waves' time goes into waits, for a unit's or set's barrier and the activations
+// staged for it, and two to four waves a SIMD leave few others to run.  2-bit, 16 tokens: vector unit 59 %, of it a quarter for the metadata.
 //
 // Error of this arithmetic alone: y of a layer against 64 bits with the activations between the halves rounded to fp16 as
 // here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), one expert of 1024 x 4096
@@ -512,13 +507,13 @@ template <int FMT, int MODE> struct TeCfg {
     // sums: 16 bytes are four groups, of a set (GS) or of one unit: XQ pieces per token and staging step
     // (8 bytes each; 2-bit codes take only the first four but with tiles of 16)
     static constexpr bool XWHOLE = F::GS || MODE == 16;
+    static_assert(!(BIG && F::GS), "3- and 4-bit codes have a large kernel of their own");
     static constexpr int XQ = F::GS ? 2 * F::GPU : SU * 2, XPITCH = F::GS ? 32 * F::GPU : (BIG ? 16 : XQ * (XWHOLE ? 16 : 8) + 16), XBUF = TOK * XPITCH;
     static constexpr int OFF_B = 2 * ABUF, OFF_D = OFF_B + 2 * BBUF, OFF_X = OFF_D + 2 * DBUF, OFF_END = OFF_X + 2 * XBUF;
     static constexpr int OFF_RED = THREADS / 64 * (RGR * MODE * 4);    // MODE 16, 32: behind the waves' partial sums
     static constexpr int ACOLS = ROWS / 2, APITCH = ACOLS * 2 + 16;      // epilogue: fp16 columns of a per token
     static constexpr int OFF_A = BIG ? 0 : OFF_RED, OFF_T = BIG || OFF_END > OFF_RED + TOK * APITCH ? OFF_END : OFF_RED + TOK * APITCH;
     static constexpr int LDS = OFF_T + TOK * 8;
-    using Tot = std::conditional_t<F::GS, float[16], f32x16_t>;
     static_assert(OFF_X >= TOK * APITCH && LDS <= (BIG || F::PLANES == 2 || (F::GPU == 2 && MODE == 32) ? 160 : 80) * 1024, "the epilogue reuses the staging buffers");
 };
 
@@ -534,6 +529,116 @@ __host__ __device__ inline void te_split(int sets, int parts, int32_t &k_parts, 
     k_parts = (sets + per - 1) / per;
 }
 
+// The item of a block.  Items of an XCD: expert by expert, its jobs (row block, part), each job's token blocks next to each other.  How
+// many token blocks an expert has is worked out here, from the sorted list's table, so that the launch need not know the routing
+// (its grid then covers the most there can be; the blocks too many get none: blob is null).
+// Lane e works it out for expert e (a chain of sixteen scalar steps, each behind a load of its arguments, cost 3 us a block).
+struct TeItem { const uint8_t *blob; int expert, first, count, tb, job, t, k_parts, units_per_part; };
+template <bool W13, class BLOCKS>
+__device__ __forceinline__ TeItem te_item(const TeArgs &A, FewPairs &few, BLOCKS &&token_blocks)
+{
+    const int lane = threadIdx.x & 63;
+    TeItem it{};
+    it.k_parts = A.k_parts;
+    it.units_per_part = A.units_per_part;
+    int j = (int)blockIdx.x / TE_XCD, count, first;
+    if (A.pair_expert) {
+        few.load(A.pair_expert, A.n_pairs);
+        count = few.counts(A.n_experts);
+        first = prefix16(count) - count;
+    } else {
+        first = A.first[lane & 15];
+        count = A.first[(lane & 15) + 1] - first;
+    }
+    const int blocks = token_blocks(count);
+    // tokens that crowd to a few experts: w2's contraction in as many parts as fill the chip then (of the whole step's
+    // experts, not the launch's: the order of the sums must not depend on the cache)
+    if (!W13 && A.few_below) {
+        const int n = __builtin_amdgcn_readlane(prefix16(blocks), 15);
+        if (n > 0 && n < A.few_below) {
+            te_split((A.K / 64 + 3) / 4, (int)(A.few >> 4 * (n - 1) & 15u), it.k_parts, it.units_per_part);
+            it.k_parts = uniform(it.k_parts);
+            it.units_per_part = uniform(it.units_per_part);
+        }
+    }
+    const int jobs = A.row_blocks * it.k_parts, per_xcd = (jobs + TE_XCD - 1) / TE_XCD;
+    const int tb = lane < 16 && (A.experts >> lane & 1u) ? blocks : 0, items = tb * per_xcd, end = prefix16(items);
+    const uint64_t mine = __ballot(lane < 16 && j >= end - items && j < end);
+    if (!mine) return it;
+    const int e = (int)__builtin_ctzll(mine);
+    it.tb = __builtin_amdgcn_readlane(tb, e);
+    j -= __builtin_amdgcn_readlane(end - items, e);
+    it.job = (j / it.tb) * TE_XCD + (int)blockIdx.x % TE_XCD;
+    it.t = j % it.tb;
+    if (it.job >= jobs) return it;
+    it.expert = e;
+    it.first = __builtin_amdgcn_readlane(first, e);
+    it.count = __builtin_amdgcn_readlane(count, e);
+    it.blob = A.blob[e];
+    return it;
+}
+
+// The block's pairs and their weights (w2), from its expert's token tok0 on; -1 past the last of n_tok.
+template <bool W13, int TOK>
+__device__ __forceinline__ void te_pairs(const TeArgs &A, const FewPairs &few, const TeItem &it, int tok0, int n_tok, int32_t *l_pair, float *l_w)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (A.pair_expert) {
+        if (tid < TOK && tid >= n_tok) l_pair[tid] = -1;
+        if (uniform(tid >> 6) == 0) {
+            int at = -tok0;                                              // a pair's place among its expert's, from the block's first token
+#pragma unroll
+            for (int c = 0; c < FEW_PAIRS / 64; ++c) {
+                const uint64_t m = few.mask(c, it.expert);
+                const int k = at + __popcll(m & ((1ull << lane) - 1)), p = c * 64 + lane;
+                if (few.e[c] == (uint32_t)it.expert && k >= 0 && k < n_tok) {
+                    l_pair[k] = p;
+                    l_w[k] = W13 ? 0.f : A.pair_w[p];
+                }
+                at += __popcll(m);
+            }
+        }
+    } else if (tid < TOK) {
+        const int p = tid < n_tok ? (int)A.plist[it.first + tok0 + tid] : -1;
+        l_pair[tid] = p;
+        l_w[tid] = p >= 0 && !W13 ? A.pair_w[p] : 0.f;
+    }
+}
+
+// w1/w3: eight columns of a, piece c of a token (pair pr, or none) in row block rb of `cols` columns, and the sums that w2 takes
+template <int GPU>
+__device__ __forceinline__ void te_copy_out(const TeArgs &A, const u32x4_t &q, int pr, int rb, int cols, int c)
+{
+    constexpr int XG = 64 / GPU;                                         // columns per sum
+    const int colg = rb * cols + c * 8;
+    const bool in = colg < A.N;                                          // N is a multiple of 64: a piece is in or out as a whole
+    const h2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    float xa = __builtin_amdgcn_fdot2(as_h2(q[0]), ones, 0.f, false), xb = __builtin_amdgcn_fdot2(as_h2(q[1]), ones, 0.f, false);
+    xa = __builtin_amdgcn_fdot2(as_h2(q[2]), ones, xa, false);
+    xb = __builtin_amdgcn_fdot2(as_h2(q[3]), ones, xb, false);
+    float xs = in ? xa + xb : 0.f;
+    xs += dpp_f<0xB1>(xs);                                               // two lanes: 16 columns
+    if constexpr (XG >= 32) xs += dpp_f<0x4E>(xs);
+    if constexpr (XG == 64) xs += dpp_f<0x141>(xs);
+    if (pr < 0) return;
+    if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
+    uint2 *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
+    const int g = colg / XG;
+    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = split3(xs);
+    if (c == 0 && (rb + 1) * cols >= A.N)                                // the padding behind the last group that no row block covers
+        for (int z = (rb + 1) * cols / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
+}
+
+// w2: one block per token block tells k_combine where the rows are
+__device__ __forceinline__ void te_rows_told(const TeArgs &A, const TeItem &it, int tok0, int n_tok, int rb, int part, const int32_t *l_pair)
+{
+    const int tid = threadIdx.x;
+    if (rb != 0 || part != 0 || tid >= n_tok) return;
+    const int pr = l_pair[tid];
+    const int row = it.k_parts == 1 ? pr : A.part_base + (it.first + tok0 + tid) * it.k_parts;
+    A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)it.k_parts);
+}
+
 template <int FMT, bool W13, int MODE>
 __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAVES_EU)) void k_tile(TeArgs A)
 {
@@ -547,48 +652,11 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6), hh = lane >> 5, col = lane & 31;
     const int rg = wv % C::RG, half = wv / C::RG;                        // rows of the wave; token half (BIG) or unit parity
 
-    // ---------------- the item ----------------
-    // Items of an XCD: expert by expert, its jobs, each job's token blocks next to each other.  How many token blocks an expert
-    // has is worked out here, from the sorted list's table, so that the launch need not know the routing (its grid then
-    // covers the most there can be; the blocks too many end here).
-    // Lane e works it out for expert e (a chain of sixteen scalar steps, each behind a load of its arguments, cost 3 us a block).
     FewPairs few;
-    int j = (int)blockIdx.x / TE_XCD;
-    struct { const uint8_t *blob; int expert, first, count, tb; } ex;
-    int k_parts = A.k_parts, units_per_part = A.units_per_part, jobs;
-    {
-        int count, first;
-        if (A.pair_expert) {
-            few.load(A.pair_expert, A.n_pairs);
-            count = few.counts(A.n_experts);
-            first = prefix16(count) - count;
-        } else {
-            first = A.first[lane & 15];
-            count = A.first[(lane & 15) + 1] - first;
-        }
-        const int blocks = te_token_blocks<C::TOK, BIG>(count);
-        // tokens that crowd to a few experts: w2's contraction in as many parts as fill the chip then (of the whole step's
-        // experts, not the launch's: the order of the sums must not depend on the cache)
-        if (!W13 && A.few_below) {
-            const int n = __builtin_amdgcn_readlane(prefix16(blocks), 15);
-            if (n > 0 && n < A.few_below) {
-                te_split((A.K / 64 + 3) / 4, (int)(A.few >> 4 * (n - 1) & 15u), k_parts, units_per_part);
-                k_parts = uniform(k_parts);
-                units_per_part = uniform(units_per_part);
-            }
-        }
-        jobs = A.row_blocks * k_parts;
-        const int per_xcd = (jobs + TE_XCD - 1) / TE_XCD;
-        const int tb = lane < 16 && (A.experts >> lane & 1u) ? blocks : 0, items = tb * per_xcd, end = prefix16(items);
-        const uint64_t mine = __ballot(lane < 16 && j >= end - items && j < end);
-        if (!mine) return;                                               // whole block, before any barrier
-        const int e = (int)__builtin_ctzll(mine);
-        ex = {A.blob[e], e, __builtin_amdgcn_readlane(first, e), __builtin_amdgcn_readlane(count, e), __builtin_amdgcn_readlane(tb, e)};
-        j -= __builtin_amdgcn_readlane(end - items, e);
-    }
-    const int job = (j / ex.tb) * TE_XCD + (int)blockIdx.x % TE_XCD, t = j % ex.tb;
-    if (job >= jobs) return;                                             // ... this one too
-    const int rb = job / k_parts, part = job % k_parts;
+    const TeItem ex = te_item<W13>(A, few, [](int count) { return te_token_blocks<C::TOK, BIG>(count); });
+    if (!ex.blob) return;                                                // whole block, before any barrier
+    const int k_parts = ex.k_parts, units_per_part = ex.units_per_part, t = ex.t;
+    const int rb = ex.job / k_parts, part = ex.job % k_parts;
     constexpr int TILE = BIG ? 32 : MODE;                                // tokens per tile
     const int tiles = (ex.count + TILE - 1) / TILE;
     const int tile0 = t * tiles / ex.tb, n_tiles = (t + 1) * tiles / ex.tb - tile0;
@@ -606,26 +674,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         fetch_b(f1, 0, u0 + 4);
         fetch_b(f1, 1, u0 + 4);
     }
-    if (A.pair_expert) {
-        if (tid < C::TOK && tid >= n_tok) l_pair[tid] = -1;
-        if (wv == 0) {
-            int at = -tok0;                                              // a pair's place among its expert's, from the block's first token
-#pragma unroll
-            for (int c = 0; c < FEW_PAIRS / 64; ++c) {
-                const uint64_t m = few.mask(c, ex.expert);
-                const int k = at + __popcll(m & ((1ull << lane) - 1)), p = c * 64 + lane;
-                if (few.e[c] == (uint32_t)ex.expert && k >= 0 && k < n_tok) {
-                    l_pair[k] = p;
-                    l_w[k] = W13 ? 0.f : A.pair_w[p];
-                }
-                at += __popcll(m);
-            }
-        }
-    } else if (tid < C::TOK) {
-        const int p = tid < n_tok ? (int)A.plist[ex.first + tok0 + tid] : -1;
-        l_pair[tid] = p;
-        l_w[tid] = p >= 0 && !W13 ? A.pair_w[p] : 0.f;
-    }
+    te_pairs<W13, C::TOK>(A, few, ex, tok0, n_tok, l_pair, l_w);
     __syncthreads();
 
     // ---------------- staging ----------------
@@ -666,10 +715,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
         if constexpr (C::XWHOLE) *reinterpret_cast<uint4 *>(lds + x_to + b * C::XBUF) = t.x;
         else *reinterpret_cast<uint2 *>(lds + x_to + b * C::XBUF) = make_uint2(t.x.x, t.x.z);
     };
-    // (the large kernel works the address of its 4-bit records out for every set: kept, it does not fit the registers; 1024 tokens 1082 -> 1073 us)
-    auto again = [&](int v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); return v; };
-    // no branch inside a loop of units: the compiler would sink the scaling of whole units behind it, their products kept in registers
-    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, A.lift, BIG && F::BITS == 4 ? again(tid) : tid); };
+    auto commit_b = [&](const F &f, int h, int b, int u) __attribute__((always_inline)) { f.commit(h, lds + C::OFF_B + b * C::BBUF, lds + C::OFF_D + b * C::DBUF, geo.units - u, A.lift, tid); };
 
     // Left alone the scheduler moves a step's loads down to just before the LDS stores that wait for them: requests stay
     // above the first mark, stores below the second; everything else may cross.
@@ -679,97 +725,6 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     // ---------------- multiply ----------------
     const uint8_t *const my_rec = lds + C::OFF_B + (rg * C::RGR + col) * C::REC;      // + 32 rows: the wave's second tile
     const CentredPatterns cp = centred_patterns<F::BITS>();
-    auto unpack = [&](h8_t (&b)[2][F::PLANES][4], int bb, int u) __attribute__((always_inline)) {
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            typename F::Raw raw;
-            F::read(raw, my_rec + bb * C::BBUF + rt * 32 * C::REC, hh, u);
-            if constexpr (F::GS) {
-                uint32_t t[4];
-                F::words(raw, t);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) b[rt][0][k] = codes_centred<F::BITS>(t[k], cp);
-            } else {
-                F::decode(raw, b[rt]);
-            }
-        }
-    };
-    // totals of NT token tiles: plain registers where the vector unit adds to them, whole tuples where only the matrix cores do
-    // one unit of the wave's NT token tiles (from LDS address src) into the totals; xsrc: the unit's sums (2-bit codes)
-    auto multiply = [&](auto nt_tag, auto &tot, const h8_t (&b)[2][F::PLANES][4], const uint8_t *src, int bb, int u, const uint8_t *xsrc) __attribute__((always_inline)) {
-        constexpr int NT = decltype(nt_tag)::value;
-        float sc[2];
-        bf8_t d[2];
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            if constexpr (F::GS) sc[rt] = *reinterpret_cast<const float *>(my_rec + bb * C::BBUF + rt * 32 * C::REC + F::SOFF + u * 4);
-            else d[rt] = slots_d(F::factors(my_rec + bb * C::BBUF + rt * 32 * C::REC, lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * 32 + col) * F::DB, hh, u));
-        }
-#pragma unroll
-        for (int mt = 0; mt < NT; ++mt) {
-            h8_t a[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + mt * 32 * C::PITCH + k * 16);
-            if constexpr (F::GS) {
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt) {
-                    f32x16_t g;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) g[i] = 0.f;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) g = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k], b[rt][0][k], g, 0, 0, 0);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) tot[rt][mt][i] = __builtin_fmaf(sc[rt], g[i], tot[rt][mt][i]);
-                    __builtin_amdgcn_sched_barrier(0);                   // one product in registers at a time
-                }
-            } else {
-                const uint2 xv = *reinterpret_cast<const uint2 *>(xsrc + mt * 32 * C::XPITCH);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int pl = 0; pl < F::PLANES; ++pl)
-#pragma unroll
-                        for (int rt = 0; rt < 2; ++rt) tot[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k], b[rt][pl][k], tot[rt][mt], 0, 0, 0);
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt) tot[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(slots_x(xv), d[rt], tot[rt][mt], 0, 0, 0);
-            }
-        }
-    };
-    // GS: the zero-point term of a set
-    auto zero_term = [&](auto nt_tag, auto &tot, int tile, int bb) __attribute__((always_inline)) {
-        if constexpr (F::GS) {
-            constexpr int NT = decltype(nt_tag)::value;
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {                                // two groups each
-                bf8_t d[2];
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
-                    d[rt] = slots3_d(*reinterpret_cast<const uint2 *>(lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * 32 + col) * F::DB + (p * 2 + hh) * 8));
-#pragma unroll
-                for (int mt = 0; mt < NT; ++mt) {
-                    const bf8_t xv = slots3_x(*reinterpret_cast<const uint2 *>(lds + C::OFF_X + bb * C::XBUF + ((tile + mt) * 32 + col) * C::XPITCH + (p * 2 + hh) * 8));
-#pragma unroll
-                    for (int rt = 0; rt < 2; ++rt) {
-                        f32x16_t z;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) z[i] = tot[rt][mt][i];
-                        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, d[rt], z, 0, 0, 0);
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) tot[rt][mt][i] = z[i];
-                    }
-                }
-            }
-        }
-    };
-    auto clear = [&](auto nt_tag, auto &tot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-            for (int mt = 0; mt < decltype(nt_tag)::value; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) tot[rt][mt][i] = 0.f;
-    };
-
     // ---------------- epilogue ----------------
     // w1/w3: even columns hold w1's rows, odd ones w3's: SiLU(u) v, rounded to fp16, collected in LDS (put) so that rows of
     // a leave in 16-byte pieces and their sums per group are taken on the way (copy_out).  w2: put stores.
@@ -789,37 +744,55 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
     auto copy_out = [&]() __attribute__((always_inline)) {
         if constexpr (W13) {
             __syncthreads();
-            constexpr int CPT = C::ACOLS / 8, XG = 64 / F::GPU;         // 16-byte pieces per token, columns per sum
+            constexpr int CPT = C::ACOLS / 8;                            // 16-byte pieces per token
             for (int p = tid; p < n_tiles * TILE * CPT; p += THREADS) {
-                const int tk = p / CPT, c = p % CPT, colg = rb * C::ACOLS + c * 8;
-                const bool in = colg < A.N;                              // N is a multiple of 64: a piece is in or out as a whole
-                const u32x4_t q = *reinterpret_cast<const u32x4_t *>(lds + C::OFF_A + tk * C::APITCH + c * 16);
-                const h2_t ones = {(_Float16)1.f, (_Float16)1.f};
-                float xa = __builtin_amdgcn_fdot2(as_h2(q[0]), ones, 0.f, false), xb = __builtin_amdgcn_fdot2(as_h2(q[1]), ones, 0.f, false);
-                xa = __builtin_amdgcn_fdot2(as_h2(q[2]), ones, xa, false);
-                xb = __builtin_amdgcn_fdot2(as_h2(q[3]), ones, xb, false);
-                float xs = in ? xa + xb : 0.f;
-                xs += dpp_f<0xB1>(xs);                                   // two lanes: 16 columns
-                if constexpr (XG >= 32) xs += dpp_f<0x4E>(xs);
-                if constexpr (XG == 64) xs += dpp_f<0x141>(xs);
-                if (tk < n_tok) {
-                    const int pr = l_pair[tk];
-                    if (in) *reinterpret_cast<u32x4_t *>(A.a + (size_t)pr * A.N + colg) = q;
-                    uint2 *const xo = A.xs_out + (size_t)pr * A.xs_out_stride;
-                    const int g = colg / XG;
-                    if (colg % XG == 0 && g < A.xs_out_stride) xo[g] = split3(xs);
-                    if (c == 0 && (rb + 1) * C::ACOLS >= A.N)            // the padding behind the last group that no row block covers
-                        for (int z = (rb + 1) * C::ACOLS / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
-                }
+                const int tk = p / CPT, c = p % CPT;
+                te_copy_out<F::GPU>(A, *reinterpret_cast<const u32x4_t *>(lds + C::OFF_A + tk * C::APITCH + c * 16), tk < n_tok ? l_pair[tk] : -1, rb, C::ACOLS, c);
             }
-        } else if (rb == 0 && part == 0 && tid < n_tok) {                // one block per token block tells k_combine where the rows are
-            const int pr = l_pair[tid];
-            const int row = A.k_parts == 1 && k_parts == 1 ? pr : A.part_base + (ex.first + tok0 + tid) * k_parts;
-            A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)k_parts);
+        } else {
+            te_rows_told(A, ex, tok0, n_tok, rb, part, l_pair);
         }
     };
 
     if constexpr (BIG) {
+        auto unpack = [&](h8_t (&b)[2][F::PLANES][4], int bb, int u) __attribute__((always_inline)) {
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                typename F::Raw raw;
+                F::read(raw, my_rec + bb * C::BBUF + rt * 32 * C::REC, hh, u);
+                F::decode(raw, b[rt]);
+            }
+        };
+        // one unit of the wave's NT token tiles (from LDS address src) into the totals; xsrc: the unit's sums
+        auto multiply = [&](auto nt_tag, auto &tot, const h8_t (&b)[2][F::PLANES][4], const uint8_t *src, int bb, int u, const uint8_t *xsrc) __attribute__((always_inline)) {
+            constexpr int NT = decltype(nt_tag)::value;
+            bf8_t d[2];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) d[rt] = slots_d(F::factors(my_rec + bb * C::BBUF + rt * 32 * C::REC, lds + C::OFF_D + bb * C::DBUF + (rg * C::RGR + rt * 32 + col) * F::DB, hh, u));
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt) {
+                h8_t a[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) a[k] = *reinterpret_cast<const h8_t *>(src + mt * 32 * C::PITCH + k * 16);
+                const uint2 xv = *reinterpret_cast<const uint2 *>(xsrc + mt * 32 * C::XPITCH);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int pl = 0; pl < F::PLANES; ++pl)
+#pragma unroll
+                        for (int rt = 0; rt < 2; ++rt) tot[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[k], b[rt][pl][k], tot[rt][mt], 0, 0, 0);
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) tot[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(slots_x(xv), d[rt], tot[rt][mt], 0, 0, 0);
+            }
+        };
+        auto clear = [&](auto nt_tag, auto &tot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int mt = 0; mt < decltype(nt_tag)::value; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) tot[rt][mt][i] = 0.f;
+        };
         // units one by one: activations double buffered per unit, weights per set
         const int nt0 = (n_tiles + 1) / 2;
         {
@@ -836,7 +809,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
             constexpr int NT = decltype(nt_tag)::value;
             constexpr bool LATE = decltype(late_tag)::value;             // unpacks a unit ahead, after its matrix work
             const int tile = LATE ? nt0 : 0;
-            typename C::Tot tot[2][NT > 0 ? NT : 1];
+            f32x16_t tot[2][NT > 0 ? NT : 1];
             clear(nt_tag, tot);
             h8_t b[2][F::PLANES][4];
             if (LATE && NT > 0) unpack(b, 0, 0);
@@ -849,21 +822,18 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                     fetch_a(t, u + s + 1);
                     if (s == 0) fetch_b(f, 0, u + 4);            // weights of the next set in two halves: registers
                     if (s == 1) fetch_b(f, 1, u + 4);
-                    if (!F::GS) fetch_x(t, u + s + 1);
-                    else if (s == 1) fetch_x(t, u + 4);
+                    fetch_x(t, u + s + 1);
                     loads_above();
                     if constexpr (NT > 0) {
                         if (!LATE) unpack(b, bb, s);
                         multiply(nt_tag, tot, b, lds + (s & 1) * C::ABUF + (tile * 32 + col) * C::PITCH + hh * 64, bb, s,
                                  lds + C::OFF_X + (s & 1) * C::XBUF + (tile * 32 + col) * C::XPITCH + hh * 8);
-                        if (s == 3) zero_term(nt_tag, tot, tile, bb);
                         if (LATE) unpack(b, s == 3 ? bb ^ 1 : bb, (s + 1) & 3);
                     }
                     stores_below();
                     commit_a(t, (s & 1) ^ 1);
                     if (s == 0) commit_b(f, 0, bb ^ 1, u + 4);
-                    if (!F::GS) commit_x(t, (s & 1) ^ 1);
-                    else if (s == 1) commit_x(t, bb ^ 1);
+                    commit_x(t, (s & 1) ^ 1);
                     if (s == 1) commit_b(f, 1, bb ^ 1, u + 4);
                     if (s == 3) bb ^= 1;
                     __syncthreads();

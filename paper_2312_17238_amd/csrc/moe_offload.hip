@@ -1449,12 +1449,13 @@ static bool tile_format(const moe_layer *l)
 static int tile_blocks(const BlobLayout &b, int count, int mode)
 {
     if (mode != TE_BIG) return (count + mode - 1) / mode;
-    return b.bits == 2 && b.scale_group ? te_token_blocks<TeCfg<28, TE_BIG>::TOK, true>(count) : te_token_blocks<TeCfg<4, TE_BIG>::TOK, true>(count);
+    if (b.bits != 2) return te_token_blocks<TbCfg::TOK, true>(count);
+    return b.scale_group ? te_token_blocks<TeCfg<28, TE_BIG>::TOK, true>(count) : te_token_blocks<TeCfg<2, TE_BIG>::TOK, true>(count);
 }
 
-constexpr int TILE_MODE32_AVERAGE = 26;                              // tokens of an expert on average from where on the large tile kernel is considered
+constexpr int TILE_MODE32_AVERAGE = 26;                              // tokens of an expert on average from where on the 2-bit large tile kernel is considered, and tile_may
 constexpr int STREAM_SMALL_AVERAGE = 14;                              // ... up to which the 16-token kernels' entries are one tile of 16
-constexpr int64_t TILE_MIDDLE_LOW = 1 << 21, TILE_MIDDLE_HIGH = 11 << 20, TILE_TWO_TILES_HIGH = 18 << 20;    // hidden * ffn, tile_may
+constexpr int64_t TILE_MIDDLE_LOW = 1 << 21, TILE_MIDDLE_HIGH = 11 << 20, TILE_TWO_TILES_HIGH = 40 << 20;    // hidden * ffn, tile_may
 
 // How a step of several tokens runs.  All of it follows from the layer, the batch and the options, nothing from the routing or
 // the cache: the kernels add in different orders, so that is what makes a result depend on neither, and it lets a step
@@ -1482,7 +1483,8 @@ static int tile_rows(int mode) { return mode == TE_BIG ? 256 : 128; }
 template <int FMT> static int tile_lds(int mode)
 {
     if (mode == 16) return TeCfg<FMT, 16>::LDS;
-    if constexpr (FMT != 5 && FMT != 58) { if (mode == TE_BIG) return TeCfg<FMT, TE_BIG>::LDS; }
+    if constexpr (FMT == 2 || FMT == 28) { if (mode == TE_BIG) return TeCfg<FMT, TE_BIG>::LDS; }
+    if (mode == TE_BIG) return TbCfg::LDS;
     return TeCfg<FMT, 32>::LDS;
 }
 static int tile_per_cu(const BlobLayout &b, int mode)
@@ -1501,18 +1503,46 @@ static int tile_per_cu(const BlobLayout &b, int mode)
     return std::min(2, 160 * 1024 / lds);
 }
 
-// One launch of a tile kernel in us: rounds of blocks, a block's start and end and its units of 64 columns.  The large kernel's
+// Blocks of `size` tokens that an expert with avg tokens on average is expected to need, its tokens spread as if the routing were random.
+static double expected_blocks(double avg, double share, int size)
+{
+    const double dev = std::sqrt(std::max(avg * (1.0 - share), 1e-9));
+    double n = 1.0;
+    for (int k = 1; k <= MOE_MAX_BATCH / size + 1; ++k) n += 0.5 * std::erfc((size * k + 0.5 - avg) / dev * M_SQRT1_2);
+    return n;
+}
+
+// One launch of a tile kernel of 3- or 4-bit codes in us, mode 32 or the large one (k_big): rounds of blocks, a block's start and end and its units of
+// 64 columns.  k_big has one block a compute unit, whose rounds are paid in whole where they are few; of the other's last round what is in it counts.
+// Fitted to 400 launches over seven layers, 5 to 128 tokens of an expert (standard deviation 11 and 14 %).  w1/w3 and w2 at 32 tokens / k_big, us a
+// launch: 8 experts 4096x14336, 4-bit, top 2, 64 tokens 139 / 159 and 65 / 66, 96 tokens 163 / 164 and 84 / 83, 128 tokens 198 / 184 and 96 / 86, 192
+// tokens 295 / 220 and 119 / 89; 4096x2048 128 tokens 38 / 45 and 23 / 23; 1856x5056, 6 experts, top 3, 32 tokens 24 / 22 and 18 / 18, 64 tokens 37 / 28
+// and 26 / 24, two-level 48 tokens 26 / 23 and 24 / 23; 512x2048, 16 experts, 384 tokens 19 / 13 and 11 / 15.
+static double scaled_half_us(const moe_layer *l, int batch, int mode, int n_rows, int cols, int parts)
+{
+    const BlobLayout &b = l->lay;
+    const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs), avg = pairs / n_exp, share = (double)l->cfg.top_k / l->cfg.n_experts;
+    const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
+    const int row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
+    const double tiles = expected_blocks(avg, share, 32), blocks = mode == TE_BIG ? expected_blocks(avg, share, TbCfg::TOK) : tiles;
+    const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
+    const bool heavy = b.bits == 3 || b.scale_group;                                                   // more unpacking
+    const double fill = tiles / blocks;                                                                // tiles of a k_big block
+    if (mode == TE_BIG) return (rounds <= 4.0 ? std::ceil(rounds - 0.02) : rounds + 0.5) * (6.9 + 2.0 * fill + units * (0.30 + (heavy ? 0.064 : 0.0) + 0.15 * fill));
+    return 3.2 + std::max(rounds, 0.42) * units * (0.58 + (heavy ? 0.126 : 0.0)) + 4.8 * std::max(rounds, 1.0);
+}
+
+// The same of 2-bit codes: rounds of blocks, a block's start and end and its units.  The large kernel's
 // rounds are paid in whole (one block a compute unit), but with few blocks their tiles run faster; of the others' last round what
 // is in it counts.  An expert has more or less than its share of the pairs, in about half of the cases a 32-token tile more.
-// Fitted to which of the two ran faster, each half by itself, over 38 layers and batches.  w1/w3 and w2 at 32 tokens / at the
-// large kernel, us a step: 8 experts 4096x14336, 4-bit, top 2, 128 tokens 305 / 392, 192 370 / 429, 256 449 / 420, 512 778 / 578;
-// 2-bit, 160 tokens 359 / 507, 300 527 / 561, 512 816 / 645; 3-bit 960x960, 352 tokens 37 / 51, 3136x1792, 503 tokens 144 / 97;
-// 4-bit 256x12288, 6 experts, 306 tokens 87 / 88, with w1/w3 alone at the large one 62.  Two-level 2-bit scales go in as two numbers,
+// Fitted to which of the two ran faster, each half by itself.  w1/w3 and w2 at 32 tokens / at the
+// large kernel, us a step: 8 experts 4096x14336, top 2, 160 tokens 359 / 507, 300 527 / 561, 512 816 / 645.  Two-level 2-bit scales go in as two numbers,
 // which costs the large kernel's units 1.3 times the matrix work, and the 32-token one has a compute unit to itself: one launch
 // each, 32 tokens / large kernel, w1/w3 of 4096x14336, 160 tokens 513 / 397, 384 tokens 862 / 489; w2 of 256x12288, 6 experts, 306 tokens 28 / 91.
 static double tile_half_us(const moe_layer *l, int batch, int mode, int n_rows, int cols, int parts)
 {
     const BlobLayout &b = l->lay;
+    if (b.bits != 2) return scaled_half_us(l, batch, mode, n_rows, cols, parts);
     const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs), avg = pairs / n_exp;
     const double spread = l->cfg.top_k == l->cfg.n_experts ? 0.0 : 0.45;
     const double tiles = spread > 0.0 ? std::max(1.0, avg / 32 + spread) : std::ceil(avg / 32);        // of 32 tokens, an expert's
@@ -1520,9 +1550,9 @@ static double tile_half_us(const moe_layer *l, int batch, int mode, int n_rows, 
     const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
     const int row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
     const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
-    if (mode != TE_BIG) return std::max(1.0, rounds) * (2.5 + units * 0.54 * (b.bits != 2 ? 1.0 : b.scale_group ? 1.05 : 0.86));
+    if (mode != TE_BIG) return std::max(1.0, rounds) * (2.5 + units * 0.54 * (b.scale_group ? 1.05 : 0.86));
     const double half_tiles = std::max(1.0, tiles / blocks / 2 + 0.25), whole = std::ceil(rounds);     // tiles of a block's fuller half
-    return whole * 3.7 + units * (b.bits == 2 && b.scale_group ? 0.68 : 0.52) * (whole + half_tiles * std::max(rounds, 0.32 * whole));
+    return whole * 3.7 + units * (b.scale_group ? 0.68 : 0.52) * (whole + half_tiles * std::max(rounds, 0.32 * whole));
 }
 
 // Tile kernels: tokens per block, and into how many parts w2 splits its contraction.
@@ -1537,7 +1567,7 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     // (groups of 32 have no large kernel: twice the metadata does not fit beside its tokens)
     const bool exact = l->cfg.top_k == E;
     const double avg = (double)pairs / E;
-    const bool g32 = b.bits == 4 && b.group == 32, many = avg > (exact ? 32 : TILE_MODE32_AVERAGE) && !g32;
+    const bool g32 = b.bits == 4 && b.group == 32, many = !g32 && avg > (b.bits == 2 ? (exact ? 32 : TILE_MODE32_AVERAGE) : exact ? 16 : 12);
     const int sets = (b.ffn / 64 + 3) / 4;
     const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
     // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
@@ -1563,10 +1593,18 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     p.mode13 = p.mode2 = c->tile_tokens ? (c->tile_tokens <= 32 ? c->tile_tokens : g32 ? 32 : TE_BIG) : avg > (exact ? 16 : 12) ? 32 : 16;
     p.parts = best_parts(p.mode2, nominal_blocks(p.mode2));
     if (many && !c->tile_tokens) {
-        // (the 32-token kernel where it is faster by more than the fit's error)
-        const int big_parts = best_parts(TE_BIG, nominal_blocks(TE_BIG));
-        if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < 1.05 * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
-        if (tile_half_us(l, batch, TE_BIG, b.hidden, b.ffn, big_parts) < 1.05 * tile_half_us(l, batch, 32, b.hidden, b.ffn, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
+        // (2 bits: the 32-token kernel where it is faster by more than the fit's error, else the large one.  A part's rows are written and read again.)
+        const double margin = b.bits == 2 ? 1.05 : 0.95, part_us = b.bits == 2 ? 0.0 : 2e-6 * pairs * b.hidden;
+        auto w2_us = [&](int mode, int parts) {
+            int32_t k_parts, units;
+            te_split(sets, parts, k_parts, units);
+            return tile_half_us(l, batch, mode, b.hidden, b.ffn, parts) + (k_parts - 1) * part_us;
+        };
+        int big_parts = best_parts(TE_BIG, nominal_blocks(TE_BIG));
+        for (int n = 1; n <= std::min(std::min(8, sets), cap) && b.bits != 2; ++n)           // by the estimate, which counts experts with more than their share as well
+            if (w2_us(TE_BIG, n) < w2_us(TE_BIG, big_parts)) big_parts = n;
+        if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < margin * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
+        if (w2_us(TE_BIG, big_parts) < margin * w2_us(32, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
     }
     // Tokens that crowd to few experts leave fewer token blocks than the nominal routing's, and its parts would leave part of the
     // chip idle.  Half as many at most: nearer to the nominal number the better of the two is a matter of a few percent either way
@@ -1582,19 +1620,14 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
 // The 16-token (streaming) kernels' windows: how many parts the w2 launches of a window split their contraction into, and
 // whether their entries are tiles of 16 tokens or of 32.  One tile of 16 costs 88 us where two cost 129 (w1/w3, Mixtral-shaped), so
 // it is the better one as long as less than about four experts in ten need a second entry: up to an average of 14.
-//
-// Returns what the step takes with them in us (tile_us: why, and where the numbers come from).
-static double plan_windows(const moe_layer *l, int batch, BatchPlan &p)
+static void plan_windows(const moe_layer *l, int batch, BatchPlan &p)
 {
     const moe_ctx *c = l->ctx;
     const moe_layer_config_t &cf = l->cfg;
     const int window = MF_MAX_PAIRS / cf.top_k, n_cu = n_cu_of(c);
-    const int row_blocks = (cf.hidden + TL_ROWS - 1) / TL_ROWS, row_blocks13 = (2 * cf.ffn + TL_ROWS - 1) / TL_ROWS;
-    const int steps = (cf.ffn / 64 + TL_SG - 1) / TL_SG, steps13 = (cf.hidden / 64 + TL_SG - 1) / TL_SG;
+    const int row_blocks = (cf.hidden + TL_ROWS - 1) / TL_ROWS;
     const uint64_t extra_rows = c->ypart_extra_floats / cf.hidden, pairs = (uint64_t)batch * cf.top_k;
     const int max_parts = (int)std::min<uint64_t>(255, std::max<uint64_t>(1, extra_rows / pairs));
-    const double two_level = cf.scale_group > 0 ? 1.0 : 0.0;
-    double us = 17.0 + 0.037 * batch;
     p.win.clear();
     for (int w0 = 0; w0 < batch; w0 += window) {
         const int mine = (std::min(batch, w0 + window) - w0) * cf.top_k;
@@ -1605,50 +1638,7 @@ static double plan_windows(const moe_layer *l, int batch, BatchPlan &p)
         // parts such a launch leaves most of the chip idle on the step's critical path
         const int want = std::max(4, (2 * n_cu + entries * row_blocks - 1) / std::max(1, entries * row_blocks));
         p.win.push_back({std::min(want, max_parts), small});
-        auto half = [&](int rb, int n_steps, int parts) {
-            parts = std::min(parts, n_steps);
-            const int part_steps = (n_steps + parts - 1) / parts, k_parts = (n_steps + part_steps - 1) / part_steps;
-            const double k = part_steps * TL_SG * 64 / 4096.0, x = (double)entries * rb * k_parts / (2 * n_cu);
-            return small ? k * (x * (31.0 + 5.0 * two_level) + 5.0) : k * (x * (33.0 + 8.0 * two_level) + 21.0);
-        };
-        us += 17.0 + half(row_blocks13, steps13, 1) + half(row_blocks, steps, p.win.back().parts);
     }
-    return us;
-}
-
-// What the step takes with the tile kernels in us, after plan_tile.
-//
-// 4-bit group-64 layers have two families of kernels for a batch, and which one is faster turns on more than the tokens:
-// the tile kernels read an expert's weights once for up to 192 tokens, but a block of the large one costs 65, 98 or 131 us
-// per 4096 columns (up to 64, 128 or 192 tokens) and there is one to a compute unit, so a round that is not full is paid in
-// whole; the 16-token kernels read them again for every 32 tokens, 37 us per round of the same work, and start again
-// for every window.  So the step's time is estimated for both, constants fitted to 548 measured steps
-// (hidden 256 to 4096, ffn 512 to 14336, 1 to 16 experts, 16 to 700 tokens, both metadata levels; standard deviation 6 %).
-static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
-{
-    const BlobLayout &b = l->lay;
-    const int n_cu = n_cu_of(l->ctx), pairs = batch * l->cfg.top_k;
-    const bool big = p.mode13 == TE_BIG;
-    const double two_level = b.scale_group > 0 ? 1.0 : 0.0;
-    double us = big ? 40.0 + 0.057 * batch : 41.0 + 0.05 * batch;
-    auto half = [&](int mode, int n_rows, int cols, int parts) {
-        int blocks = 0, halves = 0;              // token blocks; token tiles of a block's fuller half, added up over them
-        for (int e = 0; e < l->cfg.n_experts; ++e) {
-            const int count = nominal_count(l, pairs, e);
-            if (!count) continue;
-            const int tb = tile_blocks(b, count, mode), tiles = (count + 31) / 32;
-            blocks += tb;
-            halves += tb * (((tiles + tb - 1) / tb + 1) / 2);
-        }
-        const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
-        const int items = (n_rows + tile_rows(mode) - 1) / tile_rows(mode) * blocks * k_parts, slots = n_cu * tile_per_cu(b, mode);
-        // rounds of blocks, the last one whole (rounds) or by its share (x), times their columns / 4096
-        const double k = part_sets * 256 / 4096.0, rounds = (items + slots - 1) / slots * k, x = (double)items / slots * k, tiles = (double)halves / blocks;
-        us += mode == TE_BIG ? rounds * (33.0 + 26.0 * tiles + 4.5 * two_level) + x * (24.0 - 7.6 * tiles) : rounds * (11.0 + 3.5 * two_level) + x * 28.0;
-    };
-    half(p.mode13, 2 * b.ffn, b.hidden, 1);
-    half(p.mode2, b.hidden, b.ffn, p.parts);
-    return us;
 }
 
 // Whether the tile kernels may run a step.  Times of a step in us, everything resident, GEMV kernels / tile kernels.
@@ -1663,27 +1653,24 @@ static double tile_us(const moe_layer *l, int batch, const BatchPlan &p)
 // kernels at any number of tokens, as before they had tile kernels; those would be faster from four tokens of an expert on: 256 x 512, 32
 // tokens 31 / 26, 100 tokens 86 / 29; 320 x 640, the smallest that takes them, 34 / 26 and 96 / 30.)
 //
-// 4-bit group 64: beside the 16-token kernels' steps.  Layers of middle size are faster on the tile kernels at any batch
-// (16-token / tile kernels: 1024 x 4096, 16 tokens 37 / 32, 64 tokens 46 / 37; 4096 x 1792 46 / 42 and 59 / 49; two-level 40 / 34 and 49 / 38), larger ones only
-// where the 16-token kernels need tiles of 32 (16 tokens: 2048 x 5056 50 / 49, 2048 x 7168 60 / 62, 4096 x 14336 148 / 167; 64 tokens: 2048 x 7168
-// 78 / 74, 1024 x 16384 88 / 87, 4096 x 14336 205 / 210), the smallest gain little.  The line lies at 1024 x 2048, from where on few
-// tokens gain too (16 tokens / 64 tokens: 512 x 1024 26.3 / 24.9 and 33.3 / 27.9, 768 x 1536 28.6 / 29.9 and 36.4 / 34.2, 1024 x 2048 29.8 / 32.5 and
-// 38.2 / 36.8, 1024 x 2560 36.5 / 35.3 and 48.1 / 40.2; two-level 32.2 / 34.9 and 40.7 / 39.3 there, 39.4 / 36.2 and 50.4 / 41.2 beyond).  From the average at
-// which many experts need a second tile of 32 they take the tile kernels whatever their size (28 tokens of an expert: 1024 x 4096
-// 54 / 42, 2048 x 7168 92 / 85, 4096 x 14336 265 / 254, 6144 x 16384 399 / 398; 36: 4096 x 14336 445 / 329; two-level 314 / 292
-// and 541 / 372).  Elsewhere with more than 32 (two-level: 16) tokens of an expert on average, if the estimates say so.
-static bool tile_may(const moe_layer *l, int batch, bool stream, bool *surely)
+// 4-bit group 64: beside the 16-token kernels' steps.  Where those do with tiles of 16 (up to 14 tokens of an expert on average) layers of middle
+// size are faster on the tile kernels (16-token / tile kernels: 1024 x 4096, 16 tokens 37 / 32; 4096 x 1792 46 / 42, two-level 40 / 34), larger ones
+// not (16 tokens: 2048 x 5056 50 / 49, 2048 x 7168 60 / 62, 4096 x 14336 148 / 167), the smallest gain little.  That line lies at 1024 x 2048
+// (16 tokens: 512 x 1024 26.3 / 24.9, 768 x 1536 28.6 / 29.9, 1024 x 2048 29.8 / 32.5, 1024 x 2560 36.5 / 35.3; two-level 32.2 / 34.9 there, 39.4 / 36.2 beyond).
+// Where they need tiles of 32 the tile kernels take all but the largest layers (18 to 24 tokens of an expert: 4096 x 512 57 / 50, 2048 x 5056
+// 81 / 66, 4096 x 8192 147 / 139, 2048 x 14336 132 / 131; 4096 x 14336 220 / 224, two-level 262 / 265), and those too from the average at which
+// many experts need a second tile of 32 (30 tokens of an expert: 4096 x 14336 303 / 260, 2048 x 14336 166 / 154; two-level 355 / 317; 4096 x 8192
+// 201 / 156); layers up to 1024 x 2048 where the 16-token kernels start again for a second window of tokens (1024 x 2048, 136 tokens 78 / 44, 480
+// tokens 176 / 68; 144 tokens, 16 experts 92 / 49; one window, 96 tokens 44.4 / 46.3).
+static bool tile_may(const moe_layer *l, int batch, bool stream)
 {
     const moe_layer_config_t &cf = l->cfg;
     const int pairs = batch * cf.top_k;
     const int64_t size = (int64_t)cf.hidden * cf.ffn;
-    *surely = true;
     if (stream) {
-        const bool two_tiles = pairs > STREAM_SMALL_AVERAGE * cf.n_experts;
-        const bool middle = size <= (two_tiles ? TILE_TWO_TILES_HIGH : TILE_MIDDLE_HIGH);
-        if (size > TILE_MIDDLE_LOW && (middle || pairs > TILE_MODE32_AVERAGE * cf.n_experts)) return true;
-        *surely = false;
-        return pairs > (cf.scale_group ? 16 : 32) * cf.n_experts;
+        if (pairs <= STREAM_SMALL_AVERAGE * cf.n_experts) return size > TILE_MIDDLE_LOW && size <= TILE_MIDDLE_HIGH;
+        if (size <= TILE_MIDDLE_LOW) return pairs > MF_MAX_PAIRS;
+        return size <= TILE_TWO_TILES_HIGH || pairs > TILE_MODE32_AVERAGE * cf.n_experts;
     }
     const bool g64 = cf.bits == 4 && cf.group == 64;         // with runs of metadata that the 16-token kernels do not take
     if (pairs > (g64 ? 8 : 3) * cf.n_experts && (cf.bits != 4 || cf.group != 32 || size > 1 << 17)) return true;
@@ -1702,15 +1689,13 @@ static BatchPlan plan_batch(const moe_layer *l, int batch)
     // two-level metadata: a step of the streaming kernel stages one run's quad per row, so a run must cover the step
     auto runs_ok = [&](const MatLayout &m) { return m.run_len == 0 || m.run_len == m.cols / (uint32_t)cf.group || m.run_len % TL_SG == 0; };
     const bool stream = g64 && runs_ok(l->lay.m13) && runs_ok(l->lay.m2);
-    bool surely = false;
-    const bool may = tile_may(l, batch, stream, &surely);
-    const bool tile = (c->mfma_form == 6 || (c->mfma_form == 0 && may)) && tile_format(l);
-    if (tile) plan_tile(l, batch, p);
-    double stream_us = 0.0;
-    const bool chosen = tile && (surely || !stream || c->mfma_form == 6);
-    if (stream && !chosen) stream_us = plan_windows(l, batch, p);
-    if (chosen || (tile && tile_us(l, batch, p) < stream_us)) p.kind = BatchPlan::TILE;
-    else if (stream) p.kind = BatchPlan::STREAM;
+    if ((c->mfma_form == 6 || (c->mfma_form == 0 && tile_may(l, batch, stream))) && tile_format(l)) {
+        p.kind = BatchPlan::TILE;
+        plan_tile(l, batch, p);
+    } else if (stream) {
+        p.kind = BatchPlan::STREAM;
+        plan_windows(l, batch, p);
+    }
     return p;
 }
 
@@ -1900,8 +1885,9 @@ static int32_t launch_tile_fmt(moe_ctx *c, int mode, int grid, uint64_t bytes, c
 {
     if (mode == 16) return launch_tile_mode<FMT, W13, 16>(c, grid, bytes, A);
     if (mode == 32) return launch_tile_mode<FMT, W13, 32>(c, grid, bytes, A);
-    if constexpr (FMT != 5 && FMT != 58) return launch_tile_mode<FMT, W13, TE_BIG>(c, grid, bytes, A);
-    return fail(MOE_EINVAL, "no large tile kernel for groups of 32");
+    if constexpr (FMT == 2 || FMT == 28) return launch_tile_mode<FMT, W13, TE_BIG>(c, grid, bytes, A);
+    else if constexpr (FMT != 5 && FMT != 58) return launch_timed(c, W13 ? PROF_W13 : PROF_W2, bytes, k_big<FMT, W13>, dim3(grid), dim3(TbCfg::THREADS), 0, A);
+    else return fail(MOE_EINVAL, "no large tile kernel for groups of 32");
 }
 
 template <bool W13>
