@@ -96,30 +96,25 @@ __global__ __launch_bounds__(WAVES *WAVE, (WAVES == 8 && MT == 1 ? 4 : 2)) void 
         if (tid < 64) {
             FewPairs few;
             few.load(A.pair_expert, A.n_pairs);
-            const int count = few.counts(A.n_experts), first = prefix16(count) - count;      // lane e: expert e's pairs, its first place
+            const int count = few.counts(), first = prefix16(count) - count;                 // lane e: expert e's pairs, its first place
             const int tiles = lane < 16 ? (count + A.tile_tokens - 1) / A.tile_tokens : 0, end = prefix16(tiles);
             const uint8_t *const blob = A.table[lane & 15];
             for (int k = 0; k < tiles; ++k)
                 if (end - tiles + k < 32) l_e[end - tiles + k] = {blob, min(A.tile_tokens, count - k * A.tile_tokens), first + k * A.tile_tokens};
             const int n = __builtin_amdgcn_readlane(end, 15);
-            uint32_t before[FEW_PAIRS / 64] = {0};                       // pairs of the same expert before the lane's own
-            for (int x = 0; x < A.n_experts; ++x) {
-                int k = 0;
-#pragma unroll
-                for (int c = 0; c < FEW_PAIRS / 64; ++c) {
-                    const uint64_t m = few.mask(c, x);
-                    if (few.e[c] == (uint32_t)x) before[c] = k + __popcll(m & ((1ull << lane) - 1));
-                    k += __popcll(m);
-                }
-            }
+            int base = first;                                                // lane e: the place of its first pair of a chunk
+            const uint64_t below = (1ull << lane) - 1;
 #pragma unroll
             for (int c = 0; c < FEW_PAIRS / 64; ++c) {
-                const int p = c * 64 + lane, at = __shfl(first, (int)few.e[c] & 15) + (int)before[c];
+                if (c * 64 >= A.n_pairs) break;
+                const int p = c * 64 + lane, x = (int)few.e[c] & 15;
+                const int at = __shfl(base, x) + __popc((uint32_t)__shfl((int)few.own[c].x, x) & (uint32_t)below) + __popc((uint32_t)__shfl((int)few.own[c].y, x) & (uint32_t)(below >> 32));
                 if (p < A.n_pairs) {
                     l_pair[at] = (uint8_t)p;
                     l_tok[at] = (uint8_t)(p / A.top_k);
                     l_w[at] = A.pair_w[p];
                 }
+                base += __popc(few.own[c].x) + __popc(few.own[c].y);
             }
             if (lane == 0) *l_n = min(n, 32);
         }

@@ -544,7 +544,7 @@ __device__ __forceinline__ TeItem te_item(const TeArgs &A, FewPairs &few, BLOCKS
     int j = (int)blockIdx.x / TE_XCD, count, first;
     if (A.pair_expert) {
         few.load(A.pair_expert, A.n_pairs);
-        count = few.counts(A.n_experts);
+        count = few.counts();
         first = prefix16(count) - count;
     } else {
         first = A.first[lane & 15];

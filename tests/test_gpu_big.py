@@ -1,12 +1,15 @@
-"""The large tile kernel of 3- and 4-bit codes against the CPU oracle where its blocks, steps and sets end."""
+"""The large tile kernel of 3- and 4-bit codes against the CPU oracle where its blocks, steps and sets end, and the device's lookup of
+a step's pairs with as many experts as there can be."""
+import numpy as np
 import pytest
+import torch
 
 import workload as W
 from oracle import moe_oracle as O
 from paper_2312_17238_amd import binding as B
 
 from harness import Model, run_teacher_forced
-from test_gpu_tile import run
+from test_gpu_tile import one_step, run
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +31,19 @@ def test_ends_of_blocks_and_sets(fmt, sg, H, F, Bn):
 def test_rows_of_an_odd_number_of_units(fmt, sg, H, F, Bn):
     """The second unit of a row's last step does not exist; several experts, blocks of one to four tiles."""
     run(fmt, sg, H, F, 3, 2, 3, Bn, tile=192)
+
+
+@pytest.mark.parametrize("K,Bn", [(4, 16), (4, 17), (3, 64), (4, 64)])
+@pytest.mark.parametrize("form", [5, 6])
+def test_pairs_found_on_the_device_among_16_experts(K, Bn, form):
+    """64, 68, 192 and 256 pairs: a queued step, whose kernels look them up, gives the bits of one that waits (form 5: the host's tables)."""
+    model = Model(1, 128, 256, 16, K, [(4, 64)], 16, 0, 1e-5, max_batch=Bn, seed=82)
+    x = W.hidden_ar1(82, 1, Bn, 128)[0].to(model.stack.device)
+    bits = one_step(model, x, form)
+    for _ in range(2):                                   # the first step fills the slots and waits as well
+        out = torch.empty_like(x)
+        model.stack.step_layer(0, x, out)
+        model.stack.synchronize()
+    assert model.stack.total_stats()["steps_device_routed"] > 0
+    assert (model.stack.read_y(Bn, 128).view(np.uint32) == bits).all()
+    model.close()
