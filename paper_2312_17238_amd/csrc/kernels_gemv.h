@@ -594,33 +594,67 @@ __global__ __launch_bounds__(512) void k_w2(ARGS A)
 // pair's rows of ypart (parts of a split contraction in ascending order); x_out = fp16(x + y); y is kept (fp32) for
 // diagnostics.  One thread per four elements; the order of the additions is fixed, so the result is reproducible
 // bit for bit whatever order the w2 blocks finished in.
-// log (may be null): one bit per expert that has pairs, for the host's bookkeeping.
+// log (may be null): one bit per expert that has pairs, for the host's bookkeeping, from a row of blocks of its own behind the tokens'.
+// What bounds it: with few tokens a chain of loads, the table's entries and then the rows, so all entries are requested at once and
+// COMBINE_PARTS rows of each before any is added; with many the bytes.
+constexpr int COMBINE_PARTS = 4, LOG_LOADS = 8;
 __global__ __launch_bounds__(256) void k_combine(const uint16_t *x, const float *ypart, const uint32_t *ytab, float *y, uint16_t *x_out,
-                                                 int H, int K, uint32_t cap_rows, const uint8_t *pair_expert, int32_t *log)
+                                                 int H, int K, int B, uint32_t cap_rows, const uint8_t *pair_expert, int32_t *log)
 {
-    if (log && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64) {
+    if ((int)blockIdx.y == B) {
+        if (blockIdx.x || threadIdx.x >= 64) return;
         uint32_t used = 0;
-        for (int q = threadIdx.x; q < (int)gridDim.y * K; q += 64) used |= 1u << pair_expert[q];
+        const int n = B * K;
+        for (int q0 = threadIdx.x; q0 < n; q0 += 64 * LOG_LOADS) {
+            uint32_t e[LOG_LOADS];
+#pragma unroll
+            for (int k = 0; k < LOG_LOADS; ++k) e[k] = pair_expert[min(q0 + 64 * k, n - 1)];
+#pragma unroll
+            for (int k = 0; k < LOG_LOADS; ++k) used |= 1u << e[k];
+        }
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) used |= __shfl_xor(used, d);
         if (threadIdx.x == 0) *log = (int32_t)used;
+        return;
     }
     const int b = blockIdx.y, i = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= H) return;
+    const uint2 xv = *reinterpret_cast<const uint2 *>(x + (size_t)b * H + i);
+    uint32_t row[4], parts[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) row[j] = ytab[b * K + min(j, K - 1)];
+    float4 v[4][COMBINE_PARTS];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t t = uniform((int)row[j]);
+        row[j] = t & 0xffffffu;
+        parts[j] = j < K ? t >> 24 : 0;
+        if (row[j] + parts[j] > cap_rows) parts[j] = 0;          // an entry no kernel of this step wrote: never read outside the buffer
+#pragma unroll
+        for (uint32_t p = 0; p < COMBINE_PARTS; ++p)
+            if (p < parts[j]) v[j][p] = *reinterpret_cast<const float4 *>(ypart + (size_t)(row[j] + p) * H + i);
+    }
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j = 0; j < K; ++j) {
-        const uint32_t t = ytab[b * K + j];
-        const uint32_t row = t & 0xffffffu, parts = t >> 24;
-        if (parts == 0 || row + parts > cap_rows) continue;      // an entry no kernel of this step wrote: never read outside the buffer
-        float4 s = *reinterpret_cast<const float4 *>(ypart + (size_t)row * H + i);
-        for (uint32_t p = 1; p < parts; ++p) {
-            const float4 v = *reinterpret_cast<const float4 *>(ypart + (size_t)(row + p) * H + i);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (parts[j] == 0) continue;
+        float4 s = v[j][0];
+        auto add = [&](const float4 &w) { s.x += w.x; s.y += w.y; s.z += w.z; s.w += w.w; };
+#pragma unroll
+        for (uint32_t p = 1; p < COMBINE_PARTS; ++p)
+            if (p < parts[j]) add(v[j][p]);
+        for (uint32_t p0 = COMBINE_PARTS; p0 < parts[j]; p0 += COMBINE_PARTS) {
+            float4 w[COMBINE_PARTS];
+#pragma unroll
+            for (uint32_t p = 0; p < COMBINE_PARTS; ++p)
+                if (p0 + p < parts[j]) w[p] = *reinterpret_cast<const float4 *>(ypart + (size_t)(row[j] + p0 + p) * H + i);
+#pragma unroll
+            for (uint32_t p = 0; p < COMBINE_PARTS; ++p)
+                if (p0 + p < parts[j]) add(w[p]);
         }
         acc.x += s.x; acc.y += s.y; acc.z += s.z; acc.w += s.w;
     }
     *reinterpret_cast<float4 *>(y + (size_t)b * H + i) = acc;
-    const uint2 xv = *reinterpret_cast<const uint2 *>(x + (size_t)b * H + i);
     const _Float16 o0 = (_Float16)(lo_half(xv.x) + acc.x), o1 = (_Float16)(hi_half(xv.x) + acc.y);
     const _Float16 o2 = (_Float16)(lo_half(xv.y) + acc.z), o3 = (_Float16)(hi_half(xv.y) + acc.w);
     const uint2 ov = make_uint2((uint32_t)__builtin_bit_cast(uint16_t, o0) | (uint32_t)__builtin_bit_cast(uint16_t, o1) << 16,

@@ -2184,8 +2184,8 @@ static int32_t launch_combine(moe_layer *l, const uint16_t *x_in, uint16_t *x_ou
     moe_ctx *c = l->ctx;
     const moe_layer_config_t &cf = l->cfg;
     const uint64_t cap_rows = ((uint64_t)batch * cf.top_k * cf.hidden + c->ypart_extra_floats) / cf.hidden;
-    hipLaunchKernelGGL(k_combine, dim3((cf.hidden / 4 + 255) / 256, batch), dim3(256), 0, c->compute, x_in, c->ypart, c->ytab, c->yacc,
-                       x_out, cf.hidden, cf.top_k, (uint32_t)cap_rows, c->pair_expert, log);
+    hipLaunchKernelGGL(k_combine, dim3((cf.hidden / 4 + 255) / 256, batch + (log ? 1 : 0)), dim3(256), 0, c->compute, x_in, c->ypart, c->ytab, c->yacc,
+                       x_out, cf.hidden, cf.top_k, batch, (uint32_t)cap_rows, c->pair_expert, log);
     HIPCHK(hipGetLastError());
     return MOE_OK;
 }
