@@ -64,13 +64,18 @@ constexpr int GATE_DENSE_EXPERTS = 8;
 // the barriers' serial ends), so what counts is how many run at once: without slices requested up front and with 8
 // accumulators the kernel fits 64 registers, two blocks a compute unit.  The order of the sums is the same.
 // 1024 tokens x 4096 with the tile kernels' sums: 51 -> 40 us, 512 tokens 27 -> 18 us.
+// TURNS = 2: for more tokens than those blocks are at once.  Blocks of half as many threads, each of which takes two threads' slices one after
+// the other (the same sums in the same order), four blocks a compute unit.  At 4096 the
+// rows of W_g out of L2 bound both (22.7 / 22.5 us for 1024 tokens); narrower ones gain, whole steps of 1024 tokens 256 x 512 27.8 -> 25.1 us, 513 tokens
+// 1024 x 2048 39.3 -> 38.6, 1024 tokens 4096 x 2048 148.8 -> 147.9.  At 512 tokens and less every token's block has its own place anyway.
 // After the one barrier that collects the waves' partial logits, wave 0 finishes alone: lane e holds logit e (lane
 // 16 + e the next layer's), the selection runs on values read from those lanes, and the exponentials, divisions and
 // stores of the K chosen experts (and of the next layer's probabilities) are one per lane.
-template <bool SPEC, bool TILE = false, bool DENSE = false>
-__global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs a)
+template <bool SPEC, bool TILE = false, bool DENSE = false, int TURNS = 1>
+__global__ __launch_bounds__(GATE_THREADS / TURNS, (DENSE ? 8 : 4)) void k_gate(GateArgs a)
 {
-    static_assert(!(SPEC && DENSE), "one gate only");
+    static_assert(!(SPEC && DENSE) && (DENSE || TURNS == 1), "one gate only");
+    constexpr int THREADS = GATE_THREADS / TURNS, WAVES = GATE_WAVES / TURNS;
     constexpr int NE = DENSE ? GATE_DENSE_EXPERTS : 16;
     constexpr int NACC = SPEC ? 32 : NE;
     constexpr int NPRE = SPEC || DENSE ? 0 : 8;          // experts whose first slice is requested up front
@@ -81,10 +86,10 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
     const int n1 = a.wg ? a.E : 0, n2 = (SPEC && a.wg2) ? a.E2 : 0;
     const bool normed = a.eps > 0.0;
 
-    const int i0 = tid * 4;                              // the thread's first slice
+    int i0 = tid * 4;                                    // the thread's first slice
     const uint2 ones = make_uint2(0x3c003c00u, 0x3c003c00u);
-    const uint2 x0 = i0 < a.H ? *reinterpret_cast<const uint2 *>(x + i0) : make_uint2(0u, 0u);
-    const uint2 g0 = (normed && a.gamma && i0 < a.H) ? *reinterpret_cast<const uint2 *>(a.gamma + i0) : ones;
+    uint2 x0 = i0 < a.H ? *reinterpret_cast<const uint2 *>(x + i0) : make_uint2(0u, 0u);
+    uint2 g0 = (normed && a.gamma && i0 < a.H) ? *reinterpret_cast<const uint2 *>(a.gamma + i0) : ones;
     float4 wpre[NPRE > 0 ? NPRE : 1];
     if constexpr (NPRE > 0) {
 #pragma unroll
@@ -94,15 +99,18 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
 
     double scale = 1.0;
     if (normed) {
-        double ss = 0.0;
-        for (int i = i0; i < a.H; i += GATE_THREADS * 4) {
-            const uint2 p = i == i0 ? x0 : *reinterpret_cast<const uint2 *>(x + i);
-            const double v0 = half_bits_to_f64(p.x & 0xffff), v1 = half_bits_to_f64(p.x >> 16);
-            const double v2 = half_bits_to_f64(p.y & 0xffff), v3 = half_bits_to_f64(p.y >> 16);
-            ss += v0 * v0; ss += v1 * v1; ss += v2 * v2; ss += v3 * v3;
+#pragma unroll
+        for (int turn = 0; turn < TURNS; ++turn) {
+            double ss = 0.0;
+            for (int i = i0 + turn * THREADS * 4; i < a.H; i += GATE_THREADS * 4) {
+                const uint2 p = i == i0 ? x0 : *reinterpret_cast<const uint2 *>(x + i);
+                const double v0 = half_bits_to_f64(p.x & 0xffff), v1 = half_bits_to_f64(p.x >> 16);
+                const double v2 = half_bits_to_f64(p.y & 0xffff), v3 = half_bits_to_f64(p.y >> 16);
+                ss += v0 * v0; ss += v1 * v1; ss += v2 * v2; ss += v3 * v3;
+            }
+            ss = wave_sum_f64(ss);
+            if (lane == 0) red[wv + turn * WAVES][0] = ss;
         }
-        ss = wave_sum_f64(ss);
-        if (lane == 0) red[wv][0] = ss;
         __syncthreads();
         if (tid == 0) {
             double t = 0.0;
@@ -113,62 +121,70 @@ __global__ __launch_bounds__(GATE_THREADS, (DENSE ? 8 : 4)) void k_gate(GateArgs
         scale = inv_rms;
     }
 
-    double acc[NACC];
-#pragma unroll
-    for (int e = 0; e < NACC; ++e) acc[e] = 0.0;
-    for (int i = i0; i < a.H; i += GATE_THREADS * 4) {
-        const uint2 p = i == i0 ? x0 : *reinterpret_cast<const uint2 *>(x + i);
-        uint16_t hv[4] = {(uint16_t)(p.x & 0xffff), (uint16_t)(p.x >> 16), (uint16_t)(p.y & 0xffff), (uint16_t)(p.y >> 16)};
-        if (normed) {
-            uint2 g = ones;
-            if (a.gamma) g = i == i0 ? g0 : *reinterpret_cast<const uint2 *>(a.gamma + i);
-            const uint16_t gv[4] = {(uint16_t)(g.x & 0xffff), (uint16_t)(g.x >> 16), (uint16_t)(g.y & 0xffff), (uint16_t)(g.y >> 16)};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) hv[j] = f64_to_f16_rne(half_bits_to_f64(hv[j]) * scale * half_bits_to_f64(gv[j]));
+#pragma unroll 1
+    for (int turn = 0; turn < TURNS; ++turn) {
+        if (turn) {
+            i0 += THREADS * 4;
+            x0 = i0 < a.H ? *reinterpret_cast<const uint2 *>(x + i0) : make_uint2(0u, 0u);
+            g0 = (normed && a.gamma && i0 < a.H) ? *reinterpret_cast<const uint2 *>(a.gamma + i0) : ones;
         }
-        const uint2 ho = make_uint2((uint32_t)hv[0] | (uint32_t)hv[1] << 16, (uint32_t)hv[2] | (uint32_t)hv[3] << 16);
-        if (a.h_out) *reinterpret_cast<uint2 *>(a.h_out + (size_t)b * a.H + i) = ho;
-        if (a.h_out2) *reinterpret_cast<uint2 *>(a.h_out2 + (size_t)b * a.H + i) = ho;
-        if (a.yacc) *reinterpret_cast<float4 *>(a.yacc + (size_t)b * a.H + i) = make_float4(0.f, 0.f, 0.f, 0.f);
-        const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
-                     h3 = half_bits_to_f64(hv[3]);
-        if (TILE && a.xs) {       // 4, 8 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
-            float s = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
-            s += dpp_f<0xB1>(s);
-            s += dpp_f<0x4E>(s);
-            if (a.xs_group >= 32) s += dpp_f<0x141>(s);
-            if (a.xs_group == 64) s += dpp_f<0x140>(s);
-            if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = split3(s);
-        }
+        double acc[NACC];
 #pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (e < n1) {
-                float4 w;
-                if (e < NPRE && i == i0) w = wpre[e < NPRE ? e : 0];
-                else w = *reinterpret_cast<const float4 *>(a.wg + (size_t)e * a.H + i);
-                acc[e] += (double)w.x * h0; acc[e] += (double)w.y * h1; acc[e] += (double)w.z * h2; acc[e] += (double)w.w * h3;
+        for (int e = 0; e < NACC; ++e) acc[e] = 0.0;
+        for (int i = i0; i < a.H; i += GATE_THREADS * 4) {
+            const uint2 p = i == i0 ? x0 : *reinterpret_cast<const uint2 *>(x + i);
+            uint16_t hv[4] = {(uint16_t)(p.x & 0xffff), (uint16_t)(p.x >> 16), (uint16_t)(p.y & 0xffff), (uint16_t)(p.y >> 16)};
+            if (normed) {
+                uint2 g = ones;
+                if (a.gamma) g = i == i0 ? g0 : *reinterpret_cast<const uint2 *>(a.gamma + i);
+                const uint16_t gv[4] = {(uint16_t)(g.x & 0xffff), (uint16_t)(g.x >> 16), (uint16_t)(g.y & 0xffff), (uint16_t)(g.y >> 16)};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) hv[j] = f64_to_f16_rne(half_bits_to_f64(hv[j]) * scale * half_bits_to_f64(gv[j]));
             }
-        if constexpr (SPEC) {
+            const uint2 ho = make_uint2((uint32_t)hv[0] | (uint32_t)hv[1] << 16, (uint32_t)hv[2] | (uint32_t)hv[3] << 16);
+            if (a.h_out) *reinterpret_cast<uint2 *>(a.h_out + (size_t)b * a.H + i) = ho;
+            if (a.h_out2) *reinterpret_cast<uint2 *>(a.h_out2 + (size_t)b * a.H + i) = ho;
+            if (a.yacc) *reinterpret_cast<float4 *>(a.yacc + (size_t)b * a.H + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+            const double h0 = half_bits_to_f64(hv[0]), h1 = half_bits_to_f64(hv[1]), h2 = half_bits_to_f64(hv[2]),
+                         h3 = half_bits_to_f64(hv[3]);
+            if (TILE && a.xs) {       // 4, 8 or 16 lanes make a group (H is a multiple of 64: a row of 16 lanes is in or out as a whole)
+                float s = ((float)h0 + (float)h1) + ((float)h2 + (float)h3);
+                s += dpp_f<0xB1>(s);
+                s += dpp_f<0x4E>(s);
+                if (a.xs_group >= 32) s += dpp_f<0x141>(s);
+                if (a.xs_group == 64) s += dpp_f<0x140>(s);
+                if ((i & (a.xs_group - 1)) == 0) a.xs[(size_t)b * a.xs_stride + i / a.xs_group] = split3(s);
+            }
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (e < n2) {
-                    const float4 w = *reinterpret_cast<const float4 *>(a.wg2 + (size_t)e * a.H + i);
-                    acc[16 + e] += (double)w.x * h0; acc[16 + e] += (double)w.y * h1; acc[16 + e] += (double)w.z * h2; acc[16 + e] += (double)w.w * h3;
+            for (int e = 0; e < NE; ++e)
+                if (e < n1) {
+                    float4 w;
+                    if (e < NPRE && i == i0) w = wpre[e < NPRE ? e : 0];
+                    else w = *reinterpret_cast<const float4 *>(a.wg + (size_t)e * a.H + i);
+                    acc[e] += (double)w.x * h0; acc[e] += (double)w.y * h1; acc[e] += (double)w.z * h2; acc[e] += (double)w.w * h3;
                 }
+            if constexpr (SPEC) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (e < n2) {
+                        const float4 w = *reinterpret_cast<const float4 *>(a.wg2 + (size_t)e * a.H + i);
+                        acc[16 + e] += (double)w.x * h0; acc[16 + e] += (double)w.y * h1; acc[16 + e] += (double)w.z * h2; acc[16 + e] += (double)w.w * h3;
+                    }
+            }
+        }
+        // all logits' wave sums at once; accumulators of experts that do not exist hold zeros
+        if constexpr (SPEC) {
+            wave_sum_many_f64<32>(acc, lane);
+            if (lane < 32) red[wv + turn * WAVES][wave_sum_index<32>(lane)] = acc[0];
+        } else if (DENSE || n1 <= 8) {
+            wave_sum_many_f64<8>(acc, lane);
+            if (lane < 8) red[wv + turn * WAVES][wave_sum_index<8>(lane)] = acc[0];
+        } else if constexpr (!DENSE) {
+            wave_sum_many_f64<16>(acc, lane);
+            if (lane < 16) red[wv + turn * WAVES][wave_sum_index<16>(lane)] = acc[0];
         }
     }
     if (TILE && a.xs && a.H / a.xs_group + tid < a.xs_stride) a.xs[(size_t)b * a.xs_stride + a.H / a.xs_group + tid] = make_uint2(0u, 0u);
-    // all logits' wave sums at once; accumulators of experts that do not exist hold zeros
-    if constexpr (SPEC) {
-        wave_sum_many_f64<32>(acc, lane);
-        if (lane < 32) red[wv][wave_sum_index<32>(lane)] = acc[0];
-    } else if (DENSE || n1 <= 8) {
-        wave_sum_many_f64<8>(acc, lane);
-        if (lane < 8) red[wv][wave_sum_index<8>(lane)] = acc[0];
-    } else if constexpr (!DENSE) {
-        wave_sum_many_f64<16>(acc, lane);
-        if (lane < 16) red[wv][wave_sum_index<16>(lane)] = acc[0];
-    }
     __syncthreads();
     if (wv != 0) return;
 

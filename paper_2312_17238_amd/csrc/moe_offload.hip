@@ -1151,8 +1151,10 @@ static int32_t launch_gate(moe_ctx *c, GateArgs ga, int32_t batch)
     if (++c->gate_seq == 0) ++c->gate_seq;             // 0 is what a fresh context holds
     ga.seq = c->gate_seq;
     const dim3 grid(batch), block(GATE_THREADS);
-    const bool dense = ga.pair_expert && !ga.wg2 && ga.E <= GATE_DENSE_EXPERTS && batch > (c->n_cu > 0 ? c->n_cu : 256);
-    int32_t rc = dense ? launch_timed(c, PROF_GATE, 0, k_gate<false, true, true>, grid, block, 0, ga)
+    const int n_cu = c->n_cu > 0 ? c->n_cu : 256;
+    const bool dense = ga.pair_expert && !ga.wg2 && ga.E <= GATE_DENSE_EXPERTS && batch > n_cu;
+    int32_t rc = dense && batch > 2 * n_cu ? launch_timed(c, PROF_GATE, 0, k_gate<false, true, true, 2>, grid, dim3(GATE_THREADS / 2), 0, ga)
+               : dense ? launch_timed(c, PROF_GATE, 0, k_gate<false, true, true>, grid, block, 0, ga)
                : ga.pair_expert ? (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true, true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false, true>, grid, block, 0, ga))
                        : (ga.wg2 ? launch_timed(c, PROF_GATE, 0, k_gate<true>, grid, block, 0, ga) : launch_timed(c, PROF_GATE, 0, k_gate<false>, grid, block, 0, ga));
     if (rc || ga.quiet) return rc;
