@@ -346,7 +346,7 @@ __global__ __launch_bounds__(512, 2) void k_big(TeArgs A)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int tk = mt * 32 + 8 * (i / 4) + 4 * hh + i % 4;
-                    const int row = k_parts == 1 ? l_pair[tk] : A.part_base + (it.first + tok0 + tk) * k_parts + part;
+                    const int row = te_row(A, it, l_pair[tk], tok0 + tk, part);
                     if (tk < n_tok && mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = l_w[tk] * v[mt][i];
                 }
             te_rows_told(A, it, tok0, n_tok, rb, part, l_pair);

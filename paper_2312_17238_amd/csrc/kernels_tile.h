@@ -629,14 +629,20 @@ __device__ __forceinline__ void te_copy_out(const TeArgs &A, const u32x4_t &q, i
         for (int z = (rb + 1) * cols / XG; z < A.xs_out_stride; ++z) xo[z] = make_uint2(0u, 0u);
 }
 
+// w2: the row of ypart that a part's sums of the pair in place `at` of the block's expert go to: the pair's own, or behind the pairs' rows.  The one
+// answer for the kernels' stores and for the entry that k_combine finds them by: a step whose tokens crowd has other parts than its launch's arguments.
+__device__ __forceinline__ int te_row(const TeArgs &A, const TeItem &it, int pair, int at, int part)
+{
+    return it.k_parts == 1 ? pair : A.part_base + (it.first + at) * it.k_parts + part;
+}
+
 // w2: one block per token block tells k_combine where the rows are
 __device__ __forceinline__ void te_rows_told(const TeArgs &A, const TeItem &it, int tok0, int n_tok, int rb, int part, const int32_t *l_pair)
 {
     const int tid = threadIdx.x;
     if (rb != 0 || part != 0 || tid >= n_tok) return;
     const int pr = l_pair[tid];
-    const int row = it.k_parts == 1 ? pr : A.part_base + (it.first + tok0 + tid) * it.k_parts;
-    A.ytab[pr] = y_rows((uint32_t)row, (uint32_t)it.k_parts);
+    A.ytab[pr] = y_rows((uint32_t)te_row(A, it, pr, tok0 + tid, 0), (uint32_t)it.k_parts);
 }
 
 template <int FMT, bool W13, int MODE>
@@ -736,8 +742,7 @@ __global__ __launch_bounds__((TeCfg<FMT, MODE>::THREADS), (TeCfg<FMT, MODE>::WAV
                 *reinterpret_cast<uint16_t *>(lds + C::OFF_A + tk * C::APITCH + rg * C::RGR + wrow) = __builtin_bit_cast(uint16_t, (_Float16)silu_mul(v, other));
         } else {
             const int mrow = row0 + rg * C::RGR + wrow;
-            // (the argument asked as well: without it the large kernel's totals go through scratch here, 1024 tokens 1073 -> 1491 us)
-            const int row = A.k_parts == 1 && k_parts == 1 ? l_pair[tk] : A.part_base + (ex.first + tok0 + tk) * k_parts + part;
+            const int row = te_row(A, ex, l_pair[tk], tok0 + tk, part);     // outside the branch: inside it the 2-bit large kernel's totals go through scratch
             if (tk < n_tok && mrow < n_rows) A.ypart[(size_t)row * A.N + mrow] = l_w[tk] * v;
         }
     };

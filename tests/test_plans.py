@@ -1,0 +1,37 @@
+"""What the library plans for a batch, without a GPU: its source built for the host alone into tests/sanitize/plan_harness.cpp."""
+import os
+import subprocess
+
+import pytest
+
+from test_gpu_tile_crowded import ONE_PART
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def harness(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("plan")
+    exe = str(tmp / "plan_harness")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, "--offload-host-only", "-fuse-cuid=none", "-O1", "-std=c++17", "-pthread", "-o", exe, "-x", "hip",
+                    os.path.join(ROOT, "tests", "sanitize", "plan_harness.cpp")], check=True, cwd=tmp, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
+
+    def plan(fmt, *rest):
+        run = subprocess.run([exe, *map(str, (*fmt, *rest))], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=60)
+        assert run.returncode == 0, run.stderr
+        return tuple(map(int, run.stdout.split()))
+    return plan
+
+
+@pytest.mark.parametrize("case", ONE_PART, ids=str)
+def test_crowded_tokens_leave_one_part(harness, case):
+    """The cases of the test of that name on the GPU, on 256 compute units."""
+    even, crowded, _ = harness(*case)
+    assert even > 1 and crowded == 1
+
+
+def test_crowded_cases_run_every_kernel(harness):
+    kernels = {(harness(*case)[2], case[0][0], case[1] > 0 and case[0][0] == 2) for case in ONE_PART}
+    assert {k[0] for k in kernels} == {16, 32, 192}
+    assert {(192, 2, False), (192, 2, True), (192, 3, False), (192, 4, False)} <= kernels
