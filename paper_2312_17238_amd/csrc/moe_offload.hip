@@ -1513,6 +1513,9 @@ static double expected_blocks(double avg, double share, int size)
     for (int k = 1; k <= MOE_MAX_BATCH / size + 1; ++k) n += 0.5 * std::erfc((size * k + 0.5 - avg) / dev * M_SQRT1_2);
     return n;
 }
+// ... by the 32-token kernel and by k_big: of the plan alone, so worked out once for both halves and every number of parts (every queued step makes its
+// plan anew, and the 42 erfc of these, one after the other inside the loop over parts, were 800: 9 us of a step's host time).
+struct ExpectedBlocks { double tiles = 0.0, big = 0.0; };
 
 // One launch of a tile kernel of 3- or 4-bit codes in us, mode 32 or the large one (k_big): rounds of blocks, a block's start and end and its units of
 // 64 columns.  k_big has one block a compute unit, whose rounds are paid in whole where they are few; of the other's last round what is in it counts.
@@ -1520,13 +1523,13 @@ static double expected_blocks(double avg, double share, int size)
 // launch: 8 experts 4096x14336, 4-bit, top 2, 64 tokens 139 / 159 and 65 / 66, 96 tokens 163 / 164 and 84 / 83, 128 tokens 198 / 184 and 96 / 86, 192
 // tokens 295 / 220 and 119 / 89; 4096x2048 128 tokens 38 / 45 and 23 / 23; 1856x5056, 6 experts, top 3, 32 tokens 24 / 22 and 18 / 18, 64 tokens 37 / 28
 // and 26 / 24, two-level 48 tokens 26 / 23 and 24 / 23; 512x2048, 16 experts, 384 tokens 19 / 13 and 11 / 15.
-static double scaled_half_us(const moe_layer *l, int batch, int mode, int n_rows, int cols, int parts)
+static double scaled_half_us(const moe_layer *l, int batch, const ExpectedBlocks &need, int mode, int n_rows, int cols, int parts)
 {
     const BlobLayout &b = l->lay;
-    const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs), avg = pairs / n_exp, share = (double)l->cfg.top_k / l->cfg.n_experts;
+    const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs);
     const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
     const int row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
-    const double tiles = expected_blocks(avg, share, 32), blocks = mode == TE_BIG ? expected_blocks(avg, share, TbCfg::TOK) : tiles;
+    const double tiles = need.tiles, blocks = mode == TE_BIG ? need.big : tiles;
     const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
     const bool heavy = b.bits == 3 || b.scale_group;                                                   // more unpacking
     const double fill = tiles / blocks;                                                                // tiles of a k_big block
@@ -1541,10 +1544,10 @@ static double scaled_half_us(const moe_layer *l, int batch, int mode, int n_rows
 // large kernel, us a step: 8 experts 4096x14336, top 2, 160 tokens 359 / 507, 300 527 / 561, 512 816 / 645.  Two-level 2-bit scales go in as two numbers,
 // which costs the large kernel's units 1.3 times the matrix work, and the 32-token one has a compute unit to itself: one launch
 // each, 32 tokens / large kernel, w1/w3 of 4096x14336, 160 tokens 513 / 397, 384 tokens 862 / 489; w2 of 256x12288, 6 experts, 306 tokens 28 / 91.
-static double tile_half_us(const moe_layer *l, int batch, int mode, int n_rows, int cols, int parts)
+static double tile_half_us(const moe_layer *l, int batch, const ExpectedBlocks &need, int mode, int n_rows, int cols, int parts)
 {
     const BlobLayout &b = l->lay;
-    if (b.bits != 2) return scaled_half_us(l, batch, mode, n_rows, cols, parts);
+    if (b.bits != 2) return scaled_half_us(l, batch, need, mode, n_rows, cols, parts);
     const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs), avg = pairs / n_exp;
     const double spread = l->cfg.top_k == l->cfg.n_experts ? 0.0 : 0.45;
     const double tiles = spread > 0.0 ? std::max(1.0, avg / 32 + spread) : std::ceil(avg / 32);        // of 32 tokens, an expert's
@@ -1597,15 +1600,20 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     if (many && !c->tile_tokens) {
         // (2 bits: the 32-token kernel where it is faster by more than the fit's error, else the large one.  A part's rows are written and read again.)
         const double margin = b.bits == 2 ? 1.05 : 0.95, part_us = b.bits == 2 ? 0.0 : 2e-6 * pairs * b.hidden;
+        ExpectedBlocks need;
+        if (b.bits != 2) {
+            const double of_one = pairs / std::min<double>(E, pairs), share = (double)l->cfg.top_k / E;
+            need = {expected_blocks(of_one, share, 32), expected_blocks(of_one, share, TbCfg::TOK)};
+        }
         auto w2_us = [&](int mode, int parts) {
             int32_t k_parts, units;
             te_split(sets, parts, k_parts, units);
-            return tile_half_us(l, batch, mode, b.hidden, b.ffn, parts) + (k_parts - 1) * part_us;
+            return tile_half_us(l, batch, need, mode, b.hidden, b.ffn, parts) + (k_parts - 1) * part_us;
         };
         int big_parts = best_parts(TE_BIG, nominal_blocks(TE_BIG));
         for (int n = 1; n <= std::min(std::min(8, sets), cap) && b.bits != 2; ++n)           // by the estimate, which counts experts with more than their share as well
             if (w2_us(TE_BIG, n) < w2_us(TE_BIG, big_parts)) big_parts = n;
-        if (tile_half_us(l, batch, TE_BIG, 2 * b.ffn, b.hidden, 1) < margin * tile_half_us(l, batch, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
+        if (tile_half_us(l, batch, need, TE_BIG, 2 * b.ffn, b.hidden, 1) < margin * tile_half_us(l, batch, need, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
         if (w2_us(TE_BIG, big_parts) < margin * w2_us(32, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
     }
     // Tokens that crowd to few experts leave fewer token blocks than the nominal routing's, and its parts would leave part of the
@@ -2282,10 +2290,9 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     l->stepped = true;
     if (spec) next->stepped = true;
     if (!plain && device_routed_step_fits(l, next, batch, trace, spec)) return device_routed_step(l, x_in, x_out, h_out);
-    if (!plain && device_routed_batch_fits(l, next, batch, trace, spec)) {
-        const BatchPlan p = plan_batch(l, batch);
-        if (device_routed_plan_fits(l, batch, p)) return device_routed_batch(l, x_in, batch, x_out, h_out, p);
-    }
+    const BatchPlan bp = plan_batch(l, batch);
+    if (!plain && device_routed_batch_fits(l, next, batch, trace, spec) && device_routed_plan_fits(l, batch, bp))
+        return device_routed_batch(l, x_in, batch, x_out, h_out, bp);
     rc = fold_pending(c);
     if (rc) return rc;
 
@@ -2293,7 +2300,6 @@ static int32_t step_impl(moe_layer *l, moe_layer *next, const uint16_t *x_in, in
     ga.x = x_in; ga.wg = l->gate_w_dev; ga.wg2 = spec ? next->gate_w_dev : nullptr;
     ga.gamma = l->gamma_dev; ga.h_out = c->h_buf; ga.h_out2 = h_out; ga.out = c->gate_out_dev;
     ga.eps = (double)cf.rms_eps; ga.H = cf.hidden; ga.E = cf.n_experts; ga.E2 = spec ? next->cfg.n_experts : 0; ga.K = cf.top_k;
-    const BatchPlan bp = plan_batch(l, batch);
     const bool use_tile = bp.kind == BatchPlan::TILE;
     if (use_tile) tile_gate_args(l, ga);
     rc = launch_gate(c, ga, batch);

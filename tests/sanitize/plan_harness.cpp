@@ -1,5 +1,11 @@
 // What the library plans for a batch, on a machine without a GPU: built and run by tests/test_plans.py with the layer, the batch and the tokens of a
-// block as arguments.  Prints how many parts w2 has with an even routing and with every token at the same experts, and the tokens of a block of it.
+// block as arguments.  Prints how many parts w2 has with an even routing and with every token at the same experts, the calls of erfc that the plan
+// took and the tokens of a block of w2.
+#include <hip/hip_runtime.h>
+#include <cmath>
+static int g_erfc = 0;
+namespace std { static double counted_erfc(double x) { ++g_erfc; return (erfc)(x); } }
+#define erfc counted_erfc
 #define main queued_steps_main
 #include "queued_steps_harness.cpp"
 #undef main
@@ -26,13 +32,14 @@ int main(int argc, char **argv)
     ctx->ypart_extra_floats = plan_scratch(&cc).ypart_extra_floats;
     ctx->mfma_form = 6;
     ctx->tile_tokens = v[8];
+    g_erfc = 0;
     const BatchPlan p = plan_batch(layer, batch);
     CHECK(p.kind == BatchPlan::TILE);
     const int sets = (F / 64 + 3) / 4, blocks = K * tile_blocks(b, batch, p.mode2);
     int32_t even, crowded, units;
     te_split(sets, p.parts, even, units);
     te_split(sets, blocks < p.few_below ? p.few[blocks - 1] : p.parts, crowded, units);
-    std::printf("%d %d %d\n", even, crowded, p.mode2 == TE_BIG ? 192 : p.mode2);
+    std::printf("%d %d %d %d\n", even, crowded, g_erfc, p.mode2 == TE_BIG ? 192 : p.mode2);
     CHECK(moe_layer_destroy(layer) == MOE_OK && moe_ctx_destroy(ctx) == MOE_OK);
     return 0;
 }

@@ -27,11 +27,18 @@ def harness(tmp_path_factory):
 @pytest.mark.parametrize("case", ONE_PART, ids=str)
 def test_crowded_tokens_leave_one_part(harness, case):
     """The cases of the test of that name on the GPU, on 256 compute units."""
-    even, crowded, _ = harness(*case)
+    even, crowded, _, _ = harness(*case)
     assert even > 1 and crowded == 1
 
 
 def test_crowded_cases_run_every_kernel(harness):
-    kernels = {(harness(*case)[2], case[0][0], case[1] > 0 and case[0][0] == 2) for case in ONE_PART}
+    kernels = {(harness(*case)[3], case[0][0], case[1] > 0 and case[0][0] == 2) for case in ONE_PART}
     assert {k[0] for k in kernels} == {16, 32, 192}
     assert {(192, 2, False), (192, 2, True), (192, 3, False), (192, 4, False)} <= kernels
+
+
+@pytest.mark.parametrize("case", [((4, 64), 0, 4096, 14336, 8, 2, 512, 0), ((3, 64), 0, 256, 2048, 8, 2, 512, 0), ((4, 64), 0, 256, 512, 16, 4, 1024, 0), ((4, 128), 0, 512, 1024, 4, 1, 60, 0)], ids=str)
+def test_host_time_of_a_plan(harness, case):
+    """Every queued step makes its plan anew.  The expected blocks of an expert, of 32 and of 128 tokens and at most 1024 in all, take a call each and
+    one more: 33 and 9, however many parts are compared."""
+    assert 0 < harness(*case)[2] <= 33 + 9
