@@ -104,10 +104,10 @@ template <bool META8> struct Tb3 : TeScaled<META8, 256, 512, 3> {
     }
     static __device__ __forceinline__ void words(const uint8_t *b, const At &a, int rt, int s, uint32_t (&t)[4])
     {
-        typename Te3<META8, 256, 512>::Raw r;
+        Codes3::Raw r;
         r.a = *reinterpret_cast<const uint2 *>(b + (a.a ^ s * 32) + rt * 32 * 64);
         r.b = *reinterpret_cast<const uint32_t *>(b + (a.b ^ s * 16) + rt * 32 * 32);
-        Te3<META8, 256, 512>::words(r, t);
+        Codes3::words(r, t);
     }
 };
 template <> struct Tb<3> : Tb3<false> {};

@@ -93,7 +93,7 @@ struct TileRouted : TileCommon {
     const uint8_t *pair_expert;
     const float *pair_w;
     const uint8_t *table[16];
-    int32_t n_pairs, n_experts, top_k, tile_tokens;
+    int32_t n_pairs, top_k, tile_tokens;
 };
 
 struct TileStep { int it, seg, seg_hi, rb, e; bool valid; };

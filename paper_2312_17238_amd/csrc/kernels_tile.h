@@ -75,7 +75,7 @@ struct TeArgs {
     uint2 *xs_out;                       // ... and their sums
     float *ypart;                        // w2: rows of N, one per pair (k_parts == 1) or per (position, part)
     uint32_t *ytab;
-    int32_t K, N, top_k, n_pairs, n_experts;
+    int32_t K, N, top_k, n_pairs;
     int32_t xs_stride, xs_out_stride;
     uint32_t stride, meta_off, meta2_off, b_off;
     int32_t unit_shift, run_shift;       // group of unit u: u >> unit_shift; run of group g: g >> run_shift
@@ -289,39 +289,44 @@ template <int R, int T> struct Te<48, R, T> : Te4<true, R, T> {};
 template <int R, int T> struct Te<5, R, T> : Te4<false, R, T, 2> {};      // 4-bit codes in groups of 32, and with two-level metadata
 template <int R, int T> struct Te<58, R, T> : Te4<true, R, T, 2> {};
 
+// 32 codes of a 3-bit row, from its two regions, as words of the 4-bit layout: one v_bfi each; bit 3 of a field is another word's
+struct Codes3 {
+    struct Raw { uint2 a; uint32_t b; };
+    static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4])
+    {
+        t[0] = (r.a.x & 0x33333333u) | ((r.b << 2) & ~0x33333333u);
+        t[1] = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & ~0x33333333u);
+        t[2] = (r.a.y & 0x33333333u) | (r.b & ~0x33333333u);
+        t[3] = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & ~0x33333333u);
+    }
+};
+
 template <bool META8, int ROWS, int THREADS>
 struct Te3 : TeScaled<META8, ROWS, THREADS, 3> {
     static constexpr uint32_t BITS = 3;
-    static constexpr int SOFF = 96, REC = 112, NA = ROWS * 4 / THREADS;
-    static constexpr bool HALF = ROWS * 4 == THREADS;                    // region B: 8 or 16 bytes per thread
-    static_assert(NA >= 1 && (HALF || ROWS * 2 == THREADS), "region B is one piece per thread");
-    uint4 a[NA];
-    std::conditional_t<HALF, uint2, uint4> b;
-    struct Raw { uint2 a; uint32_t b; };
+    static constexpr int SOFF = 96, REC = 112;
+    static_assert(ROWS * 4 == THREADS, "a thread has 16 bytes of region A and 8 of region B");
+    uint4 a;
+    uint2 b;
+    using Raw = Codes3::Raw;
     __device__ __forceinline__ void fetch(int h, __amdgpu_buffer_rsrc_t rs, const TeGeom &g, int row0, int n_rows, int u, bool live, int tid)
     {
+        // 64 rows per half block of threads: a load covers two slabs of 64
+        const uint32_t row = (uint32_t)(tid / 4 % 64) * g.stride;
+        const int at = min(row0 + uniform(tid / 256) * 64, n_rows - 64) * (int)g.stride;
         if (h == 0) {
-            // 64 rows per half block of threads: with 8 waves a load covers two slabs of 64
-            const uint32_t v = live ? (uint32_t)(tid / 4 % 64) * g.stride + (uint32_t)(tid % 4) * 16u : TE_NONE;
-#pragma unroll
-            for (int i = 0; i < NA; ++i) a[i] = bl128(rs, v, min(row0 + (i * THREADS / 4) + uniform(tid / 256) * 64, n_rows - 64) * (int)g.stride + u * 16);
+            a = bl128(rs, live ? row + (uint32_t)(tid % 4) * 16u : TE_NONE, at + u * 16);
         } else {
-            constexpr int PR = HALF ? 4 : 2;                             // pieces per row
-            const uint32_t v = live ? (uint32_t)(tid / PR % 64) * g.stride + (uint32_t)(tid % PR) * (32u / PR) : TE_NONE;
-            const int at = min(row0 + uniform(tid / (PR * 64)) * 64, n_rows - 64) * (int)g.stride + (int)g.b_off + u * 8;
-            if constexpr (HALF) b = bl64(rs, v, at);
-            else b = bl128(rs, v, at);
+            b = bl64(rs, live ? row + (uint32_t)(tid % 4) * 8u : TE_NONE, at + (int)g.b_off + u * 8);
             this->fetch_meta(rs, g, row0, n_rows, u, live, tid);
         }
     }
     __device__ __forceinline__ void commit(int h, uint8_t *rec, uint8_t *d, int, float, int tid) const
     {
         if (h == 0) {
-#pragma unroll
-            for (int i = 0; i < NA; ++i) *reinterpret_cast<uint4 *>(rec + (tid / 4) * REC + (tid % 4) * 16 + i * (THREADS / 4) * REC) = a[i];
+            *reinterpret_cast<uint4 *>(rec + (tid / 4) * REC + (tid % 4) * 16) = a;
         } else {
-            constexpr int PR = HALF ? 4 : 2;
-            *reinterpret_cast<decltype(b) *>(rec + (tid / PR) * REC + (tid % PR) * (32 / PR) + 64) = b;
+            *reinterpret_cast<uint2 *>(rec + (tid / 4) * REC + (tid % 4) * 8 + 64) = b;
             this->template commit_meta<REC, SOFF>(rec, d, tid);
         }
     }
@@ -330,14 +335,7 @@ struct Te3 : TeScaled<META8, ROWS, THREADS, 3> {
         r.a = *reinterpret_cast<const uint2 *>(row + u * 16 + hh * 8);
         r.b = *reinterpret_cast<const uint32_t *>(row + 64 + u * 8 + hh * 4);
     }
-    static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4])
-    {
-        // one v_bfi each; bit 3 of a field is another word's
-        t[0] = (r.a.x & 0x33333333u) | ((r.b << 2) & ~0x33333333u);
-        t[1] = ((r.a.x >> 2) & 0x33333333u) | ((r.b << 1) & ~0x33333333u);
-        t[2] = (r.a.y & 0x33333333u) | (r.b & ~0x33333333u);
-        t[3] = ((r.a.y >> 2) & 0x33333333u) | ((r.b >> 1) & ~0x33333333u);
-    }
+    static __device__ __forceinline__ void words(const Raw &r, uint32_t (&t)[4]) { Codes3::words(r, t); }
     static __device__ __forceinline__ void quarter(const uint8_t *row, int kb, int u, uint32_t (&t)[2])
     {
         const uint32_t a = *reinterpret_cast<const uint32_t *>(row + u * 16 + kb * 4);

@@ -1766,7 +1766,7 @@ static int32_t launch_mfma_stream(moe_layer *l, const std::vector<PassExpert> &e
         const size_t tile_tokens = small && (c->mfma_form == 4 || c->mfma_form == 5 || c->mfma_form == 0) ? 16 : 32;
         if (!w) {
             routed.pair_expert = c->pair_expert; routed.pair_w = c->pair_w;
-            routed.n_pairs = batch * K; routed.n_experts = l->cfg.n_experts; routed.top_k = K; routed.tile_tokens = (int32_t)tile_tokens;
+            routed.n_pairs = batch * K; routed.top_k = K; routed.tile_tokens = (int32_t)tile_tokens;
             for (const PassExpert &pe : experts) routed.table[pe.expert] = pe.blob;
             const int own = std::min(l->cfg.n_experts, batch * K);
             n = own + (batch * K - own) / (int)tile_tokens;          // the most entries there can be
@@ -1934,7 +1934,7 @@ static int32_t launch_tile(moe_layer *l, const std::vector<PassExpert> &experts,
         const int own = std::min(E, pairs), per = mode == TE_BIG ? (tile_blocks(b, 192, mode) == 1 ? 192 : 128) : mode;
         return K == E ? E * tile_blocks(b, batch, mode) : own + (pairs - own) / per;
     };
-    A.n_pairs = pairs; A.n_experts = E;
+    A.n_pairs = pairs;
     if (pairs <= FEW_PAIRS) A.pair_expert = c->pair_expert;          // else k_sort_pairs' list (launch_sort)
     A.first = c->pair_first;
     A.plist = c->plist; A.pair_w = c->pair_w; A.ypart = c->ypart; A.ytab = c->ytab; A.a = c->a_buf;
