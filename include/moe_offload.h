@@ -313,13 +313,14 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                scale above 500 or a row 2^16 times below the largest; group-32 layers excepted less than 128 wide or
  *                with metadata runs of one group); smaller batches and these formats in forms 1 to 5 use the GEMV kernels;
  *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 where it is the faster one for the layer's size and the tokens an
- *                expert has on average (4-bit group-64 layers of middle size, larger ones above 26, small ones above 32, two-level 16;
- *                other formats: more than three, or more than one in all but the smallest layers), else form 5 (4-bit
- *                group-64) or the GEMV kernels.  The choice, like all that decides the order of a result's sums, follows
- *                from the layer, the batch and the options, never from the routing or the cache.  6: tile kernels,
- *                every format, up to 192 tokens of one expert multiplied per pass over its weights, codes
- *                exact and groups scaled in fp32 (2-bit: exact fp16 products of code and scale).  4: persistent streaming kernels with
- *                tiles of 16 tokens -- one, or two where an expert has more than 14 tokens of a window of up to 256 / top_k
+ *                expert has on average (4-bit group-64: up to 14, layers of middle size; above, all but the largest layers, those from 26
+ *                on, and the smallest where the step has more than 256 / top_k tokens; other formats: more than three, or more than one in
+ *                all but the smallest layers), else form 5 (4-bit group-64) or the GEMV kernels.  The choice, like all that
+ *                decides the order of a result's sums, follows from the layer, the batch and the options, never from the
+ *                routing or the cache.  6: tile kernels,
+ *                every format, up to 128 tokens of one expert multiplied per pass over its weights (2-bit codes with fp16
+ *                metadata 192, 4-bit groups of 32 32), codes exact and groups scaled in fp32 (2-bit: exact fp16 products of code
+ *                and scale).  4: persistent streaming kernels with tiles of 16 tokens -- one, or two where an expert has more than 14 tokens of a window of up to 256 / top_k
  *                tokens of the step on average, and as many entries of those as an expert needs -- each dequantised weight rounded once to fp16
  *                before the multiply, as Sec. 4.2's fp16 experts do; fp16 metadata only (form 2 runs otherwise).  5: the
  *                kernels of form 4 with the weights not dequantised at all: the codes enter the matrix cores as they are
@@ -331,8 +332,9 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                the form computes that product in fp16 -- form 2 runs).  1: row-staging kernels that keep the codes
  *                exact and scale every group's product in fp32 (batches of at most 64 tokens, fp16 metadata; otherwise
  *                form 2 runs).  All meet the output tolerance;
- *   "tile_tokens" tokens of an expert per block of form 6's kernels in both halves of a layer: 16, 32, or 192 for the large kernel
- *                (128 with two-level 2-bit codes; group-32 layers, which have none, take 32); 0 (default): from layer and batch;
+ *   "tile_tokens" tokens of an expert per block of form 6's kernels in both halves of a layer: 16, 32, or 192, which names the
+ *                large kernel whatever its blocks hold (192 with 2-bit codes and fp16 metadata, else 128; group-32 layers have none and
+ *                take 32); 0 (default): from layer and batch;
  *   "mfma16_waves" waves per block of the kernels of forms 4 and 5 for up to 16 tokens per expert: 8 (default; 128
  *                registers, four waves per SIMD) or 4 (two groups of a step per wave; form 4 only); with two token tiles
  *                they always run 4;

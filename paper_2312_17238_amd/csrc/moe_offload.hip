@@ -175,7 +175,7 @@ struct moe_ctx {
                                         // way; with two token tiles 8 waves need 194 registers, one block per unit, and measured 12 % slower)
     int32_t mfma_min_batch = 3;         // batches at least this large may use the matrix-core kernels (4-bit g64: do): measured, all experts of a
                                         // Mixtral-shaped layer resident, they are 9 % faster than the GEMV kernels at 3 tokens and 82 % at 12
-    int32_t tile_tokens = 0;            // tokens per block of the tile kernels: 16, 32, 192 (the large kernel), or 0: by layer and batch
+    int32_t tile_tokens = 0;            // tokens per block of the tile kernels: 16, 32, 192 (the large kernel, whatever its blocks hold), or 0: by layer and batch
     int32_t staged_min_batch = 0;       // matrix-core batches larger than this: resident experts first, arriving ones one by one
     uint64_t spec_head_bytes = 0;       // 0: a speculative load moves the whole expert at once (as the paper describes);
                                         // > 0: only this many leading bytes, the rest when the guess is confirmed
