@@ -1533,7 +1533,7 @@ static double scaled_half_us(const moe_layer *l, int batch, const ExpectedBlocks
     const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
     const bool heavy = b.bits == 3 || b.scale_group;                                                   // more unpacking
     const double fill = tiles / blocks;                                                                // tiles of a k_big block
-    if (mode == TE_BIG) return (rounds <= 4.0 ? std::ceil(rounds - 0.02) : rounds + 0.5) * (6.9 + 2.0 * fill + units * (0.30 + (heavy ? 0.064 : 0.0) + 0.15 * fill));
+    if (mode == TE_BIG) return (rounds <= 4.0 ? std::max(1.0, std::ceil(rounds - 0.02)) : rounds + 0.5) * (6.9 + 2.0 * fill + units * (0.30 + (heavy ? 0.064 : 0.0) + 0.15 * fill));
     return 3.2 + std::max(rounds, 0.42) * units * (0.58 + (heavy ? 0.126 : 0.0)) + 4.8 * std::max(rounds, 1.0);
 }
 

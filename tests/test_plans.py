@@ -42,3 +42,13 @@ def test_host_time_of_a_plan(harness, case):
     """Every queued step makes its plan anew.  The expected blocks of an expert, of 32 and of 128 tokens and at most 1024 in all, take a call each and
     one more: 33 and 9, however many parts are compared."""
     assert 0 < harness(*case)[2] <= 33 + 9
+
+
+@pytest.mark.parametrize("case", [((4, 64), 0, 512, 11520, 1, 1, 60, 0), ((4, 128), 128, 256, 11648, 4, 3, 17, 0), ((4, 128), 128, 512, 7296, 2, 2, 48, 0),
+                                  ((4, 64), 256, 704, 6336, 1, 1, 27, 0), ((3, 64), 0, 256, 2688, 2, 1, 49, 0), ((3, 64), 256, 384, 640, 1, 1, 107, 0)], ids=str)
+def test_parts_of_narrow_layers(harness, case):
+    """w2 of a few row blocks of a few experts leaves most compute units idle even in as many parts as there can be: it takes those, whichever kernel
+    runs it.  (A launch of fewer blocks than compute units takes a round's time, not none.)"""
+    sets = (case[3] // 64 + 3) // 4
+    per = -(-sets // min(8, sets))
+    assert harness(*case)[0] == -(-sets // per)
