@@ -313,10 +313,11 @@ int32_t moe_ctx_profile_timeline(moe_ctx_t *ctx, int32_t kind, double *start_ms,
  *                scale above 500 or a row 2^16 times below the largest; group-32 layers excepted less than 128 wide or
  *                with metadata runs of one group); smaller batches and these formats in forms 1 to 5 use the GEMV kernels;
  *   "mfma_form"  which matrix-core kernels.  0 (default): form 6 where it is the faster one for the layer's size and the tokens an
- *                expert has on average (4-bit group-64: up to 14, layers of middle size; above, all but the largest layers, those from 26
- *                on, and the smallest where the step has more than 256 / top_k tokens; other formats: more than three, or more than one in
- *                all but the smallest layers), else form 5 (4-bit group-64) or the GEMV kernels.  The choice, like all that
- *                decides the order of a result's sums, follows from the layer, the batch and the options, never from the
+ *                expert has on average (4-bit group-64: up to 14, layers of middle size; above, all but the largest layers, those
+ *                from 26 on, and the smallest where the step has more than 256 / top_k tokens or, with rows of more than 1024,
+ *                an expert more than 32, two-level 16; other formats: more than three, or more than one in all but the smallest
+ *                layers), else form 5 (4-bit group-64) or the GEMV kernels.  The choice, like all that decides the order of a
+ *                result's sums, follows from the layer, the batch and the options, never from the
  *                routing or the cache.  6: tile kernels,
  *                every format, up to 128 tokens of one expert multiplied per pass over its weights (2-bit codes with fp16
  *                metadata 192, 4-bit groups of 32 32), codes exact and groups scaled in fp32 (2-bit: exact fp16 products of code

@@ -1670,8 +1670,12 @@ static void plan_windows(const moe_layer *l, int batch, BatchPlan &p)
 // Where they need tiles of 32 the tile kernels take all but the largest layers (18 to 24 tokens of an expert: 4096 x 512 57 / 50, 2048 x 5056
 // 81 / 66, 4096 x 8192 147 / 139, 2048 x 14336 132 / 131; 4096 x 14336 220 / 224, two-level 262 / 265), and those too from the average at which
 // many experts need a second tile of 32 (30 tokens of an expert: 4096 x 14336 303 / 260, 2048 x 14336 166 / 154; two-level 355 / 317; 4096 x 8192
-// 201 / 156); layers up to 1024 x 2048 where the 16-token kernels start again for a second window of tokens (1024 x 2048, 136 tokens 78 / 44, 480
-// tokens 176 / 68; 144 tokens, 16 experts 92 / 49; one window, 96 tokens 44.4 / 46.3).
+// 201 / 156).  Layers up to 1024 x 2048 take them where the 16-token kernels start again for a second window of tokens (1024 x 2048, 136 tokens 78 / 44, 480
+// tokens 176 / 68; 144 tokens, 16 experts 92 / 49) and, above 32 tokens of an expert, two-level 16, where their rows are long and few: the 16-token
+// kernels' w1/w3 has then few blocks with a long contraction each (3136 x 640, 1 expert, 252 tokens 58 / 45; 1920 x 704, 6 experts, 116 tokens 47 / 37; 1152 x 1792, 2 experts,
+// 116 tokens 42 / 37; two-level 4032 x 512, 4 experts, 57 tokens 55 / 45; 2944 x 576, 2 experts, 17 tokens 43 / 36).  Of 98 such layers the tile kernels were the slower ones
+// in none.  Fewer tokens or shorter rows: mostly a little faster as well, not always (768 x 1152, 13 experts, 101 tokens 35 / 38; 832 x 2496, 120 tokens 50 / 55; 1152 x 1792, 96
+// tokens 45 / 48).
 static bool tile_may(const moe_layer *l, int batch, bool stream)
 {
     const moe_layer_config_t &cf = l->cfg;
@@ -1679,7 +1683,7 @@ static bool tile_may(const moe_layer *l, int batch, bool stream)
     const int64_t size = (int64_t)cf.hidden * cf.ffn;
     if (stream) {
         if (pairs <= STREAM_SMALL_AVERAGE * cf.n_experts) return size > TILE_MIDDLE_LOW && size <= TILE_MIDDLE_HIGH;
-        if (size <= TILE_MIDDLE_LOW) return pairs > MF_MAX_PAIRS;
+        if (size <= TILE_MIDDLE_LOW) return pairs > MF_MAX_PAIRS || (cf.hidden > 1024 && pairs > (cf.scale_group ? 16 : 32) * cf.n_experts);
         return size <= TILE_TWO_TILES_HIGH || pairs > TILE_MODE32_AVERAGE * cf.n_experts;
     }
     const bool g64 = cf.bits == 4 && cf.group == 64;         // with runs of metadata that the 16-token kernels do not take

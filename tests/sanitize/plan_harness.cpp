@@ -1,6 +1,6 @@
 // What the library plans for a batch, on a machine without a GPU: built and run by tests/test_plans.py with the layer, the batch and the tokens of a
-// block as arguments.  Prints how many parts w2 has with an even routing and with every token at the same experts, the calls of erfc that the plan
-// took and the tokens of a block of w2.
+// block as arguments, and the form if not the tile kernels'.  Prints how many parts w2 has with an even routing and with every token at the same experts, the calls of erfc that the plan
+// took and the tokens of a block of w2; four zeros where other kernels run the step.
 #include <hip/hip_runtime.h>
 #include <cmath>
 static int g_erfc = 0;
@@ -12,9 +12,9 @@ namespace std { static double counted_erfc(double x) { ++g_erfc; return (erfc)(x
 
 int main(int argc, char **argv)
 {
-    CHECK(argc == 10);
-    int v[9];
-    for (int i = 0; i < 9; ++i) v[i] = atoi(argv[1 + i]);
+    CHECK(argc == 10 || argc == 11);
+    int v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 6};
+    for (int i = 1; i < argc; ++i) v[i - 1] = atoi(argv[i]);
     const int bits = v[0], group = v[1], scale_group = v[2], H = v[3], F = v[4], E = v[5], K = v[6], batch = v[7];
     const BlobLayout b = blob_layout(H, F, bits, group, scale_group);
     CHECK(b.ok);
@@ -30,11 +30,11 @@ int main(int argc, char **argv)
     layer->scale_row_low.store(0x3c000000);
     ctx->n_cu = 256;
     ctx->ypart_extra_floats = plan_scratch(&cc).ypart_extra_floats;
-    ctx->mfma_form = 6;
+    ctx->mfma_form = v[9];
     ctx->tile_tokens = v[8];
     g_erfc = 0;
     const BatchPlan p = plan_batch(layer, batch);
-    CHECK(p.kind == BatchPlan::TILE);
+    if (p.kind != BatchPlan::TILE) { CHECK(v[9] != 6); std::puts("0 0 0 0"); return 0; }
     const int sets = (F / 64 + 3) / 4, blocks = K * tile_blocks(b, batch, p.mode2);
     int32_t even, crowded, units;
     te_split(sets, p.parts, even, units);

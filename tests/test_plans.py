@@ -52,3 +52,13 @@ def test_parts_of_narrow_layers(harness, case):
     sets = (case[3] // 64 + 3) // 4
     per = -(-sets // min(8, sets))
     assert harness(*case)[0] == -(-sets // per)
+
+
+@pytest.mark.parametrize("case,tile", [(((4, 64), 0, 3136, 640, 1, 1, 252, 0), True), (((4, 64), 0, 2624, 576, 2, 2, 123, 0), True), (((4, 64), 256, 2688, 576, 1, 1, 87, 0), True),
+                                       (((4, 64), 256, 4032, 512, 4, 2, 57, 0), True), (((4, 64), 128, 2688, 640, 8, 2, 102, 0), True), (((4, 64), 256, 2944, 704, 6, 4, 29, 0), True),
+                                       (((4, 64), 128, 2944, 576, 2, 2, 17, 0), True), (((4, 64), 0, 1152, 1792, 2, 2, 116, 0), True),
+                                       (((4, 64), 0, 1152, 1792, 8, 2, 96, 0), False), (((4, 64), 256, 640, 1088, 13, 2, 111, 0), False), (((4, 64), 0, 1024, 2048, 8, 2, 136, 0), True)], ids=str)
+def test_kernels_of_small_layers(harness, case, tile):
+    """4-bit layers up to 1024 x 2048: the tile kernels beyond one window of tokens, and with rows of more than 1024 where an expert has more than 32
+    tokens on average, 16 with two-level metadata."""
+    assert (harness(*case, 0)[3] > 0) == tile
