@@ -1523,14 +1523,20 @@ struct ExpectedBlocks { double tiles = 0.0, big = 0.0; };
 // launch: 8 experts 4096x14336, 4-bit, top 2, 64 tokens 139 / 159 and 65 / 66, 96 tokens 163 / 164 and 84 / 83, 128 tokens 198 / 184 and 96 / 86, 192
 // tokens 295 / 220 and 119 / 89; 4096x2048 128 tokens 38 / 45 and 23 / 23; 1856x5056, 6 experts, top 3, 32 tokens 24 / 22 and 18 / 18, 64 tokens 37 / 28
 // and 26 / 24, two-level 48 tokens 26 / 23 and 24 / 23; 512x2048, 16 experts, 384 tokens 19 / 13 and 11 / 15.
-static double scaled_half_us(const moe_layer *l, int batch, const ExpectedBlocks &need, int mode, int n_rows, int cols, int parts)
+static double scaled_half_us(const moe_layer *l, int batch, const ExpectedBlocks &need, int mode, bool w2, int parts)
 {
     const BlobLayout &b = l->lay;
+    const int n_rows = w2 ? b.hidden : 2 * b.ffn, cols = w2 ? b.ffn : b.hidden;
     const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs);
     const int sets = (cols / 64 + 3) / 4, part_sets = (sets + parts - 1) / parts, k_parts = (sets + part_sets - 1) / part_sets;
     const int row_blocks = (n_rows + tile_rows(mode) - 1) / tile_rows(mode);
     const double tiles = need.tiles, blocks = mode == TE_BIG ? need.big : tiles;
-    const double units = part_sets * 4.0, rounds = row_blocks * n_exp * blocks * k_parts / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
+    // te_item gives an XCD whole jobs: w2's four row blocks in one part leave half of the chip idle (a step with one part / two: 3-bit 1024 x 6976, 13 experts, 1009
+    // tokens 450 / 364; 1280 x 3968 with four parts / three 109 / 94).  w1/w3, always one part of many row blocks, and the 32-token kernel, whose blocks are shorter, are
+    // fitted without (with it they change kernels at steps up to 23 % slower for it: 256 x 5248, 6 experts, 301 tokens 70 / 85).
+    int jobs = row_blocks * k_parts;
+    if (w2 && mode == TE_BIG) jobs = (jobs + TE_XCD - 1) / TE_XCD * TE_XCD;
+    const double units = part_sets * 4.0, rounds = jobs * n_exp * blocks / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
     const bool heavy = b.bits == 3 || b.scale_group;                                                   // more unpacking
     const double fill = tiles / blocks;                                                                // tiles of a k_big block
     if (mode == TE_BIG) return (rounds <= 4.0 ? std::max(1.0, std::ceil(rounds - 0.02)) : rounds + 0.5) * (6.9 + 2.0 * fill + units * (0.30 + (heavy ? 0.064 : 0.0) + 0.15 * fill));
@@ -1544,10 +1550,11 @@ static double scaled_half_us(const moe_layer *l, int batch, const ExpectedBlocks
 // large kernel, us a step: 8 experts 4096x14336, top 2, 160 tokens 359 / 507, 300 527 / 561, 512 816 / 645.  Two-level 2-bit scales go in as two numbers,
 // which costs the large kernel's units 1.3 times the matrix work, and the 32-token one has a compute unit to itself: one launch
 // each, 32 tokens / large kernel, w1/w3 of 4096x14336, 160 tokens 513 / 397, 384 tokens 862 / 489; w2 of 256x12288, 6 experts, 306 tokens 28 / 91.
-static double tile_half_us(const moe_layer *l, int batch, const ExpectedBlocks &need, int mode, int n_rows, int cols, int parts)
+static double tile_half_us(const moe_layer *l, int batch, const ExpectedBlocks &need, int mode, bool w2, int parts)
 {
     const BlobLayout &b = l->lay;
-    if (b.bits != 2) return scaled_half_us(l, batch, need, mode, n_rows, cols, parts);
+    if (b.bits != 2) return scaled_half_us(l, batch, need, mode, w2, parts);
+    const int n_rows = w2 ? b.hidden : 2 * b.ffn, cols = w2 ? b.ffn : b.hidden;
     const double pairs = (double)batch * l->cfg.top_k, n_exp = std::min<double>(l->cfg.n_experts, pairs), avg = pairs / n_exp;
     const double spread = l->cfg.top_k == l->cfg.n_experts ? 0.0 : 0.45;
     const double tiles = spread > 0.0 ? std::max(1.0, avg / 32 + spread) : std::ceil(avg / 32);        // of 32 tokens, an expert's
@@ -1608,12 +1615,12 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
         auto w2_us = [&](int mode, int parts) {
             int32_t k_parts, units;
             te_split(sets, parts, k_parts, units);
-            return tile_half_us(l, batch, need, mode, b.hidden, b.ffn, parts) + (k_parts - 1) * part_us;
+            return tile_half_us(l, batch, need, mode, true, parts) + (k_parts - 1) * part_us;
         };
         int big_parts = best_parts(TE_BIG, nominal_blocks(TE_BIG));
         for (int n = 1; n <= std::min(std::min(8, sets), cap) && b.bits != 2; ++n)           // by the estimate, which counts experts with more than their share as well
             if (w2_us(TE_BIG, n) < w2_us(TE_BIG, big_parts)) big_parts = n;
-        if (tile_half_us(l, batch, need, TE_BIG, 2 * b.ffn, b.hidden, 1) < margin * tile_half_us(l, batch, need, 32, 2 * b.ffn, b.hidden, 1)) p.mode13 = TE_BIG;
+        if (tile_half_us(l, batch, need, TE_BIG, false, 1) < margin * tile_half_us(l, batch, need, 32, false, 1)) p.mode13 = TE_BIG;
         if (w2_us(TE_BIG, big_parts) < margin * w2_us(32, p.parts)) { p.mode2 = TE_BIG; p.parts = big_parts; }
     }
     // Tokens that crowd to few experts leave fewer token blocks than the nominal routing's, and its parts would leave part of the

@@ -62,3 +62,11 @@ def test_kernels_of_small_layers(harness, case, tile):
     """4-bit layers up to 1024 x 2048: the tile kernels beyond one window of tokens, and with rows of more than 1024 where an expert has more than 32
     tokens on average, 16 with two-level metadata."""
     assert (harness(*case, 0)[3] > 0) == tile
+
+
+@pytest.mark.parametrize("case", [((3, 64), 0, 1024, 6976, 13, 4, 1009, 0), ((4, 128), 0, 1280, 14336, 8, 2, 1008, 0), ((3, 64), 0, 1280, 7552, 8, 4, 587, 0)], ids=str)
+def test_parts_fill_the_xcds(harness, case):
+    """The large kernel's jobs of w2, row blocks times parts, go to eight XCDs in whole: as many parts as leave few of them short of one."""
+    parts, _, _, kernel = harness(*case)
+    jobs = -(-case[2] // 256) * parts
+    assert kernel == 192 and jobs >= 0.8 * (-(-jobs // 8) * 8)
