@@ -1519,7 +1519,10 @@ struct ExpectedBlocks { double tiles = 0.0, big = 0.0; };
 
 // One launch of a tile kernel of 3- or 4-bit codes in us, mode 32 or the large one (k_big): rounds of blocks, a block's start and end and its units of
 // 64 columns.  k_big has one block a compute unit, whose rounds are paid in whole where they are few; of the other's last round what is in it counts.
-// Fitted to 400 launches over seven layers, 5 to 128 tokens of an expert (standard deviation 11 and 14 %).  w1/w3 and w2 at 32 tokens / k_big, us a
+// Fitted to 400 launches over seven layers, 5 to 128 tokens of an expert (standard deviation 11 and 14 %); what a unit of large 3-bit layers takes, to which
+// plan was the faster one in 417 steps, 13 to 220 tokens of an expert.  (With the same for 3-bit layers of all sizes, 4096x14336 took k_big at one or two tiles: 64 tokens, a
+// step with the 32-token kernel / k_big 223 / 261, two-level 265 / 332; 96 tokens 235 / 265 and 274 / 340; and with the large layers' for all, 1152x1600 two-level, 323
+// tokens, would not take it: 82 / 73.)  w1/w3 and w2 at 32 tokens / k_big, us a
 // launch: 8 experts 4096x14336, 4-bit, top 2, 64 tokens 139 / 159 and 65 / 66, 96 tokens 163 / 164 and 84 / 83, 128 tokens 198 / 184 and 96 / 86, 192
 // tokens 295 / 220 and 119 / 89; 4096x2048 128 tokens 38 / 45 and 23 / 23; 1856x5056, 6 experts, top 3, 32 tokens 24 / 22 and 18 / 18, 64 tokens 37 / 28
 // and 26 / 24, two-level 48 tokens 26 / 23 and 24 / 23; 512x2048, 16 experts, 384 tokens 19 / 13 and 11 / 15.
@@ -1537,10 +1540,13 @@ static double scaled_half_us(const moe_layer *l, int batch, const ExpectedBlocks
     int jobs = row_blocks * k_parts;
     if (w2 && mode == TE_BIG) jobs = (jobs + TE_XCD - 1) / TE_XCD * TE_XCD;
     const double units = part_sets * 4.0, rounds = jobs * n_exp * blocks / (n_cu_of(l->ctx) * tile_per_cu(b, mode));
-    const bool heavy = b.bits == 3 || b.scale_group;                                                   // more unpacking
+    // More unpacking.  3-bit codes that the last cache does not keep come faster to the 32-token kernel's sixteen waves a compute unit, with two sets each on their
+    // way, than to the eight of a k_big block with one (4-bit two-level: 4096x8192, 80 tokens, a step 190 / 171, so not there).
+    const bool heavy = b.bits == 3 || b.scale_group, streamed = b.bits == 3 && (uint64_t)l->cfg.n_experts * b.total > 112ull << 20;
+    const double more_big = !heavy ? 0.0 : streamed ? 0.14 : 0.064, more_32 = !heavy ? 0.0 : streamed ? 0.03 : 0.126;
     const double fill = tiles / blocks;                                                                // tiles of a k_big block
-    if (mode == TE_BIG) return (rounds <= 4.0 ? std::max(1.0, std::ceil(rounds - 0.02)) : rounds + 0.5) * (6.9 + 2.0 * fill + units * (0.30 + (heavy ? 0.064 : 0.0) + 0.15 * fill));
-    return 3.2 + std::max(rounds, 0.42) * units * (0.58 + (heavy ? 0.126 : 0.0)) + 4.8 * std::max(rounds, 1.0);
+    if (mode == TE_BIG) return (rounds <= 4.0 ? std::max(1.0, std::ceil(rounds - 0.02)) : rounds + 0.5) * (6.9 + 2.0 * fill + units * (0.30 + more_big + 0.15 * fill));
+    return 3.2 + std::max(rounds, 0.42) * units * (0.58 + more_32) + 4.8 * std::max(rounds, 1.0);
 }
 
 // The same of 2-bit codes: rounds of blocks, a block's start and end and its units.  The large kernel's

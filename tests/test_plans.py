@@ -70,3 +70,10 @@ def test_parts_fill_the_xcds(harness, case):
     parts, _, _, kernel = harness(*case)
     jobs = -(-case[2] // 256) * parts
     assert kernel == 192 and jobs >= 0.8 * (-(-jobs // 8) * 8)
+
+
+@pytest.mark.parametrize("sg,hidden,ffn,batch,tokens", [(0, 4096, 14336, 64, 32), (0, 4096, 14336, 96, 32), (128, 4096, 14336, 64, 32), (0, 4096, 8192, 72, 32), (128, 4096, 8192, 80, 32),
+                                                        (128, 2048, 14336, 72, 32), (0, 4096, 14336, 200, 192), (128, 4096, 14336, 256, 192)])
+def test_kernels_of_3bit_batches(harness, sg, hidden, ffn, batch, tokens):
+    """w2 of large 3-bit layers, 8 experts, top 2: one or two tiles of an expert are the 32-token kernel's, more the large one's."""
+    assert harness((3, 64), sg, hidden, ffn, 8, 2, batch, 0)[3] == tokens
