@@ -19,15 +19,17 @@
 // at the end of its first, so that one's vector work runs under the other's matrix work (3950 -> 3730 cycles a step of 128 tokens), which
 // goes first (s_setprio; -> 3680).
 //
-// What bounds it: issue.  A step takes 1480 cycles and 560 for every 32 tokens, 3350 without any loads at 128; the matrix cores need 512 for 32
-// tokens, and beside them run 490 vector instructions a SIMD, at four cycles each while the matrix cores work: 144 unpack, 256 scale.
+// What bounds it: issue.  A step takes 1480 cycles and 560 for every 32 tokens where an expert's token blocks share its weights, 3350 without any loads at 128; counted with every
+// weight read once, 2474 at 32 tokens and 500 for every 32 more.  The matrix cores need 576 for 32 tokens (zero-point term 64), and beside them run 483 vector instructions
+// a SIMD at 128 tokens, 281 at 32, at four cycles each while the matrix cores work: 144 unpack, 256 scale.  w1/w3 of 1024 tokens: vector unit 52 %, matrix unit 45 %, waiting 30 %.
 // What did not gain: each row tile unpacked under the other's products (4500, spills; 2770 against 2560 where there are registers), a
 // product scaled under the next, 16x16x32 instructions (they leave two issue slots free where a 32x32x16 leaves six), codes read ahead of the
 // barrier.  With all compute units at work the clock is 2.0 to 2.1 GHz of 2.4.
 //
 // Measured against that kernel (192 tokens, weights and activations through registers, a barrier a unit), 8 experts 4096 x 14336, w1/w3 + w2, us a launch:
 // 4-bit 1024 tokens 705 + 355 -> 590 + 332, 512 tokens 433 + 217 -> 336 + 214, 256 tokens 342 + 163 -> 214 + 110, 128 tokens (32-token kernel 198 +
-// 96) 184 + 86; 3-bit 512 tokens 444 + 226 -> 345 + 212; two-level 128 tokens 331 + 157 -> 202 + 100.  What a block does beside its units takes
+// 96) 184 + 86; 3-bit 512 tokens 444 + 226 -> 345 + 212; two-level 128 tokens 331 + 157 -> 202 + 100.  (One or two tiles
+// of an expert are the 32-token kernel's in large 3-bit layers: 64 tokens, a step 224 us, 264 here.)  What a block does beside its units takes
 // 7 us and 2 for every 32 tokens: the pair lookup, the first requests, the halves' sums and SiLU.
 #pragma once
 #include "kernels_tile.h"

@@ -65,8 +65,9 @@ constexpr int GATE_DENSE_EXPERTS = 8;
 // accumulators the kernel fits 64 registers, two blocks a compute unit.  The order of the sums is the same.
 // 1024 tokens x 4096 with the tile kernels' sums: 51 -> 40 us, 512 tokens 27 -> 18 us.
 // TURNS = 2: for more tokens than those blocks are at once.  Blocks of half as many threads, each of which takes two threads' slices one after
-// the other (the same sums in the same order), four blocks a compute unit.  At 4096 the
-// rows of W_g out of L2 bound both (22.7 / 22.5 us for 1024 tokens); narrower ones gain, whole steps of 1024 tokens 256 x 512 27.8 -> 25.1 us, 513 tokens
+// the other (the same sums in the same order), four blocks a compute unit.  At 4096 and 1024 tokens both take 22.7 us: a block's own work is the longer part there, its fp64
+// products (vector unit 48 %) behind the slices of W_g out of L2 (6 TB/s), and the loop of turns keeps 121 scalar registers in vector lanes where the other variant keeps 38.
+// Narrower ones, where blocks' starts and ends weigh more, gain, whole steps of 1024 tokens 256 x 512 27.8 -> 25.1 us, 513 tokens
 // 1024 x 2048 39.3 -> 38.6, 1024 tokens 4096 x 2048 148.8 -> 147.9.  At 512 tokens and less every token's block has its own place anyway.
 // After the one barrier that collects the waves' partial logits, wave 0 finishes alone: lane e holds logit e (lane
 // 16 + e the next layer's), the selection runs on values read from those lanes, and the exponentials, divisions and

@@ -20,8 +20,8 @@
 // The subtraction is there for the error.  Codes that enter as 64 + q make the products some fourteen times as large, and the matrix
 // cores' roundings with them, which have one sign where the tokens have a mean: the error then grows with the length of the
 // contraction (4096 x 14336, 4-bit, below: 4.8e-5, and 24e-5 at a mean of eight deviations; minus the bias's share as a product's
-// start, one more matrix instruction, leaves 2.3 to 2.9e-5).  It costs 1 to 3 %: 1024 tokens 4-bit 1042 -> 1073 us a step, 512 tokens 3-bit
-// 605 -> 616, 37 tokens two-level 49.6 -> 50.3, 16 tokens 3-bit 183.4 -> 184.3.
+// start, one more matrix instruction, leaves 2.3 to 2.9e-5).  It costs 1 to 3 %: 37 tokens two-level 49.6 -> 50.3 us a step, 16 tokens 3-bit 183.4 -> 184.3 (and
+// 1024 tokens 4-bit 1042 -> 1073, 512 tokens 3-bit 605 -> 616 with the large kernel of these formats before k_big).
 // (Codes as the subnormal fp16 numbers their bits spell need no exponent, but the matrix cores accumulate products of
 // subnormals with fewer bits: 6 % more error in y.)
 // Groups of 32 (4 bits, tiles of 16 and 32 tokens): two products of half the length per unit, a lane half or quarter holding its share of either group.
@@ -42,10 +42,11 @@
 //
 // Error of this arithmetic alone: y of a layer against 64 bits with the activations between the halves rounded to fp16 as
 // here (an a close to the middle of two fp16 numbers then falls the other way now and then, which is most of it), one expert of 1024 x 4096
-// and of 4096 x 14336, every format, 16, 32 and 192 tokens, two seeds.  Normalised tokens of mean 0, as the decode workloads draw them / of a
-// mean of a tenth of the deviation / of mean 1 and deviation 1/8, in 1e-5: 4-bit 0.5 to 2.4 / 0.6 to 1.5 / 0.8 to 2.2 (GEMV kernels 8.6 to 10 /
-// 8.6 to 10 / 14 to 17), 3-bit 0.5 to 1.4 / 0.4 to 1.4 / 1.1 to 2.8 (GEMV 17 to 18 / 19 / 41), 2-bit tiles
-// of 16 0.7 to 2.2 / 1.5 to 1.6 / 1.2 to 1.8, others 3.5 to 4.3 / 3.7 to 4.6 / 6.3 to 7.3 (GEMV 11 to 12 / 11 / 2.9 to 3.3; the two bf16 of X and D).  With the rounding of a, the error of y at mean 0 is 2.07 to 2.1e-4 (GEMV 2.08 to 2.2e-4).
+// and of 4096 x 14336, every format (4-bit groups of 64 and 128), two seeds, steps of 16 tokens, of 32 and of as many as a block of the large kernel takes
+// (2-bit 192, two-level 128, 3 and 4 bits 128, in k_big).  Normalised tokens of mean 0, as the decode workloads draw them / of a
+// mean of a tenth of the deviation / of mean 1 and deviation 1/8, in 1e-5: 4-bit tiles of 16 and 32 0.3 to 1.3 / 0.3 to 2.0 / 0.7 to 2.4, k_big 0.7 to 1.2 / 0.7 to 1.3 / 0.9
+// to 1.7 (GEMV kernels 8.6 to 10 / 8.6 to 10 / 14 to 17), 3-bit tiles 0.2 to 1.7 / 0.6 to 1.4 / 0.7 to 3.0, k_big 0.8 to 1.3 / 0.8 to 1.2 / 1.1 to 1.7 (GEMV 17 to 18 / 19 / 41), 2-bit tiles
+// of 16 0.6 to 2.0 / 0.7 to 2.2 / 1.1 to 2.4, others 3.5 to 4.6 / 3.4 to 4.4 / 6.4 to 7.3 (GEMV 11 to 12 / 11 / 2.9 to 3.3; the two bf16 of X and D).  With the rounding of a, the error of y at mean 0 is 2.07 to 2.1e-4 (GEMV 2.08 to 2.2e-4).
 //
 // BIG: of the two waves on a SIMD (same rows, other tokens) one unpacks a unit's codes before it multiplies them, the
 // other at the end of the unit before, so that one's vector work runs under the other's matrix work.

@@ -1589,9 +1589,8 @@ static void plan_tile(const moe_layer *l, int batch, BatchPlan &p)
     const int sets = (b.ffn / 64 + 3) / 4;
     const int cap = (int)std::min<uint64_t>(255, c->ypart_extra_floats / b.hidden / (uint64_t)pairs);
     // As many parts as fill the rounds of blocks best (one block of the big kernel per compute unit, two of the small
-    // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  w2 + k_combine in us, this
-    // rule / two rounds of blocks always: 1024 tokens 4-bit 344 + 12 (1 part) / 356 + 19 (2), 512 tokens 3-bit 214 + 10 (2) /
-    // 226 + 14 (4).
+    // ones), a part costing about 3 % of the launch in starts, ends and rows for k_combine.  (k_big's parts: by the estimate, below; 512 tokens 3-bit
+    // one part, 239 + 7 us for w2 + k_combine, where this rule, which counts 128 blocks of the even routing's 128 tokens, has two; 1024 tokens 4-bit two, 341 + 18.)
     auto nominal_blocks = [&](int mode) {
         int blocks = 0;
         for (int e = 0; e < E; ++e) blocks += tile_blocks(b, nominal_count(l, pairs, e), mode);
